@@ -8,6 +8,7 @@
 #include <atomic>
 #include <type_traits>
 
+#include "attn_rows.h"
 #include "internal.h"
 #include "stream.h"
 
@@ -109,16 +110,14 @@ __device__ __forceinline__ uint32_t u4_word(const uint4& v)
     return I == 0 ? v.x : (I == 1 ? v.y : (I == 2 ? v.z : v.w));
 }
 
+// The workgroup's part: chunk c, head group hgrp, row tile `tile`; len and slot (LDS, complete) hold the tile's rows'
+// lengths (0 or less: not this call's) and slots.
 template <int G, int RT, bool DIRECT>
-__global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const uint16_t* __restrict__ q,
-                                                        const uint16_t* __restrict__ kcache,
-                                                        const uint16_t* __restrict__ vcache,
-                                                        const int32_t* __restrict__ seqlens,
-                                                        const int32_t* __restrict__ slots,
-                                                        float* __restrict__ ws_m, float* __restrict__ ws_l,
-                                                        float* __restrict__ ws_o, uint16_t* __restrict__ out, int R,
-                                                        int Hq, int Hkv, int Lmax, int ncmax, float scale,
-                                                        int len_offset)
+__device__ __forceinline__ void attn_tile(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kcache,
+                                          const uint16_t* __restrict__ vcache, float* __restrict__ ws_m,
+                                          float* __restrict__ ws_l, float* __restrict__ ws_o, uint16_t* __restrict__ out,
+                                          int Hq, int Hkv, int Lmax, int ncmax, float scale, int c, int hgrp, int tile,
+                                          const int* len, const int* slot)
 {
     constexpr int NP = G * RT;             // pairs (row, head) of the workgroup
     constexpr int CBK = (NP + 15) / 16;    // blocks of sixteen pairs
@@ -127,38 +126,12 @@ __global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const u
     __shared__ __align__(16) float sc[NP * kChunk];  // scores, then e_j
     __shared__ uint4 vt[128 * 16];                   // V^T of half a chunk: [d][token], 32 KB
     __shared__ float mc_s[NP], lc_s[NP];             // the pairs' chunk statistics (DIRECT only)
-    const int c = blockIdx.x, hgrp = blockIdx.y, tile = blockIdx.z;
     const int kvh = (hgrp * G) / (Hq / Hkv);
     const int t0 = c * kChunk;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, lr = lane & 15;
 
-    // the tile's rows: length (0: no such row) and slot; a row is active if it has tokens in this chunk
-    __shared__ int len[RT], slot[RT];
-    if (tid < RT) {
-        const int r = tile * RT + tid;
-        int l = 0, sl = -1;
-        if (r < R) {
-            l = seqlens[r] + len_offset;
-            l = l > Lmax ? Lmax : l;
-            sl = slots ? slots[r] : r;
-        }
-        len[tid] = l;
-        slot[tid] = sl;
-    }
-    __syncthreads();
-    if constexpr (DIRECT) {
-        // rows without any token get zeros, from the workgroups of chunk 0 (there is no second pass to do it)
-        if (c == 0) {
-#pragma unroll
-            for (int ri = 0; ri < RT; ++ri) {
-                const int r = tile * RT + ri;
-                if (r < R && len[ri] <= 0)
-                    for (int i = tid; i < G * kD; i += 256) out[((size_t)r * Hq + (size_t)hgrp * G) * kD + i] = 0;
-            }
-        }
-    }
     bool any = false;
 #pragma unroll
     for (int ri = 0; ri < RT; ++ri) any = any || len[ri] > t0;
@@ -389,6 +362,117 @@ __global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const u
     }
 }
 
+template <int G, int RT, bool DIRECT>
+__global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const uint16_t* __restrict__ q,
+                                                        const uint16_t* __restrict__ kcache,
+                                                        const uint16_t* __restrict__ vcache,
+                                                        const int32_t* __restrict__ seqlens,
+                                                        const int32_t* __restrict__ slots,
+                                                        float* __restrict__ ws_m, float* __restrict__ ws_l,
+                                                        float* __restrict__ ws_o, uint16_t* __restrict__ out, int R,
+                                                        int Hq, int Hkv, int Lmax, int ncmax, float scale,
+                                                        int len_offset)
+{
+    const int c = blockIdx.x, hgrp = blockIdx.y, tile = blockIdx.z, tid = threadIdx.x;
+    // the tile's rows: length (0: no such row) and slot
+    __shared__ int len[RT], slot[RT];
+    if (tid < RT) {
+        const int r = tile * RT + tid;
+        int l = 0, sl = -1;
+        if (r < R) {
+            l = seqlens[r] + len_offset;
+            l = l > Lmax ? Lmax : l;
+            sl = slots ? slots[r] : r;
+        }
+        len[tid] = l;
+        slot[tid] = sl;
+    }
+    __syncthreads();
+    if constexpr (DIRECT) {
+        // rows without any token get zeros, from the workgroups of chunk 0 (there is no second pass to do it)
+        if (c == 0) {
+#pragma unroll
+            for (int ri = 0; ri < RT; ++ri) {
+                const int r = tile * RT + ri;
+                if (r < R && len[ri] <= 0)
+                    for (int i = tid; i < G * kD; i += 256) out[((size_t)r * Hq + (size_t)hgrp * G) * kD + i] = 0;
+            }
+        }
+    }
+    attn_tile<G, RT, DIRECT>(q, kcache, vcache, ws_m, ws_l, ws_o, out, Hq, Hkv, Lmax, ncmax, scale, c, hgrp, tile, len, slot);
+}
+
+// The rows of a slot-naming call that a walking launch leaves (attn_rows.h), as a bit per row in LDS; returns the words in use.
+// All of the workgroup's threads call it.
+constexpr int kLeftWords = 1024;  // 65535 rows
+template <int G>
+__device__ __forceinline__ int find_left_rows(const int32_t* __restrict__ seqlens, const int32_t* __restrict__ slots,
+                                              int len_offset, int Lmax, int R, int Hkv, uint64_t* left, int* scratch)
+{
+    int limit = kWalkChunks;
+    if (Lmax > kWalkChunks * kChunk)
+        limit = attn_walk_limit(seqlens, len_offset, Lmax, R, (R + kWalkPairs / G - 1) / (kWalkPairs / G), kWalkPairs / G, Hkv, scratch);
+    attn_for_row_words<kWalkPairs / G>(seqlens, slots, len_offset, Lmax, R, limit, [&](int w, const attn_row_classes& k) {
+        if ((threadIdx.x & 63) == 0) left[w] = attn_left_rows<G>(k);
+    });
+    const int words = (R + 63) >> 6;
+    __syncthreads();
+    return words;
+}
+
+// Pass 1 for those rows, eight to a workgroup as in attn_tile_kernel: items are (chunk, KV head, eight rows), dealt
+// out over the grid in runs of kLeftRun, so that the rows that walk cost no workgroups.
+constexpr int kLeftRun = 4;
+template <int G, bool DIRECT>
+__global__ __launch_bounds__(256, 2) void attn_left_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kcache,
+                                                          const uint16_t* __restrict__ vcache,
+                                                          const int32_t* __restrict__ seqlens,
+                                                          const int32_t* __restrict__ slots, float* __restrict__ ws_m,
+                                                          float* __restrict__ ws_l, float* __restrict__ ws_o,
+                                                          uint16_t* __restrict__ out, int R, int Hq, int Hkv, int Lmax,
+                                                          int ncmax, float scale, int len_offset)
+{
+    constexpr int RT = 8;
+    __shared__ uint64_t left[kLeftWords];
+    __shared__ int len[RT], slot[RT], scratch;
+    const int words = find_left_rows<G>(seqlens, slots, len_offset, Lmax, R, Hkv, left, &scratch);
+    const int per_tile = Hkv * ncmax, jump = kLeftRun * ((int)gridDim.x - 1);
+    int next = kLeftRun * (int)blockIdx.x, in_run = 0;  // this workgroup's next item, counted from the current tile's first
+#pragma unroll 1
+    for (int w = 0; w < words; ++w) {
+        const uint64_t word = left[w];
+        if (word == 0) continue;
+#pragma unroll 1
+        for (int y = 0; y < 8; ++y) {
+            const uint32_t rows = (uint32_t)(word >> (8 * y)) & 255u;
+            if (rows == 0) continue;
+            const int tile = 8 * w + y;
+            if (next < per_tile) {
+                __syncthreads();  // the previous tile's lengths are no longer read
+                if (threadIdx.x < RT) {
+                    const int r = tile * RT + (int)threadIdx.x;
+                    const bool in = (rows >> threadIdx.x) & 1u;
+                    len[threadIdx.x] = in ? attn_row_len(seqlens, r, len_offset, Lmax) : 0;
+                    slot[threadIdx.x] = in ? slots[r] : -1;
+                }
+                __syncthreads();
+            }
+#pragma unroll 1
+            while (next < per_tile) {
+                attn_tile<G, RT, DIRECT>(q, kcache, vcache, ws_m, ws_l, ws_o, out, Hq, Hkv, Lmax, ncmax, scale, next / Hkv,
+                                         next % Hkv, tile, len, slot);
+                __syncthreads();  // its LDS contents are no longer read
+                ++next;
+                if (++in_run == kLeftRun) {
+                    in_run = 0;
+                    next += jump;
+                }
+            }
+            next -= per_tile;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ attention, pass 2
 
 // Grid (query head, sequence); 128 threads, thread = d.  The arithmetic is the ascending-chunk fold
@@ -401,20 +485,15 @@ __global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const u
 // reduction; `out` is then the int8 code array [B, Hq*128] and `scales` the block-major scale array
 // with row stride ldd.
 template <bool QUANT>
-__global__ __launch_bounds__(128) void attn_combine_kernel(const int32_t* __restrict__ seqlens,
-                                                           const float* __restrict__ ws_m,
-                                                           const float* __restrict__ ws_l,
-                                                           const float* __restrict__ ws_o,
-                                                           void* __restrict__ out, int Hq, int Lmax,
-                                                           int ncmax, int len_offset, float* __restrict__ scales,
-                                                           int ldd, int first_pass_wrote_short_rows)
+__device__ __forceinline__ void attn_combine(int h, int b, int len, const float* __restrict__ ws_m,
+                                             const float* __restrict__ ws_l, const float* __restrict__ ws_o,
+                                             void* __restrict__ out, int Hq, int ncmax, float* __restrict__ scales, int ldd,
+                                             int first_pass_wrote_short_rows)
 {
     __shared__ float s_w[128];
     __shared__ float s_l[128];
     __shared__ float s_red[2];
-    const int h = blockIdx.x, b = blockIdx.y, d = threadIdx.x;
-    int len = seqlens[b] + len_offset;
-    len = len > Lmax ? Lmax : len;
+    const int d = threadIdx.x;
     const size_t o_idx = ((size_t)b * Hq + h) * kD + d;
     auto store = [&](uint16_t y) {
         if constexpr (!QUANT) {
@@ -484,6 +563,51 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const int32_t* __rest
     store(f32_to_bf16_rne(O / L));
 }
 
+template <bool QUANT>
+__global__ __launch_bounds__(128) void attn_combine_kernel(const int32_t* __restrict__ seqlens,
+                                                           const float* __restrict__ ws_m,
+                                                           const float* __restrict__ ws_l,
+                                                           const float* __restrict__ ws_o,
+                                                           void* __restrict__ out, int Hq, int Lmax,
+                                                           int ncmax, int len_offset, float* __restrict__ scales,
+                                                           int ldd, int first_pass_wrote_short_rows)
+{
+    const int b = blockIdx.y;
+    attn_combine<QUANT>(blockIdx.x, b, attn_row_len(seqlens, b, len_offset, Lmax), ws_m, ws_l, ws_o, out, Hq, ncmax, scales,
+                        ldd, first_pass_wrote_short_rows);
+}
+
+// Pass 2 for those rows, (row, head) items dealt round-robin over the grid.
+template <int G, bool QUANT>
+__global__ __launch_bounds__(128) void attn_left_combine_kernel(const int32_t* __restrict__ seqlens,
+                                                                const int32_t* __restrict__ slots,
+                                                                const float* __restrict__ ws_m,
+                                                                const float* __restrict__ ws_l,
+                                                                const float* __restrict__ ws_o, void* __restrict__ out,
+                                                                int R, int Hq, int Hkv, int Lmax, int ncmax, int len_offset,
+                                                                float* __restrict__ scales, int ldd)
+{
+    __shared__ uint64_t left[kLeftWords];
+    __shared__ int scratch;
+    const int words = find_left_rows<G>(seqlens, slots, len_offset, Lmax, R, Hkv, left, &scratch);
+    int next = (int)blockIdx.x;  // this workgroup's next item, counted from the current row's first
+#pragma unroll 1
+    for (int w = 0; w < words; ++w) {
+#pragma unroll 1
+        for (uint64_t word = left[w]; word != 0; word &= word - 1) {
+            const int b = 64 * w + __builtin_ctzll(word);
+            if (next < Hq) {
+                const int len = attn_row_len(seqlens, b, len_offset, Lmax);
+                for (; next < Hq; next += (int)gridDim.x) {
+                    __syncthreads();  // the previous item's weights are no longer read
+                    attn_combine<QUANT>(next, b, len, ws_m, ws_l, ws_o, out, Hq, ncmax, scales, ldd, QUANT ? 0 : 1);
+                }
+            }
+            next -= Hq;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ softmax on given scores
 
 constexpr int kMaxChunksHook = 1024;
@@ -549,6 +673,50 @@ __global__ __launch_bounds__(256) void softmax_kernel(const float* __restrict__ 
         l_out[r] = L;
     }
 }
+
+// The rows of a walking launch that it leaves (attn_rows.h).
+template <int G>
+static void launch_left(const void* q, const void* kcache, const void* vcache, const int32_t* seqlens, const int32_t* slots,
+                        int len_offset, void* out, float* ws_m, float* ws_l, float* ws_o, float* qscales, int R, int Hq,
+                        int Hkv, int Lmax, int ncmax, float scale, hipStream_t s)
+{
+    const uint16_t *qq = static_cast<const uint16_t*>(q), *kk = static_cast<const uint16_t*>(kcache),
+                   *vv = static_cast<const uint16_t*>(vcache);
+    const dim3 grid(512);  // two workgroups a compute unit
+    if (qscales) {
+        hipLaunchKernelGGL((attn_left_kernel<G, false>), grid, dim3(256), 0, s, qq, kk, vv, seqlens, slots, ws_m, ws_l, ws_o,
+                           nullptr, R, Hq, Hkv, Lmax, ncmax, scale, len_offset);
+        hipLaunchKernelGGL((attn_left_combine_kernel<G, true>), dim3(2048), dim3(128), 0, s, seqlens, slots, ws_m, ws_l, ws_o,
+                           out, R, Hq, Hkv, Lmax, ncmax, len_offset, qscales, (R + 3) & ~3);
+    } else {
+        hipLaunchKernelGGL((attn_left_kernel<G, true>), grid, dim3(256), 0, s, qq, kk, vv, seqlens, slots, ws_m, ws_l, ws_o,
+                           static_cast<uint16_t*>(out), R, Hq, Hkv, Lmax, ncmax, scale, len_offset);
+        hipLaunchKernelGGL((attn_left_combine_kernel<G, false>), dim3(2048), dim3(128), 0, s, seqlens, slots, ws_m, ws_l, ws_o,
+                           out, R, Hq, Hkv, Lmax, ncmax, len_offset, nullptr, 0);
+    }
+}
+static int attn_left(const void* q, const void* kcache, const void* vcache, const int32_t* seqlens, const int32_t* slots,
+                     int len_offset, void* out, float* ws_m, float* ws_l, float* ws_o, float* qscales, int R, int Hq, int Hkv,
+                     int Lmax, int ncmax, float scale, hipStream_t s)
+{
+#define DET_LAUNCH_LEFT(GG)                                                                                              \
+    launch_left<GG>(q, kcache, vcache, seqlens, slots, len_offset, out, ws_m, ws_l, ws_o, qscales, R, Hq, Hkv, Lmax, ncmax, \
+                    scale, s)
+    switch (Hq / Hkv) {
+        case 1: DET_LAUNCH_LEFT(1); break;
+        case 2: DET_LAUNCH_LEFT(2); break;
+        case 4: DET_LAUNCH_LEFT(4); break;
+        default: DET_LAUNCH_LEFT(8); break;
+    }
+#undef DET_LAUNCH_LEFT
+    return check_launch();
+}
+
+// Rows that name their slots walk their chunks inside one workgroup (attn_rows.hip) where that gives every compute
+// unit one.  Below, the chunks of a row in workgroups of their own are the better split: sixteen rows at the end
+// of 4000 tokens take 23 us that way and 176 walking, 256 such rows (128 workgroups) 165 and 180, 512 rows (256
+// workgroups) 309 and 178; 1000 rows of one prompt (504) 170 and 60.
+constexpr long long kWalkWorkgroups = 256;
 
 static size_t attn_ws_floats(int B, int Hq, int Lmax)
 {
@@ -616,11 +784,20 @@ int det::attn_decode_impl(const void* q, const void* kcache, const void* vcache,
     float* ws_l = ws_m + n;
     float* ws_o = ws_l + n;
     // Launch geometry (which workgroup computes a (row, head, chunk); never its arithmetic):
-    //   * rows that name their slots (prefill: consecutive rows of a prompt share a slot) go eight to a
-    //     workgroup from sixteen rows on, so that they share each chunk of K and V;
+    //   * rows that name their slots (prefill: consecutive rows of a prompt share a slot) walk their chunks in
+    //     one workgroup where there are enough of them (kWalkWorkgroups); fewer, but sixteen or more, go eight to
+    //     a workgroup per chunk, so that they share each chunk of K and V;
     //   * launches of a few dozen workgroups (one sequence, short context) are all latency: every query
     //     head then gets a workgroup of its own, which divides a workgroup's statistics and PV work by G.
     const bool tiled = slots != nullptr && B >= 16;
+    if (tiled && attn_walk_workgroups(B, G, Hkv) >= kWalkWorkgroups) {
+        if (qscales && !aligned16(qscales)) return DET_EALIGN;
+        const int rc = attn_walk(q, kcache, vcache, seqlens, slots, len_offset, out, static_cast<float*>(qscales), B, Hq, Hkv,
+                                 Lmax, scale, s);
+        if (rc != DET_OK || (G > 1 && ncmax <= kWalkChunks)) return rc;  // no row can be left
+        return attn_left(q, kcache, vcache, seqlens, slots, len_offset, out, ws_m, ws_l, ws_o, static_cast<float*>(qscales), B,
+                         Hq, Hkv, Lmax, ncmax, scale, s);
+    }
     const int RT = tiled ? 8 : 1;
     const bool split_heads = !tiled && G > 1 && (size_t)ncmax * Hkv * B <= 128;
     const dim3 grid(ncmax, split_heads ? Hq : Hkv, (B + RT - 1) / RT);

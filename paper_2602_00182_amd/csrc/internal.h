@@ -14,5 +14,10 @@ int attn_decode_impl(const void* q, const void* kcache, const void* vcache, cons
                      const int32_t* slots, int len_offset, void* out, void* ws, size_t ws_bytes, int B, int Hq, int Hkv, int D,
                      int Lmax, float scale, hipStream_t s, void* qscales = nullptr);
 
+// The same on rows that name their slots, without workspace (attn_rows.hip): arguments checked by the caller.
+// attn_walk_workgroups: the workgroups such a launch has.
+long long attn_walk_workgroups(int R, int G, int Hkv);
+int attn_walk(const void* q, const void* kcache, const void* vcache, const int32_t* seqlens, const int32_t* slots,
+              int len_offset, void* out, float* qscales, int R, int Hq, int Hkv, int Lmax, float scale, hipStream_t s);
 
 }  // namespace det
