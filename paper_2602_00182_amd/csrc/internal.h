@@ -20,4 +20,9 @@ long long attn_walk_workgroups(int R, int G, int Hkv);
 int attn_walk(const void* q, const void* kcache, const void* vcache, const int32_t* seqlens, const int32_t* slots,
               int len_offset, void* out, float* qscales, int R, int Hq, int Hkv, int Lmax, float scale, hipStream_t s);
 
+// SwiGLU projection with quantized output (qgemm.hip), where it fits: aligned buffers as the layer lays them out.
+bool qgemm_swiglu_quant_fits(int M, int F, int K);
+int qgemm_swiglu_quant(const void* codes, const void* scales, const void* packed_gate_up, void* codes_out, void* scales_out, int M,
+                       int F, int K, void* stream);
+
 }  // namespace det

@@ -172,8 +172,8 @@ extern "C" int det_qdecoder_layer(const det_layer_weights* w, const det_layer_cf
                              c.Lmax, c.scale, s, scales));
     DET_TRY(det_qgemm_w4a8_residual(codes, scales, w->wo, x_inout, c.H, x_inout, c.H, R, c.H, nq, stream));
     DET_TRY(det_rmsnorm_quant_q8(x_inout, w->w_norm2, codes, scales, R, c.H, c.eps, stream));
-    if (det_qgemm_w4a8_swiglu_quant_supported(c.F, c.H)) {
-        DET_TRY(det_qgemm_w4a8_swiglu_quant(codes, scales, w->wgu, codes2, scales2, R, c.F, c.H, stream));
+    if (qgemm_swiglu_quant_fits(R, c.F, c.H)) {
+        DET_TRY(qgemm_swiglu_quant(codes, scales, w->wgu, codes2, scales2, R, c.F, c.H, stream));
     } else {
         DET_TRY(det_qgemm_w4a8_swiglu(codes, scales, w->wgu, mm, c.F, R, c.F, c.H, stream));
         DET_TRY(det_quant_act_q8(mm, c.F, codes2, scales2, R, c.F, stream));

@@ -18,10 +18,11 @@
 // w % CB, row blocks w / CB, w / CB + 8/CB, ...): at small M the work per stage is the unpacking of
 // the codes, which a single wave could not do at the rate the weights stream in.  Tiles of at most 8
 // rows and 2 column blocks go further and split the stages of a chunk over the waves (run_sp below):
-// only the accumulation chain has a defined order, and it keeps it.
+// only the accumulation chain has a defined order, and it keeps it.  Launches of many rows take tiles of 64 rows x
+// 128 columns instead (qgemm_tall_kernel).
 #include <type_traits>
 
-#include "common.h"
+#include "internal.h"
 #include "stream.h"
 
 namespace det {
@@ -648,6 +649,256 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same product for launches of many rows: 64 x 128 tiles, four waves of 64 rows x 32 columns.
+//
+// What bounds it is the scaling arithmetic, three vector instructions per output and block (d*s, the conversion,
+// the fma), a wave having eight 16 x 16 outputs of it a block against twelve matrix instructions; so a wave owns a tile
+// that is tall: it unpacks the codes of two column blocks for four row blocks, and the row sums -8 * (sum of p), with
+// which the matrix core starts so that the stored nibbles q + 8 serve as they are, are shared by its columns.
+// The operands of two blocks of K (a chunk) travel together through a ring of three LDS slots, two in flight, each
+// wave loading its share; activation rows come as whole 128-byte lines.  Three workgroups a compute unit (four slots
+// and two workgroups measured 5 to 15 % slower).  Against the kernel above, us: 1962 rows K x N 2048 x 2048 92 -> 27,
+// 5632 x 2048 227 -> 61, 4096 x 4096 327 -> 84, 14336 x 4096 1084 -> 278, 2048 x 11264 160 -> 106, 4096 x 28672
+// 593 -> 506 (0.91 POP/s; instruction issue alone is about 450).
+constexpr int kTallRows = 64, kTallCols = 128, kTallWaves = 4, kTallSlots = 3;
+constexpr int kTallA = kTallRows * 128;                    // activation codes of a chunk
+constexpr int kTallW = 2 * 8 * 544;                        // weight codes and scales: [slab][block][544 * CB]
+constexpr int kTallD = 2 * kTallRows * 4;                  // activation scales: [block][row]
+constexpr int kTallSlot = kTallA + kTallW + kTallD;        // 17408 bytes
+constexpr int kTallAUnits = kTallA / 1024, kTallWUnits = (kTallW + 1023) / 1024;  // 8 and 9 loads of 64 lanes
+
+template <int N>
+__device__ __forceinline__ void q_wait_then_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+template <int CB, int EPI>
+__global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
+    const int8_t* __restrict__ qa, int K, const float* __restrict__ da, int ldd, const uint8_t* __restrict__ wp, void* C,
+    int ldc, const uint16_t* R, int ldr, int out_f32, int M, float* qscales_out, gemm_rope_args ra)
+{
+    __shared__ uint4 ring[kTallSlots * kTallSlot / 16];
+    __shared__ float rowmax[EPI == kEpiSwigluQuant ? kTallWaves * kTallRows : 1];
+    constexpr int WST = qstage_w_bytes(CB);  // bytes of a block of a slab
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, lr = lane & 15;
+    const int m0 = blockIdx.y * kTallRows, n0 = blockIdx.x * kTallCols;
+    const int nblk = K >> 6, nchunks = (nblk + 1) >> 1;
+    const uint32_t ring_addr = (uint32_t)(uintptr_t)(lds_char_t*)ring;
+    const char* abytes = reinterpret_cast<const char*>(qa);
+    const char* wbytes = reinterpret_cast<const char*>(wp) + (size_t)(n0 / 16) * nblk * qstage_w_bytes(1);
+    const char* dbytes = reinterpret_cast<const char*>(da);
+
+    // This lane's sources.  Activations, unit u = 2*wave + i: row 8u + lane/8 (rows past M repeat the last), its 16-byte piece
+    // (lane%8) ^ (row/2)%8, which spreads the sixteen rows of an operand read over the banks.  Weights, unit u = wave,
+    // wave + 4 (and 8, half a unit, wave 0): piece 64u + lane of the chunk's 544, of slab piece / (68*CB).  Scales (wave 1):
+    // block lane/16, rows 4*(lane%16) .. +3.  `odd`: a last chunk of one block repeats that block's bytes.
+    uint32_t a_off[2][2];
+    const char* a_base[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int row = 8 * (2 * wave + i) + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
+        const int first = m0 + 8 * (2 * wave + i);
+        a_base[i] = abytes + (size_t)(first < M ? first : M - 1) * K;
+        const int src = m0 + row < M ? row : M - 1 - m0;                    // >= 0: a tile holds a row
+        const int rel = first < M ? src - 8 * (2 * wave + i) : 0;           // rows from a_base
+        a_off[0][i] = (uint32_t)rel * (uint32_t)K + 16u * (uint32_t)piece;
+        a_off[1][i] = (uint32_t)rel * (uint32_t)K + 16u * (uint32_t)(piece & 3);
+    }
+    auto w_source = [&](int unit, bool odd) -> size_t {
+        int p = 64 * unit + lane;
+        const int slab = p / (68 * CB);
+        p -= slab * (68 * CB);
+        if (odd && p >= 34 * CB) p -= 34 * CB;
+        return (size_t)slab * nblk * WST + 16 * (size_t)p;
+    };
+    const size_t w_off0 = w_source(wave, false), w_off1 = w_source(wave + 4, false), w_off2 = w_source(8, false);
+    const int d_piece = min((m0 >> 2) + (lane & 15), (ldd >> 2) - 1);
+
+    auto issue = [&](int c) {
+        const bool odd = 2 * c + 1 == nblk;
+        const uint32_t slot = ring_addr + (uint32_t)(c % kTallSlots) * (uint32_t)kTallSlot;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            dma_block(a_base[i] + (size_t)c * 128, a_off[odd ? 1 : 0][i], slot + (uint32_t)(2 * wave + i) * 1024u);
+        const uint32_t w = slot + kTallA;
+        const char* wsrc = wbytes + (size_t)c * (2 * WST);
+        dma_lane(wsrc + (odd ? w_source(wave, true) : w_off0), w + (uint32_t)wave * 1024u);
+        dma_lane(wsrc + (odd ? w_source(wave + 4, true) : w_off1), w + (uint32_t)(wave + 4) * 1024u);
+        if (wave == 0) {
+            if (lane < 32) dma_lane(wsrc + (odd ? w_source(8, true) : w_off2), w + 8192u);
+        } else if (wave == 1) {
+            const int b = 2 * c + ((lane >> 4) & 1);
+            if (lane < 32) dma_lane(dbytes + ((size_t)(b < nblk ? b : nblk - 1) * ldd + 4 * (size_t)d_piece) * 4, w + kTallW);
+        }
+    };
+    const int per = wave < 2 ? 5 : 4;  // loads of a chunk, this wave
+
+    f32x4 acc[4][2];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int c = 0; c < kTallSlots - 1 && c < nchunks; ++c) issue(c);
+    const int zr = (lr >> 1) & 7;
+    for (int c = 0; c < nchunks; ++c) {
+        // chunk c has landed (here, then everywhere) and everyone is done with chunk c-1
+        if (c + 1 < nchunks) {
+            if (per == 5)
+                q_wait_then_barrier<5>();
+            else
+                q_wait_then_barrier<4>();
+        } else {
+            q_wait_then_barrier<0>();
+        }
+        if (c + kTallSlots - 1 < nchunks) issue(c + kTallSlots - 1);
+        const char* slot = reinterpret_cast<const char*>(ring) + (c % kTallSlots) * kTallSlot;
+        const char* wslot = slot + kTallA;
+        const char* dslot = wslot + kTallW;
+        auto block = [&](int s) {
+            v4i xa[4];
+            float dv[4];
+            uint2 codes[2], sraw[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int cbk = 2 * wave + j;  // column block of the tile
+                const char* wst = wslot + (cbk / CB) * (2 * WST) + s * WST;
+                codes[j] = *reinterpret_cast<const uint2*>(wst + (cbk % CB) * 512 + lane * 8);
+                sraw[j] = *reinterpret_cast<const uint2*>(wst + 512 * CB + (cbk % CB) * 32 + g * 8);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                xa[r] = *reinterpret_cast<const v4i*>(slot + (16 * r + lr) * 128 + (((4 * s + g) ^ zr) << 4));
+                dv[r] = *reinterpret_cast<const float*>(dslot + s * (kTallRows * 4) + (16 * r + lr) * 4);
+            }
+            v4i wu[2];
+            float sc[2][4];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                wu[j][0] = (int)(codes[j].x & 0x0F0F0F0Fu);
+                wu[j][1] = (int)((codes[j].x >> 4) & 0x0F0F0F0Fu);
+                wu[j][2] = (int)(codes[j].y & 0x0F0F0F0Fu);
+                wu[j][3] = (int)((codes[j].y >> 4) & 0x0F0F0F0Fu);
+                sc[j][0] = bf16lo_to_f32(sraw[j].x);
+                sc[j][1] = bf16hi_to_f32(sraw[j].x);
+                sc[j][2] = bf16lo_to_f32(sraw[j].y);
+                sc[j][3] = bf16hi_to_f32(sraw[j].y);
+            }
+            v4i pr[4][2];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m8 = (int)0xF8F8F8F8u;
+                const v4i base = __builtin_amdgcn_mfma_i32_16x16x64_i8(v4i{m8, m8, m8, m8}, xa[r], v4i{0, 0, 0, 0}, 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) pr[r][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[j], xa[r], base, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[r][j][v] = __builtin_fmaf(dv[r] * sc[j][v], (float)pr[r][j][v], acc[r][j][v]);
+        };
+        block(0);
+        if (2 * c + 1 < nblk) block(1);
+    }
+
+    // Lane holds C[row = m0 + 16r + lr][n0 + 32*wave + 16j + 4g + v].
+    const int n = n0 + 32 * wave + 4 * g;
+    if constexpr (EPI == kEpiSwigluQuant) {
+        // Columns are gate/up pairs: the tile row's 64 outputs are one quantization block; the lane holds four of
+        // row lr of each row block.  Its maximum: the lane's, the four lanes of a row (g), the four waves (LDS).
+        float y[4][4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float mx = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const float gt = bf16_to_f32(f32_to_bf16_rne(acc[r][j][2 * e])), u = bf16_to_f32(f32_to_bf16_rne(acc[r][j][2 * e + 1]));
+                    y[r][2 * j + e] = bf16_to_f32(f32_to_bf16_rne(silu_mul(gt, u)));
+                    mx = j + e == 0 ? fabsf(y[r][0]) : fmaxf(mx, fabsf(y[r][2 * j + e]));
+                }
+            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            if (g == 0) rowmax[wave * kTallRows + 16 * r + lr] = mx;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int rowl = 16 * r + lr;
+            float amax = rowmax[rowl];
+#pragma unroll
+            for (int w = 1; w < kTallWaves; ++w) amax = fmaxf(amax, rowmax[w * kTallRows + rowl]);
+            const float df = amax / 127.0f;
+            if (m0 + rowl >= M) continue;
+            const size_t row = (size_t)(m0 + rowl);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                uint32_t c2 = 0;
+                if (df != 0.0f) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const float qv = rintf(y[r][2 * j + e] / df);
+                        const int iv = qv < -127.0f ? -127 : (qv > 127.0f ? 127 : (int)qv);
+                        c2 |= (uint32_t)(iv & 0xFF) << (8 * e);
+                    }
+                }
+                *reinterpret_cast<uint16_t*>(static_cast<int8_t*>(C) + row * ldc + ((n + 16 * j) >> 1)) = (uint16_t)c2;
+            }
+            if (wave == 0 && g == 0) qscales_out[(size_t)blockIdx.x * ldr + row] = df;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (m0 + 16 * r + lr >= M) continue;
+            const size_t row = (size_t)(m0 + 16 * r + lr);
+            int p = 0, slot = 0;
+            if constexpr (EPI == kEpiRopeAppend) {
+                p = ra.pos[row];
+                p = p < 0 ? 0 : (p >= ra.Lmax ? ra.Lmax - 1 : p);
+                slot = ra.slots ? ra.slots[row] : (int)row;
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float v[4] = {acc[r][j][0], acc[r][j][1], acc[r][j][2], acc[r][j][3]};
+                if constexpr (EPI == kEpiRopeAppend)
+                    gemm_epilogue_rope_append(v, ra, row, p, slot, n + 16 * j);
+                else
+                    gemm_epilogue_store<EPI>(v, C, ldc, R, ldr, row, n + 16 * j, out_f32);
+            }
+        }
+    }
+}
+
+// Where the tall tiles are faster than 256-row tiles of the packing's width.  With fewer than a workgroup for every
+// compute unit they take the time of one walk over K (4096: 33 us, 14336: 106 us) however few they are, and at 128 rows
+// the other kernel's is shorter (25 and 76 us at N = 4096); it meets theirs at about 224 rows and 112 workgroups
+// (N = 4096: 38 against 33 us; 2048 x 2048: 64 workgroups 16 against 19, 128 workgroups 26 against 19), from 129
+// rows where there are 256 of them (N = 28672, 160 rows: 87 against 75).
+static bool qgemm_tall_pays(int M, int N)
+{
+    if (N % kTallCols != 0 || M > 65535 * kTallRows) return false;
+    const long long wgs = (long long)((M + kTallRows - 1) / kTallRows) * (N / kTallCols);
+    return (M >= 224 && wgs >= 112) || (M > 128 && wgs >= 256);
+}
+
+template <int CB, int EPI>
+static void launch_qgemm_tall(const void* qa, const void* da, int ldd, const void* wp, void* C, int ldc, const void* R, int ldr,
+                              int M, int N, int K, int out_f32, hipStream_t s, float* qscales_out, const gemm_rope_args& ra)
+{
+    hipLaunchKernelGGL((qgemm_tall_kernel<CB, EPI>), dim3(N / kTallCols, (M + kTallRows - 1) / kTallRows),
+                       dim3(64 * kTallWaves), 0, s, static_cast<const int8_t*>(qa), K, static_cast<const float*>(da), ldd,
+                       static_cast<const uint8_t*>(wp), C, ldc, static_cast<const uint16_t*>(R), ldr, out_f32, M, qscales_out,
+                       ra);
+}
+
 static int q_ldd(int M) { return (M + 3) & ~3; }
 
 template <int CB, int EPI>
@@ -655,6 +906,10 @@ static void launch_qgemm(const void* qa, const void* da, int ldd, const void* wp
                          int M, int N, int K, int out_f32, hipStream_t s, float* qscales_out = nullptr,
                          const gemm_rope_args& ra = gemm_rope_args{})
 {
+    if (qgemm_tall_pays(M, N)) {
+        launch_qgemm_tall<CB, EPI>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
+        return;
+    }
     // Matrices too narrow to give every compute unit a column tile: the rows are cut into as many tiles as
     // fill the chip (a tile's rows are whole 16-row blocks; which tile a row falls in does not touch its
     // arithmetic).
@@ -683,6 +938,29 @@ static int qgemm_dispatch(const void* codes, const void* scales, const void* pac
         case 2: launch_qgemm<2, EPI>(codes, scales, q_ldd(M), packed_w, C, ldc, R, ldr, M, N, K, f32, s, nullptr, ra); break;
         case 4: launch_qgemm<4, EPI>(codes, scales, q_ldd(M), packed_w, C, ldc, R, ldr, M, N, K, f32, s, nullptr, ra); break;
         default: launch_qgemm<8, EPI>(codes, scales, q_ldd(M), packed_w, C, ldc, R, ldr, M, N, K, f32, s, nullptr, ra); break;
+    }
+    return check_launch();
+}
+
+// det_qgemm_w4a8_swiglu_quant wherever some kernel's tile row holds whole 64-output blocks (the decoder layer's own
+// call; the exported one takes the shapes that do at every row count).
+bool qgemm_swiglu_quant_fits(int M, int F, int K)
+{
+    return det_qgemm_w4a8_swiglu_quant_supported(F, K) || (F % 64 == 0 && F <= (1 << 29) && qgemm_tall_pays(M, 2 * F));
+}
+int qgemm_swiglu_quant(const void* codes, const void* scales, const void* packed_gate_up, void* codes_out, void* scales_out, int M,
+                       int F, int K, void* stream)
+{
+    if (det_qgemm_w4a8_swiglu_quant_supported(F, K))
+        return det_qgemm_w4a8_swiglu_quant(codes, scales, packed_gate_up, codes_out, scales_out, M, F, K, stream);
+    const int ld = q_ldd(M);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    float* d = static_cast<float*>(scales_out);
+    const gemm_rope_args ra{};
+    switch (qgemm_cols_per_block(2 * F)) {
+        case 1: launch_qgemm_tall<1, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
+        case 2: launch_qgemm_tall<2, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
+        default: launch_qgemm_tall<4, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
     }
     return check_launch();
 }

@@ -28,6 +28,21 @@ __device__ __forceinline__ void dma_block(const void* base, uint32_t lane_off, u
         : "memory");
 }
 
+// The same from an address of each lane's own.
+__device__ __forceinline__ void dma_lane(const void* src, uint32_t lds_addr)
+{
+    uint32_t saved_m0;
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %1\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %2, off\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved_m0)
+        : "s"(lds_addr), "v"(src)
+        : "memory");
+}
+
 // A run of such loads with constant strides, three instructions a load: M0 is set once and then
 // advanced in place, and the source advances in the per-lane offset.  (Nothing else in this file
 // uses M0, and the compiler sets it itself before any instruction of its own that reads it.)

@@ -1,0 +1,82 @@
+"""The quantized GEMM's tiles of 64 x 128 for launches of many rows: every row must have the bytes it has in a call of at
+most 100 rows, which takes the kernel that test_gpu_qgemm.py holds to the bit-exact oracle."""
+import pytest
+import torch
+
+import detsynth as ds
+from gpu_util import DEV, step, up_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def d():
+    import paper_2602_00182_amd as d
+    return d
+
+
+def parts(M, n=100):
+    return [slice(i, min(i + n, M)) for i in range(0, M, n)]
+
+
+# packings of 16, 32, 64 and 128 columns; one block of K, odd and even numbers of them; a tile of one row, whole tiles
+@pytest.mark.parametrize("M,K,N", [(385, 64, 2048), (450, 192, 2048), (449, 1088, 3072), (225, 64, 5120), (257, 320, 5248),
+                                   (129, 192, 11008), (256, 128, 11264), (129, 64, 20480), (200, 704, 28672)])
+def test_rows_equal_small_calls(d, M, K, N):
+    w = up_bf16(ds.normal_bf16(7000 + N, (K, N), 0.02))
+    a = up_bf16(ds.normal_bf16(7100 + M, (M, K)))
+    r = up_bf16(ds.normal_bf16(7200 + M, (M, N)))
+    wp, gu = d.quant_pack_weight(w), d.quant_pack_gate_up(w)
+    out = torch.full((M, N), float("nan"), device=DEV)
+    res = torch.full((M, N), 7.0, dtype=torch.bfloat16, device=DEV)
+    swi = torch.full((M, N // 2), 7.0, dtype=torch.bfloat16, device=DEV)
+    codes, scales = d.quant_activations(a)
+    step(f"tall quantized GEMM M={M} K={K} N={N}")
+    d.det_qgemm_w4a8(codes, scales, wp, out, N)
+    d.det_qgemm_w4a8_residual(codes, scales, wp, r, res, N)
+    d.det_qgemm_w4a8_swiglu(codes, scales, gu, swi, N // 2)
+    torch.cuda.synchronize()
+    for p in parts(M):
+        c, s = d.quant_activations(a[p].contiguous())
+        n = p.stop - p.start
+        o1 = torch.empty((n, N), device=DEV)
+        o2 = torch.empty((n, N), dtype=torch.bfloat16, device=DEV)
+        o3 = torch.empty((n, N // 2), dtype=torch.bfloat16, device=DEV)
+        d.det_qgemm_w4a8(c, s, wp, o1, N)
+        d.det_qgemm_w4a8_residual(c, s, wp, r[p].contiguous(), o2, N)
+        d.det_qgemm_w4a8_swiglu(c, s, gu, o3, N // 2)
+        assert torch.equal(out[p].view(torch.int32), o1.view(torch.int32))
+        assert torch.equal(res[p].view(torch.int16), o2.view(torch.int16))
+        assert torch.equal(swi[p].view(torch.int16), o3.view(torch.int16))
+
+
+# a fused SwiGLU quantizer where the packing has 64 columns (no other kernel's tile holds a block there) and where it has 128
+@pytest.mark.parametrize("R,H,Hq,Hkv,F", [(390, 256, 2, 1, 5632), (241, 128, 2, 2, 10240), (420, 128, 4, 2, 64)])
+def test_quantized_layer_rows_equal_small_calls(d, R, H, Hq, Hkv, F):
+    D, Lmax = 128, 420
+    g = lambda s, shape, std=0.05, mean=0.0: up_bf16(ds.normal_bf16(s, shape, std, mean))
+    w = d.layer_weights(g(1, (H,), 0.1, 1.0), d.quant_pack_qkv(g(2, (H, (Hq + 2 * Hkv) * D)), Hq, Hkv, D),
+                        d.quant_pack_weight(g(3, (Hq * D, H))), g(4, (H,), 0.1, 1.0), d.quant_pack_gate_up(g(5, (H, 2 * F))),
+                        d.quant_pack_weight(g(6, (F, H))))
+    cfg = d.layer_cfg(H, Hq, Hkv, D, F, Lmax, 1e-5, 0.08838834764831845)
+    pos = torch.arange(R, dtype=torch.int32, device=DEV)
+    slots = torch.zeros(R, dtype=torch.int32, device=DEV)
+    ang = torch.arange(Lmax, device=DEV, dtype=torch.float64)[:, None] * (0.9 ** torch.arange(64, device=DEV, dtype=torch.float64))
+    cos, sin = ang.cos().float().contiguous(), ang.sin().float().contiguous()
+    x0 = g(7, (R, H), 1.0)
+
+    def run(cuts):
+        x = x0.clone()
+        k = torch.zeros((1, Hkv, Lmax, D), dtype=torch.bfloat16, device=DEV)
+        v = torch.zeros_like(k)
+        for p in cuts:
+            xp = x[p].contiguous()
+            ws = torch.full((d.det_qdecoder_layer_workspace_bytes(cfg, xp.shape[0]),), 0xFF, dtype=torch.uint8, device=DEV)
+            d.det_qdecoder_layer(w, cfg, xp, k, v, pos[p].contiguous(), slots[p].contiguous(), cos, sin, ws)
+            x[p] = xp
+        torch.cuda.synchronize()
+        return x.view(torch.int16), k.view(torch.int16), v.view(torch.int16)
+
+    step(f"quantized layer R={R} H={H} heads {Hq}/{Hkv} F={F}")
+    for got, want in zip(run([slice(0, R)]), run(parts(R))):
+        assert torch.equal(got, want)
