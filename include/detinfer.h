@@ -61,7 +61,8 @@ extern "C" {
  * fused forms below) ALSO choose from M is the tile a launch cuts C into, i.e. which workgroup and wave
  * computes an element: 256 rows x the packing's width by default; rows cut into shorter tiles when N
  * alone gives fewer than 256 workgroups and M >= 17; 64-column tiles from M >= 96 (16-column packings)
- * or M >= 192 (32-column packings); 128-column tiles when ceil(M/256) * N/128 >= 256.  The bytes of a
+ * or M >= 192 (32-column packings); 128-column tiles when ceil(M/256) * N/128 >= 256; 256-column tiles of 128 to
+ * 256 rows when M >= 256, K >= 1024, N % 256 == 0 and their rounds of 256 workgroups cost less.  The bytes of a
  * row do not depend on that choice (every tile shape runs the same chain for an element; the tests
  * compare every M in 1..256 with the M = 256 launch and with det_gemm_bf16_fixed_tile), but it IS a
  * launch geometry keyed on the batch size, so it is named here and in det_fingerprint(), and

@@ -45,6 +45,7 @@
 #include <utility>
 
 #include "common.h"
+#include "gemm_wide.h"
 #include "stream.h"
 
 namespace det {
@@ -804,6 +805,11 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
     bool ok = true;  // false: the schedule would overrun the kernel's load counter (no supported shape does)
     const int cb = gemm_cols_per_block(N);
     const bool small = gemm_small_ring(N);
+    // (0) 256-column tiles (gemm_wide.hip) where their rounds cost less than those of the tiles below.
+    if (!fixed_tile) {
+        if (const int rbw = gemm_wide_rows(M, N, K, cb))
+            return gemm_wide(EPI, rbw, gemm_wide_args{A, lda, Bp, cb, C, ldc, R, ldr, M, N, K, f32, ra}, s);
+    }
     // What bounds a launch with many rows is the bytes each workgroup pulls through its compute unit's
     // memory pipe: every row of its tile of A and every column of its tile of the weights, once per K.
     // The tiling below picks, per (M, N), the tile shape that keeps that sum small while every compute

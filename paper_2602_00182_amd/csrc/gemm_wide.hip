@@ -1,0 +1,260 @@
+// The bf16 GEMM of gemm.hip for launches of many rows: tiles of 32*RBW rows x 256 columns.  Same packing, same matrix-core
+// instruction, one accumulator chain per element over ascending K: the same bytes.
+#include "gemm_wide.h"
+#include "stream.h"
+
+namespace det {
+
+namespace {
+
+constexpr int kWideCols = 256;
+constexpr int kWideWaves = 8;  // two rows of waves x four columns of them; a wave owns 16*RBW rows x 64 columns
+constexpr int kWideLds = 160 * 1024;
+
+// This wave's LDS reads have returned.  A builtin, and outside every branch, so that the compiler knows of it and adds no
+// wait of its own behind the barrier for reads that were issued before it.
+__device__ __forceinline__ void wait_reads()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+}
+// At most N of this wave's loads are in flight.
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+}  // namespace
+
+// A workgroup's 512 threads stream K in steps of 32 through a ring of LDS slots: 2*RBW KB of activations (16 rows x 64 bytes
+// a load) and 16 KB of weights (blocks in operand order) a step, each wave loading its share.  What bounds the
+// 256 x 128 tile of gemm.hip is the fill of LDS, 48 KB for 64 * 256 * 128 products; 256 x 256 is 64 KB for twice the work.
+// The operands of step t+1 are read from LDS into registers while step t is in the matrix cores, so a step needs one
+// barrier and no wait for its own reads, and its slot is free as soon as it starts.  A 256-row tile then takes 13 ns a
+// matrix instruction (8 ns with operands that never change and nothing else in the loop): with the loads taken out 11, with
+// the operand reads taken out 11.6, the loads alone 7.5.
+template <int RBW, int EPI>
+__global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uint16_t* __restrict__ A, int lda,
+                                                                     const uint4* __restrict__ Bp, int cb, void* C, int ldc,
+                                                                     const uint16_t* R, int ldr, int M, int K, int ntm, int ntn,
+                                                                     int out_f32, gemm_rope_args ra)
+{
+    constexpr int TM = 32 * RBW, AU = TM / 16, UNITS = AU + 16;  // 1 KB loads of a step
+    constexpr int SLOT = UNITS * 1024;
+    constexpr int NS = kWideLds / SLOT < 6 ? kWideLds / SLOT : 6;
+    static_assert(NS >= 4, "ring");
+    constexpr int LMAX = (UNITS + kWideWaves - 1) / kWideWaves, LMIN = UNITS / kWideWaves;  // loads of a step, one wave
+    static_assert((NS - 2) * LMAX <= 60, "load counter");
+    __shared__ uint4 ring[NS * SLOT / 16];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, lr = lane & 15;
+    const int wr = wave >> 2, wc = wave & 3;
+
+    // Workgroups go round-robin over the eight XCDs; each XCD gets a run of consecutive tiles, in groups of eight row tiles by
+    // all columns, so that the tiles it has at a time share rows and columns in its L2.
+    int tm, tn;
+    {
+        const int T = ntm * ntn, x = blockIdx.x & 7, j = blockIdx.x >> 3;
+        const int base = T >> 3, extra = T & 7;
+        const int L = x * base + (x < extra ? x : extra) + j;
+        const int grp = L / (8 * ntn), in = L - grp * (8 * ntn);
+        const int gs = ntm - 8 * grp < 8 ? ntm - 8 * grp : 8;
+        tm = 8 * grp + in % gs;
+        tn = in / gs;
+    }
+    const int m0 = tm * TM, n0 = tn * kWideCols;
+    const int nst = K >> 5;  // steps, even
+    const uint32_t ring_addr = (uint32_t)(uintptr_t)(lds_char_t*)ring;
+
+    // This wave's loads of a step: units wave, wave + 8, ..; below AU activations, above weights.
+    const char* abase = reinterpret_cast<const char*>(A + (size_t)m0 * lda);
+    const char* wbase = reinterpret_cast<const char*>(Bp) + (size_t)(n0 / 16) * (K >> 6) * 2048;
+    const int mrem = M - m0;
+    uint32_t a_off[LMAX];
+#pragma unroll
+    for (int i = 0; i < LMAX; ++i) {
+        const int u = wave + 8 * i;
+        int row = 16 * u + (lane >> 2);
+        row = row < mrem ? row : mrem - 1;  // rows past M repeat the last: their outputs are never stored
+        a_off[i] = (uint32_t)row * (uint32_t)lda * 2u + 16u * (uint32_t)((lane & 3) ^ ((lane >> 4) & 3));
+    }
+    auto issue = [&](int t, int slot) __attribute__((always_inline)) {
+        const uint32_t dst = ring_addr + (uint32_t)slot * (uint32_t)SLOT;
+        const char* asrc = abase + (size_t)t * 64;
+#pragma unroll
+        for (int i = 0; i < LMAX; ++i) {
+            const int u = wave + 8 * i;
+            if (i >= LMIN && u >= UNITS) break;
+            if (u < AU) {
+                dma_block(asrc, a_off[i], dst + (uint32_t)u * 1024u);
+            } else {
+                const int j = u - AU, slab = j / cb, jj = j - slab * cb;  // column block j of the tile
+                const char* src = wbase + ((size_t)slab * (K >> 6) + (size_t)(t >> 1)) * (size_t)(cb * 2048) +
+                                  (size_t)(2 * jj + (t & 1)) * 1024;
+                dma_block(src, (uint32_t)lane * 16u, dst + (uint32_t)u * 1024u);
+            }
+        }
+    };
+
+    struct Frags {
+        bf16x8 w[4], x[RBW];
+    };
+    const int x_off = (wr * RBW) * 1024 + lr * 64 + ((g ^ (lr >> 2)) << 4);
+    const int w_off = (AU + 4 * wc) * 1024 + lane * 16;
+    auto read = [&](Frags& f, int slot) __attribute__((always_inline)) {
+        const char* base = reinterpret_cast<const char*>(ring) + slot * SLOT;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f.w[j] = *reinterpret_cast<const bf16x8*>(base + w_off + j * 1024);
+#pragma unroll
+        for (int r = 0; r < RBW; ++r) f.x[r] = *reinterpret_cast<const bf16x8*>(base + x_off + r * 1024);
+    };
+    f32x4 acc[RBW][4];
+#pragma unroll
+    for (int r = 0; r < RBW; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto products = [&](const Frags& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < RBW; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[j], f.x[r], acc[r][j], 0, 0, 0);
+    };
+    const bool more = wave < UNITS % kWideWaves;  // this wave has LMAX loads a step, not LMIN
+    // Passing this: step t+1 has landed for everyone, and everyone has the operands of step t in registers, so its slot
+    // takes step t+NS.
+    int slot_r = 0, slot_w = NS - 1;  // slot of the step read next, and of the step issued next
+    auto open = [&](int t) __attribute__((always_inline)) {
+        wait_reads();
+        if (t + NS - 1 < nst) {  // steps t+2 .. t+NS-1 are behind step t+1
+            if (LMAX != LMIN && more)
+                wait_loads<(NS - 2) * LMAX>();
+            else
+                wait_loads<(NS - 2) * LMIN>();
+        } else {
+            wait_loads<0>();
+        }
+        asm volatile("s_barrier" ::: "memory");
+        if (t + NS < nst) issue(t + NS, slot_w);
+        slot_w = slot_w + 1 == NS ? 0 : slot_w + 1;
+    };
+    auto next = [&](Frags& f) __attribute__((always_inline)) {
+        read(f, slot_r);
+        slot_r = slot_r + 1 == NS ? 0 : slot_r + 1;
+    };
+
+#pragma unroll
+    for (int t = 0; t < NS - 1; ++t)
+        if (t < nst) issue(t, t);
+    Frags f0, f1;
+    open(-1);
+    next(f0);
+    for (int t = 0; t < nst; t += 2) {
+        open(t);
+        next(f1);
+        products(f0);
+        if (t + 2 < nst) {
+            open(t + 1);
+            next(f0);
+        }
+        products(f1);
+    }
+
+    // Lane holds C[row = m0 + 16*(wr*RBW + r) + lr][n0 + 64*wc + 16j + 4g + v].
+    const int n1 = n0 + 64 * wc + 4 * g;
+#pragma unroll
+    for (int r = 0; r < RBW; ++r) {
+        const int rowl = 16 * (wr * RBW + r) + lr;
+        if (rowl >= mrem) continue;
+        const size_t row = (size_t)(m0 + rowl);
+        int p = 0, slot = 0;
+        if constexpr (EPI == kEpiRopeAppend) {
+            p = ra.pos[row];
+            p = p < 0 ? 0 : (p >= ra.Lmax ? ra.Lmax - 1 : p);
+            slot = ra.slots ? ra.slots[row] : (int)row;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float v[4] = {acc[r][j][0], acc[r][j][1], acc[r][j][2], acc[r][j][3]};
+            if constexpr (EPI == kEpiRopeAppend)
+                gemm_epilogue_rope_append(v, ra, row, p, slot, n1 + 16 * j);
+            else
+                gemm_epilogue_store<EPI>(v, C, ldc, R, ldr, row, n1 + 16 * j, out_f32);
+        }
+    }
+}
+
+template <int RBW, int EPI>
+static void launch(const gemm_wide_args& a, hipStream_t s)
+{
+    const int ntm = (a.M + 32 * RBW - 1) / (32 * RBW), ntn = a.N / kWideCols;
+    hipLaunchKernelGGL((gemm_wide_kernel<RBW, EPI>), dim3(ntm * ntn), dim3(64 * kWideWaves), 0, s,
+                       static_cast<const uint16_t*>(a.A), a.lda, static_cast<const uint4*>(a.Bp), a.cb, a.C, a.ldc,
+                       static_cast<const uint16_t*>(a.R), a.ldr, a.M, a.K, ntm, ntn, a.out_f32, a.ra);
+}
+
+template <int EPI>
+static void launch_rows(int rbw, const gemm_wide_args& a, hipStream_t s)
+{
+    switch (rbw) {
+        case 4: launch<4, EPI>(a, s); break;
+        case 5: launch<5, EPI>(a, s); break;
+        case 6: launch<6, EPI>(a, s); break;
+        default: launch<8, EPI>(a, s); break;
+    }
+}
+
+// What a launch costs is the rounds of 256 workgroups it takes, times what one of its tiles takes for a step of K, which is
+// nearly the same over all shapes (measured over K = 2048 .. 14336, N = 2048 .. 28672, 300 to 4096 rows): 0.52 / 0.65 /
+// 0.70 / 0.85 us for 128 / 160 / 192 / 256 rows here, 8 % more in launches of four rounds and more; for gemm.hip 0.53 us a
+// round of its 256 x 128 tiles (0.51 in long launches, less for the rows a last tile lacks), and in its narrower tilings,
+// which it takes where those do not fill the chip, 1.4 ns for each row and column of a tile (16- and 32-column packings)
+// or the share of a round that 256 x 128 tiles would fill, in us (64-column packings).  So the choice is the tile height
+// whose tiles fit the rounds best: 3302 rows of N = 6144, K = 4096 are 13 x 48 tiles there (three rounds, 216 us), 13 x 24
+// of 256 rows here (two, 220 us), 21 x 24 of 160 rows (two, 170 us).  10 % must be won by this
+// count, 25 % where a tile there is as wide as the packing and the weights alone are much of the time.  Others: K x N
+// 4096 x 6144 700 rows 114 -> 67 us, 14336 x 4096 1500 rows 377 -> 208, 4096 x 28672 4096 rows 950 -> 856 (1.12 PFLOP/s;
+// torch's product of two 8192 x 8192 matrices reaches 1.19 on the same card).
+int gemm_wide_rows(int M, int N, int K, int cb)
+{
+    if (N % kWideCols != 0 || 16 % cb != 0 || M < 256 || K < 1024) return 0;
+    auto rounds = [](long long wgs) { return (wgs + 255) / 256; };
+    // both costs in units of 10 ns
+    const long long row_tiles = (M + 255) / 256, there = row_tiles * (N / 128);
+    const long long live = 256 * (row_tiles - 1) + 160 + 96 * (M - 256 * (row_tiles - 1)) / 256;  // of 256 * row_tiles
+    long long cost;
+    if (there < 256 && cb < 4) {
+        const int fit = 256 / (N / 64) > 1 ? 256 / (N / 64) : 1;
+        const int even = 16 * (((M + 15) / 16 + fit - 1) / fit), rows = even < 256 ? even : 256;
+        cost = rounds((long long)(N / 64) * ((M + rows - 1) / rows)) * (rows + 64) * 14 / 100;
+    } else {
+        const long long full = there < 256 && cb < 8 ? there * 100 / 256 : rounds(there) * (rounds(there) < 4 ? 53 : 51);
+        cost = full * live / (256 * row_tiles);
+    }
+    static const struct {
+        int rbw, cost;
+    } kTiles[4] = {{4, 52}, {5, 65}, {6, 70}, {8, 85}};
+    int best = 0;
+    long long best_cost = 100 * cost;
+    for (const auto& t : kTiles) {
+        const long long n = rounds((long long)((M + 32 * t.rbw - 1) / (32 * t.rbw)) * (N / kWideCols));
+        const long long c = n * t.cost * (n >= 4 ? 119 : (cb < 8 ? 110 : 125));
+        if (c < best_cost) best = t.rbw, best_cost = c;
+    }
+    return best;
+}
+
+int gemm_wide(int epi, int rbw, const gemm_wide_args& a, hipStream_t s)
+{
+    switch (epi) {
+        case kEpiStore: launch_rows<kEpiStore>(rbw, a, s); break;
+        case kEpiResidual: launch_rows<kEpiResidual>(rbw, a, s); break;
+        case kEpiSwiglu: launch_rows<kEpiSwiglu>(rbw, a, s); break;
+        default: launch_rows<kEpiRopeAppend>(rbw, a, s); break;
+    }
+    return check_launch();
+}
+
+}  // namespace det
