@@ -8,6 +8,7 @@
 #include <atomic>
 #include <type_traits>
 
+#include "attn_lane.h"
 #include "attn_rows.h"
 #include "internal.h"
 #include "stream.h"
@@ -402,6 +403,200 @@ __global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const u
     attn_tile<G, RT, DIRECT>(q, kcache, vcache, ws_m, ws_l, ws_o, out, Hq, Hkv, Lmax, ncmax, scale, c, hgrp, tile, len, slot);
 }
 
+// Pass 1 for rows that share nothing (one row a workgroup: decode), one chunk for the G heads of a KV head.  The order of
+// every operation is attn_tile's; what differs is where things are: V is loaded with the keys in one go and lies in LDS as
+// it does in memory, transposed by the LDS read, so that the whole chunk's weighted sums follow one another, and a lane gets
+// the scores of eight tokens of each 32-token step of its pair in registers (the tokens are dealt to the operand's rows that
+// way), so that maximum, exp and tree need no pass over LDS.  Two barriers: the waves' maxima, then e and V.
+// What bounds the launches that take it is this chain of one memory round trip and two barriers.
+template <int G, bool DIRECT>
+__global__ __launch_bounds__(256, 2) void attn_chunk_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kcache,
+                                                           const uint16_t* __restrict__ vcache,
+                                                           const int32_t* __restrict__ seqlens,
+                                                           const int32_t* __restrict__ slots, float* __restrict__ ws_m,
+                                                           float* __restrict__ ws_l, float* __restrict__ ws_o,
+                                                           uint16_t* __restrict__ out, int Hq, int Hkv, int Lmax, int ncmax,
+                                                           float scale, int len_offset)
+{
+    __shared__ uint4 vbuf[kChunk * 16];             // V of the chunk, [token][piece], swizzled as in attn_rows.hip
+    __shared__ __align__(16) float es[G * kChunk];  // e, [pair][token], sc_index
+    __shared__ float wave_m[4][16], wave_l[4][16];
+    const int c = blockIdx.x, hgrp = blockIdx.y, r = blockIdx.z;
+    const int kvh = (hgrp * G) / (Hq / Hkv);
+    const int t0 = c * kChunk;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, lr = lane & 15;
+    const int len = __builtin_amdgcn_readfirstlane(attn_row_len(seqlens, r, len_offset, Lmax));
+    uint16_t* orow = DIRECT ? out + ((size_t)r * Hq + (size_t)hgrp * G) * kD : nullptr;
+    if (DIRECT && c == 0 && len <= 0) {  // a row without any token: zeros (there is no second pass to write them)
+        for (int i = tid; i < G * kD; i += 256) orow[i] = 0;
+    }
+    if (len <= t0) return;
+    const int slot = slots ? __builtin_amdgcn_readfirstlane(slots[r]) : r;
+    const int held = min(kChunk, len - t0);  // tokens of the chunk
+    const size_t kv_base = (((size_t)slot * Hkv + kvh) * (size_t)Lmax + t0) * kD;
+    const uint4* kp = reinterpret_cast<const uint4*>(kcache + kv_base);
+    const uint4* vp = reinterpret_cast<const uint4*>(vcache + kv_base);
+
+    // ---- loads: this lane's query piece, its keys (token 64w + 32st + 8(lr/4) + 4b + lr%4 is row lr of operand block (st, b)),
+    // and its share of V; tokens past the length are zeros and never read
+    uint4 qf[4], kf[2][2][4], vr[16];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) qf[i] = make_uint4(0, 0, 0, 0);
+    if (lr < G) {
+        const uint4* qp = reinterpret_cast<const uint4*>(q + ((size_t)r * Hq + (size_t)hgrp * G + lr) * kD + 32 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qf[i] = qp[i];
+    }
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int tok = 64 * wave + 32 * st + 8 * (lr >> 2) + 4 * b + (lr & 3);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) kf[st][b][i] = make_uint4(0, 0, 0, 0);
+            if (tok < held) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) kf[st][b][i] = kp[tok * 16 + 4 * g + i];
+            }
+        }
+#pragma unroll
+    for (int b = 0; b < 16; ++b) {
+        const int tok = 64 * wave + 4 * b + g;
+        vr[b] = make_uint4(0, 0, 0, 0);
+        if (tok < held) vr[b] = vp[tok * 16 + lr];
+    }
+
+    // ---- scores and the chunk's maximum
+    float s[2][8];
+    float m_c = -INFINITY;
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[st][b][i]),
+                                                              __builtin_bit_cast(bf16x8, qf[i]), acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int tok = 64 * wave + 32 * st + 8 * g + 4 * b + v;
+                s[st][4 * b + v] = tok < held ? acc[v] * scale : -INFINITY;
+                m_c = fmaxf(m_c, s[st][4 * b + v]);
+            }
+        }
+    m_c = max_rows(m_c);
+    if (g == 0) wave_m[wave][lr] = m_c;
+    __syncthreads();
+    m_c = fmaxf(fmaxf(wave_m[0][lr], wave_m[1][lr]), fmaxf(wave_m[2][lr], wave_m[3][lr]));
+
+    // ---- e and this wave's 64 leaves of the tree: stride 32 pairs the steps, 16 and 8 lanes, 4 registers, 2 and 1 lanes
+    {
+        float a[8];
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                s[st][k] = exp_nonpos(s[st][k] - m_c);
+                a[k] = st == 0 ? s[st][k] : a[k] + s[st][k];
+            }
+        const float r0 = add32(a[0], a[1]), r1 = add32(a[2], a[3]), r2 = add32(a[4], a[5]), r3 = add32(a[6], a[7]);
+        const float t4 = add16(r0, r1) + add16(r2, r3);
+        const float t2 = add16(t4, t4);
+        const float t1 = add32(t2, t2);
+        if (g == 0) wave_l[wave][lr] = t1;
+        if (lr < G) {
+#pragma unroll
+            for (int st = 0; st < 2; ++st)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    *reinterpret_cast<float4*>(&es[sc_index(lr, 64 * wave + 32 * st + 8 * g + 4 * h)]) =
+                        make_float4(s[st][4 * h], s[st][4 * h + 1], s[st][4 * h + 2], s[st][4 * h + 3]);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < 16; ++b) {
+        const int tok = 64 * wave + 4 * b + g;  // token % 4 = g, token / 8 % 2 = b / 2 % 2
+        vbuf[tok * 16 + ((((lr >> 1) ^ (g | (((b >> 1) & 1) << 2))) << 1) | (lr & 1))] = vr[b];
+    }
+    __syncthreads();
+    const float l_c = (wave_l[0][lr] + wave_l[2][lr]) + (wave_l[1][lr] + wave_l[3][lr]);
+
+    // ---- weighted sums: wave w owns d = 32w .. 32w+31, all tokens in ascending steps (steps past the length would add zeros)
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    typedef __attribute__((address_space(3))) short4v lds_short4;
+    const uint32_t vbase = (uint32_t)(uintptr_t)(lds_char_t*)vbuf + (uint32_t)(8 * g + (lr >> 2)) * 256u + 8u * (uint32_t)(lr & 3);
+    const uint32_t f = (uint32_t)((lr >> 2) | ((g & 1) << 2));
+    auto pv_step = [&](int st) {
+        float e[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) e[k] = 0.0f;
+        if (lr < G) {
+            const float4 a = *reinterpret_cast<const float4*>(&es[sc_index(lr, 32 * st + 8 * g)]);
+            const float4 b = *reinterpret_cast<const float4*>(&es[sc_index(lr, 32 * st + 8 * g + 4)]);
+            e[0] = a.x, e[1] = a.y, e[2] = a.z, e[3] = a.w;
+            e[4] = b.x, e[5] = b.y, e[6] = b.z, e[7] = b.w;
+        }
+        bf16x8 piece[3];
+        split_pieces(e, piece);
+        bf16x8 vf[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t at = vbase + (uint32_t)st * 8192u + (((uint32_t)(2 * wave + u) ^ f) << 5);
+            typedef short short8v __attribute__((ext_vector_type(8)));
+            const short4v v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(uintptr_t)at);
+            const short4v v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(uintptr_t)(at + 1024u));
+            vf[u] = __builtin_bit_cast(bf16x8, (short8v)__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+#pragma unroll
+        for (int y = 0; y < 3; ++y)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[u], piece[y], acc[u], 0, 0, 0);
+    };
+    if (held > kChunk - 32) {
+#pragma unroll
+        for (int st = 0; st < 8; ++st) pv_step(st);
+    } else {
+        for (int st = 0; 32 * st < held; ++st) pv_step(st);
+    }
+
+    // lane holds O[d = 32w + 16u + 4g + v][pair lr]
+    if (lr >= G) return;
+    if (DIRECT && len <= kChunk) {
+        // the row's only chunk: what the second pass would compute from the single partial, with its operations
+        const float w = det_expf(m_c - m_c);
+        const float wl = w * l_c;
+        const float L = 0.0f + wl;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            float y[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float wo = w * acc[u][v];
+                const float O = 0.0f + wo;
+                y[v] = O / L;
+            }
+            *reinterpret_cast<uint2*>(orow + lr * kD + 32 * wave + 16 * u + 4 * g) =
+                make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+        }
+    }
+    const size_t part = ((size_t)r * Hq + (size_t)hgrp * G + lr) * ncmax + c;
+    if (wave == 0 && g == 0) {
+        ws_m[part] = m_c;
+        ws_l[part] = l_c;
+    }
+    if (DIRECT && len <= kChunk) return;
+    float* op = ws_o + part * kD + 32 * wave + 4 * g;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        float2* dst = reinterpret_cast<float2*>(op + 16 * u);  // 8-byte stores: ws_o is only that aligned
+        dst[0] = make_float2(acc[u][0], acc[u][1]);
+        dst[1] = make_float2(acc[u][2], acc[u][3]);
+    }
+}
+
 // The rows of a slot-naming call that a walking launch leaves (attn_rows.h), as a bit per row in LDS; returns the words in use.
 // All of the workgroup's threads call it.
 constexpr int kLeftWords = 1024;  // 65535 rows
@@ -787,8 +982,11 @@ int det::attn_decode_impl(const void* q, const void* kcache, const void* vcache,
     //   * rows that name their slots (prefill: consecutive rows of a prompt share a slot) walk their chunks in
     //     one workgroup where there are enough of them (kWalkWorkgroups); fewer, but sixteen or more, go eight to
     //     a workgroup per chunk, so that they share each chunk of K and V;
-    //   * launches of a few dozen workgroups (one sequence, short context) are all latency: every query
-    //     head then gets a workgroup of its own, which divides a workgroup's statistics and PV work by G.
+    //   * other rows: launches that are one round of two workgroups a compute unit are all latency and take
+    //     attn_chunk_kernel (one sequence of 4096 tokens, 32/8 heads 15.7 -> 12.6 us, where a workgroup for every query
+    //     head, each reading the chunk again, was the best of the other; 64 of 100 tokens 10.0 -> 8.1); larger ones
+    //     want the four workgroups a compute unit that attn_tile_kernel has room for (64 ragged sequences of up to 1024
+    //     tokens 37.1 against 39.2, 32 of 600 21.8 against 24.7), and so do heads with K and V of their own (G = 1).
     const bool tiled = slots != nullptr && B >= 16;
     if (tiled && attn_walk_workgroups(B, G, Hkv) >= kWalkWorkgroups) {
         if (qscales && !aligned16(qscales)) return DET_EALIGN;
@@ -799,36 +997,44 @@ int det::attn_decode_impl(const void* q, const void* kcache, const void* vcache,
                          Hq, Hkv, Lmax, ncmax, scale, s);
     }
     const int RT = tiled ? 8 : 1;
-    const bool split_heads = !tiled && G > 1 && (size_t)ncmax * Hkv * B <= 128;
-    const dim3 grid(ncmax, split_heads ? Hq : Hkv, (B + RT - 1) / RT);
+    const bool by_chunk = !tiled && G > 1 && (size_t)ncmax * Hkv * B <= 512;
+    const dim3 grid(ncmax, Hkv, (B + RT - 1) / RT);
     const uint16_t* qq = static_cast<const uint16_t*>(q);
     const uint16_t* kk = static_cast<const uint16_t*>(kcache);
     const uint16_t* vv = static_cast<const uint16_t*>(vcache);
     // Without the quantizing second pass, the first pass itself finishes every row of at most one chunk.
     const bool direct = qscales == nullptr;
     uint16_t* out16 = static_cast<uint16_t*>(out);
-#define DET_LAUNCH_ATTN2(GG, RTV, DIR)                                                                              \
+#define DET_LAUNCH_TILE(GG, RTV, DIR)                                                                                   \
     hipLaunchKernelGGL((attn_tile_kernel<GG, RTV, DIR>), grid, dim3(256), 0, s, qq, kk, vv, seqlens, slots, ws_m, ws_l, \
                        ws_o, out16, B, Hq, Hkv, Lmax, ncmax, scale, len_offset)
+#define DET_LAUNCH_CHUNK(GG, DIR)                                                                                       \
+    hipLaunchKernelGGL((attn_chunk_kernel<GG, DIR>), grid, dim3(256), 0, s, qq, kk, vv, seqlens, slots, ws_m, ws_l, ws_o, \
+                       out16, Hq, Hkv, Lmax, ncmax, scale, len_offset)
 #define DET_LAUNCH_ATTN(GG)                                \
     do {                                                   \
         if (tiled && direct)                               \
-            DET_LAUNCH_ATTN2(GG, 8, true);                 \
+            DET_LAUNCH_TILE(GG, 8, true);                  \
         else if (tiled)                                    \
-            DET_LAUNCH_ATTN2(GG, 8, false);                \
+            DET_LAUNCH_TILE(GG, 8, false);                 \
+        else if (GG > 1 && by_chunk && direct)             \
+            DET_LAUNCH_CHUNK((GG > 1 ? GG : 2), true);     \
+        else if (GG > 1 && by_chunk)                       \
+            DET_LAUNCH_CHUNK((GG > 1 ? GG : 2), false);    \
         else if (direct)                                   \
-            DET_LAUNCH_ATTN2(GG, 1, true);                 \
+            DET_LAUNCH_TILE(GG, 1, true);                  \
         else                                               \
-            DET_LAUNCH_ATTN2(GG, 1, false);                \
+            DET_LAUNCH_TILE(GG, 1, false);                 \
     } while (0)
-    switch (split_heads ? 1 : G) {
+    switch (G) {
         case 1: DET_LAUNCH_ATTN(1); break;
         case 2: DET_LAUNCH_ATTN(2); break;
         case 4: DET_LAUNCH_ATTN(4); break;
         default: DET_LAUNCH_ATTN(8); break;
     }
 #undef DET_LAUNCH_ATTN
-#undef DET_LAUNCH_ATTN2
+#undef DET_LAUNCH_CHUNK
+#undef DET_LAUNCH_TILE
     int rc = check_launch();
     if (rc != DET_OK) return rc;
     if (qscales) {

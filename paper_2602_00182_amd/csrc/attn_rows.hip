@@ -4,6 +4,7 @@
 // and who computes them differs.
 #include <math.h>
 
+#include "attn_lane.h"
 #include "attn_rows.h"
 #include "internal.h"
 #include "stream.h"
@@ -17,55 +18,6 @@ constexpr int kSub = 64;      // tokens of a staged subtile: 16 KB of K or V, on
 constexpr int kD = 128;
 constexpr int kSlots = 4;     // ring of staged subtiles
 constexpr int kTableChunks = 44;  // chunks whose maxima are kept in LDS between the sweeps
-
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t fbits(float v) { return __builtin_bit_cast(uint32_t, v); }
-__device__ __forceinline__ float bitsf(uint32_t v) { return __builtin_bit_cast(float, v); }
-
-// Rows of sixteen lanes 0..3.  add32(a, b): rows 0, 1 get a[row] + a[row+2], rows 2, 3 get b[row-2] + b[row].
-// add16(a, b): rows 0, 2 get a[row] + a[row+1], rows 1, 3 get b[row-1] + b[row].
-__device__ __forceinline__ float add32(float a, float b)
-{
-    const uint2v r = __builtin_amdgcn_permlane32_swap(fbits(a), fbits(b), false, false);
-    return bitsf(r[0]) + bitsf(r[1]);
-}
-__device__ __forceinline__ float add16(float a, float b)
-{
-    const uint2v r = __builtin_amdgcn_permlane16_swap(fbits(a), fbits(b), false, false);
-    return bitsf(r[0]) + bitsf(r[1]);
-}
-// maximum over the four lanes that hold one pair (lr, lr+16, lr+32, lr+48), in all four
-__device__ __forceinline__ float max_rows(float v)
-{
-    uint2v r = __builtin_amdgcn_permlane32_swap(fbits(v), fbits(v), false, false);
-    v = fmaxf(bitsf(r[0]), bitsf(r[1]));
-    r = __builtin_amdgcn_permlane16_swap(fbits(v), fbits(v), false, false);
-    return fmaxf(bitsf(r[0]), bitsf(r[1]));
-}
-
-// det_expf for arguments that are never positive (a score minus the maximum of its chunk): the same operations
-// without the overflow test.  NaN stays NaN (the integer conversion of NaN is 0 in hardware; written as the
-// instruction because the C conversion is undefined there).
-__device__ __forceinline__ float exp_nonpos(float x)
-{
-    const float n = __builtin_rintf(x * 0x1.715476p+0f);
-    float r = __builtin_fmaf(n, -0x1.62e4p-1f, x);
-    r = __builtin_fmaf(n, -0x1.7f7d1cp-20f, r);
-    float p = 0x1.a01a02p-13f;
-    p = __builtin_fmaf(p, r, 0x1.6c16c2p-10f);
-    p = __builtin_fmaf(p, r, 0x1.111112p-7f);
-    p = __builtin_fmaf(p, r, 0x1.555556p-5f);
-    p = __builtin_fmaf(p, r, 0x1.555556p-3f);
-    p = __builtin_fmaf(p, r, 0.5f);
-    p = __builtin_fmaf(p, r, 1.0f);
-    p = __builtin_fmaf(p, r, 1.0f);
-    int ni;
-    asm("v_cvt_i32_f32 %0, %1" : "=v"(ni) : "v"(n));
-    const float y = bitsf(fbits(p) + ((uint32_t)ni << 23));
-    return x < -87.0f ? 0.0f : y;
-}
 
 // the value of a variable that is the same in every lane, for the scalar unit
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -319,30 +271,12 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
                         vt[h & 1][x][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(uintptr_t)(at + 1024u));
                     }
                 };
-                // e = hi + mid + lo exactly, by truncation
                 bf16x8 piece[3];
-                auto split = [&](int st) __attribute__((always_inline)) {
-                    uint32_t w[3][8];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const float x = e[st][k];
-                        w[0][k] = fbits(x) & 0xFFFF0000u;
-                        const float r1 = x - bitsf(w[0][k]);
-                        w[1][k] = fbits(r1) & 0xFFFF0000u;
-                        w[2][k] = fbits(r1 - bitsf(w[1][k]));  // at most 8 significant bits: exact in bf16
-                    }
-#pragma unroll
-                    for (int y = 0; y < 3; ++y)  // the upper halves, in order
-                        piece[y] = __builtin_bit_cast(bf16x8, make_uint4(__builtin_amdgcn_perm(w[y][1], w[y][0], 0x07060302u),
-                                                                         __builtin_amdgcn_perm(w[y][3], w[y][2], 0x07060302u),
-                                                                         __builtin_amdgcn_perm(w[y][5], w[y][4], 0x07060302u),
-                                                                         __builtin_amdgcn_perm(w[y][7], w[y][6], 0x07060302u)));
-                };
                 read_v(0);
-                split(0);
+                split_pieces(e[0], piece);
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
-                    if (h == 2) split(1);
+                    if (h == 2) split_pieces(e[1], piece);
                     if (h < 3) read_v(h + 1);
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

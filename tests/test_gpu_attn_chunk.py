@@ -1,0 +1,57 @@
+"""Decode attention in the form small launches take (at most 512 workgroups, one for a chunk and KV head): the bytes of the
+same sequences in a larger batch, which takes the other form, at lengths around the steps, subtiles and chunks, with cache
+tails that are not finite, and with the output quantized."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import detsynth as ds
+from gpu_util import DEV, step, up, up_bf16
+
+pytestmark = pytest.mark.gpu
+
+SCALE = float(np.float32(1.0 / math.sqrt(128.0)))
+LENS = [700, 1, 31, 32, 33, 63, 64, 65, 0, -3, 127, 224, 225, 255, 256, 257, 288, 300, 511, 512, 513, 699]
+
+
+@pytest.fixture(scope="module")
+def d():
+    import paper_2602_00182_amd as d
+    return d
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(32, 8), (16, 2), (8, 4)])
+@pytest.mark.parametrize("quant", [False, True])
+def test_small_launch_equals_large_launch(d, Hq, Hkv, quant):
+    Lmax = 700
+    B = 3 * 512 // (3 * Hkv) + len(LENS)          # more than 512 workgroups of three chunks
+    lens = LENS + [1] * (B - len(LENS))
+    q = up_bf16(ds.normal_bf16(9500 + Hq, (B, Hq, 128)))
+    k = up_bf16(ds.normal_bf16(9501 + Hq, (B, Hkv, Lmax, 128)))
+    v = up_bf16(ds.normal_bf16(9502 + Hq, (B, Hkv, Lmax, 128)))
+    for b, n in enumerate(lens):
+        k[b, :, max(n, 0):] = float("inf")
+        v[b, :, max(n, 0):] = float("nan")
+    lens_t = up(np.asarray(lens, dtype=np.int32))
+
+    def run(p):
+        n = p.stop - p.start
+        ws = torch.full((d.det_attn_decode_workspace_bytes(n, Hq, 128, Lmax),), 0xFF, dtype=torch.uint8, device=DEV)
+        if not quant:
+            out = torch.full((n, Hq, 128), 7.0, dtype=torch.bfloat16, device=DEV)
+            d.det_attn_decode(q[p], k[p], v[p], lens_t[p], out, ws, SCALE)
+            return out.view(torch.int16)
+        codes = torch.full((n, Hq * 128), 99, dtype=torch.int8, device=DEV)
+        scales = torch.full((Hq * 2, (n + 3) & ~3), 7.0, dtype=torch.float32, device=DEV)
+        d.det_attn_decode_quant_q8(q[p], k[p], v[p], lens_t[p], None, codes, scales.view(-1), ws, SCALE)
+        return torch.cat([codes.view(torch.int32), scales[:, :n].t().contiguous().view(torch.int32)], 1)
+
+    step(f"attention by chunk, heads {Hq}/{Hkv} quant={quant}")
+    want = run(slice(0, B))
+    torch.cuda.synchronize()
+    for i in range(0, len(LENS), 5):
+        p = slice(i, min(i + 5, len(LENS)))
+        assert 3 * Hkv * (p.stop - p.start) <= 512 < 3 * Hkv * B
+        assert torch.equal(run(p), want[p]), LENS[p]
