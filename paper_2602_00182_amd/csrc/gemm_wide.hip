@@ -31,9 +31,9 @@ __device__ __forceinline__ void wait_loads()
 // a load) and 16 KB of weights (blocks in operand order) a step, each wave loading its share.  What bounds the
 // 256 x 128 tile of gemm.hip is the fill of LDS, 48 KB for 64 * 256 * 128 products; 256 x 256 is 64 KB for twice the work.
 // The operands of step t+1 are read from LDS into registers while step t is in the matrix cores, so a step needs one
-// barrier and no wait for its own reads, and its slot is free as soon as it starts.  A 256-row tile then takes 13 ns a
-// matrix instruction (8 ns with operands that never change and nothing else in the loop): with the loads taken out 11, with
-// the operand reads taken out 11.6, the loads alone 7.5.
+// barrier and no wait for its own reads, and its slot is free as soon as it starts.  A 256-row tile then takes 12.2 ns a
+// matrix instruction (8 ns with operands that never change and nothing else in the loop; before the reads were dealt out
+// among the products 13, then 11 with the loads taken out, 11.6 with the reads taken out, 7.5 for the loads alone).
 template <int RBW, int EPI>
 __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uint16_t* __restrict__ A, int lda,
                                                                      const uint4* __restrict__ Bp, int cb, void* C, int ldc,
@@ -144,6 +144,15 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uin
         read(f, slot_r);
         slot_r = slot_r + 1 == NS ? 0 : slot_r + 1;
     };
+    // Deals a step's operand reads out among its products, one after each: read in a row, they leave the matrix cores idle
+    // behind the barrier (4096 x 6144, 700 rows 68.6 -> 63.8 us, 3302 rows 175 -> 165).
+    auto alternate = []() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4 + RBW; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a matrix-core instruction
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // an LDS read
+        }
+    };
 
 #pragma unroll
     for (int t = 0; t < NS - 1; ++t)
@@ -155,11 +164,11 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uin
         open(t);
         next(f1);
         products(f0);
-        if (t + 2 < nst) {
-            open(t + 1);
-            next(f0);
-        }
+        alternate();
+        if (t + 2 < nst) open(t + 1);
+        next(f0);  // (past the last step: whatever the slot holds, not used)
         products(f1);
+        alternate();
     }
 
     // Lane holds C[row = m0 + 16*(wr*RBW + r) + lr][n0 + 64*wc + 16j + 4g + v].
@@ -207,15 +216,15 @@ static void launch_rows(int rbw, const gemm_wide_args& a, hipStream_t s)
 }
 
 // What a launch costs is the rounds of 256 workgroups it takes, times what one of its tiles takes for a step of K, which is
-// nearly the same over all shapes (measured over K = 2048 .. 14336, N = 2048 .. 28672, 300 to 4096 rows): 0.52 / 0.65 /
-// 0.70 / 0.85 us for 128 / 160 / 192 / 256 rows here, 8 % more in launches of four rounds and more; for gemm.hip 0.53 us a
+// nearly the same over all shapes (measured over K = 2048 .. 14336, N = 2048 .. 28672, 300 to 4096 rows): 0.49 / 0.61 /
+// 0.66 / 0.79 us for 128 / 160 / 192 / 256 rows here, 8 % more in launches of four rounds and more; for gemm.hip 0.53 us a
 // round of its 256 x 128 tiles (0.51 in long launches, less for the rows a last tile lacks), and in its narrower tilings,
 // which it takes where those do not fill the chip, 1.4 ns for each row and column of a tile (16- and 32-column packings)
 // or the share of a round that 256 x 128 tiles would fill, in us (64-column packings).  So the choice is the tile height
-// whose tiles fit the rounds best: 3302 rows of N = 6144, K = 4096 are 13 x 48 tiles there (three rounds, 216 us), 13 x 24
-// of 256 rows here (two, 220 us), 21 x 24 of 160 rows (two, 170 us).  10 % must be won by this
+// whose tiles fit the rounds best: 3302 rows of N = 6144, K = 4096 are 13 x 48 tiles there (three rounds, 214 us), 13 x 24
+// of 256 rows here (two, 205 us), 21 x 24 of 160 rows (two, 159 us).  10 % must be won by this
 // count, 25 % where a tile there is as wide as the packing and the weights alone are much of the time.  Others: K x N
-// 4096 x 6144 700 rows 114 -> 67 us, 14336 x 4096 1500 rows 377 -> 208, 4096 x 28672 4096 rows 950 -> 856 (1.12 PFLOP/s;
+// 4096 x 6144 700 rows 114 -> 61 us, 14336 x 4096 1500 rows 373 -> 208, 4096 x 28672 4096 rows 919 -> 788 (1.22 PFLOP/s;
 // torch's product of two 8192 x 8192 matrices reaches 1.19 on the same card).
 int gemm_wide_rows(int M, int N, int K, int cb)
 {
@@ -235,7 +244,7 @@ int gemm_wide_rows(int M, int N, int K, int cb)
     }
     static const struct {
         int rbw, cost;
-    } kTiles[4] = {{4, 52}, {5, 65}, {6, 70}, {8, 85}};
+    } kTiles[4] = {{4, 49}, {5, 61}, {6, 66}, {8, 79}};
     int best = 0;
     long long best_cost = 100 * cost;
     for (const auto& t : kTiles) {

@@ -106,3 +106,17 @@ def test_infinite_and_nan_cache_rows(d):
     k[0, :, 300:] = float("nan")
     v[1, :, 229:] = float("inf")
     check(d, "not finite", q, k, v, lens, slots)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(32, 8), (32, 16), (64, 8), (32, 32)])
+@pytest.mark.parametrize("quant", [False, True])
+def test_few_long_rows_among_short_ones(d, Hq, Hkv, quant):
+    """Rows many times longer than the call's others are left to the per-chunk kernels, inside a tile of short rows too."""
+    Lmax = 5120
+    lens, slots = prompts([600])
+    for at, n in ((0, 5000), (17, 4097), (18, 2049), (300, 5120), (599, 4864)):
+        lens.insert(at, n)
+        slots.insert(at, 1 + at % 2)
+    q, k, v = inputs(4500 + Hq + Hkv, len(lens), Hq, 3, Hkv, Lmax)
+    pick = [i for i, n in enumerate(lens) if n > 600] + list(range(0, len(lens), 41))
+    check(d, "few long rows", q, k, v, lens, slots, quant, pick=pick)
