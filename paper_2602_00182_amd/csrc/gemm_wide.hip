@@ -217,13 +217,14 @@ static void launch_rows(int rbw, const gemm_wide_args& a, hipStream_t s)
 
 // What a launch costs is the rounds of 256 workgroups it takes, times what one of its tiles takes for a step of K, which is
 // nearly the same over all shapes (measured over K = 2048 .. 14336, N = 2048 .. 28672, 300 to 4096 rows): 0.49 / 0.61 /
-// 0.66 / 0.79 us for 128 / 160 / 192 / 256 rows here, 8 % more in launches of four rounds and more; for gemm.hip 0.53 us a
+// 0.66 / 0.79 us for 128 / 160 / 192 / 256 rows here; for gemm.hip 0.53 us a
 // round of its 256 x 128 tiles (0.51 in long launches, less for the rows a last tile lacks), and in its narrower tilings,
 // which it takes where those do not fill the chip, 1.4 ns for each row and column of a tile (16- and 32-column packings)
 // or the share of a round that 256 x 128 tiles would fill, in us (64-column packings).  So the choice is the tile height
 // whose tiles fit the rounds best: 3302 rows of N = 6144, K = 4096 are 13 x 48 tiles there (three rounds, 214 us), 13 x 24
 // of 256 rows here (two, 205 us), 21 x 24 of 160 rows (two, 159 us).  10 % must be won by this
-// count, 25 % where a tile there is as wide as the packing and the weights alone are much of the time.  Others: K x N
+// count, 25 % (19 % in launches of four rounds and more) where a tile there is as wide as the packing and the weights alone
+// are much of the time.  Others: K x N
 // 4096 x 6144 700 rows 114 -> 61 us, 14336 x 4096 1500 rows 373 -> 208, 4096 x 28672 4096 rows 919 -> 788 (1.22 PFLOP/s;
 // torch's product of two 8192 x 8192 matrices reaches 1.19 on the same card).
 int gemm_wide_rows(int M, int N, int K, int cb)
@@ -249,7 +250,7 @@ int gemm_wide_rows(int M, int N, int K, int cb)
     long long best_cost = 100 * cost;
     for (const auto& t : kTiles) {
         const long long n = rounds((long long)((M + 32 * t.rbw - 1) / (32 * t.rbw)) * (N / kWideCols));
-        const long long c = n * t.cost * (n >= 4 ? 119 : (cb < 8 ? 110 : 125));
+        const long long c = n * t.cost * (cb < 8 ? 110 : (n >= 4 ? 119 : 125));
         if (c < best_cost) best = t.rbw, best_cost = c;
     }
     return best;
