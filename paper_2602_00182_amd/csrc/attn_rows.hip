@@ -49,10 +49,10 @@ __device__ __forceinline__ void wait_then_barrier()
 // What bounds it is instruction issue: about 30 vector instructions a score (16 of them exp, 6 the split) and
 // 5 matrix instructions per 16 of them a lane; two workgroups a compute unit (247 registers).  Measured on
 // one layer, against eight rows a workgroup with chunk partials in memory and a second pass: prompts of 2000 +
-// 1400 + 1002 tokens, 32/8 heads 1276 -> 268 us; one of 4000 tokens 2240 -> 540 us; 24 of 16..512 tokens,
-// 16/4 heads 195 -> 100 us; 512 rows of 512 slots at 1000 tokens 533 -> 527 us.  Without the exponentials it
-// takes 233 us in the first case, with a third of the second product's instructions 232, with the loads and
-// barriers alone 109.
+// 1402 + 1000 tokens, 32/8 heads 1267 -> 242 us; one of 4000 tokens 2240 -> 540 us; 24 of 16..512 tokens,
+// 16/4 heads 195 -> 100 us; 512 rows of 512 slots at 1000 tokens 533 -> 527 us.  Copies cut
+// down from an earlier form that took 297 us on prompts of 2000 + 1400 + 1000 tokens: 234 without the exponentials, 109 with
+// the loads and barriers alone.
 //
 // The grid: `helpers` workgroups, then Hkv per tile, tiles from the last (longest prefixes first).  The (row, KV head)
 // groups of mixed tiles (attn_rows.h) are dealt out over the helpers, which find those tiles by looking at all rows.
