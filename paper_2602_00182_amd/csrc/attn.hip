@@ -91,8 +91,12 @@ __device__ __forceinline__ float combine_max(const float* mc, int nc)
 //           the hi, then the mid, then the lo products (V^T is the row operand, the pieces the column
 //           operand).  Tokens at or past the row's length have e = 0 and add +0.
 // Rows of a tile that name different slots are handled one slot after the other (same arithmetic, no
-// sharing).  V rows at or past the longest length in the workgroup are never read (zeros instead), K rows
-// likewise; what the cache holds there cannot reach an output.
+// sharing).  V rows at or past the longest length of such a group are never read (zeros instead), K rows
+// likewise.  A V row between two lengths of a group meets e = 0 in the shorter ones, which keeps a finite
+// value out of their sums but not an infinity or a NaN (0 * inf = NaN): where a group of several lengths ends
+// with a NaN, its rows are taken again one by one (the look for it costs 0.3 to 0.7 us a launch: sixteen rows at the end of
+// 300 tokens, 32/8 heads 20.5 -> 20.7 us, 100 rows of one prompt, 16/16 heads 10.0 -> 10.4).  So what the cache holds at and
+// past a row's length cannot reach that row's output.
 
 // Index (in uint4 = eight tokens of one head dimension) into the transposed V half tile: 128 rows (d) of 16
 // pieces (128 tokens), the pieces of a row rotated by d + d/8 so that both the transposing writes (rows 8
@@ -127,6 +131,7 @@ __device__ __forceinline__ void attn_tile(const uint16_t* __restrict__ q, const 
     __shared__ __align__(16) float sc[NP * kChunk];  // scores, then e_j
     __shared__ uint4 vt[128 * 16];                   // V^T of half a chunk: [d][token], 32 KB
     __shared__ float mc_s[NP], lc_s[NP];             // the pairs' chunk statistics (DIRECT only)
+    __shared__ int s_nan;                            // some sum of the group is a NaN
     const int kvh = (hgrp * G) / (Hq / Hkv);
     const int t0 = c * kChunk;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -138,25 +143,29 @@ __device__ __forceinline__ void attn_tile(const uint16_t* __restrict__ q, const 
     for (int ri = 0; ri < RT; ++ri) any = any || len[ri] > t0;
     if (!any) return;  // uniform over the workgroup
 
-    uint32_t done = 0;
+    uint32_t done = 0, alone = 0;  // rows computed, and rows that are groups of their own
     bool first_group = true;
 #pragma unroll 1
     for (int first = 0; first < RT; ++first) {
-        if (((done >> first) & 1u) || len[first] <= t0) continue;
-        const int group_slot = slot[first];
+        if (((done >> first) & 1u) || uni(len[first]) <= t0) continue;
+        const int group_slot = uni(slot[first]);
         uint32_t mask = 0;
-        int maxlen = 0;
+        int minlen = 0x7FFFFFFF, maxlen = 0;
 #pragma unroll
         for (int ri = 0; ri < RT; ++ri) {
-            const int l = len[ri];
-            if (l > t0 && slot[ri] == group_slot) {
+            const int l = uni(len[ri]);
+            if (l > t0 && uni(slot[ri]) == group_slot && (ri == first || !((alone >> first | alone >> ri) & 1u))) {
                 mask |= 1u << ri;
+                minlen = l < minlen ? l : minlen;
                 maxlen = l > maxlen ? l : maxlen;
             }
         }
         done |= mask;
         if (!first_group) __syncthreads();  // the previous group's LDS contents are no longer read
         first_group = false;
+        // tokens of this chunk at or past the shortest length and below the longest (uniform over the workgroup)
+        const bool window = RT > 1 && minlen < maxlen && minlen < t0 + kChunk;
+        if (window && tid == 0) s_nan = 0;  // (set below, barriers later)
 
         const size_t kv_base = ((size_t)group_slot * Hkv + kvh) * (size_t)Lmax * kD;
         const uint16_t* kp = kcache + kv_base;
@@ -320,6 +329,20 @@ __device__ __forceinline__ void attn_tile(const uint16_t* __restrict__ q, const 
         store_vt();
         __syncthreads();
         pv_half(1);
+        if (window) {
+            f32x4 t = acc[0];  // a NaN stays one (so does inf - inf, at the cost of a needless repetition)
+#pragma unroll
+            for (int u = 1; u < DPW; ++u) t += acc[u];
+            const float nan = (t[0] + t[1]) + (t[2] + t[3]);
+            if (nan != nan && pp < NP && ((mask >> (pp / G)) & 1u)) s_nan = 1;
+            __syncthreads();
+            if (s_nan) {  // again, one by one
+                alone |= mask;
+                done &= ~mask;
+                --first;
+                continue;
+            }
+        }
 
         // lane holds O[d = 16*(db0+u) + 4g + v][pair pp]
         bool mine = false;

@@ -12,6 +12,9 @@ typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t fbits(float v) { return __builtin_bit_cast(uint32_t, v); }
 __device__ __forceinline__ float bitsf(uint32_t v) { return __builtin_bit_cast(float, v); }
 
+// the value of a variable that is the same in every lane, for the scalar unit
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // Rows of sixteen lanes 0..3.  add32(a, b): rows 0, 1 get a[row] + a[row+2], rows 2, 3 get b[row-2] + b[row].
 // add16(a, b): rows 0, 2 get a[row] + a[row+1], rows 1, 3 get b[row-1] + b[row].
 __device__ __forceinline__ float add32(float a, float b)

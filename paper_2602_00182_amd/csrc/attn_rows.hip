@@ -19,9 +19,6 @@ constexpr int kD = 128;
 constexpr int kSlots = 4;     // ring of staged subtiles
 constexpr int kTableChunks = 44;  // chunks whose maxima are kept in LDS between the sweeps
 
-// the value of a variable that is the same in every lane, for the scalar unit
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
 template <int N>
 __device__ __forceinline__ void wait_then_barrier()
 {
