@@ -942,29 +942,6 @@ static int qgemm_dispatch(const void* codes, const void* scales, const void* pac
     return check_launch();
 }
 
-// det_qgemm_w4a8_swiglu_quant wherever some kernel's tile row holds whole 64-output blocks (the decoder layer's own
-// call; the exported one takes the shapes that do at every row count).
-bool qgemm_swiglu_quant_fits(int M, int F, int K)
-{
-    return det_qgemm_w4a8_swiglu_quant_supported(F, K) || (F % 64 == 0 && F <= (1 << 29) && qgemm_tall_pays(M, 2 * F));
-}
-int qgemm_swiglu_quant(const void* codes, const void* scales, const void* packed_gate_up, void* codes_out, void* scales_out, int M,
-                       int F, int K, void* stream)
-{
-    if (det_qgemm_w4a8_swiglu_quant_supported(F, K))
-        return det_qgemm_w4a8_swiglu_quant(codes, scales, packed_gate_up, codes_out, scales_out, M, F, K, stream);
-    const int ld = q_ldd(M);
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    float* d = static_cast<float*>(scales_out);
-    const gemm_rope_args ra{};
-    switch (qgemm_cols_per_block(2 * F)) {
-        case 1: launch_qgemm_tall<1, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
-        case 2: launch_qgemm_tall<2, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
-        default: launch_qgemm_tall<4, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
-    }
-    return check_launch();
-}
-
 static bool qgemm_shape_ok(int N, int K) { return N > 0 && K > 0 && N % 16 == 0 && K % 64 == 0 && K <= (1 << 22); }
 
 }  // namespace det
@@ -1094,6 +1071,33 @@ extern "C" int det_qgemm_w4a8_swiglu_quant(const void* codes, const void* scales
     // the kernel's ldr argument carries the row stride of the output scales
     launch_qgemm<8, kEpiSwigluQuant>(codes, scales, q_ldd(M), packed_gate_up, codes_out, F, nullptr, q_ldd(M), M, 2 * F, K, 0,
                                      static_cast<hipStream_t>(stream), static_cast<float*>(scales_out));
+    return check_launch();
+}
+
+// det_qgemm_w4a8_swiglu_quant wherever some kernel's tile row holds whole 64-output blocks (the decoder layer's own
+// call; the exported one takes the shapes that do at every row count).
+bool det::qgemm_swiglu_quant_fits(int M, int F, int K)
+{
+    return det_qgemm_w4a8_swiglu_quant_supported(F, K) || (F % 64 == 0 && F <= (1 << 29) && qgemm_tall_pays(M, 2 * F));
+}
+int det::qgemm_swiglu_quant(const void* codes, const void* scales, const void* packed_gate_up, void* codes_out,
+                            void* scales_out, int M, int F, int K, void* stream)
+{
+    if (det_qgemm_w4a8_swiglu_quant_supported(F, K))
+        return det_qgemm_w4a8_swiglu_quant(codes, scales, packed_gate_up, codes_out, scales_out, M, F, K, stream);
+    const int rc = qgemm_args_ok(codes, scales, packed_gate_up, codes_out, F, M, 2 * F, F, K);
+    if (rc != DET_OK) return rc;
+    if (!scales_out) return DET_EINVAL;
+    if (!aligned16(scales_out)) return DET_EALIGN;
+    const int ld = q_ldd(M);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    float* d = static_cast<float*>(scales_out);
+    const gemm_rope_args ra{};
+    switch (qgemm_cols_per_block(2 * F)) {
+        case 1: launch_qgemm_tall<1, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
+        case 2: launch_qgemm_tall<2, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
+        default: launch_qgemm_tall<4, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
+    }
     return check_launch();
 }
 

@@ -80,3 +80,32 @@ def test_quantized_layer_rows_equal_small_calls(d, R, H, Hq, Hkv, F):
     step(f"quantized layer R={R} H={H} heads {Hq}/{Hkv} F={F}")
     for got, want in zip(run([slice(0, R)]), run(parts(R))):
         assert torch.equal(got, want)
+
+
+def test_quantized_layer_refuses_misaligned_gate_up_weights(d):
+    """Whichever kernel quantizes the SwiGLU output: 390 rows of F = 5632 take the tall tiles, 5 rows the two steps."""
+    H, Hq, Hkv, D, F, Lmax = 256, 2, 1, 128, 5632, 390
+    g = lambda s, shape, std=0.05, mean=0.0: up_bf16(ds.normal_bf16(s, shape, std, mean))
+    gu = d.quant_pack_gate_up(g(5, (H, 2 * F)))
+    shifted = torch.zeros(gu.numel() * gu.element_size() + 16, dtype=torch.uint8, device=DEV)
+    w = d.layer_weights(g(1, (H,), 0.1, 1.0), d.quant_pack_qkv(g(2, (H, (Hq + 2 * Hkv) * D)), Hq, Hkv, D),
+                        d.quant_pack_weight(g(3, (Hq * D, H))), g(4, (H,), 0.1, 1.0), gu, d.quant_pack_weight(g(6, (F, H))))
+    cfg = d.layer_cfg(H, Hq, Hkv, D, F, Lmax, 1e-5, 0.08838834764831845)
+    cos = sin = torch.zeros((Lmax, 64), device=DEV)
+    k = torch.zeros((1, Hkv, Lmax, D), dtype=torch.bfloat16, device=DEV)
+    v = torch.zeros_like(k)
+
+    def run(R):
+        ws = torch.empty((d.det_qdecoder_layer_workspace_bytes(cfg, R),), dtype=torch.uint8, device=DEV)
+        pos = torch.arange(R, dtype=torch.int32, device=DEV)
+        d.det_qdecoder_layer(w, cfg, g(7, (R, H), 1.0), k, v, pos, torch.zeros_like(pos), cos, sin, ws)
+        torch.cuda.synchronize()
+
+    for R in (390, 5):
+        step(f"misaligned gate/up weights R={R}")
+        w.wgu = gu.data_ptr()
+        run(R)
+        w.wgu = shifted.data_ptr() + 8
+        with pytest.raises(d.DetError) as e:
+            run(R)
+        assert e.value.code == 3
