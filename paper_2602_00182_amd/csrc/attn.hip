@@ -639,8 +639,8 @@ __device__ __forceinline__ int find_left_rows(const int32_t* __restrict__ seqlen
 }
 
 // Pass 1 for those rows, eight to a workgroup as in attn_tile_kernel: items are (chunk, KV head, eight rows), dealt
-// out over the grid in runs of kLeftRun, so that the rows that walk cost no workgroups.
-constexpr int kLeftRun = 4;
+// round-robin over the grid, so that the rows that walk cost no workgroups.  (Dealt in runs of four, a few long rows kept few
+// workgroups busy: 32 sequences of 1000 to 4000 tokens beside a prompt of 497, 32/8 heads 449 us for the call, 230 so.)
 template <int G, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void attn_left_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kcache,
                                                           const uint16_t* __restrict__ vcache,
@@ -654,8 +654,8 @@ __global__ __launch_bounds__(256, 2) void attn_left_kernel(const uint16_t* __res
     __shared__ uint64_t left[kLeftWords];
     __shared__ int len[RT], slot[RT], scratch;
     const int words = find_left_rows<G>(seqlens, slots, len_offset, Lmax, R, Hkv, left, &scratch);
-    const int per_tile = Hkv * ncmax, jump = kLeftRun * ((int)gridDim.x - 1);
-    int next = kLeftRun * (int)blockIdx.x, in_run = 0;  // this workgroup's next item, counted from the current tile's first
+    const int per_tile = Hkv * ncmax;
+    int next = (int)blockIdx.x;  // this workgroup's next item, counted from the current tile's first
 #pragma unroll 1
     for (int w = 0; w < words; ++w) {
         const uint64_t word = left[w];
@@ -676,15 +676,10 @@ __global__ __launch_bounds__(256, 2) void attn_left_kernel(const uint16_t* __res
                 __syncthreads();
             }
 #pragma unroll 1
-            while (next < per_tile) {
+            for (; next < per_tile; next += (int)gridDim.x) {
                 attn_tile<G, RT, DIRECT>(q, kcache, vcache, ws_m, ws_l, ws_o, out, Hq, Hkv, Lmax, ncmax, scale, next / Hkv,
                                          next % Hkv, tile, len, slot);
                 __syncthreads();  // its LDS contents are no longer read
-                ++next;
-                if (++in_run == kLeftRun) {
-                    in_run = 0;
-                    next += jump;
-                }
             }
             next -= per_tile;
         }
@@ -795,7 +790,8 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const int32_t* __rest
                         ldd, first_pass_wrote_short_rows);
 }
 
-// Pass 2 for those rows, (row, head) items dealt round-robin over the grid.
+// Pass 2 for those rows, (row, head) items dealt round-robin over the grid.  A workgroup finds its next item's row by
+// counting the rows of whole words (looking at the rows one by one took 80 us for 961 of them).
 template <int G, bool QUANT>
 __global__ __launch_bounds__(128) void attn_left_combine_kernel(const int32_t* __restrict__ seqlens,
                                                                 const int32_t* __restrict__ slots,
@@ -808,21 +804,23 @@ __global__ __launch_bounds__(128) void attn_left_combine_kernel(const int32_t* _
     __shared__ uint64_t left[kLeftWords];
     __shared__ int scratch;
     const int words = find_left_rows<G>(seqlens, slots, len_offset, Lmax, R, Hkv, left, &scratch);
-    int next = (int)blockIdx.x;  // this workgroup's next item, counted from the current row's first
+    const int lane = (int)threadIdx.x & 63;
+    int word = 0, before = 0;  // the word of the current item's row, and the rows of the words before it
 #pragma unroll 1
-    for (int w = 0; w < words; ++w) {
-#pragma unroll 1
-        for (uint64_t word = left[w]; word != 0; word &= word - 1) {
-            const int b = 64 * w + __builtin_ctzll(word);
-            if (next < Hq) {
-                const int len = attn_row_len(seqlens, b, len_offset, Lmax);
-                for (; next < Hq; next += (int)gridDim.x) {
-                    __syncthreads();  // the previous item's weights are no longer read
-                    attn_combine<QUANT>(next, b, len, ws_m, ws_l, ws_o, out, Hq, ncmax, scales, ldd, QUANT ? 0 : 1);
-                }
-            }
-            next -= Hq;
+    for (int item = (int)blockIdx.x;; item += (int)gridDim.x) {
+        const int row = item / Hq;  // counted over those rows
+        for (; word < words; ++word) {
+            const int n = __builtin_popcountll(left[word]);
+            if (row < before + n) break;
+            before += n;
         }
+        if (word >= words) return;
+        const uint64_t bits = left[word];
+        const bool it = ((bits >> lane) & 1ull) && __builtin_popcountll(bits & ((1ull << lane) - 1ull)) == row - before;
+        const int b = 64 * word + __builtin_ctzll(__ballot(it));
+        __syncthreads();  // the previous item's weights are no longer read
+        attn_combine<QUANT>(item % Hq, b, attn_row_len(seqlens, b, len_offset, Lmax), ws_m, ws_l, ws_o, out, Hq, ncmax, scales,
+                            ldd, QUANT ? 0 : 1);
     }
 }
 
@@ -900,17 +898,18 @@ static void launch_left(const void* q, const void* kcache, const void* vcache, c
 {
     const uint16_t *qq = static_cast<const uint16_t*>(q), *kk = static_cast<const uint16_t*>(kcache),
                    *vv = static_cast<const uint16_t*>(vcache);
-    const dim3 grid(512);  // two workgroups a compute unit
+    const dim3 grid(G == 8 ? 256 : 512), grid2(1024);  // pass 1: what is resident at a time (G = 8 needs 104 KB of LDS)
     if (qscales) {
         hipLaunchKernelGGL((attn_left_kernel<G, false>), grid, dim3(256), 0, s, qq, kk, vv, seqlens, slots, ws_m, ws_l, ws_o,
                            nullptr, R, Hq, Hkv, Lmax, ncmax, scale, len_offset);
-        hipLaunchKernelGGL((attn_left_combine_kernel<G, true>), dim3(2048), dim3(128), 0, s, seqlens, slots, ws_m, ws_l, ws_o,
+        hipLaunchKernelGGL((attn_left_combine_kernel<G, true>), grid2, dim3(128), 0, s, seqlens, slots, ws_m, ws_l, ws_o,
                            out, R, Hq, Hkv, Lmax, ncmax, len_offset, qscales, (R + 3) & ~3);
     } else {
         hipLaunchKernelGGL((attn_left_kernel<G, true>), grid, dim3(256), 0, s, qq, kk, vv, seqlens, slots, ws_m, ws_l, ws_o,
                            static_cast<uint16_t*>(out), R, Hq, Hkv, Lmax, ncmax, scale, len_offset);
-        hipLaunchKernelGGL((attn_left_combine_kernel<G, false>), dim3(2048), dim3(128), 0, s, seqlens, slots, ws_m, ws_l, ws_o,
-                           out, R, Hq, Hkv, Lmax, ncmax, len_offset, nullptr, 0);
+        if (ncmax > 1)  // else every row is complete
+            hipLaunchKernelGGL((attn_left_combine_kernel<G, false>), grid2, dim3(128), 0, s, seqlens, slots, ws_m, ws_l, ws_o,
+                               out, R, Hq, Hkv, Lmax, ncmax, len_offset, nullptr, 0);
     }
 }
 static int attn_left(const void* q, const void* kcache, const void* vcache, const int32_t* seqlens, const int32_t* slots,

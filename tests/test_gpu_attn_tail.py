@@ -80,3 +80,15 @@ def test_many_slots_a_tile(d, Hq, Hkv, quant):
     lens, slots = [int(x) for x in r.integers(0, 584, 530)], [int(x) for x in r.integers(0, 6, 530)]
     poison = [(s, t, float(x)) for s, t, x in ((0, 500, "nan"), (1, 250, "inf"), (2, 80, "-inf"), (3, 580, "nan"), (4, 3, "inf"))]
     check(d, "many slots", 6300 + Hq + Hkv, Hq, Hkv, 6, 583, lens, slots, poison, quant, range(0, 530, 9))
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(32, 8), (32, 16), (64, 8), (32, 32)])
+@pytest.mark.parametrize("quant", [False, True])
+def test_long_rows_all_over_a_call(d, Hq, Hkv, quant):
+    """Seventy long rows of three slots scattered over seven hundred short ones."""
+    r = np.random.default_rng(62)
+    lens, slots = [int(x) for x in r.integers(0, 50, 700)], [0] * 700
+    at = sorted(int(x) for x in r.choice(700, 70, replace=False))
+    for i in at:
+        lens[i], slots[i] = int(r.integers(2049, 2900)), int(r.integers(1, 4))
+    check(d, "long rows all over", 6400 + Hq + Hkv, Hq, Hkv, 4, 2900, lens, slots, [(1, 2500, float("inf"))], quant, at + list(range(0, 700, 37)))
