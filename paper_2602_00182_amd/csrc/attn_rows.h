@@ -7,7 +7,6 @@
 namespace det {
 
 constexpr int kWalkPairs = 64;    // (row, head) pairs of a walking workgroup: 64 / G consecutive rows, a "tile"
-constexpr int kWalkGroups = 2, kWalkShortGroups = 8;  // see attn_classify_rows
 constexpr int kWalkChunks = 8;    // rows of at most this many chunks are never left for their length
 constexpr int kWalkSamples = 128;
 
@@ -43,13 +42,15 @@ __device__ __forceinline__ int attn_walk_limit(const int32_t* seqlens, int len_o
 
 // Rows of 64 consecutive ones (the first a multiple of 64), or of one tile, by how they are computed; lane i holds row
 // i's length (0 or less: no tokens) and slot.  ROWS: rows of a tile, 8, 16, 32 or 64, neighbouring lanes.
-//   deep : longer than `limit` chunks.
-//   mixed: the other rows of a tile that names many slots: more than kWalkGroups if it holds rows of more than a chunk,
-//          else more than kWalkShortGroups (counted as changes from row to row).  A walk shares nothing between
-//          slots, so they are not walked one after the other by the tile's own workgroup: sixteen slots of 1000 tokens
-//          would take it 500 us, sixteen of 100 tokens 140.
+//   deep  : longer than `limit` chunks: left to the per-chunk kernels.
+//   walks : the others that have tokens.  Those of a tile, in order, fall into runs of one slot; `starts` are the runs' first
+//           rows.  (The first row of a slot in its tile always starts a run.)
+//   mixed : rows that walk, of tiles of more than one run; where every head has K and V of its own (tiles of 64 rows), of more
+//           than two or, if it holds no row of more than a chunk, more than eight.  A walk shares nothing between slots, so they are not walked one
+//           after the other by the tile's own workgroup (sixteen slots of 1000 tokens would take it 500 us; eight rows
+//           a slot at 200 tokens, 994 rows, 32/8 heads 48 us that way, 45 dealt out; 18 prompts of up to 119 tokens 42 and 37).
 struct attn_row_classes {
-    uint64_t deep, mixed;
+    uint64_t deep, walks, starts, mixed;
 };
 template <int ROWS>
 __device__ __forceinline__ attn_row_classes attn_classify_rows(int len, int slot, int limit)
@@ -59,20 +60,22 @@ __device__ __forceinline__ attn_row_classes attn_classify_rows(int len, int slot
     attn_row_classes k;
     k.deep = __ballot(len > limit * 256);
     const bool walks = len > 0 && len <= limit * 256;
-    const int before = __shfl_up(slot, 1, 64);
-    const int changes = __builtin_popcountll(__ballot(walks && slot != before && (lane & (ROWS - 1)) != 0) & mine);
+    k.walks = __ballot(walks);
+    const uint64_t above = k.walks & mine & ((1ull << lane) - 1ull);  // walking rows of the tile before this one
+    const int before = __shfl(slot, above != 0 ? 63 - __builtin_clzll(above) : lane, 64);
+    k.starts = __ballot(walks && (above == 0 || slot != before));
     const uint64_t longer = __ballot(walks && len > 256) & mine;
-    k.mixed = __ballot(walks && changes + 1 > (longer != 0 ? kWalkGroups : kWalkShortGroups));
+    const int most = ROWS < 64 ? 1 : (longer != 0 ? 2 : 8);
+    k.mixed = __ballot(walks && __builtin_popcountll(k.starts & mine) > most);
     return k;
 }
 
 // The rows a walking launch leaves to the per-chunk kernels: the deep ones and, where every head has K and V of its
-// own (G = 1), the mixed ones: those read their cache from HBM, and a walk reads K twice (1024 rows of 1024 slots at
-// 500 tokens, 16/16 heads: 1147 us walked, 780 per chunk; with eight heads a KV head 201 walked, 500 per chunk).
+// own (G = 1), the mixed ones: those read their cache from HBM, and a walk reads K twice.
 template <int G>
 __device__ __forceinline__ uint64_t attn_left_rows(const attn_row_classes& k)
 {
-    return G == 1 ? k.deep | k.mixed : k.deep;
+    return G == 1 ? k.deep | (k.mixed & k.walks) : k.deep;
 }
 
 // f(w, classes) for the 64-row words w of all rows, dealt to the waves of the workgroup; eight words' loads at a time.
@@ -82,17 +85,17 @@ __device__ __forceinline__ void attn_for_row_words(const int32_t* __restrict__ s
 {
     constexpr int U = 8;
     const int words = (R + 63) >> 6, lane = threadIdx.x & 63, waves = (int)(blockDim.x >> 6);
-    for (int w0 = U * (int)(threadIdx.x >> 6); w0 < words; w0 += U * waves) {
+    for (int w0 = (int)(threadIdx.x >> 6); w0 < words; w0 += U * waves) {
         int l[U], sl[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int r = 64 * (w0 + u) + lane;
+            const int r = 64 * (w0 + u * waves) + lane;
             l[u] = r < R ? attn_row_len(seqlens, r, len_offset, Lmax) : 0;
             sl[u] = r < R ? slots[r] : -1;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (w0 + u < words) f(w0 + u, attn_classify_rows<ROWS>(l[u], sl[u], limit));
+            if (w0 + u * waves < words) f(w0 + u * waves, attn_classify_rows<ROWS>(l[u], sl[u], limit));
     }
 }
 

@@ -51,8 +51,8 @@ __device__ __forceinline__ void wait_then_barrier()
 // down from an earlier form that took 297 us on prompts of 2000 + 1400 + 1000 tokens: 234 without the exponentials, 109 with
 // the loads and barriers alone.
 //
-// The grid: `helpers` workgroups, then Hkv per tile, tiles from the last (longest prefixes first).  The (row, KV head)
-// groups of mixed tiles (attn_rows.h) are dealt out over the helpers, which find those tiles by looking at all rows.
+// The grid: `helpers` workgroups, then Hkv per tile, tiles from the last (longest prefixes first).  The (run of rows, KV
+// head) items of mixed tiles (attn_rows.h) are dealt out over the helpers, which count them by looking at all rows.
 // Rows that attn_left_rows names are not touched here.
 template <int G, bool QUANT>
 __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kcache,
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
     __shared__ uint4 ring[kSlots * 1024];
     __shared__ float mc_table[kTableChunks * NP];
     __shared__ int samples;
-    __shared__ uint8_t mixed[1024];  // bit t of byte w: tile t of the rows 64w .. 64w+63 is mixed
+    __shared__ uint8_t mixed[1024];  // byte w: the runs of mixed tiles among the rows 64w .. 64w+63
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -352,6 +352,10 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
     };
     // the shortest and the longest of the rows in `members`
     auto length_range = [&](uint64_t members, int& minlen, int& maxlen) {
+        if ((members & (members - 1)) == 0) {
+            minlen = maxlen = __builtin_amdgcn_readlane(tlen, __builtin_ctzll(members));
+            return;
+        }
         const bool in = (members >> lane) & 1ull;
         int lo = in ? tlen : 0x7FFFFFFF, hi = in ? tlen : 0;
 #pragma unroll
@@ -362,9 +366,7 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
         minlen = uni(lo);
         maxlen = uni(hi);
     };
-    auto do_group = [&](int tile, int kvh, int group_slot, uint64_t members) __attribute__((always_inline)) {
-        int minlen, maxlen;
-        length_range(members, minlen, maxlen);
+    auto do_group = [&](int tile, int kvh, int group_slot, uint64_t members, int minlen, int maxlen) __attribute__((always_inline)) {
         const int ri = pair / G, row = tile * RT + ri;
         const int l = __shfl(tlen, ri, kWave);
         const int my_len = ((members >> ri) & 1ull) ? l : 0;
@@ -385,9 +387,8 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
     };
     // A row shorter than its group's longest gives the tokens past its length the weight 0, which keeps them out
     // of its output as long as their V is finite.  If some is not, the group's rows are walked one by one.
-    auto window_finite = [&](int kvh, int group_slot, uint64_t members) {
-        int minlen, maxlen;
-        length_range(members, minlen, maxlen);
+    auto window_finite = [&](int kvh, int group_slot, int minlen, int maxlen) {
+        if (minlen == maxlen) return true;
         const uint4* vp = reinterpret_cast<const uint4*>(vcache + ((size_t)group_slot * Hkv + kvh) * (size_t)Lmax * kD);
         bool bad = false;
         for (size_t i = (size_t)minlen * 16 + tid; i < (size_t)maxlen * 16; i += 256) {
@@ -403,11 +404,14 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
     auto do_group_checked = [&](int tile, int kvh, int first) __attribute__((always_inline)) {
         const int group_slot = slot_of(first);
         uint64_t rest = with_slot(group_slot);
-        const bool together = window_finite(kvh, group_slot, rest);
+        int minlen, maxlen;
+        length_range(rest, minlen, maxlen);
+        const bool together = window_finite(kvh, group_slot, minlen, maxlen);
 #pragma unroll 1
         while (rest != 0) {
             const uint64_t members = together ? rest : rest & (~rest + 1);
-            do_group(tile, kvh, group_slot, members);
+            if (!together) length_range(members, minlen, maxlen);
+            do_group(tile, kvh, group_slot, members, minlen, maxlen);
             rest &= ~members;
         }
     };
@@ -436,9 +440,8 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
         return G > 1 && k.mixed != 0;
     };
     const bool helper = (int)blockIdx.x < helpers;
-    int tile = 0, kvh = 0, first = RT;  // the current item
-    int word = -1, ordinal = -1, item = 0;
-    uint32_t bits = 0;
+    int tile = 0, kvh = 0, first = 0;  // the current item
+    int word = 0, items = 0, item = 0;  // a helper's word, the items of the word, and its current one among them
     if (!helper) {
         const int i = (int)blockIdx.x - helpers;
         kvh = i % Hkv;
@@ -458,16 +461,15 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
     } else {
         if (Lmax > kWalkChunks * kChunk) limit = attn_walk_limit(seqlens, len_offset, Lmax, R, ntiles, RT, Hkv, &samples);
         attn_for_row_words<RT>(seqlens, slots, len_offset, Lmax, R, limit, [&](int w, const attn_row_classes& k) {
-            uint32_t t8 = 0;
-#pragma unroll
-            for (int t = 0; t < 64 / RT; ++t)
-                if ((k.mixed >> (RT * t)) & (RT == 64 ? ~0ull : (1ull << (RT & 63)) - 1ull)) t8 |= 1u << t;
-            if (lane == 0) mixed[w] = (uint8_t)t8;
+            if (lane == 0) mixed[w] = (uint8_t)__builtin_popcountll(k.starts & k.mixed);
         });
         __syncthreads();
+        items = uni((int)mixed[0]) * Hkv;
+        item = (int)blockIdx.x - helpers;
     }
-    // moves to the next item; false: none left.  A mixed tile has RT x Hkv items (first row of a group, KV
-    // head); the items of all mixed tiles in ascending order are dealt round-robin over the helpers.
+    // Moves to the next item; false: none left.  A word of 64 rows has Hkv items for each run of its mixed tiles; the items of
+    // all words in ascending order are dealt round-robin over the helpers.  (Dealt by row instead of by run, regular slots put
+    // all the work on a few helpers: 962 rows, eight a slot at 400 tokens, 32/16 heads 911 us instead of 134.)
     auto advance = [&]() __attribute__((always_inline)) -> bool {
         if (!helper) {
             if (lead == 0) return false;
@@ -476,30 +478,28 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
             return true;
         }
         for (;;) {
-            while (first < RT) {  // inside a tile
-                item += helpers;
-                if (item >= RT * Hkv) {
-                    first = RT;
-                    break;
-                }
-                first = item / Hkv;
-                kvh = item % Hkv;
-                if ((lead >> first) & 1ull) return true;
-            }
-            while (bits == 0) {  // the next mixed tile
+            item += helpers;
+            while (item >= items) {
+                item -= items;
                 if (++word >= (R + 63) / 64) return false;
-                bits = (uint32_t)uni((int)mixed[word]);
+                items = uni((int)mixed[word]) * Hkv;
             }
-            tile = (64 / RT) * word + __builtin_ctz(bits);
-            bits &= bits - 1;
-            ++ordinal;
-            item = (int)blockIdx.x - (int)(((long long)ordinal * (RT * Hkv)) % helpers);
-            if (item < 0) item += helpers;
-            if (item >= RT * Hkv) continue;
-            load_tile(tile);
-            classify();
-            item -= helpers;  // the loop above steps to it
-            first = 0;
+            const int r = 64 * word + lane;
+            const int l = r < R ? attn_row_len(seqlens, r, len_offset, Lmax) : 0;
+            const int sl = r < R ? slots[r] : -1;
+            const attn_row_classes k = attn_classify_rows<RT>(l, sl, limit);
+            uint64_t starts = k.starts & k.mixed;
+            for (int n = item / Hkv; n > 0; --n) starts &= starts - 1;
+            const int bit = __builtin_ctzll(starts);
+            kvh = item % Hkv;
+            tile = (64 * word + bit) / RT;
+            first = bit % RT;
+            const int from = (bit & ~(RT - 1)) + (lane & (RT - 1));  // lane i takes row i of the tile
+            tslot = __shfl(sl, from, kWave);
+            tlen = __shfl(l, from, kWave);
+            if (lane >= RT || ((k.walks >> from) & 1ull) == 0) tlen = 0;
+            // a slot's later runs went with its first
+            if (__builtin_ctzll(with_slot(slot_of(first))) == first) return true;
         }
     };
 #pragma unroll 1

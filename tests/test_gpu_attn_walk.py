@@ -120,3 +120,14 @@ def test_few_long_rows_among_short_ones(d, Hq, Hkv, quant):
     q, k, v = inputs(4500 + Hq + Hkv, len(lens), Hq, 3, Hkv, Lmax)
     pick = [i for i, n in enumerate(lens) if n > 600] + list(range(0, len(lens), 41))
     check(d, "few long rows", q, k, v, lens, slots, quant, pick=pick)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(32, 8), (32, 16), (64, 8), (32, 32)])
+@pytest.mark.parametrize("per", [2, 9, 24])
+def test_slots_at_regular_intervals(d, Hq, Hkv, per):
+    """Tiles of several slots, in runs of equal size that begin anywhere in a tile, with rows of no tokens among them."""
+    R, S, Lmax = 541, 11, 300
+    lens = [0 if i % 31 == 5 else 300 - 7 * (i % per) for i in range(R)]
+    slots = [(i // per) % S for i in range(R)]
+    q, k, v = inputs(4600 + Hq + Hkv + per, R, Hq, S, Hkv, Lmax)
+    check(d, f"runs of {per}", q, k, v, lens, slots, pick=range(0, R, 4))
