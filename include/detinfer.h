@@ -195,9 +195,9 @@ int det_attn_decode(const void *q, const void *kcache, const void *vcache, const
  * 0 <= slots[r] < S is the caller's responsibility.  Workspace: det_attn_decode_workspace_bytes(R, ...).
  * From sixteen rows on, eight consecutive rows go to one workgroup, and those of them that name the same
  * slot share each 256-token chunk of K and V (causal prefill: one read of the prompt's cache per eight
- * query tokens instead of one per token); from 256 (KV head, tile of 64 / G rows) pairs on, G = Hq / Hkv, a
- * tile's rows walk their chunks inside one workgroup, but for rows much longer than the call's others (and, for
- * G = 1, tiles that name many slots).  Which rows share a workgroup changes no row's arithmetic. */
+ * query tokens instead of one per token); from 256 (KV head, tile of 64 / G rows) pairs on, G = Hq / Hkv, the
+ * rows of a tile that name one slot go through all their chunks inside one workgroup, but for rows much longer than the
+ * call's others.  Which rows share a workgroup changes no row's arithmetic. */
 int det_attn_decode_rows(const void *q, const void *kcache, const void *vcache, const int32_t *seqlens,
                          const int32_t *slots, void *out, void *ws, size_t ws_bytes, int R, int Hq,
                          int Hkv, int D, int Lmax, float scale, void *stream);

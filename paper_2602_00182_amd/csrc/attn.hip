@@ -631,7 +631,7 @@ __device__ __forceinline__ int find_left_rows(const int32_t* __restrict__ seqlen
     if (Lmax > kWalkChunks * kChunk)
         limit = attn_walk_limit(seqlens, len_offset, Lmax, R, (R + kWalkPairs / G - 1) / (kWalkPairs / G), kWalkPairs / G, Hkv, scratch);
     attn_for_row_words<kWalkPairs / G>(seqlens, slots, len_offset, Lmax, R, limit, [&](int w, const attn_row_classes& k) {
-        if ((threadIdx.x & 63) == 0) left[w] = attn_left_rows<G>(k);
+        if ((threadIdx.x & 63) == 0) left[w] = k.deep;
     });
     const int words = (R + 63) >> 6;
     __syncthreads();
@@ -1012,9 +1012,9 @@ int det::attn_decode_impl(const void* q, const void* kcache, const void* vcache,
     const bool tiled = slots != nullptr && B >= 16;
     if (tiled && attn_walk_workgroups(B, G, Hkv) >= kWalkWorkgroups) {
         if (qscales && !aligned16(qscales)) return DET_EALIGN;
-        const int rc = attn_walk(q, kcache, vcache, seqlens, slots, len_offset, out, static_cast<float*>(qscales), B, Hq, Hkv,
-                                 Lmax, scale, s);
-        if (rc != DET_OK || (G > 1 && ncmax <= kWalkChunks)) return rc;  // no row can be left
+        const int rc = attn_walk(q, kcache, vcache, seqlens, slots, len_offset, out, static_cast<float*>(qscales), ws_o, B, Hq,
+                                 Hkv, Lmax, ncmax, scale, s);
+        if (rc != DET_OK || ncmax <= kWalkChunks) return rc;  // no row can be left
         return attn_left(q, kcache, vcache, seqlens, slots, len_offset, out, ws_m, ws_l, ws_o, static_cast<float*>(qscales), B,
                          Hq, Hkv, Lmax, ncmax, scale, s);
     }

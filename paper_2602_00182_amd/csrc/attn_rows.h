@@ -45,8 +45,7 @@ __device__ __forceinline__ int attn_walk_limit(const int32_t* seqlens, int len_o
 //   deep  : longer than `limit` chunks: left to the per-chunk kernels.
 //   walks : the others that have tokens.  Those of a tile, in order, fall into runs of one slot; `starts` are the runs' first
 //           rows.  (The first row of a slot in its tile always starts a run.)
-//   mixed : rows that walk, of tiles of more than one run; where every head has K and V of its own (tiles of 64 rows), of more
-//           than two or, if it holds no row of more than a chunk, more than eight.  A walk shares nothing between slots, so they are not walked one
+//   mixed : rows that walk, of tiles of more than one run.  A walk shares nothing between slots, so they are not walked one
 //           after the other by the tile's own workgroup (sixteen slots of 1000 tokens would take it 500 us; eight rows
 //           a slot at 200 tokens, 994 rows, 32/8 heads 48 us that way, 45 dealt out; 18 prompts of up to 119 tokens 42 and 37).
 struct attn_row_classes {
@@ -64,18 +63,8 @@ __device__ __forceinline__ attn_row_classes attn_classify_rows(int len, int slot
     const uint64_t above = k.walks & mine & ((1ull << lane) - 1ull);  // walking rows of the tile before this one
     const int before = __shfl(slot, above != 0 ? 63 - __builtin_clzll(above) : lane, 64);
     k.starts = __ballot(walks && (above == 0 || slot != before));
-    const uint64_t longer = __ballot(walks && len > 256) & mine;
-    const int most = ROWS < 64 ? 1 : (longer != 0 ? 2 : 8);
-    k.mixed = __ballot(walks && __builtin_popcountll(k.starts & mine) > most);
+    k.mixed = __ballot(walks && __builtin_popcountll(k.starts & mine) > 1);
     return k;
-}
-
-// The rows a walking launch leaves to the per-chunk kernels: the deep ones and, where every head has K and V of its
-// own (G = 1), the mixed ones: those read their cache from HBM, and a walk reads K twice.
-template <int G>
-__device__ __forceinline__ uint64_t attn_left_rows(const attn_row_classes& k)
-{
-    return G == 1 ? k.deep | (k.mixed & k.walks) : k.deep;
 }
 
 // f(w, classes) for the 64-row words w of all rows, dealt to the waves of the workgroup; eight words' loads at a time.

@@ -14,11 +14,12 @@ int attn_decode_impl(const void* q, const void* kcache, const void* vcache, cons
                      const int32_t* slots, int len_offset, void* out, void* ws, size_t ws_bytes, int B, int Hq, int Hkv, int D,
                      int Lmax, float scale, hipStream_t s, void* qscales = nullptr);
 
-// The same on rows that name their slots, without workspace (attn_rows.hip): arguments checked by the caller.
-// attn_walk_workgroups: the workgroups such a launch has.
+// The same on rows that name their slots (attn_rows.hip): arguments checked by the caller.  ws_o: the chunk outputs of the
+// workspace, [R, Hq, ncmax, D].  attn_walk_workgroups: the (row tile, KV head) workgroups such a launch has.
 long long attn_walk_workgroups(int R, int G, int Hkv);
 int attn_walk(const void* q, const void* kcache, const void* vcache, const int32_t* seqlens, const int32_t* slots,
-              int len_offset, void* out, float* qscales, int R, int Hq, int Hkv, int Lmax, float scale, hipStream_t s);
+              int len_offset, void* out, float* qscales, float* ws_o, int R, int Hq, int Hkv, int Lmax, int ncmax, float scale,
+              hipStream_t s);
 
 // SwiGLU projection with quantized output (qgemm.hip), where it fits: aligned buffers as the layer lays them out.
 bool qgemm_swiglu_quant_fits(int M, int F, int K);
