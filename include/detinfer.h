@@ -84,6 +84,10 @@ int det_gemm_bf16(const void *A, int lda, const void *B_packed, void *C, int ldc
 int det_gemm_bf16_fixed_tile(const void *A, int lda, const void *B_packed, void *C, int ldc, int M, int N,
                              int K, int out_dtype, void *stream);
 
+/* Test hook: rows of the 256-column tiles that det_gemm_bf16 and its fused forms cut a launch of M rows into (128, 160,
+ * 192 or 256), 0 where they take another tiling. */
+int det_gemm_wide_rows(int M, int N, int K);
+
 /* Bytes of the packed form of a [K, N] bf16 matrix (= 2*K*N). 0 if the shape is unsupported. */
 size_t det_gemm_packed_b_bytes(int N, int K);
 

@@ -896,6 +896,11 @@ static bool gemm_shape_ok(int N, int K) { return N > 0 && K > 0 && N % 16 == 0 &
 
 using namespace det;
 
+extern "C" int det_gemm_wide_rows(int M, int N, int K)
+{
+    return M < 1 || !gemm_shape_ok(N, K) ? 0 : 32 * gemm_wide_rows(M, N, K, gemm_cols_per_block(N));
+}
+
 extern "C" size_t det_gemm_packed_b_bytes(int N, int K)
 {
     if (!gemm_shape_ok(N, K)) return 0;

@@ -215,42 +215,63 @@ static void launch_rows(int rbw, const gemm_wide_args& a, hipStream_t s)
     }
 }
 
-// What a launch costs is the rounds of 256 workgroups it takes, times what one of its tiles takes for a step of K, which is
-// nearly the same over all shapes (measured over K = 2048 .. 14336, N = 2048 .. 28672, 300 to 4096 rows): 0.49 / 0.61 /
-// 0.66 / 0.79 us for 128 / 160 / 192 / 256 rows here; for gemm.hip 0.53 us a
-// round of its 256 x 128 tiles (0.51 in long launches, less for the rows a last tile lacks), and in its narrower tilings,
-// which it takes where those do not fill the chip, 1.4 ns for each row and column of a tile (16- and 32-column packings)
-// or the share of a round that 256 x 128 tiles would fill, in us (64-column packings).  So the choice is the tile height
-// whose tiles fit the rounds best: 3302 rows of N = 6144, K = 4096 are 13 x 48 tiles there (three rounds, 214 us), 13 x 24
-// of 256 rows here (two, 205 us), 21 x 24 of 160 rows (two, 159 us).  10 % must be won by this
-// count, 25 % (19 % in launches of four rounds and more) where a tile there is as wide as the packing and the weights alone
-// are much of the time.  Others: K x N
-// 4096 x 6144 700 rows 114 -> 61 us, 14336 x 4096 1500 rows 373 -> 208, 4096 x 28672 4096 rows 919 -> 788 (1.22 PFLOP/s;
-// torch's product of two 8192 x 8192 matrices reaches 1.19 on the same card).
+// What a launch costs is the rounds of 256 workgroups it takes, times what one of its tiles takes for a step of 32 of K, which is
+// nearly the same over all shapes (measured over K = 1024 .. 14336, N = 1024 .. 28672, 256 to 5000 rows).  Here 0.49 / 0.61 /
+// 0.66 / 0.79 us for tiles of 128 / 160 / 192 / 256 rows.  In gemm.hip 0.53 us for a 256 x 128 tile (0.51 in launches of four
+// rounds and more), and in its narrower tilings, which it takes where those do not fill the chip, 1.4 ns (16- and 32-column
+// packings) or 1.12 ns (64-column packings) for each row and column of a tile.  The last row of tiles there is as short as
+// its rows: 0.34 of a whole 256 x 128 tile's time and the rest by rows, and it fills the compute units that the last round of
+// whole tiles leaves idle.  (Counted as whole tiles, 258 rows of K = 4416, N = 11264 took this form in 62 us instead of 42, 519 rows
+// of 2048 x 6144 in 34 instead of 28.)  So the choice is the tile height whose tiles fit the rounds best: 3302 rows of N = 6144,
+// K = 4096 are 13 x 48 tiles there (three rounds, 214 us), 13 x 24 of 256 rows here (two, 205 us), 21 x 24 of 160 rows
+// (two, 159 us).  10 % must be won by this count, 25 % (21 % in launches of four rounds and more) where a tile there is as wide as the
+// packing and the weights alone are much of the time.  Of 1239 shapes, a third of them a few rows past whole 256-row tiles,
+// the choice is slower by more than 2 % in two (3 and 5 %).  Others: K x N 4096 x 6144 700 rows 114 -> 61 us, 14336 x 4096
+// 1500 rows 373 -> 208, 4096 x 28672 4096 rows 919 -> 788 (1.22 PFLOP/s; torch's product of two 8192 x 8192 matrices reaches
+// 1.19 on the same card).
+namespace {
+
+long long rounds(long long wgs) { return (wgs + 255) / 256; }
+
+// Time of n columns of tiles over M rows, `rows` to a tile; tile(x): time of a tile of x rows.
+template <class F>
+long long span(int M, int n, int rows, F&& tile)
+{
+    const int full = (M - 1) / rows, last = 16 * ((M - rows * full + 15) / 16);
+    const long long t_full = tile(rows), t_last = tile(last < rows ? last : rows);
+    const long long wgs = (long long)n * full, idle = (256 - wgs % 256) % 256;
+    const long long rest = n - idle * (t_full / t_last);  // last tiles that do not fit the last round of whole ones
+    return rounds(wgs) * t_full + (rest > 0 ? rounds(rest) * t_last : 0);
+}
+
+}  // namespace
+
 int gemm_wide_rows(int M, int N, int K, int cb)
 {
     if (N % kWideCols != 0 || 16 % cb != 0 || M < 256 || K < 1024) return 0;
-    auto rounds = [](long long wgs) { return (wgs + 255) / 256; };
-    // both costs in units of 10 ns
+    // costs in units of 0.1 ns
     const long long row_tiles = (M + 255) / 256, there = row_tiles * (N / 128);
-    const long long live = 256 * (row_tiles - 1) + 160 + 96 * (M - 256 * (row_tiles - 1)) / 256;  // of 256 * row_tiles
     long long cost;
-    if (there < 256 && cb < 4) {
-        const int fit = 256 / (N / 64) > 1 ? 256 / (N / 64) : 1;
-        const int even = 16 * (((M + 15) / 16 + fit - 1) / fit), rows = even < 256 ? even : 256;
-        cost = rounds((long long)(N / 64) * ((M + rows - 1) / rows)) * (rows + 64) * 14 / 100;
+    if (there < 256 && cb <= 4) {
+        int rows = 256;
+        if (cb < 4) {
+            const int fit = 256 / (N / 64) > 1 ? 256 / (N / 64) : 1;
+            const int even = 16 * (((M + 15) / 16 + fit - 1) / fit);
+            rows = even < 256 ? even : 256;
+        }
+        cost = span(M, N / 64, rows, [&](int x) { return (long long)(x + 64) * (cb < 4 ? 1400 : 1120) / 100; });
     } else {
-        const long long full = there < 256 && cb < 8 ? there * 100 / 256 : rounds(there) * (rounds(there) < 4 ? 53 : 51);
-        cost = full * live / (256 * row_tiles);
+        const int t = rounds(there) < 4 ? 5300 : 5100;
+        cost = span(M, N / 128, 256, [&](int x) { return (long long)t * (34 * 256 + 66 * x) / 25600; });
     }
     static const struct {
         int rbw, cost;
-    } kTiles[4] = {{4, 49}, {5, 61}, {6, 66}, {8, 79}};
+    } kTiles[4] = {{4, 4900}, {5, 6100}, {6, 6600}, {8, 7900}};
     int best = 0;
     long long best_cost = 100 * cost;
     for (const auto& t : kTiles) {
         const long long n = rounds((long long)((M + 32 * t.rbw - 1) / (32 * t.rbw)) * (N / kWideCols));
-        const long long c = n * t.cost * (cb < 8 ? 110 : (n >= 4 ? 119 : 125));
+        const long long c = n * t.cost * (cb < 8 ? 110 : (n >= 4 ? 121 : 125));
         if (c < best_cost) best = t.rbw, best_cost = c;
     }
     return best;
