@@ -50,7 +50,8 @@ def test_rows_equal_small_calls(d, M, K, N):
         assert torch.equal(swi[p].view(torch.int16), o3.view(torch.int16))
 
 
-# a fused SwiGLU quantizer where the packing has 64 columns (no other kernel's tile holds a block there) and where it has 128
+# a fused SwiGLU quantizer where the packing has 64 columns (no other kernel's tile holds a block there) and where it has 128, and a
+# launch too small for it, which takes the two steps
 @pytest.mark.parametrize("R,H,Hq,Hkv,F", [(390, 256, 2, 1, 5632), (241, 128, 2, 2, 10240), (420, 128, 4, 2, 64)])
 def test_quantized_layer_rows_equal_small_calls(d, R, H, Hq, Hkv, F):
     D, Lmax = 128, 420
@@ -109,3 +110,33 @@ def test_quantized_layer_refuses_misaligned_gate_up_weights(d):
         with pytest.raises(d.DetError) as e:
             run(R)
         assert e.value.code == 3
+
+
+# 2F of 2048 and 5120 columns: packings of 16 and 32, whose SwiGLU output only the tall tiles quantize (112 and 280 workgroups)
+@pytest.mark.parametrize("R,H,Hq,Hkv,F", [(400, 256, 2, 1, 1024), (390, 128, 2, 2, 2560)])
+def test_quantized_layer_of_narrow_packings(d, R, H, Hq, Hkv, F):
+    test_quantized_layer_rows_equal_small_calls(d, R, H, Hq, Hkv, F)
+
+
+@pytest.mark.parametrize("M,K,N", [(385, 64, 2048), (450, 192, 2048), (225, 64, 5120), (129, 192, 11008), (200, 704, 28672)])
+def test_strided_rows(d, M, K, N):
+    """Outputs and residuals whose rows lie apart: nothing is written between them."""
+    w = up_bf16(ds.normal_bf16(7300 + N, (K, N), 0.02))
+    wp, gu = d.quant_pack_weight(w), d.quant_pack_gate_up(w)
+    codes, scales = d.quant_activations(up_bf16(ds.normal_bf16(7400 + M, (M, K))))
+    r = up_bf16(ds.normal_bf16(7500 + M, (M, N + 12)))[:, :N]
+    nan = lambda cols: torch.full((M, cols), float("nan"), dtype=torch.bfloat16, device=DEV)
+    out, res, swi = nan(N + 8), nan(N + 4), nan(N // 2 + 20)
+    o1, o2, o3 = nan(N), nan(N), nan(N // 2)
+    step(f"tall quantized GEMM, strided M={M} K={K} N={N}")
+    d.det_qgemm_w4a8(codes, scales, wp, out[:, :N], N)
+    d.det_qgemm_w4a8_residual(codes, scales, wp, r, res[:, :N], N)
+    d.det_qgemm_w4a8_swiglu(codes, scales, gu, swi[:, :N // 2], N // 2)
+    d.det_qgemm_w4a8(codes, scales, wp, o1, N)
+    d.det_qgemm_w4a8_residual(codes, scales, wp, r.contiguous(), o2, N)
+    d.det_qgemm_w4a8_swiglu(codes, scales, gu, o3, N // 2)
+    torch.cuda.synchronize()
+    for got, want in ((out, o1), (res, o2), (swi, o3)):
+        cols = want.shape[1]
+        assert torch.isnan(got[:, cols:]).all(), "written between the rows"
+        assert torch.equal(got[:, :cols].contiguous().view(torch.int16), want.view(torch.int16))
