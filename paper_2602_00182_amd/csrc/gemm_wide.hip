@@ -219,16 +219,17 @@ static void launch_rows(int rbw, const gemm_wide_args& a, hipStream_t s)
 // nearly the same over all shapes (measured over K = 1024 .. 14336, N = 1024 .. 28672, 256 to 5000 rows).  Here 0.49 / 0.61 /
 // 0.66 / 0.79 us for tiles of 128 / 160 / 192 / 256 rows.  In gemm.hip 0.53 us for a 256 x 128 tile (0.51 in launches of four
 // rounds and more), and in its narrower tilings, which it takes where those do not fill the chip, 1.4 ns (16- and 32-column
-// packings) or 1.12 ns (64-column packings) for each row and column of a tile.  The last row of tiles there is as short as
+// packings) or 1.18 ns (64-column packings) for each row and column of a tile.  The last row of tiles there is as short as
 // its rows: 0.34 of a whole 256 x 128 tile's time and the rest by rows, and it fills the compute units that the last round of
 // whole tiles leaves idle.  (Counted as whole tiles, 258 rows of K = 4416, N = 11264 took this form in 62 us instead of 42, 519 rows
 // of 2048 x 6144 in 34 instead of 28.)  So the choice is the tile height whose tiles fit the rounds best: 3302 rows of N = 6144,
 // K = 4096 are 13 x 48 tiles there (three rounds, 214 us), 13 x 24 of 256 rows here (two, 205 us), 21 x 24 of 160 rows
-// (two, 159 us).  10 % must be won by this count, 25 % (21 % in launches of four rounds and more) where a tile there is as wide as the
-// packing and the weights alone are much of the time.  Of 1239 shapes, a third of them a few rows past whole 256-row tiles,
-// the choice is slower by more than 2 % in two (3 and 5 %).  Others: K x N 4096 x 6144 700 rows 114 -> 61 us, 14336 x 4096
-// 1500 rows 373 -> 208, 4096 x 28672 4096 rows 919 -> 788 (1.22 PFLOP/s; torch's product of two 8192 x 8192 matrices reaches
-// 1.19 on the same card).
+// (two, 159 us).  6 % must be won by this count, 21 % where a tile there is as wide as the
+// packing and the weights alone are much of the time.  Of 665 shapes that could take this form, half of them a few rows past
+// whole 256-row tiles, the choice is slower by more than 2 % in one (3 %); where it stays in gemm.hip this form would have taken up to
+// a quarter less time (476 rows of 14336 x 8192).  Others: K x N 4096 x 6144 700 rows 114 -> 61 us, 14336 x 4096 1500 rows
+// 373 -> 208, 4096 x 28672 4096 rows 919 -> 788 (1.22 PFLOP/s; torch's product of two 8192 x 8192 matrices reaches 1.19 on the
+// same card).
 namespace {
 
 long long rounds(long long wgs) { return (wgs + 255) / 256; }
@@ -259,7 +260,7 @@ int gemm_wide_rows(int M, int N, int K, int cb)
             const int even = 16 * (((M + 15) / 16 + fit - 1) / fit);
             rows = even < 256 ? even : 256;
         }
-        cost = span(M, N / 64, rows, [&](int x) { return (long long)(x + 64) * (cb < 4 ? 1400 : 1120) / 100; });
+        cost = span(M, N / 64, rows, [&](int x) { return (long long)(x + 64) * (cb < 4 ? 1400 : 1180) / 100; });
     } else {
         const int t = rounds(there) < 4 ? 5300 : 5100;
         cost = span(M, N / 128, 256, [&](int x) { return (long long)t * (34 * 256 + 66 * x) / 25600; });
@@ -271,7 +272,7 @@ int gemm_wide_rows(int M, int N, int K, int cb)
     long long best_cost = 100 * cost;
     for (const auto& t : kTiles) {
         const long long n = rounds((long long)((M + 32 * t.rbw - 1) / (32 * t.rbw)) * (N / kWideCols));
-        const long long c = n * t.cost * (cb < 8 ? 110 : (n >= 4 ? 121 : 125));
+        const long long c = n * t.cost * (cb < 8 ? 106 : 121);
         if (c < best_cost) best = t.rbw, best_cost = c;
     }
     return best;

@@ -5,7 +5,8 @@ import paper_2602_00182_amd as d
 
 
 @pytest.mark.parametrize("M,K,N,rows", [(3302, 4096, 6144, 160), (700, 4096, 6144, 128), (1500, 14336, 4096, 128), (2000, 1024, 11264, 192),
-                                        (4096, 4096, 28672, 256), (300, 1088, 28672, 160)])
+                                        (4096, 4096, 28672, 256), (300, 1088, 28672, 160), (351, 2048, 11264, 128),
+                                        (552, 14336, 11264, 128)])
 def test_taken(M, K, N, rows):
     assert d.det_gemm_wide_rows(M, N, K) == rows
 
