@@ -143,18 +143,21 @@ __device__ __forceinline__ void attn_tile(const uint16_t* __restrict__ q, const 
     for (int ri = 0; ri < RT; ++ri) any = any || len[ri] > t0;
     if (!any) return;  // uniform over the workgroup
 
+    // (a tile of one row, which has no groups to find, is 1 % slower with its length and slot in scalar registers)
+    auto row_len = [&](int ri) { return RT > 1 ? uni(len[ri]) : len[ri]; };
+    auto row_slot = [&](int ri) { return RT > 1 ? uni(slot[ri]) : slot[ri]; };
     uint32_t done = 0, alone = 0;  // rows computed, and rows that are groups of their own
     bool first_group = true;
 #pragma unroll 1
     for (int first = 0; first < RT; ++first) {
-        if (((done >> first) & 1u) || uni(len[first]) <= t0) continue;
-        const int group_slot = uni(slot[first]);
+        if (((done >> first) & 1u) || row_len(first) <= t0) continue;
+        const int group_slot = row_slot(first);
         uint32_t mask = 0;
         int minlen = 0x7FFFFFFF, maxlen = 0;
 #pragma unroll
         for (int ri = 0; ri < RT; ++ri) {
-            const int l = uni(len[ri]);
-            if (l > t0 && uni(slot[ri]) == group_slot && (ri == first || !((alone >> first | alone >> ri) & 1u))) {
+            const int l = row_len(ri);
+            if (l > t0 && row_slot(ri) == group_slot && (ri == first || !((alone >> first | alone >> ri) & 1u))) {
                 mask |= 1u << ri;
                 minlen = l < minlen ? l : minlen;
                 maxlen = l > maxlen ? l : maxlen;
