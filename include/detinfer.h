@@ -196,7 +196,9 @@ int det_attn_decode(const void *q, const void *kcache, const void *vcache, const
 /* The same operation on R rows that name their cache slot: row r reads slot slots[r] of caches
  * [S, Hkv, Lmax, D] with length seqlens[r].  Several rows may share a slot (the tokens of one prompt
  * at lengths 1..T: batch-invariant prefill, since each row is exactly the single-token operation).
- * 0 <= slots[r] < S is the caller's responsibility.  Workspace: det_attn_decode_workspace_bytes(R, ...).
+ * 0 <= slots[r] < S is the caller's responsibility.  Workspace: det_attn_decode_workspace_bytes(R, ...); what it holds
+ * after the call is as above for calls of fewer than 256 pairs (next sentence), and unspecified for larger ones, which
+ * write the partials of some rows only.
  * From sixteen rows on, eight consecutive rows go to one workgroup, and those of them that name the same
  * slot share each 256-token chunk of K and V (causal prefill: one read of the prompt's cache per eight
  * query tokens instead of one per token); from 256 (KV head, tile of 64 / G rows) pairs on, G = Hq / Hkv, the
@@ -223,8 +225,10 @@ int det_attn_decode_static(const void *q, const void *kcache, const void *vcache
                            void *out, int B, int Hq, int Hkv, int D, int Lmax, float scale, void *stream);
 
 /* Test hook: the softmax statistics of det_attn_decode on caller-provided fp32 scores.  The per-chunk
- * statistics (m_c, e_j, l_c) come from the one device routine the attention kernel itself calls; the
- * combination over chunks is the same ascending fold, written for one row per workgroup.
+ * statistics (m_c, e_j, l_c) come from the device routine that the attention of larger decode launches and of
+ * eight rows a workgroup calls; small decode launches and calls of many rows compute them in the same order with code
+ * of their own, which the tests hold to those bytes.  The combination over chunks is the same ascending fold, written
+ * for one row per workgroup.
  * s, p [R, Lmax] fp32; lens [R]; m_out, l_out [R] fp32.
  * p_j = (w_c * e_j) / L for j < lens[r]; entries at or past lens[r] are not written.
  * lens[r] = 0 gives m = -inf, L = 0.  Lmax <= 262144. */

@@ -29,8 +29,9 @@ constexpr int kHalfTok = 128;  // tokens of the half chunk whose V^T sits in LDS
 //   l_c = the 256-leaf sum of e: inside each group of 64 leaves, leaf j takes leaf j+off for off = 32, 16, .., 1,
 //         and the four group sums q0..q3 combine as (q0+q2)+(q1+q3).
 // m_c and l_c are returned in every lane.  No LDS, no barrier: the waves of a workgroup run it independently
-// on different rows.  This is the only implementation of these statistics in the library: the attention kernel
-// and det_softmax_f32 both call it.
+// on different rows.  attn_tile and det_softmax_f32 call it.  attn_chunk_kernel below and attn_walk_kernel (attn_rows.hip) compute
+// the same statistics, in the same order, from other lane layouts (add32, add16 and exp_nonpos of attn_lane.h); the tests hold
+// their bytes to attn_tile's (test_gpu_attn_chunk.py, test_gpu_attn_walk.py, test_gpu_attn_few.py).
 __device__ __forceinline__ int chunk_token(int lane, int k) { return ((lane >> 4) << 6) + (k << 4) + (lane & 15); }
 __device__ __forceinline__ float lane_value(float v, int lane)
 {
@@ -75,9 +76,10 @@ __device__ __forceinline__ float combine_max(const float* mc, int nc)
 // ------------------------------------------------------------------ attention, pass 1
 
 // One workgroup: one 256-token chunk of one cache slot's K/V, for up to RT query rows (tokens) times G
-// query heads that share the KV head ("pairs").  Decode launches it with RT = 1 (every row has a cache slot
-// of its own); the rows form with RT = 8 lets the rows of one prompt share each chunk of K and V (causal
-// prefill: row i of a prompt has length p + i).  Grid (chunk, head group, row tile); 256 threads.
+// query heads that share the KV head ("pairs").  Decode launches of more than 512 workgroups (and all with G = 1) take it with
+// RT = 1 (every row has a cache slot of its own); the rows form with RT = 8 lets the rows of one prompt share each chunk of K
+// and V (causal prefill: row i of a prompt has length p + i), in calls too small for attn_rows.hip and for the rows it leaves.
+// Grid (chunk, head group, row tile); 256 threads.
 //
 // The arithmetic of one (row, head, chunk) is the same whatever else sits in the workgroup:
 //   scores: wave w takes tokens 64w..64w+63 of the chunk as four 16-token blocks; the K rows are the row

@@ -45,6 +45,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 //   n = rint(x*log2e);  r = fma(n,-ln2_hi,x);  r = fma(n,-ln2_lo,r);
 //   p = degree-7 Taylor polynomial of exp(r), Horner form in fma;  result = p * 2^n by adding n to
 //   the exponent bits.   x > 88.72 -> +inf;  x < -87 -> 0 (no subnormal results);  NaN -> 0x7FC00000.
+// exp_nonpos (attn_lane.h) repeats these operations for arguments that are never positive: the two change together.
 __device__ __forceinline__ float det_expf(float x)
 {
     if (x != x) return __uint_as_float(0x7FC00000u);

@@ -161,7 +161,9 @@ __global__ __launch_bounds__(256) void sample_kernel(const float* __restrict__ l
 constexpr int kSampleThreads = 1024;
 // Up to this top-k the candidates come from the threads' maxima: of 32000 normal logits about 1.1 k reach the bound.
 // 64 rows of 32000: top-k 1 18.7 -> 13.3 us, 50 24.2 -> 16.4, 200 31.5 -> 23.7, 256 32.2 -> 29.7; of 50000 with ties
-// (bf16 values) top-k 50 75.9 -> 29.6.
+// (bf16 values) top-k 50 75.9 -> 29.6.  A row where more than kMaxRanked keys reach the bound has paid for it in vain: 4.5 us
+// where all logits are equal (V = 1000 16.4 -> 20.9, 32000 153 -> 157), up to 15 where they take a dozen values (V = 50000,
+// top-k 256: 87 -> 102).  Above 32768 logits the keys do not all fit the registers (104 spilled).
 constexpr int kBoundTopK = 256, kMaxRanked = 512;
 template <int KPT>
 __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float* __restrict__ logits, int V,
