@@ -53,7 +53,7 @@ __device__ __forceinline__ void wait_then_barrier()
 // Two workgroups a compute unit (243 to 256 registers), so two waves a SIMD.  No unit bounds it alone: on the prompts of 2000 + 1402
 // + 1000 tokens below, vector instructions take 47 % of the cycles (about 30 a score, 16 of them exp, 6 the split), the matrix
 // cores 24 %, LDS 25 %, and scores, exponentials and weighted sums follow one another inside a wave.  Measured on one layer, against eight rows a workgroup with chunk
-// partials in memory and a second pass: prompts of 2000 + 1402 + 1000 tokens, 32/8 heads 1267 -> 242 us; one of 4000 tokens
+// partials in memory and a second pass: prompts of 2000 + 1402 + 1000 tokens, 32/8 heads 1267 -> 244 us; one of 4000 tokens
 // 2240 -> 540 us; 24 of 16..512 tokens, 16/4 heads 195 -> 100 us.  Copies cut down from an earlier form that took 297 us on
 // prompts of 2000 + 1400 + 1000 tokens: 234 without the exponentials, 109 with the loads and barriers alone.
 //
