@@ -25,15 +25,16 @@
 //     visible.  The weight slab of a workgroup is one contiguous run of the packed matrix.
 //   * 16-row blocks are dealt round-robin to the waves 0..NW-1 (block rb -> wave rb % NW).  A wave
 //     with a row block only computes; every other wave only loads.  What bounds a tall tile is the
-//     compute unit's memory pipe (about 25 bytes a clock into LDS for data that hits in L2, and
-//     every load, hit or miss, completes in issue order), so the load queue must never run dry: a
+//     compute unit's memory pipe (every load, hit or miss, completes in issue order; a loop of such loads
+//     takes 94 bytes a ns of data that hits in L2, 50 to 55 of data that does not, whether 32 KB or 128 KB
+//     of them are under way), so the load queue must never run dry: a
 //     wave that both loads and computes either blocks on a full queue with matrix-core work
 //     unissued or computes while the queue drains.
 //   * Weights are the ROW operand of the MFMA (16 output columns of C), activations its COLUMN
 //     operand (16 rows of C): a lane then holds 4 consecutive columns of one row of C and the
 //     store is one 8- or 16-byte write.  Rows of the operand are independent in the matrix core,
-//     so rows past M may hold anything: their lanes load nothing and their outputs are never
-//     stored.
+//     so rows past M may hold anything (their lanes load the last row again, or nothing): their
+//     outputs are never stored.
 //   * Fused forms of the same kernel, each giving the bytes of the unfused sequence: epilogues on the
 //     accumulator rounded to bf16 (residual add, SwiGLU on gate/up-interleaved columns, rotation and cache
 //     append on pair-interleaved query/key/value columns), and, up to four rows, the RMSNorm of the rows
@@ -163,7 +164,8 @@ struct gemm_tile_plan {
     int nchunks;
     int last_cnt;     // stages of the last chunk
     int nload;        // waves that load
-    uint32_t inv_nload, inv_hb;  // floor(2^20/d)+1: n/d = (n * inv) >> 20, exact for the small n used here
+    int groups;       // teams of HB loading waves that share out the stages, 1 where a team has them all (HB >= nload)
+    uint32_t inv_nload, inv_hb, inv_groups;  // floor(2^20/d)+1: n/d = (n * inv) >> 20, exact for the small n used here
 };
 
 // a_res: the activations do not travel through the ring (the kernel that normalizes its rows itself keeps them
@@ -196,6 +198,8 @@ static gemm_tile_plan make_tile_plan(int mrem, int cb, int ringb, int nw, int nl
     t.nload = a_res ? nl : nw + nl - (t.RB < nw ? t.RB : nw);
     t.inv_nload = (1u << 20) / (uint32_t)t.nload + 1u;
     t.inv_hb = (1u << 20) / (uint32_t)t.HB + 1u;
+    t.groups = t.HB < t.nload ? t.nload / t.HB : 1;
+    t.inv_groups = (1u << 20) / (uint32_t)t.groups + 1u;
     return t;
 }
 
@@ -354,37 +358,50 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
         // first slab of this workgroup (a slab holds nstages stages of 2*PCB blocks)
         const char* wbytes = reinterpret_cast<const char*>(Bp + (size_t)blockIdx.x * (CB / PCB) * nstages * (2 * PCB * 64));
         const char* abytes = reinterpret_cast<const char*>(A + (size_t)m0 * lda);
-        const size_t half_bytes = (size_t)lda * 16;  // 8 rows of A
         const uint32_t w_lane_off = (uint32_t)lane * 16u;
-        const int lrow = lane >> 3;  // row of this lane inside a half block
-        const uint32_t zl = (uint32_t)(((lane >> 4) & 3) << 1);
-        const uint32_t a_lane_off0 = (uint32_t)lrow * (uint32_t)lda * 2u + 16u * ((uint32_t)(lane & 7) ^ zl);
-        const uint32_t a_lane_off1 = (uint32_t)lrow * (uint32_t)lda * 2u + 16u * ((uint32_t)(lane & 7) ^ (zl | 1u));
-        const uint32_t a_lane_off_mine = (lrank & 1) ? a_lane_off1 : a_lane_off0;
-        // Split of a chunk's loads over the loading waves.  Weight blocks: q = lrank, lrank+nload, ...
-        // below s_cnt*2*CB.  Half blocks: if every half block is whole and there are at least nload of
-        // them, hb = lrank, lrank+nload, ... below HB in every stage (short loop: the loaders'
-        // instruction count per load matters for tall tiles); else unit pp = sl*HB + hb = lrank,
-        // lrank+nload, ... below s_cnt*HB.  A half block that holds data always has a live lane.
-        const bool stage_split = (mrem & 7) == 0 && HB >= nload;
-        auto strided = [&](int n) { return n > lrank ? (int)(((uint32_t)(n - lrank + nload - 1) * tp.inv_nload) >> 20) : 0; };
+        // Split of a chunk's loads over the loading waves.  Half blocks: with at least nload of them a wave has hb = lrank,
+        // lrank+nload, ... below HB in every stage; with fewer, teams of HB waves take the stages in turn, a wave always the
+        // same half block.  So a wave's half blocks, and with them its lanes' offsets (rows past the tile's last one repeat
+        // it: their LDS bytes feed only outputs that are never stored), are fixed, and a load is one instruction and a scalar
+        // addition.  Weight blocks: q = wrank, wrank+nload, ... below s_cnt*2*CB, dealt from the other end, so that the waves
+        // with the fewer half blocks have the more weight blocks.
+        // A launch of 17 to 256 rows is bound by these loads up to about 128 rows (with the computing waves' work taken out it
+        // is no faster), so what a load costs its wave shows.  While a tile whose rows are no multiple of 8, or fewer half
+        // blocks than loading waves, masked and stepped every load by itself, K x N 14336 x 4096 took 29.3 / 43 / 71 us at
+        // 23 / 45 / 95 rows, now 25.0 / 33.9 / 52.6 (loads alone, in a loop that does nothing else, 25.7 / 32.8 / -);
+        // 5632 x 2048 at 24 rows 10.7 -> 7.7, 4096 x 6144 at 161 rows 46.7 -> 29.9, 4096 x 28672 at 201 rows 77 -> 62.
+        constexpr int kMaxHalf = 32 / NL;  // most half blocks of a stage, one wave: nload >= NL
+        const int wrank = nload - 1 - lrank;
+        const bool teams = HB < nload;
+        const int team = teams ? (int)(((uint32_t)lrank * tp.inv_hb) >> 20) : 0;  // lrank / HB
+        const int hb0 = lrank - team * (teams ? HB : 0);
+        const int s_stride = tp.groups;
+        auto strided = [&](int n, int rank) { return n > rank ? (int)(((uint32_t)(n - rank + nload - 1) * tp.inv_nload) >> 20) : 0; };
+        const int nh = NORM || team >= tp.groups ? 0 : (teams ? 1 : strided(HB, lrank));  // half blocks of a stage, this wave
+        uint32_t a_off[kMaxHalf];
+#pragma unroll
+        for (int i = 0; i < kMaxHalf; ++i) {
+            const int hb = hb0 + i * nload;
+            const int row = min(8 * hb + (lane >> 3), mrem - 1);
+            const uint32_t z = (uint32_t)(2 * ((lane >> 4) & 3) + (hb & 1));  // swizzle of row 8*hb + lane/8 (see above)
+            a_off[i] = (uint32_t)row * (uint32_t)lda * 2u + 16u * ((uint32_t)(lane & 7) ^ z);
+        }
         // With the weights in several slabs (PCB < CB) the split is by position inside a stage instead:
-        // u = lrank, lrank+nload, ... below 2*CB, the same for every stage, since block u of successive
+        // u = wrank, wrank+nload, ... below 2*CB, the same for every stage, since block u of successive
         // stages is evenly spaced both in its slab and in LDS.
-        const int nw_stage = strided(2 * CB);
+        const int nw_stage = strided(2 * CB, wrank);
+        auto a_stages = [&](int s_cnt) {  // stages of a chunk of which this wave has half blocks
+            return s_cnt > team ? (int)(((uint32_t)(s_cnt - team + s_stride - 1) * tp.inv_groups) >> 20) : 0;
+        };
         auto loads_for = [&](int s_cnt) {
-            return (PCB == CB ? strided(s_cnt * 2 * CB) : s_cnt * nw_stage) +
-                   (NORM ? 0 : (stage_split ? s_cnt * strided(HB) : strided(s_cnt * HB)));
+            return (PCB == CB ? strided(s_cnt * 2 * CB, wrank) : s_cnt * nw_stage) + nh * a_stages(s_cnt);
         };
         // every chunk but the last has SPC stages, so two values cover all chunks
         const int loads_full = loads_for(SPC);
         const int loads_last = loads_for(tp.last_cnt);
         auto wave_loads = [&](int c) { return c < nchunks - 1 ? loads_full : (c == nchunks - 1 ? loads_last : 0); };
-        const int nw_full = strided(SPC * 2 * CB);  // weight blocks of a chunk, this wave
-        const int nw_last = strided(tp.last_cnt * 2 * CB);
-        const int nh_stage = strided(HB);  // half blocks of a stage, this wave, under the stage split
-        const int first_sl = (int)(((uint32_t)lrank * tp.inv_hb) >> 20);  // lrank / HB: first unit of a chunk under the unit split
-        const int first_hb = lrank - first_sl * HB;
+        const int nw_full = strided(SPC * 2 * CB, wrank);  // weight blocks of a chunk, this wave
+        const int nw_last = strided(tp.last_cnt * 2 * CB, wrank);
 
         auto load_chunk = [&](int c, int slot_idx) {
             const int s_cnt = chunk_stages(c);
@@ -393,11 +410,11 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
             const int nw = s_cnt * 2 * CB;
             const uint32_t slot_addr = ring_addr + (uint32_t)(slot_idx * slot_blocks) * 1024u;
             if constexpr (PCB == CB) {
-                dma_run(wbytes, w_lane_off + (uint32_t)(s0 * (2 * CB) + lrank) * 1024u, (uint32_t)nload * 1024u,
-                        slot_addr + (uint32_t)lrank * 1024u, (uint32_t)nload * 1024u, s_cnt == SPC ? nw_full : nw_last);
+                dma_run(wbytes, w_lane_off + (uint32_t)(s0 * (2 * CB) + wrank) * 1024u, (uint32_t)nload * 1024u,
+                        slot_addr + (uint32_t)wrank * 1024u, (uint32_t)nload * 1024u, s_cnt == SPC ? nw_full : nw_last);
             } else {
                 // block u of a stage = block u % 2PCB of that stage in slab u / 2PCB
-                for (int u = lrank; u < 2 * CB; u += nload) {
+                for (int u = wrank; u < 2 * CB; u += nload) {
                     const int j2 = u / (2 * PCB), t = u % (2 * PCB);
                     dma_run(wbytes + (size_t)j2 * nstages * (2 * PCB * 1024),
                             w_lane_off + (uint32_t)(s0 * (2 * PCB) + t) * 1024u, (uint32_t)(2 * PCB) * 1024u,
@@ -405,55 +422,14 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
                 }
             }
             if constexpr (NORM) return;  // the activations are resident
-            // Half block hb of stage sl comes from abytes + hb*half_bytes + 128*(s0+sl) and goes to block
-            // 2*RB*sl + hb of the tile area; both are walked with running addresses.
-            if (stage_split && (nload & 1) == 0) {  // all of this wave's half blocks have the parity of its rank
-                uint32_t off = a_lane_off_mine + (uint32_t)lrank * (uint32_t)half_bytes + ((uint32_t)s0 << 7);
-                uint32_t adst = slot_addr + (uint32_t)(nw + lrank) * 1024u;
-                for (int sl = 0; sl < s_cnt; ++sl) {
-                    dma_run(abytes, off, (uint32_t)nload * (uint32_t)half_bytes, adst, (uint32_t)nload * 1024u, nh_stage);
-                    off += 128;
-                    adst += (uint32_t)(2 * RB) * 1024u;
-                }
-                return;
-            }
-            if (stage_split) {
-                const char* src0 = abytes + (size_t)lrank * half_bytes + ((size_t)s0 << 7);
-                uint32_t dst0 = slot_addr + (uint32_t)(nw + lrank) * 1024u;
-                for (int sl = 0; sl < s_cnt; ++sl) {
-                    const char* asrc = src0;
-                    uint32_t adst = dst0;
-                    for (int hb = lrank; hb < HB; hb += nload) {
-                        dma_block(asrc, (hb & 1) ? a_lane_off1 : a_lane_off0, adst);
-                        asrc += (size_t)nload * half_bytes;
-                        adst += (uint32_t)nload * 1024u;
-                    }
-                    src0 += 128;
-                    dst0 += (uint32_t)(2 * RB) * 1024u;
-                }
-                return;
-            }
-            if (HB == 1) {  // at most 8 rows: one half block a stage, stages lrank, lrank+nload, ...
-                if (lrow < mrem)
-                    dma_run(abytes, a_lane_off0 + ((uint32_t)(s0 + lrank) << 7), (uint32_t)nload << 7,
-                            slot_addr + (uint32_t)(nw + lrank * 2 * RB) * 1024u, (uint32_t)(nload * 2 * RB) * 1024u,
-                            strided(s_cnt));
-                return;
-            }
-            const int nhalf = s_cnt * HB;
-            int hb = first_hb;
-            const char* asrc = abytes + (size_t)hb * half_bytes + ((size_t)(s0 + first_sl) << 7);
-            uint32_t adst = slot_addr + (uint32_t)(nw + first_sl * 2 * RB + hb) * 1024u;
-            for (int pp = lrank; pp < nhalf; pp += nload) {
-                // rows past M load nothing: their LDS bytes feed only outputs that are never stored
-                if (8 * hb + lrow < mrem) dma_block(asrc, (hb & 1) ? a_lane_off1 : a_lane_off0, adst);
-                hb += nload;
-                asrc += (size_t)nload * half_bytes;
-                adst += (uint32_t)nload * 1024u;
-                while (hb >= HB) {  // next stage
-                    hb -= HB;
-                    asrc += 128 - (ptrdiff_t)((size_t)HB * half_bytes);
-                    adst += (uint32_t)(2 * RB - HB) * 1024u;
+            // half block hb of stage sl goes to block 2*RB*sl + hb of the tile area
+            for (int sl = team; sl < s_cnt && nh > 0; sl += s_stride) {
+                const char* asrc = abytes + ((size_t)(s0 + sl) << 7);
+                dma_run_begin(slot_addr + (uint32_t)(nw + 2 * RB * sl + hb0) * 1024u);
+#pragma unroll
+                for (int i = 0; i < kMaxHalf; ++i) {
+                    if (i >= nh) break;
+                    dma_run_next(asrc, a_off[i], (uint32_t)nload * 1024u);
                 }
             }
         };

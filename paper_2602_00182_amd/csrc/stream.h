@@ -60,6 +60,16 @@ __device__ __forceinline__ void dma_run_next(const void* base, uint32_t& lane_of
         : "s"(base), "s"(src_stride), "s"(lds_stride)
         : "memory", "scc");
 }
+// The next load of a run whose sources have no constant stride: a base and offset of its own.
+__device__ __forceinline__ void dma_run_next(const void* base, uint32_t lane_off, uint32_t lds_stride)
+{
+    asm volatile(
+        "global_load_lds_dwordx4 %0, %1\n\t"
+        "s_add_u32 m0, m0, %2"
+        :
+        : "v"(lane_off), "s"(base), "s"(lds_stride)
+        : "memory", "scc");
+}
 __device__ __forceinline__ void dma_run(const void* base, uint32_t lane_off, uint32_t src_stride, uint32_t lds_addr,
                                         uint32_t lds_stride, int n)
 {

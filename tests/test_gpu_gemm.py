@@ -76,6 +76,24 @@ def test_integer_matrices_are_exact(d, orc, M, N, K):
     assert np.array_equal(got32, exact.astype(np.float32))
 
 
+@pytest.mark.parametrize("N", [2048, 6224, 11264])
+@pytest.mark.parametrize("M", [7, 9, 23, 33, 45, 57, 65, 95, 121, 129, 250, 256])
+def test_ragged_rows_whatever_the_split_of_the_loads(d, orc, M, N):
+    """Row counts around every split of a tile's half blocks over the loading waves, in the row-cut (N = 2048), two-workgroups-a-
+    compute-unit (6224) and wide (11264) forms, the rows behind the last one NaN: small integers, so exact."""
+    K = 64 * 11
+    A = ds.small_int_bf16(500 + M, (M, K))
+    Bm = ds.small_int_bf16(600 + N, (K, N))
+    want = orc.bf16_rne((ds.bf16_bits_to_f32(A) @ ds.bf16_bits_to_f32(Bm)).astype(np.float32))  # |sum| < 2^24: exact in fp32
+    buf = torch.full((M + 16, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+    buf[:M] = up_bf16(A)
+    C = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    step(f"gemm ragged M={M} N={N}")
+    d.det_gemm_bf16(buf[:M], d.pack_weight(up_bf16(Bm)), C, N, K)
+    torch.cuda.synchronize()
+    assert np.array_equal(down_bf16(C), want)
+
+
 def test_rne_ties_and_identity(d, orc):
     """Identity weights copy A; a product of 257 must round to 256 (tie to even)."""
     K = N = 256
