@@ -29,6 +29,21 @@ namespace det {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
+// The codes q of a column block's 64 k, stored as q + 8, two a byte, become 16*q as signed bytes (the nibble in the upper half
+// of a byte, its top bit flipped), and the matrix core sums 16*p*q from the bits of 786432, a float whose last place is worth
+// 1/16: read as a float the sum is 786432 + P, exactly (|P| <= 64 * 128 * 8), and one subtraction gives P.  Neither the +8 (which
+// took a matrix instruction more for every row block, or six vector instructions more a column block) nor the conversion to
+// floating point, which issues at half the rate of a subtraction, costs anything of its own.  us before and after: 1962 rows
+// 2048 x 11264 113 -> 102, 5632 x 2048 58 -> 52, 14336 x 4096 266 -> 245, 4096 x 28672 521 -> 465; 24 rows of 4096 x 28672
+// 22.7 -> 20.6, 128 rows of 14336 x 4096 77 -> 73, one row of 4096 x 28672 16.2 -> 15.2.
+constexpr v4i kProductStart = {0x49400000, 0x49400000, 0x49400000, 0x49400000};
+__device__ __forceinline__ float product(int sum) { return __int_as_float(sum) - 786432.0f; }
+__device__ __forceinline__ v4i code_bytes(const uint2& c)
+{
+    auto hi = [](uint32_t x) { return (int)((x & 0xF0F0F0F0u) ^ 0x80808080u); };
+    return v4i{hi(c.x << 4), hi(c.x), hi(c.y << 4), hi(c.y)};
+}
+
 constexpr int kQRing = 144;   // KB of LDS ring
 constexpr int kQWaves = 8;    // waves that can compute
 constexpr int kQLoaders = 4;  // waves that only load
@@ -433,26 +448,17 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
                     xa[u] = *reinterpret_cast<const v4i*>(tiles + (size_t)(s * RB + rg) * TB + 64 * lrc +
                                                           16 * (g ^ ((lrc >> 2) & 3)));
                     dv[u] = *reinterpret_cast<const float*>(scales + (size_t)s * RB * 64 + (16 * rg + lr) * 4);
-                    // the stored nibble is q + 8: taken as it is, with -8 * (sum of the block's activation
-                    // codes) as the matrix core's starting value, which is the same integer
-                    wu[u][0] = (int)(codes.x & 0x0F0F0F0Fu);
-                    wu[u][1] = (int)((codes.x >> 4) & 0x0F0F0F0Fu);
-                    wu[u][2] = (int)(codes.y & 0x0F0F0F0Fu);
-                    wu[u][3] = (int)((codes.y >> 4) & 0x0F0F0F0Fu);
+                    wu[u] = code_bytes(codes);
                 }
                 v4i pr[UU];
 #pragma unroll
-                for (int u = 0; u < UU; ++u) {
-                    const int m8 = (int)0xF8F8F8F8u;
-                    const v4i base = __builtin_amdgcn_mfma_i32_16x16x64_i8(v4i{m8, m8, m8, m8}, xa[u], v4i{0, 0, 0, 0}, 0, 0, 0);
-                    pr[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[u], xa[u], base, 0, 0, 0);
-                }
+                for (int u = 0; u < UU; ++u) pr[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[u], xa[u], kProductStart, 0, 0, 0);
 #pragma unroll
                 for (int u = 0; u < UU; ++u) {
                     const int s = sl + u * SG;
                     const float4 t = make_float4(dv[u] * bf16lo_to_f32(sraw[u].x), dv[u] * bf16hi_to_f32(sraw[u].x),
                                                  dv[u] * bf16lo_to_f32(sraw[u].y), dv[u] * bf16hi_to_f32(sraw[u].y));
-                    const float4 pf = make_float4((float)pr[u][0], (float)pr[u][1], (float)pr[u][2], (float)pr[u][3]);
+                    const float4 pf = make_float4(product(pr[u][0]), product(pr[u][1]), product(pr[u][2]), product(pr[u][3]));
                     if (row_kept) {
                         *reinterpret_cast<float4*>(rw + (size_t)s * res_stage) = t;
                         *reinterpret_cast<float4*>(rw + (size_t)s * res_stage + RT * 64) = pf;
@@ -509,12 +515,6 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
             auto stages = [&](int sl, auto uu_tag) {
                 constexpr int UU = decltype(uu_tag)::value;
                 constexpr int G = NR < 4 ? NR : 4;  // row blocks at a time
-                // With one or two row blocks the wave's time goes into vector instructions, not the matrix
-                // core: the stored nibbles q + 8 are then used as they are and the matrix core starts from
-                // -8 * (sum of the block's activation codes), one more matrix instruction per row block
-                // instead of twelve vector instructions per stage; the integer is the same.
-                constexpr bool kBias = NR <= 2;
-                auto expand = [](uint32_t x) { return (((x & 0x0F0F0F0Fu) | 0x80808080u) - 0x08080808u) ^ 0x80808080u; };
                 v4i wq[UU];
                 float sc[UU][4];
 #pragma unroll
@@ -522,18 +522,7 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
                     const char* wst = slot + (sl + u) * WST;
                     const uint2 codes = *reinterpret_cast<const uint2*>(wst + j * 512 + lane * 8);
                     const uint2 sraw = *reinterpret_cast<const uint2*>(wst + 512 * CB + j * 32 + g * 8);
-                    if constexpr (kBias) {
-                        wq[u][0] = (int)(codes.x & 0x0F0F0F0Fu);
-                        wq[u][1] = (int)((codes.x >> 4) & 0x0F0F0F0Fu);
-                        wq[u][2] = (int)(codes.y & 0x0F0F0F0Fu);
-                        wq[u][3] = (int)((codes.y >> 4) & 0x0F0F0F0Fu);
-                    } else {
-                        // 16 codes -> 16 signed bytes: per byte (u | 0x80) - 8, then the top bit flipped back
-                        wq[u][0] = (int)expand(codes.x);
-                        wq[u][1] = (int)expand(codes.x >> 4);
-                        wq[u][2] = (int)expand(codes.y);
-                        wq[u][3] = (int)expand(codes.y >> 4);
-                    }
+                    wq[u] = code_bytes(codes);
                     sc[u][0] = bf16lo_to_f32(sraw.x);
                     sc[u][1] = bf16hi_to_f32(sraw.x);
                     sc[u][2] = bf16lo_to_f32(sraw.y);
@@ -551,13 +540,7 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
                                                                          64 * lrc + 16 * (g ^ ((lrc >> 2) & 3)));
                             dv[u][r] = *reinterpret_cast<const float*>(scales + (size_t)(sl + u) * RB * 64 +
                                                                        (16 * rbs[r0 + r] + lr) * 4);
-                            if constexpr (kBias) {
-                                const int m8 = (int)0xF8F8F8F8u;
-                                const v4i base = __builtin_amdgcn_mfma_i32_16x16x64_i8(v4i{m8, m8, m8, m8}, xa, v4i{0, 0, 0, 0}, 0, 0, 0);
-                                pr[u][r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wq[u], xa, base, 0, 0, 0);
-                            } else {
-                                pr[u][r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wq[u], xa, v4i{0, 0, 0, 0}, 0, 0, 0);
-                            }
+                            pr[u][r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wq[u], xa, kProductStart, 0, 0, 0);
                         }
 #pragma unroll
                     for (int u = 0; u < UU; ++u)
@@ -565,7 +548,7 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
                         for (int r = 0; r < G; ++r)
 #pragma unroll
                             for (int v = 0; v < 4; ++v)
-                                acc[r0 + r][v] = __builtin_fmaf(dv[u][r] * sc[u][v], (float)pr[u][r][v], acc[r0 + r][v]);
+                                acc[r0 + r][v] = __builtin_fmaf(dv[u][r] * sc[u][v], product(pr[u][r][v]), acc[r0 + r][v]);
                 }
             };
             constexpr int U = NR == 1 ? 4 : (NR == 2 ? 2 : 1);
@@ -652,16 +635,16 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
 // ------------------------------------------------------------------------------------------------
 // The same product for launches of many rows: 64 x 128 tiles, four waves of 64 rows x 32 columns.
 //
-// What bounds it is the scaling arithmetic, three vector instructions per output and block (d*s, the conversion,
-// the fma), a wave having eight 16 x 16 outputs of it a block against twelve matrix instructions; so a wave owns a tile
-// that is tall: it unpacks the codes of two column blocks for four row blocks, and the row sums -8 * (sum of p), with
-// which the matrix core starts so that the stored nibbles q + 8 serve as they are, are shared by its columns.
-// The operands of two blocks of K (a chunk) travel together through a ring of three LDS slots, two in flight, each
-// wave loading its share; activation rows come as whole 128-byte lines.  Three workgroups a compute unit (four slots
-// and two workgroups measured 5 to 15 % slower).  Against the kernel above, us: 1962 rows K x N 2048 x 2048 92 -> 27,
-// 5632 x 2048 227 -> 61, 4096 x 4096 327 -> 84, 14336 x 4096 1084 -> 278, 2048 x 11264 160 -> 106, 4096 x 28672
-// 593 -> 506 (0.91 POP/s; instruction issue alone is about 450).  Of the cycles of the last but one, vector instructions take 84 %,
-// the matrix cores 23, LDS 20.
+// What bounds it is the scaling arithmetic, three vector instructions per output and block (d*s, the subtraction that makes
+// the product a float, the fma), a wave having eight 16 x 16 outputs of it a block against eight matrix instructions, and a SIMD's
+// vector and matrix instructions add up: 16 clocks each of these, at best 2.3 each of those whatever the waves (measured
+// in a loop of nothing else), 410 clocks a wave and block, of which a launch reaches 75 %.  So a wave owns a tile that is
+// tall: it unpacks the codes of two column blocks for four row blocks.  The operands of two blocks of K (a chunk) travel
+// together through a ring of three LDS slots, two in flight, each wave loading its share; activation rows come as whole
+// 128-byte lines.  Three workgroups a compute unit (four slots and two workgroups measured 5 to 15 % slower).  The outer
+// products d*s on the matrix cores (four 16 x 16 x 1 of fp32 an instruction) were no faster: while they run a SIMD issues no
+// vector instruction.  Against the kernel above, us: 1962 rows K x N 2048 x 2048 92 -> 23, 5632 x 2048 227 -> 52, 14336 x 4096
+// 1084 -> 245, 2048 x 11264 160 -> 102, 4096 x 28672 593 -> 465 (0.99 POP/s).
 constexpr int kTallRows = 64, kTallCols = 128, kTallWaves = 4, kTallSlots = 3;
 constexpr int kTallA = kTallRows * 128;                    // activation codes of a chunk
 constexpr int kTallW = 2 * 8 * 544;                        // weight codes and scales: [slab][block][544 * CB]
@@ -779,10 +762,7 @@ __global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
             float sc[2][4];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                wu[j][0] = (int)(codes[j].x & 0x0F0F0F0Fu);
-                wu[j][1] = (int)((codes[j].x >> 4) & 0x0F0F0F0Fu);
-                wu[j][2] = (int)(codes[j].y & 0x0F0F0F0Fu);
-                wu[j][3] = (int)((codes[j].y >> 4) & 0x0F0F0F0Fu);
+                wu[j] = code_bytes(codes[j]);
                 sc[j][0] = bf16lo_to_f32(sraw[j].x);
                 sc[j][1] = bf16hi_to_f32(sraw[j].x);
                 sc[j][2] = bf16lo_to_f32(sraw[j].y);
@@ -791,10 +771,8 @@ __global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
             v4i pr[4][2];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int m8 = (int)0xF8F8F8F8u;
-                const v4i base = __builtin_amdgcn_mfma_i32_16x16x64_i8(v4i{m8, m8, m8, m8}, xa[r], v4i{0, 0, 0, 0}, 0, 0, 0);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) pr[r][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[j], xa[r], base, 0, 0, 0);
+                for (int j = 0; j < 2; ++j) pr[r][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[j], xa[r], kProductStart, 0, 0, 0);
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -802,7 +780,7 @@ __global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        acc[r][j][v] = __builtin_fmaf(dv[r] * sc[j][v], (float)pr[r][j][v], acc[r][j][v]);
+                        acc[r][j][v] = __builtin_fmaf(dv[r] * sc[j][v], product(pr[r][j][v]), acc[r][j][v]);
         };
         block(0);
         if (2 * c + 1 < nblk) block(1);

@@ -82,6 +82,26 @@ def test_qgemm_bytes_match_oracle(d, orc, M, K, N):
     assert np.array_equal(down_bf16(c), cb)
 
 
+@pytest.mark.parametrize("M", [1, 8, 20, 60, 130, 300])
+def test_qgemm_of_the_largest_sums(d, orc, M):
+    """Blocks whose codes are all of one sign and the largest (-128 among the activations, which a caller may bring): the
+    integer sums at both ends of their range, in every form of the kernel."""
+    K, N = 192, 4096
+    a = np.where(np.arange(M)[:, None] % 2 == 0, 1.0, -1.0).astype(np.float32) * np.ones((M, K), np.float32)
+    w = np.where(np.arange(N)[None, :] % 3 == 0, 0.02, -0.02).astype(np.float32) * np.ones((K, N), np.float32)
+    packed, q, s = gpu_quant_w(d, ds.f32_to_bf16_bits(w))
+    codes, scales, p, dd = gpu_quant_a(d, ds.f32_to_bf16_bits(a))
+    codes[:, 64:128] = torch.where(codes[:, 64:128] < 0, -128, codes[:, 64:128].int()).to(torch.int8)
+    p = codes.cpu().numpy()
+    assert abs(p.astype(int)).min() >= 127 and abs(q.astype(int)).min() == 7
+    cf = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
+    step(f"qgemm largest sums M={M}")
+    d.det_qgemm_w4a8(codes, scales, packed, cf, N)
+    torch.cuda.synchronize()
+    acc, _ = orc.qgemm_w4a8(p, dd, q, s)
+    assert np.array_equal(cf.cpu().numpy().view(np.uint32), acc.view(np.uint32))
+
+
 def test_qgemm_batch_invariance_and_repeats(d):
     K, N = 4096, 6144
     a = ds.normal_bf16(ds.tensor_seed(6, 40), (256, K), 1.0, 0.0)
