@@ -18,8 +18,8 @@
 // w % CB, row blocks w / CB, w / CB + 8/CB, ...): at small M the work per stage is the unpacking of
 // the codes, which a single wave could not do at the rate the weights stream in.  Tiles of at most 8
 // rows and 2 column blocks go further and split the stages of a chunk over the waves (run_sp below):
-// only the accumulation chain has a defined order, and it keeps it.  Launches of many rows take tiles of 64 rows x
-// 128 columns instead (qgemm_tall_kernel).
+// only the accumulation chain has a defined order, and it keeps it.  Launches of more rows take tiles of 32
+// or 64 rows x 64 or 128 columns instead (qgemm_tile_kernel).
 #include <type_traits>
 
 #include "internal.h"
@@ -633,23 +633,28 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// The same product for launches of many rows: 64 x 128 tiles, four waves of 64 rows x 32 columns.
+// The same product for launches of more rows than the kernel above is made for: tiles of 16*RB rows and 64*JB columns, four waves
+// side by side of 16*RB rows x 16*JB columns each.  64 x 128 (RB 4, JB 2) where there are enough of them, 64 x 64 and 32 x 64
+// below (qgemm_pick).
 //
-// What bounds it is the scaling arithmetic, three vector instructions per output and block (d*s, the subtraction that makes
+// What bounds the first is the scaling arithmetic, three vector instructions per output and block (d*s, the subtraction that makes
 // the product a float, the fma), a wave having eight 16 x 16 outputs of it a block against eight matrix instructions, and a SIMD's
 // vector and matrix instructions add up: 16 clocks each of these, at best 2.3 each of those whatever the waves (measured
 // in a loop of nothing else), 410 clocks a wave and block, of which a launch reaches 75 %.  So a wave owns a tile that is
 // tall: it unpacks the codes of two column blocks for four row blocks.  The operands of two blocks of K (a chunk) travel
-// together through a ring of three LDS slots, two in flight, each wave loading its share; activation rows come as whole
-// 128-byte lines.  Three workgroups a compute unit (four slots and two workgroups measured 5 to 15 % slower).  The outer
-// products d*s on the matrix cores (four 16 x 16 x 1 of fp32 an instruction) were no faster: while they run a SIMD issues no
-// vector instruction.  Against the kernel above, us: 1962 rows K x N 2048 x 2048 92 -> 23, 5632 x 2048 227 -> 52, 14336 x 4096
+// together through a ring of LDS slots, each wave loading its share; activation rows come as whole 128-byte lines.  Three slots
+// and three workgroups a compute unit (four slots and two workgroups measured 5 to 15 % slower).  The outer products d*s on the
+// matrix cores (four 16 x 16 x 1 of fp32 an instruction) were no faster: while they run a SIMD issues no vector
+// instruction.  Against the kernel above, us: 1962 rows K x N 2048 x 2048 92 -> 23, 5632 x 2048 227 -> 52, 14336 x 4096
 // 1084 -> 245, 2048 x 11264 160 -> 102, 4096 x 28672 593 -> 465 (0.99 POP/s).
-constexpr int kTallRows = 64, kTallCols = 128, kTallWaves = 4, kTallSlots = 3;
-constexpr int kTallA = kTallRows * 128;                    // activation codes of a chunk
-constexpr int kTallW = 2 * 8 * 544;                        // weight codes and scales: [slab][block][544 * CB]
-constexpr int kTallD = 2 * kTallRows * 4;                  // activation scales: [block][row]
-constexpr int kTallSlot = kTallA + kTallW + kTallD;        // 17408 bytes
+//
+// A launch of fewer workgroups than the chip holds takes the time of one walk over K, a chain of 0.2 (32 x 64) to 0.45 us
+// (64 x 128) a block: loads' latency where the ring is short (32 x 64 tiles 0.25 us with three slots), one wave's instructions
+// otherwise (reading a chunk's operands while the chunk before it is computed gained nothing).  So the smaller the launch, the
+// smaller its tile: 4096 x 4096 33.5 -> 19 us at 192 rows, 14336 x 4096 106 -> 57, 5632 x 2048 at 500 rows 43 -> 26.
+// Six and four slots, so that three workgroups of every size fit a compute unit.
+constexpr int kTileWaves = 4;
+__host__ __device__ constexpr int qtile_slots(int rb, int jb) { return rb * jb == 8 ? 3 : (rb * jb == 4 ? 4 : 6); }
 
 template <int N>
 __device__ __forceinline__ void q_wait_then_barrier()
@@ -657,18 +662,26 @@ __device__ __forceinline__ void q_wait_then_barrier()
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-template <int CB, int EPI>
-__global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
+template <int CB, int EPI, int RB, int JB>
+__global__ __launch_bounds__(64 * kTileWaves, 3) void qgemm_tile_kernel(
     const int8_t* __restrict__ qa, int K, const float* __restrict__ da, int ldd, const uint8_t* __restrict__ wp, void* C,
     int ldc, const uint16_t* R, int ldr, int out_f32, int M, float* qscales_out, gemm_rope_args ra)
 {
-    __shared__ uint4 ring[kTallSlots * kTallSlot / 16];
-    __shared__ float rowmax[EPI == kEpiSwigluQuant ? kTallWaves * kTallRows : 1];
+    constexpr int TR = 16 * RB, CBT = kTileWaves * JB, TC = 16 * CBT;  // rows, column blocks and columns of a tile
+    constexpr int ABYTES = TR * 128;          // activation codes of a chunk
+    constexpr int WBYTES = 2 * CBT * 544;     // weight codes and scales: [slab][block][544 * CB]
+    constexpr int SLOT = ABYTES + WBYTES + 2 * TR * 4;  // and activation scales: [block][row]
+    constexpr int AU = TR / 8 / kTileWaves;   // loads of activations of a chunk, one wave
+    static_assert(CBT % CB == 0 && TR % 32 == 0, "whole slabs, a load of every wave");
+    static_assert(EPI != kEpiSwigluQuant || CBT == 8, "a 128-column tile holds one 64-output block per row");
+    constexpr int NS = qtile_slots(RB, JB);
+    __shared__ uint4 ring[NS * SLOT / 16];
+    __shared__ float rowmax[EPI == kEpiSwigluQuant ? kTileWaves * TR : 1];
     constexpr int WST = qstage_w_bytes(CB);  // bytes of a block of a slab
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, lr = lane & 15;
-    const int m0 = blockIdx.y * kTallRows, n0 = blockIdx.x * kTallCols;
+    const int m0 = blockIdx.y * TR, n0 = blockIdx.x * TC;
     const int nblk = K >> 6, nchunks = (nblk + 1) >> 1;
     const uint32_t ring_addr = (uint32_t)(uintptr_t)(lds_char_t*)ring;
     const char* abytes = reinterpret_cast<const char*>(qa);
@@ -679,15 +692,15 @@ __global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
     // (lane%8) ^ (row/2)%8, which spreads the sixteen rows of an operand read over the banks.  Weights, unit u = wave,
     // wave + 4 (and 8, half a unit, wave 0): piece 64u + lane of the chunk's 544, of slab piece / (68*CB).  Scales (wave 1):
     // block lane/16, rows 4*(lane%16) .. +3.  `odd`: a last chunk of one block repeats that block's bytes.
-    uint32_t a_off[2][2];
-    const char* a_base[2];
+    uint32_t a_off[2][AU];
+    const char* a_base[AU];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int row = 8 * (2 * wave + i) + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
-        const int first = m0 + 8 * (2 * wave + i);
+    for (int i = 0; i < AU; ++i) {
+        const int row = 8 * (AU * wave + i) + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
+        const int first = m0 + 8 * (AU * wave + i);
         a_base[i] = abytes + (size_t)(first < M ? first : M - 1) * K;
         const int src = m0 + row < M ? row : M - 1 - m0;                    // >= 0: a tile holds a row
-        const int rel = first < M ? src - 8 * (2 * wave + i) : 0;           // rows from a_base
+        const int rel = first < M ? src - 8 * (AU * wave + i) : 0;           // rows from a_base
         a_off[0][i] = (uint32_t)rel * (uint32_t)K + 16u * (uint32_t)piece;
         a_off[1][i] = (uint32_t)rel * (uint32_t)K + 16u * (uint32_t)(piece & 3);
     }
@@ -698,105 +711,111 @@ __global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
         if (odd && p >= 34 * CB) p -= 34 * CB;
         return (size_t)slab * nblk * WST + 16 * (size_t)p;
     };
-    const size_t w_off0 = w_source(wave, false), w_off1 = w_source(wave + 4, false), w_off2 = w_source(8, false);
-    const int d_piece = min((m0 >> 2) + (lane & 15), (ldd >> 2) - 1);
+    const size_t w_off0 = w_source(wave, false), w_off1 = w_source(wave + 4 * (JB - 1), false), w_off2 = w_source(4 * JB, false);
+    const int d_piece = min((m0 >> 2) + (lane & (TR / 4 - 1)), (ldd >> 2) - 1);
 
     auto issue = [&](int c) {
         const bool odd = 2 * c + 1 == nblk;
-        const uint32_t slot = ring_addr + (uint32_t)(c % kTallSlots) * (uint32_t)kTallSlot;
+        const uint32_t slot = ring_addr + (uint32_t)(c % NS) * (uint32_t)SLOT;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            dma_block(a_base[i] + (size_t)c * 128, a_off[odd ? 1 : 0][i], slot + (uint32_t)(2 * wave + i) * 1024u);
-        const uint32_t w = slot + kTallA;
+        for (int i = 0; i < AU; ++i)
+            dma_block(a_base[i] + (size_t)c * 128, a_off[odd ? 1 : 0][i], slot + (uint32_t)(AU * wave + i) * 1024u);
+        const uint32_t w = slot + ABYTES;
         const char* wsrc = wbytes + (size_t)c * (2 * WST);
         dma_lane(wsrc + (odd ? w_source(wave, true) : w_off0), w + (uint32_t)wave * 1024u);
-        dma_lane(wsrc + (odd ? w_source(wave + 4, true) : w_off1), w + (uint32_t)(wave + 4) * 1024u);
+        if (JB == 2) dma_lane(wsrc + (odd ? w_source(wave + 4, true) : w_off1), w + (uint32_t)(wave + 4) * 1024u);
         if (wave == 0) {
-            if (lane < 32) dma_lane(wsrc + (odd ? w_source(8, true) : w_off2), w + 8192u);
+            if (lane < 16 * JB) dma_lane(wsrc + (odd ? w_source(4 * JB, true) : w_off2), w + 4096u * JB);
         } else if (wave == 1) {
-            const int b = 2 * c + ((lane >> 4) & 1);
-            if (lane < 32) dma_lane(dbytes + ((size_t)(b < nblk ? b : nblk - 1) * ldd + 4 * (size_t)d_piece) * 4, w + kTallW);
+            const int b = 2 * c + lane / (TR / 4);
+            if (lane < TR / 2) dma_lane(dbytes + ((size_t)(b < nblk ? b : nblk - 1) * ldd + 4 * (size_t)d_piece) * 4, w + WBYTES);
         }
     };
-    const int per = wave < 2 ? 5 : 4;  // loads of a chunk, this wave
+    constexpr int PER = AU + JB;  // loads of a chunk, one wave; the first two have one more
 
-    f32x4 acc[4][2];
+    f32x4 acc[RB][JB];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < RB; ++r)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < JB; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    for (int c = 0; c < kTallSlots - 1 && c < nchunks; ++c) issue(c);
+    const int per = wave < 2 ? PER + 1 : PER;
+    for (int c = 0; c < NS - 1 && c < nchunks; ++c) issue(c);
     const int zr = (lr >> 1) & 7;
-    for (int c = 0; c < nchunks; ++c) {
+    auto open = [&](int c) __attribute__((always_inline)) {
         // chunk c has landed (here, then everywhere) and everyone is done with chunk c-1
-        if (c + 1 < nchunks) {
-            if (per == 5)
-                q_wait_then_barrier<5>();
+        if (c + NS - 2 < nchunks) {
+            if (wave < 2)
+                q_wait_then_barrier<(NS - 2) * (PER + 1)>();
             else
-                q_wait_then_barrier<4>();
+                q_wait_then_barrier<(NS - 2) * PER>();
         } else {
-            q_wait_then_barrier<0>();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            wait_loads_then_barrier((nchunks - 1 - c) * per);
         }
-        if (c + kTallSlots - 1 < nchunks) issue(c + kTallSlots - 1);
-        const char* slot = reinterpret_cast<const char*>(ring) + (c % kTallSlots) * kTallSlot;
-        const char* wslot = slot + kTallA;
-        const char* dslot = wslot + kTallW;
-        auto block = [&](int s) {
-            v4i xa[4];
-            float dv[4];
-            uint2 codes[2], sraw[2];
+        if (c + NS - 1 < nchunks) issue(c + NS - 1);
+        return reinterpret_cast<const char*>(ring) + (c % NS) * SLOT;
+    };
+    auto block = [&](const char* slot, int s) __attribute__((always_inline)) {
+            const char* wslot = slot + ABYTES;
+            const char* dslot = wslot + WBYTES;
+            v4i xa[RB];
+            float dv[RB];
+            uint2 codes[JB], sraw[JB];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int cbk = 2 * wave + j;  // column block of the tile
+            for (int j = 0; j < JB; ++j) {
+                const int cbk = JB * wave + j;  // column block of the tile
                 const char* wst = wslot + (cbk / CB) * (2 * WST) + s * WST;
                 codes[j] = *reinterpret_cast<const uint2*>(wst + (cbk % CB) * 512 + lane * 8);
                 sraw[j] = *reinterpret_cast<const uint2*>(wst + 512 * CB + (cbk % CB) * 32 + g * 8);
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < RB; ++r) {
                 xa[r] = *reinterpret_cast<const v4i*>(slot + (16 * r + lr) * 128 + (((4 * s + g) ^ zr) << 4));
-                dv[r] = *reinterpret_cast<const float*>(dslot + s * (kTallRows * 4) + (16 * r + lr) * 4);
+                dv[r] = *reinterpret_cast<const float*>(dslot + s * (TR * 4) + (16 * r + lr) * 4);
             }
-            v4i wu[2];
-            float sc[2][4];
+            v4i wu[JB];
+            float sc[JB][4];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < JB; ++j) {
                 wu[j] = code_bytes(codes[j]);
                 sc[j][0] = bf16lo_to_f32(sraw[j].x);
                 sc[j][1] = bf16hi_to_f32(sraw[j].x);
                 sc[j][2] = bf16lo_to_f32(sraw[j].y);
                 sc[j][3] = bf16hi_to_f32(sraw[j].y);
             }
-            v4i pr[4][2];
+            v4i pr[RB][JB];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < RB; ++r) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j) pr[r][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[j], xa[r], kProductStart, 0, 0, 0);
+                for (int j = 0; j < JB; ++j) pr[r][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[j], xa[r], kProductStart, 0, 0, 0);
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int r = 0; r < RB; ++r)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < JB; ++j)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         acc[r][j][v] = __builtin_fmaf(dv[r] * sc[j][v], product(pr[r][j][v]), acc[r][j][v]);
         };
-        block(0);
-        if (2 * c + 1 < nblk) block(1);
+    for (int c = 0; c < (nblk >> 1); ++c) {
+        const char* slot = open(c);
+        block(slot, 0);
+        block(slot, 1);
     }
+    if (nblk & 1) block(open(nchunks - 1), 0);
 
-    // Lane holds C[row = m0 + 16r + lr][n0 + 32*wave + 16j + 4g + v].
-    const int n = n0 + 32 * wave + 4 * g;
+    // Lane holds C[row = m0 + 16r + lr][n0 + 16*JB*wave + 16j + 4g + v].
+    const int n = n0 + 16 * JB * wave + 4 * g;
     if constexpr (EPI == kEpiSwigluQuant) {
         // Columns are gate/up pairs: the tile row's 64 outputs are one quantization block; the lane holds four of
         // row lr of each row block.  Its maximum: the lane's, the four lanes of a row (g), the four waves (LDS).
-        float y[4][4];
+        float y[RB][4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < RB; ++r) {
             float mx = 0.0f;
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < JB; ++j)
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     const float gt = bf16_to_f32(f32_to_bf16_rne(acc[r][j][2 * e])), u = bf16_to_f32(f32_to_bf16_rne(acc[r][j][2 * e + 1]));
@@ -805,20 +824,20 @@ __global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
                 }
             mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            if (g == 0) rowmax[wave * kTallRows + 16 * r + lr] = mx;
+            if (g == 0) rowmax[wave * TR + 16 * r + lr] = mx;
         }
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < RB; ++r) {
             const int rowl = 16 * r + lr;
             float amax = rowmax[rowl];
 #pragma unroll
-            for (int w = 1; w < kTallWaves; ++w) amax = fmaxf(amax, rowmax[w * kTallRows + rowl]);
+            for (int w = 1; w < kTileWaves; ++w) amax = fmaxf(amax, rowmax[w * TR + rowl]);
             const float df = amax / 127.0f;
             if (m0 + rowl >= M) continue;
             const size_t row = (size_t)(m0 + rowl);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < JB; ++j) {
                 uint32_t c2 = 0;
                 if (df != 0.0f) {
 #pragma unroll
@@ -834,7 +853,7 @@ __global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < RB; ++r) {
             if (m0 + 16 * r + lr >= M) continue;
             const size_t row = (size_t)(m0 + 16 * r + lr);
             int p = 0, slot = 0;
@@ -844,7 +863,7 @@ __global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
                 slot = ra.slots ? ra.slots[row] : (int)row;
             }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < JB; ++j) {
                 const float v[4] = {acc[r][j][0], acc[r][j][1], acc[r][j][2], acc[r][j][3]};
                 if constexpr (EPI == kEpiRopeAppend)
                     gemm_epilogue_rope_append(v, ra, row, p, slot, n + 16 * j);
@@ -855,24 +874,43 @@ __global__ __launch_bounds__(64 * kTallWaves, 3) void qgemm_tall_kernel(
     }
 }
 
-// Where the tall tiles are faster than 256-row tiles of the packing's width.  With fewer than a workgroup for every
-// compute unit they take the time of one walk over K (4096: 33 us, 14336: 106 us) however few they are, and at 128 rows
-// the other kernel's is shorter (25 and 76 us at N = 4096); it meets theirs at about 224 rows and 112 workgroups
-// (N = 4096: 38 against 33 us; 2048 x 2048: 64 workgroups 16 against 19, 128 workgroups 26 against 19), from 129
-// rows where there are 256 of them (N = 28672, 160 rows: 87 against 75).
+// The kernel and tile of a launch, a function of M, N and the packing (which is one of N).
+//   * `rows`, the height of the tiles the kernel above would cut the launch into (launch_qgemm), decides whether it does: a stage
+//     of it takes about 0.0025 us a row from 64 rows on, and a chain of 32 x 64 tiles 0.2 us a block, less against wider
+//     packings.  They meet at about 90, 80 and 60 rows (us there and here: N = 4096, K = 4096 80 rows 15.7 and 17.0, 96 rows
+//     18.5 and 17.1; N = 6144 64 rows 15.6 and 18.4, 80 rows 18.9 and 18.6; 2048 x 11264 48 rows 10.4 and 10.8, 64 rows 11.9 and 11.0).
+//     128-column packings have no tile of 64 columns; they meet 64 x 128 tiles between 64 and 96 rows (28672: 31.6 and
+//     35.6, 44.8 and 38.5).
+//   * The smallest tile of which the chip holds all (768): 2048 x 11264 128 rows, 704 of 32 x 64: 13.2 us against 14.7 in 64 x 64 and
+//     18.1 in 64 x 128; 256 rows, 704 of 64 x 64: 19.1 against 24.2 and 22.3; 4096 x 4096 768 rows, 768 of 64 x 64: 34.4 against 43.8
+//     and 38.3; 300 rows of 2048 x 11264, 880 of 64 x 64: 26.9 against 23.0 in 64 x 128, which is taken.
+enum qgemm_form { kQBase, kQ32x64, kQ64x64, kQ64x128 };
+static long long qtiles(int M, int N, int rows, int cols) { return (long long)((M + rows - 1) / rows) * (N / cols); }
+static qgemm_form qgemm_pick(int M, int N, int cb, int rows)
+{
+    constexpr int kHeld = 768;
+    if (M > 65535 * 64 || N % 64 != 0) return kQBase;
+    if (cb == 8) return rows > 80 && qtiles(M, N, 64, 128) >= 256 ? kQ64x128 : kQBase;
+    if (rows + 10 * cb < 100) return kQBase;
+    if (qtiles(M, N, 32, 64) <= kHeld) return kQ32x64;
+    return qtiles(M, N, 64, 64) <= kHeld || N % 128 != 0 ? kQ64x64 : kQ64x128;
+}
+
+// Where the SwiGLU output is quantized by 64 x 128 tiles rather than in a step of its own behind a product in the form
+// above: there are enough of them, and enough rows, that the step (4 to 5 us) costs more than the larger tile.
 static bool qgemm_tall_pays(int M, int N)
 {
-    if (N % kTallCols != 0 || M > 65535 * kTallRows) return false;
-    const long long wgs = (long long)((M + kTallRows - 1) / kTallRows) * (N / kTallCols);
+    if (N % 128 != 0 || M > 65535 * 64) return false;
+    const long long wgs = qtiles(M, N, 64, 128);
     return (M >= 224 && wgs >= 112) || (M > 128 && wgs >= 256);
 }
 
-template <int CB, int EPI>
-static void launch_qgemm_tall(const void* qa, const void* da, int ldd, const void* wp, void* C, int ldc, const void* R, int ldr,
+template <int CB, int EPI, int RB, int JB>
+static void launch_qgemm_tile(const void* qa, const void* da, int ldd, const void* wp, void* C, int ldc, const void* R, int ldr,
                               int M, int N, int K, int out_f32, hipStream_t s, float* qscales_out, const gemm_rope_args& ra)
 {
-    hipLaunchKernelGGL((qgemm_tall_kernel<CB, EPI>), dim3(N / kTallCols, (M + kTallRows - 1) / kTallRows),
-                       dim3(64 * kTallWaves), 0, s, static_cast<const int8_t*>(qa), K, static_cast<const float*>(da), ldd,
+    hipLaunchKernelGGL((qgemm_tile_kernel<CB, EPI, RB, JB>), dim3(N / (64 * JB), (M + 16 * RB - 1) / (16 * RB)),
+                       dim3(64 * kTileWaves), 0, s, static_cast<const int8_t*>(qa), K, static_cast<const float*>(da), ldd,
                        static_cast<const uint8_t*>(wp), C, ldc, static_cast<const uint16_t*>(R), ldr, out_f32, M, qscales_out,
                        ra);
 }
@@ -884,10 +922,6 @@ static void launch_qgemm(const void* qa, const void* da, int ldd, const void* wp
                          int M, int N, int K, int out_f32, hipStream_t s, float* qscales_out = nullptr,
                          const gemm_rope_args& ra = gemm_rope_args{})
 {
-    if (qgemm_tall_pays(M, N)) {
-        launch_qgemm_tall<CB, EPI>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
-        return;
-    }
     // Matrices too narrow to give every compute unit a column tile: the rows are cut into as many tiles as
     // fill the chip (a tile's rows are whole 16-row blocks; which tile a row falls in does not touch its
     // arithmetic).
@@ -897,6 +931,18 @@ static void launch_qgemm(const void* qa, const void* da, int ldd, const void* wp
         const int row_tiles = row_blocks < fit ? row_blocks : fit;
         const int rows = 16 * ((row_blocks + row_tiles - 1) / row_tiles);
         tile_rows = rows < 256 ? rows : 256;
+    }
+    switch (qgemm_pick(M, N, CB, tile_rows < M ? tile_rows : M)) {
+        case kQ64x128:
+            launch_qgemm_tile<CB, EPI, 4, 2>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
+            return;
+        case kQ64x64:
+            if constexpr (CB <= 4) launch_qgemm_tile<CB, EPI, 4, 1>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
+            return;
+        case kQ32x64:
+            if constexpr (CB <= 4) launch_qgemm_tile<CB, EPI, 2, 1>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
+            return;
+        default: break;
     }
     dim3 grid(N / (16 * CB), (M + tile_rows - 1) / tile_rows);
     const qgemm_plan full = make_qgemm_plan(tile_rows, CB, K);
@@ -1072,9 +1118,9 @@ int det::qgemm_swiglu_quant(const void* codes, const void* scales, const void* p
     float* d = static_cast<float*>(scales_out);
     const gemm_rope_args ra{};
     switch (qgemm_cols_per_block(2 * F)) {
-        case 1: launch_qgemm_tall<1, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
-        case 2: launch_qgemm_tall<2, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
-        default: launch_qgemm_tall<4, kEpiSwigluQuant>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
+        case 1: launch_qgemm_tile<1, kEpiSwigluQuant, 4, 2>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
+        case 2: launch_qgemm_tile<2, kEpiSwigluQuant, 4, 2>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
+        default: launch_qgemm_tile<4, kEpiSwigluQuant, 4, 2>(codes, scales, ld, packed_gate_up, codes_out, F, nullptr, ld, M, 2 * F, K, 0, s, d, ra); break;
     }
     return check_launch();
 }

@@ -1,5 +1,5 @@
-"""The quantized GEMM's tiles of 64 x 128 for launches of many rows: every row must have the bytes it has in a call of at
-most 100 rows, which takes the kernel that test_gpu_qgemm.py holds to the bit-exact oracle."""
+"""The quantized GEMM's tiles of 32 or 64 rows for launches of many rows: every row must have the bytes it has in calls of
+fewer rows, down to the 48 that take the kernel test_gpu_qgemm.py holds to the bit-exact oracle."""
 import pytest
 import torch
 
@@ -23,6 +23,18 @@ def parts(M, n=100):
 @pytest.mark.parametrize("M,K,N", [(385, 64, 2048), (450, 192, 2048), (449, 1088, 3072), (225, 64, 5120), (257, 320, 5248),
                                    (129, 192, 11008), (256, 128, 11264), (129, 64, 20480), (200, 704, 28672)])
 def test_rows_equal_small_calls(d, M, K, N):
+    rows_equal_small_calls(d, M, K, N, 100)
+
+
+# 32 x 64 tiles of packings of 16, 32 and 64 columns, the last row in a tile of its own, at its end and before it; 64 x 64 tiles, also of
+# a width that is no multiple of 128; 64 x 128 of the first row count that takes them with 128-column packings
+@pytest.mark.parametrize("M,K,N", [(97, 64, 4096), (96, 192, 3072), (161, 320, 2048), (129, 128, 6144), (65, 64, 11264),
+                                   (257, 192, 8192), (700, 64, 3072), (1000, 64, 4160), (96, 192, 20480)])
+def test_rows_of_small_tiles_equal_small_calls(d, M, K, N):
+    rows_equal_small_calls(d, M, K, N, 48)
+
+
+def rows_equal_small_calls(d, M, K, N, few):
     w = up_bf16(ds.normal_bf16(7000 + N, (K, N), 0.02))
     a = up_bf16(ds.normal_bf16(7100 + M, (M, K)))
     r = up_bf16(ds.normal_bf16(7200 + M, (M, N)))
@@ -36,7 +48,7 @@ def test_rows_equal_small_calls(d, M, K, N):
     d.det_qgemm_w4a8_residual(codes, scales, wp, r, res, N)
     d.det_qgemm_w4a8_swiglu(codes, scales, gu, swi, N // 2)
     torch.cuda.synchronize()
-    for p in parts(M):
+    for p in parts(M, few):
         c, s = d.quant_activations(a[p].contiguous())
         n = p.stop - p.start
         o1 = torch.empty((n, N), device=DEV)
@@ -52,7 +64,7 @@ def test_rows_equal_small_calls(d, M, K, N):
 
 # a fused SwiGLU quantizer where the packing has 64 columns (no other kernel's tile holds a block there) and where it has 128, and a
 # launch too small for it, which takes the two steps
-@pytest.mark.parametrize("R,H,Hq,Hkv,F", [(390, 256, 2, 1, 5632), (241, 128, 2, 2, 10240), (420, 128, 4, 2, 64)])
+@pytest.mark.parametrize("R,H,Hq,Hkv,F", [(390, 256, 2, 1, 5632), (241, 128, 2, 2, 10240), (420, 128, 4, 2, 64), (131, 2048, 16, 4, 512)])
 def test_quantized_layer_rows_equal_small_calls(d, R, H, Hq, Hkv, F):
     D, Lmax = 128, 420
     g = lambda s, shape, std=0.05, mean=0.0: up_bf16(ds.normal_bf16(s, shape, std, mean))
@@ -79,7 +91,7 @@ def test_quantized_layer_rows_equal_small_calls(d, R, H, Hq, Hkv, F):
         return x.view(torch.int16), k.view(torch.int16), v.view(torch.int16)
 
     step(f"quantized layer R={R} H={H} heads {Hq}/{Hkv} F={F}")
-    for got, want in zip(run([slice(0, R)]), run(parts(R))):
+    for got, want in zip(run([slice(0, R)]), run(parts(R, 48))):
         assert torch.equal(got, want)
 
 
