@@ -55,3 +55,28 @@ def test_small_launch_equals_large_launch(d, Hq, Hkv, quant):
         p = slice(i, min(i + 5, len(LENS)))
         assert 3 * Hkv * (p.stop - p.start) <= 512 < 3 * Hkv * B
         assert torch.equal(run(p), want[p]), LENS[p]
+
+
+# KV heads that do and do not spread over eight XCDs by themselves, caches of odd and even numbers of chunks on both sides of the
+# largest whose heads come first in the grid
+@pytest.mark.parametrize("Hq,Hkv,Lmax,B", [(8, 1, 2100, 60), (4, 2, 1300, 45), (3, 3, 2048, 70), (8, 4, 1025, 30), (16, 16, 600, 12),
+                                           (4, 2, 8192, 9), (4, 2, 8200, 9)])
+def test_every_chunk_is_computed_whatever_the_order_of_the_grid(d, Hq, Hkv, Lmax, B):
+    lens = [Lmax, 1, Lmax - 255, 256, 257, 0] + [(37 * i * i) % Lmax + 1 for i in range(B - 6)]
+    q = up_bf16(ds.normal_bf16(9600 + Hq, (B, Hq, 128)))
+    k = up_bf16(ds.normal_bf16(9601 + Hq, (B, Hkv, Lmax, 128)))
+    v = up_bf16(ds.normal_bf16(9602 + Hq, (B, Hkv, Lmax, 128)))
+    lens_t = up(np.asarray(lens, dtype=np.int32))
+
+    def run(p):
+        n = p.stop - p.start
+        ws = torch.full((d.det_attn_decode_workspace_bytes(n, Hq, 128, Lmax),), 0xFF, dtype=torch.uint8, device=DEV)
+        out = torch.full((n, Hq, 128), 7.0, dtype=torch.bfloat16, device=DEV)
+        d.det_attn_decode(q[p], k[p], v[p], lens_t[p], out, ws, SCALE)
+        return out.view(torch.int16)
+
+    step(f"attention of {B} rows, heads {Hq}/{Hkv}, cache of {Lmax}")
+    want = run(slice(0, B))
+    for b in range(B):
+        assert torch.equal(run(slice(b, b + 1)), want[b:b + 1]), lens[b]
+    torch.cuda.synchronize()
