@@ -25,15 +25,21 @@ __device__ __forceinline__ void wait_loads()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Where the four 16-byte pieces of a row lie in its 64 bytes of LDS: piece p of row i at p ^ wide_swizzle(i / 4 % 4).
+__device__ __forceinline__ int wide_swizzle(int q) { return (0x78 >> (2 * q)) & 3; }
+
 }  // namespace
 
 // A workgroup's 512 threads stream K in steps of 32 through a ring of LDS slots: 2*RBW KB of activations (16 rows x 64 bytes
 // a load) and 16 KB of weights (blocks in operand order) a step, each wave loading its share.  What bounds the
 // 256 x 128 tile of gemm.hip is the fill of LDS, 48 KB for 64 * 256 * 128 products; 256 x 256 is 64 KB for twice the work.
-// The operands of step t+1 are read from LDS into registers while step t is in the matrix cores, so a step needs one
-// barrier and no wait for its own reads, and its slot is free as soon as it starts.  A 256-row tile then takes 12.2 ns a
-// matrix instruction (8 ns with operands that never change and nothing else in the loop; before the reads were dealt out
-// among the products 13, then 11 with the loads taken out, 11.6 with the reads taken out, 7.5 for the loads alone).
+// The operands of step t+1 are read from LDS into registers while step t is in the matrix cores, so a step needs no wait for
+// its own reads, and its slot is free as soon as it starts; every second step has a barrier, whose turn it is for the loads of
+// the two steps behind it.  Reads and loads are dealt out among the products: issued in a row behind the barrier they left the
+// matrix cores idle, and a barrier a step cost 1 to 4 % (K x N 4096 x 6144, 3302 rows 171 us with both, 158 dealt out, 156 with
+// half the barriers; 14336 x 4096, 1500 rows 206, 206, 198).  Of 160-row tiles' 158 us the products alone take 115, and 133 with no
+// loads, 148 with no reads, 151 with no barriers, 155 with no wait for the loads: what is left is the fill, 26 KB a step at 43
+// bytes a ns, near what a compute unit gets of data that does not hit in L2 (50 to 55).
 template <int RBW, int EPI>
 __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uint16_t* __restrict__ A, int lda,
                                                                      const uint4* __restrict__ Bp, int cb, void* C, int ldc,
@@ -45,7 +51,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uin
     constexpr int NS = kWideLds / SLOT < 6 ? kWideLds / SLOT : 6;
     static_assert(NS >= 4, "ring");
     constexpr int LMAX = (UNITS + kWideWaves - 1) / kWideWaves, LMIN = UNITS / kWideWaves;  // loads of a step, one wave
-    static_assert((NS - 2) * LMAX <= 60, "load counter");
+    static_assert(NS * LMAX <= 60, "load counter");
     __shared__ uint4 ring[NS * SLOT / 16];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -69,106 +75,112 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uin
     const int nst = K >> 5;  // steps, even
     const uint32_t ring_addr = (uint32_t)(uintptr_t)(lds_char_t*)ring;
 
-    // This wave's loads of a step: units wave, wave + 8, ..; below AU activations, above weights.
-    const char* abase = reinterpret_cast<const char*>(A + (size_t)m0 * lda);
-    const char* wbase = reinterpret_cast<const char*>(Bp) + (size_t)(n0 / 16) * (K >> 6) * 2048;
+    // This wave's loads of a step: units wave, wave + 8, ..; below AU activations, above weights (block j = unit - AU of the
+    // tile's sixteen).  A load's source is src[i] plus a lane's off[i]; src[i] moves on by inc[i][t & 1] behind step t.
+    const char* src[LMAX];
+    uint32_t off[LMAX], inc[LMAX][2];
     const int mrem = M - m0;
-    uint32_t a_off[LMAX];
 #pragma unroll
     for (int i = 0; i < LMAX; ++i) {
         const int u = wave + 8 * i;
-        int row = 16 * u + (lane >> 2);
-        row = row < mrem ? row : mrem - 1;  // rows past M repeat the last: their outputs are never stored
-        a_off[i] = (uint32_t)row * (uint32_t)lda * 2u + 16u * (uint32_t)((lane & 3) ^ ((lane >> 4) & 3));
-    }
-    auto issue = [&](int t, int slot) __attribute__((always_inline)) {
-        const uint32_t dst = ring_addr + (uint32_t)slot * (uint32_t)SLOT;
-        const char* asrc = abase + (size_t)t * 64;
-#pragma unroll
-        for (int i = 0; i < LMAX; ++i) {
-            const int u = wave + 8 * i;
-            if (i >= LMIN && u >= UNITS) break;
-            if (u < AU) {
-                dma_block(asrc, a_off[i], dst + (uint32_t)u * 1024u);
-            } else {
-                const int j = u - AU, slab = j / cb, jj = j - slab * cb;  // column block j of the tile
-                const char* src = wbase + ((size_t)slab * (K >> 6) + (size_t)(t >> 1)) * (size_t)(cb * 2048) +
-                                  (size_t)(2 * jj + (t & 1)) * 1024;
-                dma_block(src, (uint32_t)lane * 16u, dst + (uint32_t)u * 1024u);
-            }
+        if (u < AU) {
+            int row = 16 * u + (lane >> 2);
+            row = row < mrem ? row : mrem - 1;  // rows past M repeat the last: their outputs are never stored
+            src[i] = reinterpret_cast<const char*>(A + (size_t)m0 * lda);
+            off[i] = (uint32_t)row * (uint32_t)lda * 2u + 16u * (uint32_t)((lane & 3) ^ wide_swizzle((lane >> 4) & 3));
+            inc[i][0] = inc[i][1] = 64;
+        } else {
+            const int j = u - AU < 16 ? u - AU : 15, slab = j / cb, jj = j - slab * cb;
+            src[i] = reinterpret_cast<const char*>(Bp) + ((size_t)(n0 / 16) + (size_t)slab * cb) * (K >> 6) * 2048 + jj * 2048;
+            off[i] = (uint32_t)lane * 16u;
+            inc[i][0] = 1024, inc[i][1] = (uint32_t)cb * 2048u - 1024u;
         }
+    }
+    auto issue = [&](int odd, int slot, int i) __attribute__((always_inline)) {
+        const int u = wave + 8 * i;
+        if (i >= LMIN && u >= UNITS) return;
+        dma_block(src[i], off[i], ring_addr + (uint32_t)(slot * SLOT + u * 1024));
+        src[i] += inc[i][odd];
     };
 
     struct Frags {
         bf16x8 w[4], x[RBW];
     };
-    const int x_off = (wr * RBW) * 1024 + lr * 64 + ((g ^ (lr >> 2)) << 4);
+    const int x_off = (wr * RBW) * 1024 + lr * 64 + ((g ^ wide_swizzle(lr >> 2)) << 4);
     const int w_off = (AU + 4 * wc) * 1024 + lane * 16;
-    auto read = [&](Frags& f, int slot) __attribute__((always_inline)) {
-        const char* base = reinterpret_cast<const char*>(ring) + slot * SLOT;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) f.w[j] = *reinterpret_cast<const bf16x8*>(base + w_off + j * 1024);
-#pragma unroll
-        for (int r = 0; r < RBW; ++r) f.x[r] = *reinterpret_cast<const bf16x8*>(base + x_off + r * 1024);
-    };
     f32x4 acc[RBW][4];
 #pragma unroll
     for (int r = 0; r < RBW; ++r)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto products = [&](const Frags& f) __attribute__((always_inline)) {
+    const bool more = wave < UNITS % kWideWaves;  // this wave has LMAX loads a step, not LMIN
+    // Passing this in front of step t (even): steps t+1 and t+2 have landed for everyone, and everyone has the operands of step t
+    // in registers, so its slot and the one before it take the steps t+NS and t+NS-1.
+    int slot_r = 1, slot_w = NS - 1;  // slot of the step read next, and of the step issued next
+    auto open = [&](bool steady) __attribute__((always_inline)) {
+        wait_reads();
+        if (!steady)
+            wait_loads<0>();
+        else if (LMAX != LMIN && more)  // steps t+3 .. t+NS-2 are behind step t+2
+            wait_loads<(NS - 4) * LMAX>();
+        else
+            wait_loads<(NS - 4) * LMIN>();
+        asm volatile("s_barrier" ::: "memory");
+    };
+    // The products of a step (operands f), with the reads of the next step's operands (into nf) and, if `load`, the loads of the
+    // step whose slot is free (its parity is that of odd + NS) dealt out among them: after every row block a share.
+    auto step = [&](bool load, int odd, const Frags& f, Frags& nf) __attribute__((always_inline)) {
+        const char* base = reinterpret_cast<const char*>(ring) + slot_r * SLOT;
 #pragma unroll
-        for (int r = 0; r < RBW; ++r)
+        for (int r = 0; r < RBW; ++r) {
+            constexpr int NR = 4 + RBW;
+            const int i0 = NR * r / RBW, i1 = NR * (r + 1) / RBW;
+#pragma unroll
+            for (int i = i0; i < i1; ++i) {
+                if (i < 4)
+                    nf.w[i] = *reinterpret_cast<const bf16x8*>(base + w_off + i * 1024);
+                else
+                    nf.x[i - 4] = *reinterpret_cast<const bf16x8*>(base + x_off + (i - 4) * 1024);
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[j], f.x[r], acc[r][j], 0, 0, 0);
-    };
-    const bool more = wave < UNITS % kWideWaves;  // this wave has LMAX loads a step, not LMIN
-    // Passing this: step t+1 has landed for everyone, and everyone has the operands of step t in registers, so its slot
-    // takes step t+NS.
-    int slot_r = 0, slot_w = NS - 1;  // slot of the step read next, and of the step issued next
-    auto open = [&](int t) __attribute__((always_inline)) {
-        wait_reads();
-        if (t + NS - 1 < nst) {  // steps t+2 .. t+NS-1 are behind step t+1
-            if (LMAX != LMIN && more)
-                wait_loads<(NS - 2) * LMAX>();
-            else
-                wait_loads<(NS - 2) * LMIN>();
-        } else {
-            wait_loads<0>();
-        }
-        asm volatile("s_barrier" ::: "memory");
-        if (t + NS < nst) issue(t + NS, slot_w);
-        slot_w = slot_w + 1 == NS ? 0 : slot_w + 1;
-    };
-    auto next = [&](Frags& f) __attribute__((always_inline)) {
-        read(f, slot_r);
-        slot_r = slot_r + 1 == NS ? 0 : slot_r + 1;
-    };
-    // Deals a step's operand reads out among its products, one after each: read in a row, they leave the matrix cores idle
-    // behind the barrier (4096 x 6144, 700 rows 68.6 -> 63.8 us, 3302 rows 175 -> 165).
-    auto alternate = []() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 4 + RBW; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a matrix-core instruction
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // an LDS read
+            for (int i = 0; i < i1 - i0; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a matrix-core instruction
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // an LDS read
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < LMAX; ++i)
+                if (i * RBW / LMAX == r) {
+                    if (load) issue((odd + NS) & 1, slot_w, i);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
         }
+        slot_r = slot_r + 1 == NS ? 0 : slot_r + 1;
+        slot_w = slot_w + 1 == NS ? 0 : slot_w + 1;
     };
 
 #pragma unroll
     for (int t = 0; t < NS - 1; ++t)
-        if (t < nst) issue(t, t);
+        if (t < nst) {
+#pragma unroll
+            for (int i = 0; i < LMAX; ++i) issue(t & 1, t, i);
+        }
     Frags f0, f1;
-    open(-1);
-    next(f0);
+    open(true);
+    {
+        const char* base = reinterpret_cast<const char*>(ring);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f0.w[j] = *reinterpret_cast<const bf16x8*>(base + w_off + j * 1024);
+#pragma unroll
+        for (int r = 0; r < RBW; ++r) f0.x[r] = *reinterpret_cast<const bf16x8*>(base + x_off + r * 1024);
+    }
+    open(true);
     for (int t = 0; t < nst; t += 2) {
-        open(t);
-        next(f1);
-        products(f0);
-        alternate();
-        if (t + 2 < nst) open(t + 1);
-        next(f0);  // (past the last step: whatever the slot holds, not used)
-        products(f1);
-        alternate();
+        step(t - 1 + NS < nst, 1, f0, f1);
+        step(t + NS < nst, 0, f1, f0);  // (past the last step: reads whatever the slot holds, not used)
+        if (t + 2 < nst) open(t + 2 + NS - 2 < nst);
     }
 
     // Lane holds C[row = m0 + 16*(wr*RBW + r) + lr][n0 + 64*wc + 16j + 4g + v].
@@ -216,19 +228,19 @@ static void launch_rows(int rbw, const gemm_wide_args& a, hipStream_t s)
 }
 
 // What a launch costs is the rounds of 256 workgroups it takes, times what one of its tiles takes for a step of 32 of K, which is
-// nearly the same over all shapes (measured over K = 1024 .. 14336, N = 1024 .. 28672, 256 to 5000 rows).  Here 0.49 / 0.61 /
-// 0.66 / 0.79 us for tiles of 128 / 160 / 192 / 256 rows.  In gemm.hip 0.53 us for a 256 x 128 tile (0.51 in launches of four
+// nearly the same over all shapes (measured over K = 1024 .. 14336, N = 1024 .. 28672, 256 to 5000 rows).  Here 0.45 / 0.54 /
+// 0.60 / 0.78 us for tiles of 128 / 160 / 192 / 256 rows, a little more for 160 rows of 128-column packings.  In gemm.hip 0.53 us for a 256 x 128 tile (0.51 in launches of four
 // rounds and more), and in its narrower tilings, which it takes where those do not fill the chip, 1.4 ns (16- and 32-column
 // packings) or 1.18 ns (64-column packings) for each row and column of a tile.  The last row of tiles there is as short as
 // its rows: 0.34 of a whole 256 x 128 tile's time and the rest by rows, and it fills the compute units that the last round of
 // whole tiles leaves idle.  (Counted as whole tiles, 258 rows of K = 4416, N = 11264 took this form in 62 us instead of 42, 519 rows
 // of 2048 x 6144 in 34 instead of 28.)  So the choice is the tile height whose tiles fit the rounds best: 3302 rows of N = 6144,
-// K = 4096 are 13 x 48 tiles there (three rounds, 214 us), 13 x 24 of 256 rows here (two, 205 us), 21 x 24 of 160 rows
-// (two, 159 us).  6 % must be won by this count, 21 % where a tile there is as wide as the
+// K = 4096 are 13 x 48 tiles there (three rounds, 208 us), 13 x 24 of 256 rows here (two, 207 us), 21 x 24 of 160 rows
+// (two, 156 us).  6 % must be won by this count, 21 % where a tile there is as wide as the
 // packing and the weights alone are much of the time.  Of 665 shapes that could take this form, half of them a few rows past
 // whole 256-row tiles, the choice is slower by more than 2 % in one (3 %); where it stays in gemm.hip this form would have taken up to
-// a quarter less time (476 rows of 14336 x 8192).  Others: K x N 4096 x 6144 700 rows 114 -> 61 us, 14336 x 4096 1500 rows
-// 373 -> 208, 4096 x 28672 4096 rows 919 -> 788 (1.22 PFLOP/s; torch's product of two 8192 x 8192 matrices reaches 1.19 on the
+// a quarter less time (476 rows of 14336 x 8192).  Others: K x N 4096 x 6144 700 rows 90 -> 60 us, 14336 x 4096 1500 rows
+// 302 -> 202, 4096 x 28672 4096 rows 919 -> 760 (1.27 PFLOP/s; torch's product of two 8192 x 8192 matrices reaches 1.19 on the
 // same card).
 namespace {
 
@@ -266,13 +278,13 @@ int gemm_wide_rows(int M, int N, int K, int cb)
         cost = span(M, N / 128, 256, [&](int x) { return (long long)t * (34 * 256 + 66 * x) / 25600; });
     }
     static const struct {
-        int rbw, cost;
-    } kTiles[4] = {{4, 4900}, {5, 6100}, {6, 6600}, {8, 7900}};
+        int rbw, cost, cost8;  // cost8: 128-column packings
+    } kTiles[4] = {{4, 4500, 4500}, {5, 5400, 6060}, {6, 6000, 6060}, {8, 7800, 7800}};
     int best = 0;
     long long best_cost = 100 * cost;
     for (const auto& t : kTiles) {
         const long long n = rounds((long long)((M + 32 * t.rbw - 1) / (32 * t.rbw)) * (N / kWideCols));
-        const long long c = n * t.cost * (cb < 8 ? 106 : 121);
+        const long long c = cb < 8 ? n * t.cost * 106 : n * t.cost8 * 121;
         if (c < best_cost) best = t.rbw, best_cost = c;
     }
     return best;
