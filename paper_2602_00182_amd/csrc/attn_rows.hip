@@ -52,9 +52,10 @@ __device__ __forceinline__ void wait_then_barrier()
 //
 // Two workgroups a compute unit (243 to 256 registers), so two waves a SIMD.  No unit bounds it alone: on the prompts of 2000 + 1402
 // + 1000 tokens below, vector instructions take 47 % of the cycles (about 30 a score, 16 of them exp, 6 the split), the matrix
-// cores 24 %, LDS 25 %, and scores, exponentials and weighted sums follow one another inside a wave.  Measured on one layer, against eight rows a workgroup with chunk
-// partials in memory and a second pass: prompts of 2000 + 1402 + 1000 tokens, 32/8 heads 1267 -> 244 us; one of 4000 tokens
-// 2240 -> 540 us; 24 of 16..512 tokens, 16/4 heads 195 -> 100 us.  Copies cut down from an earlier form that took 297 us on
+// cores 24 % (the two of them add up on a SIMD), LDS 25 % before the K rows' swizzle (10 % bank conflicts; 244 -> 237 us), and
+// scores, exponentials and weighted sums follow one another inside a wave.  Measured on one layer, against eight rows a workgroup with chunk
+// partials in memory and a second pass: prompts of 2000 + 1402 + 1000 tokens, 32/8 heads 1267 -> 237 us; one of 4000 tokens
+// 2240 -> 491 us; 24 of 16..512 tokens, 16/4 heads 195 -> 100 us.  Copies cut down from an earlier form that took 297 us on
 // prompts of 2000 + 1400 + 1000 tokens: 234 without the exponentials, 109 with the loads and barriers alone.
 //
 // The grid: `helpers` workgroups, then Hkv per tile, tiles from the last (longest prefixes first).  The (run of rows, KV
@@ -66,6 +67,11 @@ __device__ __forceinline__ void wait_then_barrier()
 // The form does not pay for 17 to 32 pairs (five to eight rows of four heads), which walk and are the slowest here: 497 rows,
 // eight a slot, 32/8 heads, 200 tokens 25 -> 37 us, 1000 108 -> 117, 2048 198 -> 243; 994 rows 46 -> 47, 214 -> 154.
 // Deep rows are not touched here.
+// Where the pieces of a K row lie (piece p at p ^ k_swizzle): row 4q + r of an operand block.  A read of sixteen bytes a lane is
+// served in quarters of lanes 0-3, 12-15 and, of the next sixteen, 4-11 (the other way round in the second), which ask for
+// pieces four apart: with the row's own number as the swizzle the two halves met in the same banks.
+__device__ __forceinline__ int k_swizzle(int q, int r) { return r | (((0x78 >> (2 * q)) & 3) << 2); }
+
 template <int G, bool QUANT>
 __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kcache,
                                                           const uint16_t* __restrict__ vcache,
@@ -94,7 +100,7 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
     // the operand reads (one piece of sixteen rows), for V so that the transposing reads (one 32-byte unit of
     // sixteen rows) spread over the banks.
     const int sp = lane & 15, rl = lane >> 4;
-    auto k_piece = [&](int b) { return sp ^ (rl | (((2 * wave + (b >> 1)) & 3) << 2)); };
+    auto k_piece = [&](int b) { return sp ^ k_swizzle((2 * wave + (b >> 1)) & 3, rl); };
     auto v_piece = [&](int b) { return (((sp >> 1) ^ (rl | (((b >> 1) & 1) << 2))) << 1) | (sp & 1); };
     // subtile `sub` of K or V (rows past maxlen repeat its last row: K rows there are masked, V rows cleared)
     auto stage = [&](const uint16_t* base, bool is_v, int sub, int maxlen, int slot) __attribute__((always_inline)) {
@@ -114,6 +120,7 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
     // The operand reads of a 32-token step go out together; its two chains advance in turn.
     auto products = [&](int slot, const uint4 (&qf)[4], f32x4 (&acc)[2][2]) __attribute__((always_inline)) {
         const char* base = ringc + slot * 16384 + (8 * (lr >> 2) + (lr & 3)) * 256;
+        const int kz = k_swizzle(lr >> 2, lr & 3);
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
             uint4 kf[2][4];
@@ -121,7 +128,7 @@ __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __res
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int b = 0; b < 2; ++b)
-                    kf[b][i] = *reinterpret_cast<const uint4*>(base + st * 8192 + b * 1024 + (((4 * g + i) ^ lr) << 4));
+                    kf[b][i] = *reinterpret_cast<const uint4*>(base + st * 8192 + b * 1024 + (((4 * g + i) ^ kz) << 4));
 #pragma unroll
             for (int b = 0; b < 2; ++b) acc[st][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
