@@ -460,8 +460,10 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
     // -------------------------------------------------------------------- computing wave
     // NRB (row blocks of the wave) is a compile-time constant inside so that the loop bodies have no
     // branches.
-    auto run = [&](auto nrb_tag) {
+    // DEEP: the two-deep pipeline also where a step has few matrix-core instructions.
+    auto run = [&](auto nrb_tag, auto deep_tag) {
         constexpr int NRB = decltype(nrb_tag)::value;
+        constexpr bool DEEP = CB * NRB >= 6 || decltype(deep_tag)::value;
         struct Frags {  // operands of one matrix-core step
             bf16x8 wf[CB];
             bf16x8 xf[NRB];
@@ -497,7 +499,7 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
         auto open_chunk = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
         if constexpr (NORM) normalize_rows();
 
-        if constexpr (CB * NRB >= 6) {
+        if constexpr (DEEP) {
             // One two-deep pipeline over the whole K range: the operands of a step are read while the step
             // before it is in the matrix core, also across a chunk boundary (a chunk is a single stage for the
             // tallest tiles), so that no LDS latency is exposed.  The barrier that opens chunk c+1 therefore
@@ -666,19 +668,25 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
             }
         }
     };
+    const std::false_type no{};
     if constexpr (NORM) {
-        run(std::integral_constant<int, 1>{});
+        run(std::integral_constant<int, 1>{}, no);
     } else if constexpr (NW == 8) {
-        if (nrb == 1)
-            run(std::integral_constant<int, 1>{});
+        // Tiles of several slabs and three or four row blocks: a chunk is three stages of 16 KB, and starting the reads anew behind
+        // every barrier costs more than a step's exposed latency (K x N 14336 x 4096 201 rows 64.1 -> 59.1 us, 4096 x 4096 19.9 ->
+        // 18.6; two row blocks, whose chunks are longer, 97 rows of 4096 x 4096 14.2 -> 15.1, eight 500 rows 26.2 -> 27.3).
+        if (PCB < CB && (RB == 3 || RB == 4))
+            run(std::integral_constant<int, 1>{}, std::integral_constant<bool, PCB < CB>{});
+        else if (nrb == 1)
+            run(std::integral_constant<int, 1>{}, no);
         else
-            run(std::integral_constant<int, 2>{});
+            run(std::integral_constant<int, 2>{}, no);
     } else {
         switch (nrb) {
-            case 1: run(std::integral_constant<int, 1>{}); break;
-            case 2: run(std::integral_constant<int, 2>{}); break;
-            case 3: run(std::integral_constant<int, 3>{}); break;
-            default: run(std::integral_constant<int, 4>{}); break;
+            case 1: run(std::integral_constant<int, 1>{}, no); break;
+            case 2: run(std::integral_constant<int, 2>{}, no); break;
+            case 3: run(std::integral_constant<int, 3>{}, no); break;
+            default: run(std::integral_constant<int, 4>{}, no); break;
         }
     }
 }
@@ -833,11 +841,18 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
         (long long)(base_live + 16 * cb) * rounds((long long)(N / (16 * cb)) * ((M + base_rows - 1) / base_rows));
     const bool sq_pays = 115 * sq_cost <= 100 * base_cost;
     if (!fixed_tile && !small && N % 64 == 0 && sq_pays && ((cb == 1 && M >= 96) || (cb == 2 && M >= 192))) {
+        // Up to 64 rows, and at 128, eight waves own a row block each (or the tile has fewer); at other heights four waves of up to four
+        // blocks, in one two-deep pipeline over K, and eight that load are faster: 14336 x 4096 400 rows (tiles of 112) 83.3 -> 76.5,
+        // 520 rows (144) 143 -> 118, 2048 x 3072 700 rows (144) 26.0 -> 23.0, 4096 x 4096 1000 rows (256) 46.6 -> 44.1; 500 rows
+        // (128) 26.2 -> 27.1, 4096 x 6144 256 rows (128) 27.3 -> 28.4.
         const int rows = sq_rows;
+        const bool four = rows > 64 && rows != 128;
         if (cb == 1)
-            ok = launch_gemm<4, kRingBig, EPI, 8, 4, 1>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, rows);
+            ok = four ? launch_gemm<4, kRingBig, EPI, 4, 8, 1>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, rows)
+                      : launch_gemm<4, kRingBig, EPI, 8, 4, 1>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, rows);
         else
-            ok = launch_gemm<4, kRingBig, EPI, 8, 4, 2>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, rows);
+            ok = four ? launch_gemm<4, kRingBig, EPI, 4, 8, 2>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, rows)
+                      : launch_gemm<4, kRingBig, EPI, 8, 4, 2>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, rows);
         return ok ? check_launch() : DET_ESHAPE;
     }
 #define DET_GEMM_CASE(CBV)                                                                                  \
