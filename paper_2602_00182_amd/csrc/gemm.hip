@@ -739,7 +739,7 @@ static bool launch_gemm(const void* A, int lda, const void* Bp, void* C, int ldc
                         const gemm_rope_args& ra, int M, int N, int K, int out_f32, hipStream_t s,
                         int tile_rows = 256, float eps = 0.0f)
 {
-    // tile_rows: a multiple of 16 in 16..256 (the kernel handles 1..16 row blocks of 16 rows)
+    // tile_rows: a multiple of 8 in 16..256 (the kernel handles 1..16 row blocks of 16 rows, the last one half full or less)
     dim3 grid(N / (16 * CB), (M + tile_rows - 1) / tile_rows);
     if (NORM && (M > kNormRows || grid.y != 1 || (K >> 6) + 4 * CB > RINGB)) return false;
     const gemm_tile_plan tail = make_tile_plan(M - tile_rows * ((M - 1) / tile_rows), CB, RINGB, NW, NL, K, NORM);
@@ -816,13 +816,19 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
     // (2) Matrices too narrow to give every compute unit a column tile (N / (16 cb) < 256): the rows are
     //     cut into as many tiles as fill the chip, which also shortens each workgroup's pass over A.
     const int row_blocks = (M + 15) / 16;
-    int base_rows = 256;
+    // Rows are dealt out over n tiles in half blocks of 8, what one load brings, and not in blocks of 16 (which stay where every
+    // block has a tile of its own: half of one costs the matrix core as much and doubles the weights' reads).  K x N 14336 x 4096
+    // 130 rows (tiles of 40, not 48) 55.7 -> 53.1 us, 201 rows (56, not 64) 59.3 -> 57.3, 400 rows (104, not 112) 85.0 -> 81.4;
+    // 4096 x 4096 390 rows 25.5 -> 24.9; level where the heights are the same or K is short.
+    auto even_rows = [&](int n) { return n >= row_blocks ? 16 : 8 * ((((M + 7) >> 3) + n - 1) / n); };
+    int base_rows = 256, base_height = 256;
     {
         const int fit = 256 / (N / (16 * cb));
         if (!fixed_tile && !small && fit >= 2 && row_blocks >= 2) {
             const int row_tiles = row_blocks < fit ? row_blocks : fit;
             const int rows = 16 * ((row_blocks + row_tiles - 1) / row_tiles);
             base_rows = rows < 256 ? rows : 256;
+            base_height = rows <= 256 ? even_rows(row_tiles) : 256;
         }
     }
     // (3) Tall launches of 16- or 32-column packings: a 256-row x 16-column tile (all of A for a sliver of
@@ -845,8 +851,9 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
         // blocks, in one two-deep pipeline over K, and eight that load are faster: 14336 x 4096 400 rows (tiles of 112) 83.3 -> 76.5,
         // 520 rows (144) 143 -> 118, 2048 x 3072 700 rows (144) 26.0 -> 23.0, 4096 x 4096 1000 rows (256) 46.6 -> 44.1; 500 rows
         // (128) 26.2 -> 27.1, 4096 x 6144 256 rows (128) 27.3 -> 28.4.
-        const int rows = sq_rows;
-        const bool four = rows > 64 && rows != 128;
+        const int rows = sq_even <= 256 ? even_rows(sq_row_tiles) : 256;
+        const int blocks = (rows + 15) / 16;
+        const bool four = blocks > 4 && blocks != 8;
         if (cb == 1)
             ok = four ? launch_gemm<4, kRingBig, EPI, 4, 8, 1>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, rows)
                       : launch_gemm<4, kRingBig, EPI, 8, 4, 1>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, rows);
@@ -863,7 +870,7 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
                 break;                                                                                      \
             }                                                                                               \
         }                                                                                                   \
-        ok = launch_gemm<CBV, kRingBig, EPI, gemm_waves(CBV), gemm_loader_waves(CBV, false)>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, base_rows);            \
+        ok = launch_gemm<CBV, kRingBig, EPI, gemm_waves(CBV), gemm_loader_waves(CBV, false)>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, base_height);          \
         break;
     switch (cb) {
         DET_GEMM_CASE(1)
@@ -874,7 +881,7 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
         DET_GEMM_CASE(6)
         DET_GEMM_CASE(7)
         default:
-            ok = launch_gemm<8, kRingBig, EPI, gemm_waves(8), gemm_loader_waves(8, false)>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, base_rows);
+            ok = launch_gemm<8, kRingBig, EPI, gemm_waves(8), gemm_loader_waves(8, false)>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, base_height);
             break;
     }
 #undef DET_GEMM_CASE
