@@ -322,7 +322,7 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
                 const float a = s4[0] + s4[2];
                 const float b = s4[1] + s4[3];
                 const float r = rms_scale(a + b, K, eps);
-                const int z = ((row >> 1) & 3) << 1;  // the swizzle of the activation tiles (see above)
+                const int z = ((row >> 1) & 3) << 1;  // the swizzle of the activation tiles (see below)
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const int v = vt + 256 * i;
@@ -341,8 +341,12 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
     // handles a quarter wave at a time, and sixteen lanes on sixteen different lines cost it nearly
     // twice the time).  The row sits at 128*(row%8) inside its half block with its eight 16-byte
     // pieces XOR-swizzled: piece p (k = 8p .. 8p+7 of the stage) lies at slot p ^ z(row),
-    // z(row) = 2*((row/2)%4) + row/8, which spreads the sixteen rows a quarter wave reads for one
-    // matrix-core step (same piece of rows 0..15) over all sixteen 16-byte bank groups.
+    // z(row) = 2*((row/2)%4).  A read of sixteen bytes a lane is served in quarters of lanes 0-3, 12-15 and, of the next sixteen,
+    // 4-11 (or the other way round), which ask for neighbouring pieces, an even and an odd one: rows of one parity take the
+    // even slots for the one and the odd slots for the other, and all sixteen 16-byte bank groups are busy.
+    // K x N 14336 x 4096 520 rows 119.0 -> 116.5 us, 4096 x 6144 161 rows 27.9 -> 27.0, 90 rows 18.5 -> 18.0 against a swizzle for
+    // sixteen rows of one piece (two-way conflicts, + row/8); row/2 is free of conflicts too and better at 520 rows (112) and
+    // 1000 (4096 x 4096 43.4 -> 42.5), but its loads swap neighbouring pieces: 230 rows of 4096 x 6144 25.6 -> 25.9.
 
     if (nrb == 0) {
         if constexpr (NORM) {
@@ -383,7 +387,7 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
         for (int i = 0; i < kMaxHalf; ++i) {
             const int hb = hb0 + i * nload;
             const int row = min(8 * hb + (lane >> 3), mrem - 1);
-            const uint32_t z = (uint32_t)(2 * ((lane >> 4) & 3) + (hb & 1));  // swizzle of row 8*hb + lane/8 (see above)
+            const uint32_t z = (uint32_t)(2 * ((lane >> 4) & 3));  // swizzle of row 8*hb + lane/8 (see above)
             a_off[i] = (uint32_t)row * (uint32_t)lda * 2u + 16u * ((uint32_t)(lane & 7) ^ z);
         }
         // With the weights in several slabs (PCB < CB) the split is by position inside a stage instead:
@@ -475,7 +479,7 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
             for (int j = 0; j < CB; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
         // this lane's two pieces (k group g of step 0 and of step 1) of row lr in the tile of row block `wave`
-        const int zr = (((lr >> 1) & 3) << 1) | (lr >> 3);
+        const int zr = ((lr >> 1) & 3) << 1;
         const int a_lane = 2 * wave * 64 + 64 * (lr >> 3) + 8 * (lr & 7);
         const int a0_off = a_lane + (g ^ zr), a1_off = a_lane + ((g ^ zr) ^ 4);
         auto mm = [&](const Frags& fr) {
