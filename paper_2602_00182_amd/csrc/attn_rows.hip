@@ -51,8 +51,8 @@ __device__ __forceinline__ void wait_then_barrier()
 // (16, 8, 2, 1) and registers (4); V^T operands are transposed by the LDS read itself.
 //
 // Two workgroups a compute unit (243 to 256 registers), so two waves a SIMD.  No unit bounds it alone: on the prompts of 2000 + 1402
-// + 1000 tokens below, vector instructions take 47 % of the cycles (about 30 a score, 16 of them exp, 6 the split), the matrix
-// cores 24 % (the two of them add up on a SIMD), LDS 25 % before the K rows' swizzle (10 % bank conflicts; 244 -> 237 us), and
+// + 1000 tokens below, vector instructions take 48 % of the cycles (about 30 a score, 16 of them exp, 6 the split), the matrix
+// cores 24 % (the two of them add up on a SIMD), LDS 15 % (25 with the bank conflicts that the K rows' swizzle took out; 244 -> 237 us), and
 // scores, exponentials and weighted sums follow one another inside a wave.  Measured on one layer, against eight rows a workgroup with chunk
 // partials in memory and a second pass: prompts of 2000 + 1402 + 1000 tokens, 32/8 heads 1267 -> 237 us; one of 4000 tokens
 // 2240 -> 491 us; 24 of 16..512 tokens, 16/4 heads 195 -> 100 us.  Copies cut down from an earlier form that took 297 us on
