@@ -836,7 +836,7 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
         }
     }
     // (3) Tall launches of 16- or 32-column packings: a 256-row x 16-column tile (all of A for a sliver of
-    //     the weights) is the wrong shape from about a hundred rows on; 64-column tiles of M/row_tiles rows
+    //     the weights) is the wrong shape from about seventy rows on; 64-column tiles of M/row_tiles rows
     //     move up to half as many bytes (measured: K = 14336, N = 4096 at M = 256 in 63 us instead of 112).
     //     Taken from the row counts where the measured times cross, and only where the 64-column tiles
     //     move clearly fewer bytes per compute unit than the tiles of (2).
@@ -850,7 +850,11 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
     const long long base_cost =
         (long long)(base_live + 16 * cb) * rounds((long long)(N / (16 * cb)) * ((M + base_rows - 1) / base_rows));
     const bool sq_pays = 115 * sq_cost <= 100 * base_cost;
-    if (!fixed_tile && !small && N % 64 == 0 && sq_pays && ((cb == 1 && M >= 96) || (cb == 2 && M >= 192))) {
+    // From 65 rows on at 16 columns: K x N 14336 x 4096 95 rows 61.9 -> 46.6 us, 4096 x 4096 15.5 -> 13.4, 2048 x 3072 65 rows 9.0 ->
+    // 8.1, level where the bytes keep the tiles of (2).  At 32 columns with tiles of at most 64 rows (4096 x 8192 128 rows 24.3 ->
+    // 21.8) or above 160 rows, where the 256-row tile's eleventh block costs a wave a third one (4096 x 6144 176 rows 27.1 -> 23.4,
+    // 4096 x 8192 30.7 -> 26.9; 144 and 160 rows of 6144 20.8 -> 23.1 and 21.8 -> 23.2).
+    if (!fixed_tile && !small && N % 64 == 0 && sq_pays && ((cb == 1 && M > 64) || (cb == 2 && M >= 64 && (sq_rows <= 64 || M > 160)))) {
         // Up to 64 rows, and at 128, eight waves own a row block each (or the tile has fewer); at other heights four waves of up to four
         // blocks, in one two-deep pipeline over K, and eight that load are faster: 14336 x 4096 400 rows (tiles of 112) 83.3 -> 76.5,
         // 520 rows (144) 143 -> 118, 2048 x 3072 700 rows (144) 26.0 -> 23.0, 4096 x 4096 1000 rows (256) 46.6 -> 44.1; 500 rows

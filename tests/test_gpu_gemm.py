@@ -77,7 +77,7 @@ def test_integer_matrices_are_exact(d, orc, M, N, K):
 
 
 @pytest.mark.parametrize("M,N", [(M, N) for N in (2048, 6224, 11264) for M in (7, 9, 23, 33, 35, 45, 57, 65, 95, 121, 129, 250, 256)] +
-                         [(M, 4096) for M in (97, 129, 131, 201, 300, 393, 420, 500, 601, 999)] + [(M, 6144) for M in (193, 290, 401)])
+                         [(M, 4096) for M in (66, 95, 97, 129, 131, 201, 300, 393, 420, 500, 601, 999)] + [(M, 6144) for M in (161, 193, 290, 401)] + [(M, 3072) for M in (65, 81)] + [(M, 8192) for M in (97, 128, 129, 163)])
 def test_ragged_rows_whatever_the_split_of_the_loads(d, orc, M, N):
     """Row counts around every split of a tile's half blocks over the loading waves, in the row-cut (N = 2048), two-workgroups-a-
     compute-unit (6224) and wide (11264) forms, and every pipeline of the 64-column tiles (4096 and 6144: tiles of 32 to 256
