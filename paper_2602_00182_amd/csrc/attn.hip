@@ -79,7 +79,7 @@ __device__ __forceinline__ float combine_max(const float* mc, int nc)
 // query heads that share the KV head ("pairs").  Decode launches of more than 512 workgroups (and all with G = 1) take it with
 // RT = 1 (every row has a cache slot of its own); the rows form with RT = 8 lets the rows of one prompt share each chunk of K
 // and V (causal prefill: row i of a prompt has length p + i), in calls too small for attn_rows.hip and for the rows it leaves.
-// Grid (chunk, head group, row tile) or, one row a workgroup, (head group, chunk, row), see attn_heads_first; 256 threads.
+// Grid (chunk, head group, row tile), one row a workgroup with the chunks permuted, see attn_chunk_of; 256 threads.
 //
 // The arithmetic of one (row, head, chunk) is the same whatever else sits in the workgroup:
 //   scores: wave w takes tokens 64w..64w+63 of the chunk as four 16-token blocks; the K rows are the row
@@ -391,14 +391,23 @@ __device__ __forceinline__ void attn_tile(const uint16_t* __restrict__ q, const 
     }
 }
 
-// Order of the grid of attn_tile_kernel with one row a workgroup.  Workgroups go round-robin over the eight XCDs; with the chunks in
-// front and a cache of 8, 16, .. chunks an XCD had the same chunk of every row, and the first chunks, which more rows reach,
-// always fell to the same XCDs (of a call of 48 rows of 200 to 4096 tokens the first got 1.37 times the mean, 2.3 times the
-// last's).  So the KV heads go first: 48 such rows, 32/8 heads 110 -> 88 us (the bytes at the rate of a copy 80), 32 of 1024 to 2048
-// tokens 45.9 -> 38.7, 33 of 100 to 2000, 16/16 heads 75 -> 54.  In caches of more than 32 chunks, which then are read in eight
-// places at a time, that gains 2 % or costs up to 5 (16 rows of 500 to 16000 tokens 116 -> 114, 8 of 1000 to 32768 128 -> 134); there
-// the chunks stay in front.
-__host__ __device__ __forceinline__ bool attn_heads_first(int ncmax) { return ncmax <= 32; }
+// The chunk of workgroup (x, stream) of attn_tile_kernel with one row a workgroup, a stream being one (row, KV head), counted in grid
+// order.  Workgroups go round-robin over the eight XCDs, and inside one over its compute units: where the number of chunks has
+// factors of two, chunk x of every stream would fall to the same places, and those that always get the first chunks, which more
+// rows reach, work while the others wait (16 chunks, 48 rows of 200 to 4096 tokens: the first XCD 1.37 times the mean).  So the
+// chunks of a group as long as that power of two change places from stream to stream, by the leading bits of the stream's
+// number times the golden ratio, whose values are even over any run of streams; a stream stays in eight-chunk order or nearly so.
+// us without, and with: 48 rows of 200 to 4096 tokens, 32/8 heads 110.8 -> 89.1 (the bytes at the rate of a copy 80), of 100 to 2000,
+// 16/16 heads 103 -> 84.5, 32 rows of 1001, 32/8 heads 43 -> 34.  Over 800 launches (2 to 32 chunks, 8 to 64 rows, 2 to 16 KV heads;
+// lengths equal, all half, of the upper half and of twenty to one) 4.5 % less time, equal lengths level, 15 launches slower by more
+// than 1.5 %, at most 4.  Heads in front of chunks in the grid, an earlier order for the same reason, took 3 % less, 86 launches
+// slower, up to 17 % (9 chunks, 16 rows of 1151 tokens, 16/4 heads 17.8 -> 20.5, now 17.4).  An odd number of chunks spreads by
+// itself.  Above 32 the chunks stay where they are: as even already (level over 60 launches).
+__device__ __forceinline__ int attn_chunk_of(int x, int stream, int ncmax)
+{
+    const int group = ncmax <= 32 ? ncmax & -ncmax : 1;
+    return x ^ (int)__umulhi((uint32_t)stream * 0x9E3779B9u, (uint32_t)group);
+}
 
 template <int G, int RT, bool DIRECT>
 __global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const uint16_t* __restrict__ q,
@@ -411,16 +420,8 @@ __global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const u
                                                         int Hq, int Hkv, int Lmax, int ncmax, float scale,
                                                         int len_offset)
 {
-    const int tile = blockIdx.z, tid = threadIdx.x;
-    int c = blockIdx.x, hgrp = blockIdx.y;
-    if constexpr (RT == 1) {
-        if (attn_heads_first(ncmax)) {
-            // neighbouring rows swap chunks where an XCD would always have the same ones
-            const int m = Hkv >= 8 ? 0 : (Hkv >= 4 ? 1 : (Hkv >= 2 ? 3 : 7));
-            c = blockIdx.y, hgrp = blockIdx.x;
-            if ((c | m) < ncmax) c ^= tile & m;
-        }
-    }
+    const int hgrp = blockIdx.y, tile = blockIdx.z, tid = threadIdx.x;
+    const int c = RT == 1 ? attn_chunk_of(blockIdx.x, hgrp + Hkv * tile, ncmax) : (int)blockIdx.x;
     // the tile's rows: length (0: no such row) and slot
     __shared__ int len[RT], slot[RT];
     if (tid < RT) {
@@ -1043,8 +1044,7 @@ int det::attn_decode_impl(const void* q, const void* kcache, const void* vcache,
     }
     const int RT = tiled ? 8 : 1;
     const bool by_chunk = !tiled && G > 1 && (size_t)ncmax * Hkv * B <= 512;
-    const bool heads_first = !tiled && !by_chunk && attn_heads_first(ncmax);
-    const dim3 grid(heads_first ? Hkv : ncmax, heads_first ? ncmax : Hkv, (B + RT - 1) / RT);
+    const dim3 grid(ncmax, Hkv, (B + RT - 1) / RT);
     const uint16_t* qq = static_cast<const uint16_t*>(q);
     const uint16_t* kk = static_cast<const uint16_t*>(kcache);
     const uint16_t* vv = static_cast<const uint16_t*>(vcache);

@@ -80,3 +80,10 @@ def test_every_chunk_is_computed_whatever_the_order_of_the_grid(d, Hq, Hkv, Lmax
     for b in range(B):
         assert torch.equal(run(slice(b, b + 1)), want[b:b + 1]), lens[b]
     torch.cuda.synchronize()
+
+
+# numbers of chunks with every power of two in them that the chunks' places turn by, up to the whole number, and the smallest
+@pytest.mark.parametrize("Hq,Hkv,Lmax,B", [(16, 16, 200, 40), (16, 16, 512, 40), (8, 4, 1024, 64), (4, 2, 3072, 45), (8, 2, 4096, 33),
+                                           (4, 2, 6144, 22), (4, 4, 16384, 9)])
+def test_every_chunk_is_computed_wherever_it_is_placed(d, Hq, Hkv, Lmax, B):
+    test_every_chunk_is_computed_whatever_the_order_of_the_grid(d, Hq, Hkv, Lmax, B)
