@@ -88,6 +88,10 @@ int det_gemm_bf16_fixed_tile(const void *A, int lda, const void *B_packed, void 
  * 192 or 256), 0 where they take another tiling. */
 int det_gemm_wide_rows(int M, int N, int K);
 
+/* Test hook: rows of the tiles that det_gemm_bf16 and its fused forms cut a launch of M rows into (0 if the shape is unsupported), and
+ * their columns. */
+int det_gemm_tile(int M, int N, int K, int *columns);
+
 /* Bytes of the packed form of a [K, N] bf16 matrix (= 2*K*N). 0 if the shape is unsupported. */
 size_t det_gemm_packed_b_bytes(int N, int K);
 

@@ -782,41 +782,37 @@ static int gemm_dispatch_norm(const void* X, int ldx, const void* wn, float eps,
 }
 static bool gemm_norm_fusable(int M, int K) { return M <= kNormRows && K <= 4096; }
 
-// Picks the kernel configuration (packing from N, tiling from N and M) and launches it.
-// fixed_tile: the one tiling per (N, K) that does not look at M: 256-row tiles of the packing's own width,
-// whatever the row count (det_gemm_bf16_fixed_tile).
-template <int EPI>
-static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ldc, const void* R, int ldr, int M,
-                         int N, int K, int f32, hipStream_t s, bool fixed_tile = false,
-                         const gemm_rope_args& ra = gemm_rope_args{})
+// The tiles a launch cuts C into: a function of M, N and K, `fixed` (det_gemm_bf16_fixed_tile) of N alone.
+// What bounds a launch with many rows is the bytes each workgroup pulls through its compute unit's memory pipe: every row of its
+// tile of A and every column of its tile of the weights, once per K.  The choice is, per (M, N), the tile shape that keeps that sum
+// small while every compute unit still gets a workgroup.  The packing is untouched (a workgroup streams as many adjacent slabs
+// as its tile is wide), and so is the arithmetic of an output element: the same chain of matrix-core steps over ascending K in
+// every instantiation, so its bytes do not depend on which ran.
+enum gemm_form { kGemmOwn, kGemm64, kGemm128, kGemmWide };  // columns of a tile: the packing's, 64, 128, 256 (gemm_wide.hip)
+struct gemm_tiling {
+    gemm_form form;
+    int rows;
+};
+
+// Of `n` row tiles of a matrix `cols` tiles wide, how many lie on different XCDs in one column: workgroups, columns first, go
+// round-robin over eight.  So often a launch reads each weight from behind the XCDs' L2.
+static int gemm_column_xcds(int cols, int n)
 {
-    bool ok = true;  // false: the schedule would overrun the kernel's load counter (no supported shape does)
+    const int pow2 = cols & -cols, d = pow2 < 8 ? 8 / pow2 : 1;
+    return n < d ? n : d;
+}
+
+static gemm_tiling gemm_pick(int M, int N, int K, bool fixed)
+{
     const int cb = gemm_cols_per_block(N);
     const bool small = gemm_small_ring(N);
+    if (fixed) return {kGemmOwn, 256};
     // (0) 256-column tiles (gemm_wide.hip) where their rounds cost less than those of the tiles below.
-    if (!fixed_tile) {
-        if (const int rbw = gemm_wide_rows(M, N, K, cb))
-            return gemm_wide(EPI, rbw, gemm_wide_args{A, lda, Bp, cb, C, ldc, R, ldr, M, N, K, f32, ra}, s);
-    }
-    // What bounds a launch with many rows is the bytes each workgroup pulls through its compute unit's
-    // memory pipe: every row of its tile of A and every column of its tile of the weights, once per K.
-    // The tiling below picks, per (M, N), the tile shape that keeps that sum small while every compute
-    // unit still gets a workgroup.  The packing is untouched (a workgroup streams as many adjacent slabs
-    // as its tile is wide), and so is the arithmetic of an output element: the same chain of matrix-core
-    // steps over ascending K in every instantiation, so its bytes do not depend on which ran.
-    //
+    if (const int rbw = gemm_wide_rows(M, N, K, cb)) return {kGemmWide, 32 * rbw};
+    if (small) return {kGemmOwn, 256};
     // (1) Launches with enough rows that 128-column tiles of 256 rows still fill the chip (prefill): the
     //     widest tile moves the fewest bytes per flop, whatever the packing.
-    if (!fixed_tile && !small && cb < 8 && 8 % cb == 0 && N % 128 == 0 &&
-        (long long)((M + 255) / 256) * (N / 128) >= 256) {
-        if (cb == 1)
-            ok = launch_gemm<8, kRingBig, EPI, 8, 4, 1>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s);
-        else if (cb == 2)
-            ok = launch_gemm<8, kRingBig, EPI, 8, 4, 2>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s);
-        else
-            ok = launch_gemm<8, kRingBig, EPI, 8, 4, 4>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s);
-        return ok ? check_launch() : DET_ESHAPE;
-    }
+    if (cb < 8 && 8 % cb == 0 && N % 128 == 0 && (long long)((M + 255) / 256) * (N / 128) >= 256) return {kGemm128, 256};
     // (2) Matrices too narrow to give every compute unit a column tile (N / (16 cb) < 256): the rows are
     //     cut into as many tiles as fill the chip, which also shortens each workgroup's pass over A.
     const int row_blocks = (M + 15) / 16;
@@ -828,7 +824,7 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
     int base_rows = 256, base_height = 256;
     {
         const int fit = 256 / (N / (16 * cb));
-        if (!fixed_tile && !small && fit >= 2 && row_blocks >= 2) {
+        if (fit >= 2 && row_blocks >= 2) {
             const int row_tiles = row_blocks < fit ? row_blocks : fit;
             const int rows = 16 * ((row_blocks + row_tiles - 1) / row_tiles);
             base_rows = rows < 256 ? rows : 256;
@@ -854,13 +850,46 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
     // 8.1, level where the bytes keep the tiles of (2).  At 32 columns with tiles of at most 64 rows (4096 x 8192 128 rows 24.3 ->
     // 21.8) or above 160 rows, where the 256-row tile's eleventh block costs a wave a third one (4096 x 6144 176 rows 27.1 -> 23.4,
     // 4096 x 8192 30.7 -> 26.9; 144 and 160 rows of 6144 20.8 -> 23.1 and 21.8 -> 23.2).
-    if (!fixed_tile && !small && N % 64 == 0 && sq_pays && ((cb == 1 && M > 64) || (cb == 2 && M >= 64 && (sq_rows <= 64 || M > 160)))) {
+    if (N % 64 == 0 && sq_pays && ((cb == 1 && M > 64) || (cb == 2 && M >= 64 && (sq_rows <= 64 || M > 160)))) {
+        // Half blocks may make more tiles of the same rows.  Not where more XCDs then read each weight: these launches are bound by
+        // such reads too (about 6.5 TB/s of them were measured), K x N 11904 x 2624 123 rows (six tiles of 24, not four of 32)
+        // 45.1 -> 57.7 us, 10496 x 3008 98 rows 39.8 -> 48.6, 9728 x 2368 202 rows 40.3 -> 45.3; where the number of reads stays,
+        // more tiles win (4224 x 2816 173 rows, five of 40, 19.2 -> 17.5; 10368 x 1792 335 rows 39.5 -> 34.8).
+        const int blocks_tiles = (row_blocks + sq_even / 16 - 1) / (sq_even / 16);
+        const int height = even_rows(sq_row_tiles), tiles = (M + height - 1) / height;
+        const bool more_reads = gemm_column_xcds(N / 64, tiles) > gemm_column_xcds(N / 64, blocks_tiles);
+        return {kGemm64, sq_even > 256 ? 256 : (more_reads ? even_rows(blocks_tiles) : height)};
+    }
+    return {kGemmOwn, base_height};
+}
+
+// Picks the kernel configuration (packing from N, tiling from M, N and K) and launches it.
+template <int EPI>
+static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ldc, const void* R, int ldr, int M,
+                         int N, int K, int f32, hipStream_t s, bool fixed_tile = false,
+                         const gemm_rope_args& ra = gemm_rope_args{})
+{
+    bool ok = true;  // false: the schedule would overrun the kernel's load counter (no supported shape does)
+    const int cb = gemm_cols_per_block(N);
+    const bool small = gemm_small_ring(N);
+    const gemm_tiling tile = gemm_pick(M, N, K, fixed_tile);
+    if (tile.form == kGemmWide)
+        return gemm_wide(EPI, tile.rows / 32, gemm_wide_args{A, lda, Bp, cb, C, ldc, R, ldr, M, N, K, f32, ra}, s);
+    if (tile.form == kGemm128) {
+        if (cb == 1)
+            ok = launch_gemm<8, kRingBig, EPI, 8, 4, 1>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s);
+        else if (cb == 2)
+            ok = launch_gemm<8, kRingBig, EPI, 8, 4, 2>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s);
+        else
+            ok = launch_gemm<8, kRingBig, EPI, 8, 4, 4>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s);
+        return ok ? check_launch() : DET_ESHAPE;
+    }
+    if (tile.form == kGemm64) {
         // Up to 64 rows, and at 128, eight waves own a row block each (or the tile has fewer); at other heights four waves of up to four
         // blocks, in one two-deep pipeline over K, and eight that load are faster: 14336 x 4096 400 rows (tiles of 112) 83.3 -> 76.5,
         // 520 rows (144) 143 -> 118, 2048 x 3072 700 rows (144) 26.0 -> 23.0, 4096 x 4096 1000 rows (256) 46.6 -> 44.1; 500 rows
         // (128) 26.2 -> 27.1, 4096 x 6144 256 rows (128) 27.3 -> 28.4.
-        const int rows = sq_even <= 256 ? even_rows(sq_row_tiles) : 256;
-        const int blocks = (rows + 15) / 16;
+        const int rows = tile.rows, blocks = (rows + 15) / 16;
         const bool four = blocks > 4 && blocks != 8;
         if (cb == 1)
             ok = four ? launch_gemm<4, kRingBig, EPI, 4, 8, 1>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, rows)
@@ -878,7 +907,7 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
                 break;                                                                                      \
             }                                                                                               \
         }                                                                                                   \
-        ok = launch_gemm<CBV, kRingBig, EPI, gemm_waves(CBV), gemm_loader_waves(CBV, false)>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, base_height);          \
+        ok = launch_gemm<CBV, kRingBig, EPI, gemm_waves(CBV), gemm_loader_waves(CBV, false)>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, tile.rows);          \
         break;
     switch (cb) {
         DET_GEMM_CASE(1)
@@ -889,7 +918,7 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
         DET_GEMM_CASE(6)
         DET_GEMM_CASE(7)
         default:
-            ok = launch_gemm<8, kRingBig, EPI, gemm_waves(8), gemm_loader_waves(8, false)>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, base_height);
+            ok = launch_gemm<8, kRingBig, EPI, gemm_waves(8), gemm_loader_waves(8, false)>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, tile.rows);
             break;
     }
 #undef DET_GEMM_CASE
@@ -905,6 +934,14 @@ using namespace det;
 extern "C" int det_gemm_wide_rows(int M, int N, int K)
 {
     return M < 1 || !gemm_shape_ok(N, K) ? 0 : 32 * gemm_wide_rows(M, N, K, gemm_cols_per_block(N));
+}
+
+extern "C" int det_gemm_tile(int M, int N, int K, int* columns)
+{
+    if (M < 1 || !columns || !gemm_shape_ok(N, K)) return 0;
+    const gemm_tiling t = gemm_pick(M, N, K, false);
+    *columns = t.form == kGemmOwn ? 16 * gemm_cols_per_block(N) : (t.form == kGemm64 ? 64 : (t.form == kGemm128 ? 128 : 256));
+    return t.rows;
 }
 
 extern "C" size_t det_gemm_packed_b_bytes(int N, int K)
