@@ -798,7 +798,7 @@ struct gemm_tiling {
 // round-robin over eight.  So often a launch reads each weight from behind the XCDs' L2.
 static int gemm_column_xcds(int cols, int n)
 {
-    const int pow2 = cols & -cols, d = pow2 < 8 ? 8 / pow2 : 1;
+    const int pow2 = cols & -cols, d = pow2 > 0 && pow2 < 8 ? 8 / pow2 : 1;
     return n < d ? n : d;
 }
 
@@ -845,21 +845,25 @@ static gemm_tiling gemm_pick(int M, int N, int K, bool fixed)
     const long long sq_cost = (long long)(sq_rows + 64) * rounds((long long)(N / 64) * ((M + sq_rows - 1) / sq_rows));
     const long long base_cost =
         (long long)(base_live + 16 * cb) * rounds((long long)(N / (16 * cb)) * ((M + base_rows - 1) / base_rows));
-    const bool sq_pays = 115 * sq_cost <= 100 * base_cost;
+    // Tile counts of blocks and of half blocks.  Half blocks may make more tiles of the same rows.  Not where more XCDs then read
+    // each weight: these launches are bound by such reads too (about 6.5 TB/s of them were measured), K x N 11904 x 2624 123 rows (six
+    // tiles of 24, not four of 32) 45.1 -> 57.7 us, 10496 x 3008 98 rows 39.8 -> 48.6, 9728 x 2368 202 rows 40.3 -> 45.3; where the
+    // number of reads stays, more tiles win (4224 x 2816 173 rows, five of 40, 19.2 -> 17.5; 10368 x 1792 335 rows 39.5 -> 34.8).
+    const int block_tiles = (row_blocks + sq_even / 16 - 1) / (sq_even / 16), half_height = even_rows(sq_row_tiles);
+    const int block_reads = gemm_column_xcds(N / 64, block_tiles);
+    const bool more_reads = gemm_column_xcds(N / 64, (M + half_height - 1) / half_height) > block_reads;
+    const int sq_height = sq_even > 256 ? 256 : (more_reads ? even_rows(block_tiles) : half_height);
+    // In few rows those reads also decide between these tiles and (2): in units of a compute unit's bytes one of them costs N / 115.
+    // 3584 x 2624 88 rows (six reads) 15.7 us in tiles of (2), 19.9 here, 12800 x 3200 73 rows 38.1 and 49.2, 14080 x 5440 72 rows (32
+    // columns) 55.1 and 68.1; up to N = 1856 level.  From 96 and 192 rows on the bytes alone decide (reads not measured there).
+    const long long reads_cost = M < (cb == 1 ? 96 : 192) ? (long long)block_reads * N / 115 : 0;
+    const bool sq_pays = 115 * (sq_cost > reads_cost ? sq_cost : reads_cost) <= 100 * base_cost;
     // From 65 rows on at 16 columns: K x N 14336 x 4096 95 rows 61.9 -> 46.6 us, 4096 x 4096 15.5 -> 13.4, 2048 x 3072 65 rows 9.0 ->
     // 8.1, level where the bytes keep the tiles of (2).  At 32 columns with tiles of at most 64 rows (4096 x 8192 128 rows 24.3 ->
     // 21.8) or above 160 rows, where the 256-row tile's eleventh block costs a wave a third one (4096 x 6144 176 rows 27.1 -> 23.4,
     // 4096 x 8192 30.7 -> 26.9; 144 and 160 rows of 6144 20.8 -> 23.1 and 21.8 -> 23.2).
-    if (N % 64 == 0 && sq_pays && ((cb == 1 && M > 64) || (cb == 2 && M >= 64 && (sq_rows <= 64 || M > 160)))) {
-        // Half blocks may make more tiles of the same rows.  Not where more XCDs then read each weight: these launches are bound by
-        // such reads too (about 6.5 TB/s of them were measured), K x N 11904 x 2624 123 rows (six tiles of 24, not four of 32)
-        // 45.1 -> 57.7 us, 10496 x 3008 98 rows 39.8 -> 48.6, 9728 x 2368 202 rows 40.3 -> 45.3; where the number of reads stays,
-        // more tiles win (4224 x 2816 173 rows, five of 40, 19.2 -> 17.5; 10368 x 1792 335 rows 39.5 -> 34.8).
-        const int blocks_tiles = (row_blocks + sq_even / 16 - 1) / (sq_even / 16);
-        const int height = even_rows(sq_row_tiles), tiles = (M + height - 1) / height;
-        const bool more_reads = gemm_column_xcds(N / 64, tiles) > gemm_column_xcds(N / 64, blocks_tiles);
-        return {kGemm64, sq_even > 256 ? 256 : (more_reads ? even_rows(blocks_tiles) : height)};
-    }
+    if (N % 64 == 0 && sq_pays && ((cb == 1 && M > 64) || (cb == 2 && M >= 64 && (sq_rows <= 64 || M > 160))))
+        return {kGemm64, sq_height};
     return {kGemmOwn, base_height};
 }
 
