@@ -95,6 +95,12 @@ def test_ragged_rows_whatever_the_split_of_the_loads(d, orc, M, N):
     assert np.array_equal(down_bf16(C), want)
 
 
+# Tiles of 64 to 112 columns whose rows are loaded in front of the weights (57 to 96 of them), and the heights beside those
+@pytest.mark.parametrize("M,N", [(M, N) for N in (10752, 12800, 15360, 17920) for M in (56, 57, 64, 75, 96, 97)])
+def test_rows_loaded_in_front_of_the_weights(d, orc, M, N):
+    test_ragged_rows_whatever_the_split_of_the_loads(d, orc, M, N)
+
+
 def test_rne_ties_and_identity(d, orc):
     """Identity weights copy A; a product of 257 must round to 256 (tie to even)."""
     K = N = 256
