@@ -390,6 +390,10 @@ int det_quant_act_q8(const void *A, int lda, void *codes, void *scales, int M, i
 int det_qgemm_w4a8(const void *codes, const void *scales, const void *packed_w, void *C, int ldc, int M,
                    int N, int K, int out_dtype, void *stream);
 
+/* Test hook: rows of the tiles that det_qgemm_w4a8 and its fused forms cut a launch of M rows into (0 if the shape is unsupported), and
+ * their columns. */
+int det_qgemm_tile(int M, int N, int K, int *columns);
+
 /* Fused forms for the quantized decoder layer; each gives the bytes of the unfused sequence.
  * det_quant_pack_w4_gate_up: det_quant_pack_w4 of a [K, 2F] matrix (F gate columns, then F up columns)
  *   with gate_j and up_j made neighbours, for det_qgemm_w4a8_swiglu.  F % 8 == 0.

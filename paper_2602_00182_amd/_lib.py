@@ -32,6 +32,7 @@ SIGNATURES = {
     "det_gemm_bf16_fixed_tile": (_i, [_vp, _i, _vp, _vp, _i, _i, _i, _i, _i, _vp]),
     "det_gemm_wide_rows": (_i, [_i, _i, _i]),
     "det_gemm_tile": (_i, [_i, _i, _i, C.POINTER(C.c_int)]),
+    "det_qgemm_tile": (_i, [_i, _i, _i, C.POINTER(C.c_int)]),
     "det_gemm_packed_b_bytes": (_sz, [_i, _i]),
     "det_gemm_pack_b": (_i, [_vp, _vp, _i, _i, _vp]),
     "det_gemm_bf16_residual": (_i, [_vp, _i, _vp, _vp, _i, _vp, _i, _i, _i, _i, _vp]),

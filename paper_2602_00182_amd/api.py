@@ -11,7 +11,7 @@ import torch
 from ._lib import LayerCfg, LayerWeights, Sha256Ctx, lib
 
 __all__ = [
-    "DetError", "det_gemm_bf16", "det_gemm_bf16_fixed_tile", "det_probe_lds_fill", "det_gemm_wide_rows", "det_gemm_tile", "det_gemm_packed_b_bytes", "det_gemm_pack_b", "det_gemm_bf16_residual",
+    "DetError", "det_gemm_bf16", "det_gemm_bf16_fixed_tile", "det_probe_lds_fill", "det_gemm_wide_rows", "det_gemm_tile", "det_qgemm_tile", "det_gemm_packed_b_bytes", "det_gemm_pack_b", "det_gemm_bf16_residual",
     "det_gemm_pack_gate_up", "det_gemm_swiglu_bf16", "pack_gate_up", "det_gemm_pack_qkv", "pack_qkv",
     "det_gemm_qkv_rope_append", "det_rmsnorm_gemm_qkv_rope_append", "det_rmsnorm_gemm_swiglu_bf16", "det_rmsnorm_gemm_bf16", "det_rmsnorm",
     "det_attn_decode_workspace_bytes", "det_attn_decode", "det_attn_decode_static", "det_attn_decode_rows", "det_decoder_layer_rows",
@@ -299,6 +299,12 @@ def det_gemm_wide_rows(M: int, N: int, K: int) -> int:
 def det_gemm_tile(M: int, N: int, K: int) -> tuple[int, int]:
     columns = C.c_int(0)
     rows = lib().det_gemm_tile(M, N, K, C.byref(columns))
+    return rows, columns.value
+
+
+def det_qgemm_tile(M: int, N: int, K: int) -> tuple[int, int]:
+    columns = C.c_int(0)
+    rows = lib().det_qgemm_tile(M, N, K, C.byref(columns))
     return rows, columns.value
 
 

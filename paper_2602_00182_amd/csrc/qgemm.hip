@@ -757,47 +757,47 @@ __global__ __launch_bounds__(64 * kTileWaves, 3) void qgemm_tile_kernel(
         return reinterpret_cast<const char*>(ring) + (c % NS) * SLOT;
     };
     auto block = [&](const char* slot, int s) __attribute__((always_inline)) {
-            const char* wslot = slot + ABYTES;
-            const char* dslot = wslot + WBYTES;
-            v4i xa[RB];
-            float dv[RB];
-            uint2 codes[JB], sraw[JB];
+        const char* wslot = slot + ABYTES;
+        const char* dslot = wslot + WBYTES;
+        v4i xa[RB];
+        float dv[RB];
+        uint2 codes[JB], sraw[JB];
 #pragma unroll
-            for (int j = 0; j < JB; ++j) {
-                const int cbk = JB * wave + j;  // column block of the tile
-                const char* wst = wslot + (cbk / CB) * (2 * WST) + s * WST;
-                codes[j] = *reinterpret_cast<const uint2*>(wst + (cbk % CB) * 512 + lane * 8);
-                sraw[j] = *reinterpret_cast<const uint2*>(wst + 512 * CB + (cbk % CB) * 32 + g * 8);
-            }
+        for (int j = 0; j < JB; ++j) {
+            const int cbk = JB * wave + j;  // column block of the tile
+            const char* wst = wslot + (cbk / CB) * (2 * WST) + s * WST;
+            codes[j] = *reinterpret_cast<const uint2*>(wst + (cbk % CB) * 512 + lane * 8);
+            sraw[j] = *reinterpret_cast<const uint2*>(wst + 512 * CB + (cbk % CB) * 32 + g * 8);
+        }
 #pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                xa[r] = *reinterpret_cast<const v4i*>(slot + (16 * r + lr) * 128 + (((4 * s + g) ^ zr) << 4));
-                dv[r] = *reinterpret_cast<const float*>(dslot + s * (TR * 4) + (16 * r + lr) * 4);
-            }
-            v4i wu[JB];
-            float sc[JB][4];
+        for (int r = 0; r < RB; ++r) {
+            xa[r] = *reinterpret_cast<const v4i*>(slot + (16 * r + lr) * 128 + (((4 * s + g) ^ zr) << 4));
+            dv[r] = *reinterpret_cast<const float*>(dslot + s * (TR * 4) + (16 * r + lr) * 4);
+        }
+        v4i wu[JB];
+        float sc[JB][4];
 #pragma unroll
-            for (int j = 0; j < JB; ++j) {
-                wu[j] = code_bytes(codes[j]);
-                sc[j][0] = bf16lo_to_f32(sraw[j].x);
-                sc[j][1] = bf16hi_to_f32(sraw[j].x);
-                sc[j][2] = bf16lo_to_f32(sraw[j].y);
-                sc[j][3] = bf16hi_to_f32(sraw[j].y);
-            }
-            v4i pr[RB][JB];
+        for (int j = 0; j < JB; ++j) {
+            wu[j] = code_bytes(codes[j]);
+            sc[j][0] = bf16lo_to_f32(sraw[j].x);
+            sc[j][1] = bf16hi_to_f32(sraw[j].x);
+            sc[j][2] = bf16lo_to_f32(sraw[j].y);
+            sc[j][3] = bf16hi_to_f32(sraw[j].y);
+        }
+        v4i pr[RB][JB];
 #pragma unroll
-            for (int r = 0; r < RB; ++r) {
+        for (int r = 0; r < RB; ++r) {
 #pragma unroll
-                for (int j = 0; j < JB; ++j) pr[r][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[j], xa[r], kProductStart, 0, 0, 0);
-            }
+            for (int j = 0; j < JB; ++j) pr[r][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[j], xa[r], kProductStart, 0, 0, 0);
+        }
 #pragma unroll
-            for (int r = 0; r < RB; ++r)
+        for (int r = 0; r < RB; ++r)
 #pragma unroll
-                for (int j = 0; j < JB; ++j)
+            for (int j = 0; j < JB; ++j)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        acc[r][j][v] = __builtin_fmaf(dv[r] * sc[j][v], product(pr[r][j][v]), acc[r][j][v]);
-        };
+                for (int v = 0; v < 4; ++v)
+                    acc[r][j][v] = __builtin_fmaf(dv[r] * sc[j][v], product(pr[r][j][v]), acc[r][j][v]);
+    };
     for (int c = 0; c < (nblk >> 1); ++c) {
         const char* slot = open(c);
         block(slot, 0);
@@ -874,8 +874,19 @@ __global__ __launch_bounds__(64 * kTileWaves, 3) void qgemm_tile_kernel(
     }
 }
 
+// Rows of the kernel above's tiles.  Matrices too narrow to give every compute unit a column tile: the rows are cut into as many
+// tiles as fill the chip (a tile's rows are whole 16-row blocks; which tile a row falls in does not touch its arithmetic).
+static int qgemm_tile_rows(int M, int N, int cb)
+{
+    const int row_blocks = (M + 15) / 16, fit = 256 / (N / (16 * cb));
+    if (fit < 2 || row_blocks < 2) return 256;
+    const int row_tiles = row_blocks < fit ? row_blocks : fit;
+    const int rows = 16 * ((row_blocks + row_tiles - 1) / row_tiles);
+    return rows < 256 ? rows : 256;
+}
+
 // The kernel and tile of a launch, a function of M, N and the packing (which is one of N).
-//   * `rows`, the height of the tiles the kernel above would cut the launch into (launch_qgemm), decides whether it does: a stage
+//   * `rows`, the height of the tiles the kernel above would cut the launch into, decides whether it does: a stage
 //     of it takes about 0.0025 us a row from 64 rows on, and a chain of 32 x 64 tiles 0.2 us a block, less against wider
 //     packings.  They meet at about 90, 80 and 60 rows (us there and here: N = 4096, K = 4096 80 rows 15.7 and 17.0, 96 rows
 //     18.5 and 17.1; N = 6144 64 rows 15.6 and 18.4, 80 rows 18.9 and 18.6; 2048 x 11264 48 rows 10.4 and 10.8, 64 rows 11.9 and 11.0).
@@ -886,9 +897,10 @@ __global__ __launch_bounds__(64 * kTileWaves, 3) void qgemm_tile_kernel(
 //     and 38.3; 300 rows of 2048 x 11264, 880 of 64 x 64: 26.9 against 23.0 in 64 x 128, which is taken.
 enum qgemm_form { kQBase, kQ32x64, kQ64x64, kQ64x128 };
 static long long qtiles(int M, int N, int rows, int cols) { return (long long)((M + rows - 1) / rows) * (N / cols); }
-static qgemm_form qgemm_pick(int M, int N, int cb, int rows)
+static qgemm_form qgemm_pick(int M, int N, int cb)
 {
     constexpr int kHeld = 768;
+    const int tile_rows = qgemm_tile_rows(M, N, cb), rows = tile_rows < M ? tile_rows : M;
     if (M > 65535 * 64 || N % 64 != 0) return kQBase;
     if (cb == 8) return rows > 80 && qtiles(M, N, 64, 128) >= 256 ? kQ64x128 : kQBase;
     if (rows + 10 * cb < 100) return kQBase;
@@ -922,28 +934,22 @@ static void launch_qgemm(const void* qa, const void* da, int ldd, const void* wp
                          int M, int N, int K, int out_f32, hipStream_t s, float* qscales_out = nullptr,
                          const gemm_rope_args& ra = gemm_rope_args{})
 {
-    // Matrices too narrow to give every compute unit a column tile: the rows are cut into as many tiles as
-    // fill the chip (a tile's rows are whole 16-row blocks; which tile a row falls in does not touch its
-    // arithmetic).
-    int tile_rows = 256;
-    const int col_tiles = N / (16 * CB), row_blocks = (M + 15) / 16, fit = 256 / col_tiles;
-    if (fit >= 2 && row_blocks >= 2) {
-        const int row_tiles = row_blocks < fit ? row_blocks : fit;
-        const int rows = 16 * ((row_blocks + row_tiles - 1) / row_tiles);
-        tile_rows = rows < 256 ? rows : 256;
+    const qgemm_form form = qgemm_pick(M, N, CB);
+    if (form == kQ64x128) {
+        launch_qgemm_tile<CB, EPI, 4, 2>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
+        return;
     }
-    switch (qgemm_pick(M, N, CB, tile_rows < M ? tile_rows : M)) {
-        case kQ64x128:
-            launch_qgemm_tile<CB, EPI, 4, 2>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
+    if constexpr (CB <= 4) {  // a slab of 128 columns is not cut (qgemm_pick)
+        if (form == kQ64x64) {
+            launch_qgemm_tile<CB, EPI, 4, 1>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
             return;
-        case kQ64x64:
-            if constexpr (CB <= 4) launch_qgemm_tile<CB, EPI, 4, 1>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
+        }
+        if (form == kQ32x64) {
+            launch_qgemm_tile<CB, EPI, 2, 1>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
             return;
-        case kQ32x64:
-            if constexpr (CB <= 4) launch_qgemm_tile<CB, EPI, 2, 1>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
-            return;
-        default: break;
+        }
     }
+    const int tile_rows = qgemm_tile_rows(M, N, CB);
     dim3 grid(N / (16 * CB), (M + tile_rows - 1) / tile_rows);
     const qgemm_plan full = make_qgemm_plan(tile_rows, CB, K);
     const qgemm_plan tail = make_qgemm_plan(M - tile_rows * ((M - 1) / tile_rows), CB, K);
@@ -976,6 +982,18 @@ extern "C" size_t det_qgemm_packed_w_bytes(int N, int K)
 {
     if (!qgemm_shape_ok(N, K)) return 0;
     return (size_t)(N / 16) * (K / 64) * qstage_w_bytes(1);
+}
+
+extern "C" int det_qgemm_tile(int M, int N, int K, int* columns)
+{
+    if (M < 1 || !columns || !qgemm_shape_ok(N, K)) return 0;
+    const int cb = qgemm_cols_per_block(N);
+    switch (qgemm_pick(M, N, cb)) {
+        case kQ64x128: *columns = 128; return 64;
+        case kQ64x64: *columns = 64; return 64;
+        case kQ32x64: *columns = 64; return 32;
+        default: *columns = 16 * cb; return qgemm_tile_rows(M, N, cb);
+    }
 }
 
 static int quant_pack_impl(const void* B_kn, void* packed, int N, int K, int gate_up_f, void* stream, int rope_d = 0)
