@@ -59,10 +59,12 @@ extern "C" {
  * What depends on (N, K) only: the packing, the matrix-core instruction, the K staging and the order
  * of the steps, i.e. everything that enters an element's arithmetic.  What det_gemm_bf16 (and the
  * fused forms below) ALSO choose from M is the tile a launch cuts C into, i.e. which workgroup and wave
- * computes an element: 256 rows x the packing's width by default; rows cut into shorter tiles when N
- * alone gives fewer than 256 workgroups and M >= 17; 64-column tiles from M >= 96 (16-column packings)
- * or M >= 192 (32-column packings); 128-column tiles when ceil(M/256) * N/128 >= 256; 256-column tiles of 128 to
- * 256 rows when M >= 256, K >= 1024, N % 256 == 0 and their rounds of 256 workgroups cost less.  The bytes of a
+ * computes an element: 256 rows x the packing's width by default; rows cut into shorter tiles, in half blocks of 8,
+ * when N alone gives fewer than 256 workgroups and M >= 17; 64-column tiles, where they move clearly fewer bytes, from
+ * M >= 65 (16-column packings) or, 32-column packings, from M >= 64 in tiles of at most 64 rows and from M >= 161 in any,
+ * up to M = 95 and M = 191 only where few of the eight XCDs read each weight; 128-column tiles when ceil(M/256) * N/128 >= 256;
+ * 256-column tiles of 128 to 256 rows when M >= 256, K >= 1024, N % 256 == 0 and their rounds of 256 workgroups cost less
+ * (det_gemm_tile gives the tile of a launch).  The bytes of a
  * row do not depend on that choice (every tile shape runs the same chain for an element; the tests
  * compare every M in 1..256 with the M = 256 launch and with det_gemm_bf16_fixed_tile), but it IS a
  * launch geometry keyed on the batch size, so it is named here and in det_fingerprint(), and

@@ -162,7 +162,7 @@ def test_llama_shapes_sampled_vs_oracle_and_batch_invariance(d, orc, K, N):
 
 @pytest.mark.parametrize("K,N", [(4096, 4096), (1024, 6144), (512, 1024), (14336, 4096)])
 def test_tile_shape_switch_points_keep_bytes(d, orc, K, N):
-    """Narrow matrices change tile shape with M (16- or 32-column tiles of up to 256 rows below 96 or 192
+    """Narrow matrices change tile shape with M (16- or 32-column tiles of up to 256 rows up to 64, 80, 112 or 160
     rows, 64-column tiles of fewer rows from there on; M = 1100 is more rows than one round of tiles
     holds, with a ragged last tile): every row's bytes are those of the M = 1 launch that computes it
     alone, and a sample agrees with fp64."""
@@ -179,7 +179,7 @@ def test_tile_shape_switch_points_keep_bytes(d, orc, K, N):
 
     step(f"gemm tile switch K={K} N={N} M=1100")
     full = gemm(0, 1100)
-    for M in [1, 17, 95, 96, 97, 111, 129, 160, 191, 192, 193, 255, 256, 257, 513, 1025]:
+    for M in [1, 17, 64, 65, 66, 80, 81, 95, 96, 97, 111, 112, 113, 129, 160, 161, 177, 191, 192, 193, 255, 256, 257, 513, 1025]:
         step(f"gemm tile switch K={K} N={N} M={M}")
         assert np.array_equal(gemm(0, M), full[:M]), f"rows changed between M={M} and M=1100"
     for r in [0, 95, 96, 200, 255, 256, 512, 1099]:
