@@ -406,13 +406,14 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
         auto wave_loads = [&](int c) { return c < nchunks - 1 ? loads_full : (c == nchunks - 1 ? loads_last : 0); };
         const int nw_full = strided(SPC * 2 * CB, wrank);  // weight blocks of a chunk, this wave
         const int nw_last = strided(tp.last_cnt * 2 * CB, wrank);
-        // Tiles of 64 to 112 columns and 57 to 96 rows load a chunk's rows in front of its weights: issued behind them, without the
-        // twenty instructions a load that ragged rows once took, they made such launches up to 6 % slower than those had been.
-        // 4096 x 12800 80 rows 29.4 -> 28.6 us, 9216 x 12800 60.5 -> 58.1, 4096 x 15360 88 rows 34.4 -> 32.5; a tile of 128 columns
-        // becomes 1 to 2 % slower by it, other heights stay level (45 to 56 rows of 64 columns are 2 to 3 % slower than ragged rows
-        // once were in either order).
-        constexpr bool kRowsFirst = CB >= 4 && CB < 8 && PCB == CB && !NORM;
-        const bool rows_first = HB >= 8 && HB <= 12;
+        // Whether a chunk's rows are loaded in front of its weights.  Issued behind them, without the twenty instructions a load that
+        // ragged rows once took, they made tiles of 48 to 112 columns 1 to 6 % slower than those had been.  Medians over random shapes,
+        // behind and in front against then: 48 columns, 3, 5 or 6 half blocks 1.01 and 0.99; 64 columns, 8 to 12 half blocks
+        // 1.00 and 0.985; 80 to 112 columns, 3 to 12 half blocks 1.01 and 0.99 (4096 x 15360 88 rows 32.5 us then, 34.4 behind, 32.5 in
+        // front; 9216 x 12800 80 rows 58.1, 60.5, 58.1).  Elsewhere in front is level or slower (four half blocks of 48 columns 1 %,
+        // 128 columns 1 to 2 %); 33 to 56 rows of 64 columns stay up to 4 % slower than then in either order, with K of 10000 and more.
+        constexpr bool kRowsFirst = CB >= 3 && CB < 8 && PCB == CB && RINGB == kRingBig && !NORM;
+        const bool rows_first = HB <= 12 && (CB >= 5 ? HB >= 3 : (CB == 4 ? HB >= 8 : HB == 3 || HB == 5 || HB == 6));
 
         auto load_chunk = [&](int c, int slot_idx) {
             const int s_cnt = chunk_stages(c);
