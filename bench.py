@@ -9,10 +9,11 @@ A step is one pass over the Llama-3-8B-shaped projection GEMM workload: the four
 through three distinct sets (1.3 GB) so that every launch streams its weights from HBM, not from
 the 256 MB last-level cache.  `value` is the step's total FLOP over its wall time.
 
-The JSON line also carries: the per-(shape, M) table measured with HIP events inside the timed
-region (cache-cold) and a cache-warm rerun; the roofline record of the dominant kernel; the CPU
-oracle timed on this host as a reported baseline; decoder-layer and greedy-decode tokens/s; and a
-bit-identical rate over repeated and re-batched runs.
+The JSON line also carries: the roofline record of the dominant kernel; the CPU oracle timed on this host as a
+reported baseline; greedy-decode tokens/s; and a bit-identical rate over repeated and re-batched runs.
+It is kept short (LINE_BYTES), since what reads it may keep only so much of the output.  The tables (every (shape, M) measured
+with HIP events, cache-cold and cache-warm, attention, decoder layers, quantized and library products, token selection) go
+to stderr as one JSON object, and to a file with --tables.
 """
 from __future__ import annotations
 
@@ -35,6 +36,25 @@ N_SETS = 3
 PEAK_MFMA_TFLOPS = 2500.0   # MI355X dense bf16
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 DOMINANT = (4096, 28672)    # the launch that moves most of the step's bytes (gemm_kernel<8,144,0,8,4,8,false>)
+LINE_BYTES = 4000
+LINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+             "dtype", "data", "config", "roofline", "fingerprint", "cpu_baseline", "bit_identical")
+
+
+def split_record(result):
+    """(the JSON line's object, the tables' object) of everything a run measured."""
+    line = {k: dict(result[k]) if isinstance(result[k], dict) else result[k] for k in LINE_KEYS if k in result}
+    tables = {k: v for k, v in result.items() if k not in line}
+    if "other_legs" in line.get("cpu_baseline", {}):
+        tables["cpu_baseline_other_legs"] = line["cpu_baseline"].pop("other_legs")
+    peaks = result.get("measured_peaks", {})
+    line["measured_peaks"] = {k: peaks[k] for k in ("copy_1GiB_gbs", "read_1GiB_gbs") if k in peaks}
+    line["decode_tokens_per_s"] = {
+        k: v["generated_tokens_per_s"] if isinstance(v, dict) else {f"B{r['B']}": r["tokens_per_s"] for r in v}
+        for k, v in result.get("decode", {}).items() if isinstance(v, dict) or "tokens_per_s" in v[0]}
+    return line, tables
+
+
 def dominant_traffic_bytes():
     """HBM bytes per launch of the dominant kernel as measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
     (scaled by a plain copy kernel of known size): read from the committed summary of those runs,
@@ -62,6 +82,7 @@ def main():
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=3)
+    ap.add_argument("--tables", default=None, metavar="FILE", help="also write the tables to this file")
     ap.add_argument("--skip-extras", action="store_true", help="only the timed GEMM workload")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="run a plain device-to-device copy of known size (for scaling rocprofv3 --pmc "
@@ -262,7 +283,12 @@ def main():
         result["qgemm_w4a8"] = qgemm_numbers(torch, det, ds, dev)
         result["library_gemm"] = library_gemm(torch, ds, dev, sweep_cold)
         result["token_selection"] = selection_numbers(torch, det, ds, dev)
-    print(json.dumps(result))
+    line, tables = split_record(result)
+    print(json.dumps(tables), file=sys.stderr, flush=True)
+    if args.tables:
+        with open(args.tables, "w") as f:
+            json.dump(tables, f, indent=1)
+    print(json.dumps(line))
 
 
 def probe(torch, det, ds, dev, spec):
