@@ -261,7 +261,7 @@ def main():
         "value": round(value, 3), "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16", "data": "synthetic",
-        "config": {"workload": "configs[1]: Llama-3-8B-shaped projection GEMMs, K=4096 x N in {4096,6144,28672} and "
+        "config": {"workload": "Llama-3-8B-shaped projection GEMMs, K=4096 x N in {4096,6144,28672} and "
                                "K=14336 x N=4096, M in {1,2,4,8,16,32,64,128,256}, bf16 in, fp32 accumulate, "
                                "bf16 out; weights rotate over 3 sets (HBM-cold)",
                    "launches_per_step": len(SHAPES) * len(MS), "flop_per_step": step_flops},
