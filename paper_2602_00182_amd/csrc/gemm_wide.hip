@@ -34,10 +34,15 @@ __device__ __forceinline__ int wide_swizzle(int q) { return (0x78 >> (2 * q)) & 
 // a load) and 16 KB of weights (blocks in operand order) a step, each wave loading its share.  What bounds the
 // 256 x 128 tile of gemm.hip is the fill of LDS, 48 KB for 64 * 256 * 128 products; 256 x 256 is 64 KB for twice the work.
 // The operands of step t+1 are read from LDS into registers while step t is in the matrix cores, so a step needs no wait for
-// its own reads, and its slot is free as soon as it starts; every second step has a barrier, whose turn it is for the loads of
-// the two steps behind it.  Reads and loads are dealt out among the products: issued in a row behind the barrier they left the
-// matrix cores idle, and a barrier a step cost 1 to 4 % (K x N 4096 x 6144, 3302 rows 171 us with both, 158 dealt out, 156 with
-// half the barriers; 14336 x 4096, 1500 rows 206, 206, 198).  Of 160-row tiles' 158 us the products alone take 115, and 133 with no
+// its own reads, and its slot is free as soon as it starts.  Reads and loads are dealt out among the products: issued in a row behind
+// the barrier they left the matrix cores idle.  Up to 192 rows every second step has a barrier, whose turn it is for the loads of
+// the two steps behind it: a barrier a step cost 1 to 4 % (K x N 4096 x 6144, 3302 rows 171 us with both, 158 dealt out, 156 with
+// half the barriers; 14336 x 4096, 1500 rows 206, 206, 198).  256-row tiles have one a step: of their five slots a barrier every second
+// step leaves a load one to two steps to land in instead of three to four, and where weights come from memory or a round is
+// not full that is too short.  129 launches that take them, K = 1024 to 14336, 1.3 % less time with half the barriers than with reads
+// and loads in a row, 29 of them more, up to 8 %; 2.9 % less with a barrier a step, none more (4096 x 28672 512 rows 122.3, 128.3, 118.7;
+// 4480 x 6400 2041 rows 113.4, 121.0, 110.5; full rounds lose 1 to 2 % of their gain, 4096 x 4096 4096 rows 119.9, 115.7, 117.6).
+// Of 160-row tiles' 158 us the products alone take 115, and 133 with no
 // loads, 148 with no reads, 151 with no barriers, 155 with no wait for the loads: what is left is the fill, 26 KB a step at 43
 // bytes a ns, near what a compute unit gets of data that does not hit in L2 (50 to 55).
 template <int RBW, int EPI>
@@ -52,6 +57,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uin
     static_assert(NS >= 4, "ring");
     constexpr int LMAX = (UNITS + kWideWaves - 1) / kWideWaves, LMIN = UNITS / kWideWaves;  // loads of a step, one wave
     static_assert(NS * LMAX <= 60, "load counter");
+    constexpr bool kEvery = RBW == 8;  // a barrier a step
     __shared__ uint4 ring[NS * SLOT / 16];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -114,17 +120,19 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uin
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const bool more = wave < UNITS % kWideWaves;  // this wave has LMAX loads a step, not LMIN
-    // Passing this in front of step t (even): steps t+1 and t+2 have landed for everyone, and everyone has the operands of step t
-    // in registers, so its slot and the one before it take the steps t+NS and t+NS-1.
-    int slot_r = 1, slot_w = NS - 1;  // slot of the step read next, and of the step issued next
+    // Passing this in front of step t: everyone has the operands of step t in registers, so its slot is free.  With a barrier a step,
+    // step t+1 has landed for everyone and the free slot takes step t+NS; else t is even, steps t+1 and t+2 have landed, and the slot and
+    // the one before it take the steps t+NS and t+NS-1.
+    int slot_r = 1, slot_w = kEvery ? 0 : NS - 1;  // slot of the step read next, and of the step issued next
+    constexpr int kBehind = kEvery ? NS - 2 : NS - 4;  // steps behind those, under way
     auto open = [&](bool steady) __attribute__((always_inline)) {
         wait_reads();
         if (!steady)
             wait_loads<0>();
-        else if (LMAX != LMIN && more)  // steps t+3 .. t+NS-2 are behind step t+2
-            wait_loads<(NS - 4) * LMAX>();
+        else if (LMAX != LMIN && more)
+            wait_loads<kBehind * LMAX>();
         else
-            wait_loads<(NS - 4) * LMIN>();
+            wait_loads<kBehind * LMIN>();
         asm volatile("s_barrier" ::: "memory");
     };
     // The products of a step (operands f), with the reads of the next step's operands (into nf) and, if `load`, the loads of the
@@ -162,7 +170,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uin
     };
 
 #pragma unroll
-    for (int t = 0; t < NS - 1; ++t)
+    for (int t = 0; t < (kEvery ? NS : NS - 1); ++t)
         if (t < nst) {
 #pragma unroll
             for (int i = 0; i < LMAX; ++i) issue(t & 1, t, i);
@@ -177,10 +185,19 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void gemm_wide_kernel(const uin
         for (int r = 0; r < RBW; ++r) f0.x[r] = *reinterpret_cast<const bf16x8*>(base + x_off + r * 1024);
     }
     open(true);
-    for (int t = 0; t < nst; t += 2) {
-        step(t - 1 + NS < nst, 1, f0, f1);
-        step(t + NS < nst, 0, f1, f0);  // (past the last step: reads whatever the slot holds, not used)
-        if (t + 2 < nst) open(t + 2 + NS - 2 < nst);
+    if constexpr (kEvery) {
+        for (int t = 0; t < nst; t += 2) {
+            step(t + NS < nst, 0, f0, f1);
+            open(t + NS < nst);
+            step(t + 1 + NS < nst, 1, f1, f0);  // (past the last step: reads whatever the slot holds, not used)
+            if (t + 2 < nst) open(t + 2 + NS - 1 < nst);
+        }
+    } else {
+        for (int t = 0; t < nst; t += 2) {
+            step(t - 1 + NS < nst, 1, f0, f1);
+            step(t + NS < nst, 0, f1, f0);  // (past the last step: reads whatever the slot holds, not used)
+            if (t + 2 < nst) open(t + 2 + NS - 2 < nst);
+        }
     }
 
     // Lane holds C[row = m0 + 16*(wr*RBW + r) + lr][n0 + 64*wc + 16j + 4g + v].
