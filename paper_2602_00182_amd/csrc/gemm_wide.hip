@@ -245,20 +245,21 @@ static void launch_rows(int rbw, const gemm_wide_args& a, hipStream_t s)
 }
 
 // What a launch costs is the rounds of 256 workgroups it takes, times what one of its tiles takes for a step of 32 of K, which is
-// nearly the same over all shapes (measured over K = 1024 .. 14336, N = 1024 .. 28672, 256 to 5000 rows).  Here 0.45 / 0.54 /
-// 0.60 / 0.78 us for tiles of 128 / 160 / 192 / 256 rows, a little more for 160 rows of 128-column packings.  In gemm.hip 0.53 us for a 256 x 128 tile (0.51 in launches of four
-// rounds and more), and in its narrower tilings, which it takes where those do not fill the chip, 1.4 ns (16- and 32-column
+// nearly the same over all shapes (fitted over K = 1024 .. 14336, N = 1024 .. 28672, 256 to 5000 rows; single launches are up to 15 %
+// off).  Here 0.45 / 0.54 / 0.60 / 0.78 us for tiles of 128 / 160 / 192 / 256 rows, 0.49 / 0.61 / 0.61 / 0.78 of 128-column packings.  In
+// gemm.hip 0.53 us for a 256 x 128 tile (0.51 in launches of four rounds and more), and in its narrower tilings, which it takes where those
+// do not fill the chip, 1.4 ns (16- and 32-column
 // packings) or 1.18 ns (64-column packings) for each row and column of a tile.  The last row of tiles there is as short as
 // its rows: 0.34 of a whole 256 x 128 tile's time and the rest by rows, and it fills the compute units that the last round of
 // whole tiles leaves idle.  (Counted as whole tiles, 258 rows of K = 4416, N = 11264 took this form in 62 us instead of 42, 519 rows
 // of 2048 x 6144 in 34 instead of 28.)  So the choice is the tile height whose tiles fit the rounds best: 3302 rows of N = 6144,
-// K = 4096 are 13 x 48 tiles there (three rounds, 208 us), 13 x 24 of 256 rows here (two, 207 us), 21 x 24 of 160 rows
-// (two, 156 us).  6 % must be won by this count, 21 % where a tile there is as wide as the
-// packing and the weights alone are much of the time.  Of 665 shapes that could take this form, half of them a few rows past
-// whole 256-row tiles, the choice is slower by more than 2 % in one (3 %); where it stays in gemm.hip this form would have taken up to
-// a quarter less time (476 rows of 14336 x 8192).  Others: K x N 4096 x 6144 700 rows 90 -> 60 us, 14336 x 4096 1500 rows
-// 302 -> 202, 4096 x 28672 4096 rows 919 -> 760 (1.27 PFLOP/s; torch's product of two 8192 x 8192 matrices reaches 1.19 on the
-// same card).
+// K = 4096 are 13 x 48 tiles there (three rounds, 193 us), 13 x 24 of 256 rows here (two), 21 x 24 of 160 rows
+// (two, 153 us).  6 % must be won by this count, 21 % where a tile there is as wide as the
+// packing and the weights alone are much of the time.  522 random launches that take this form take 19 % less time than in the tilings of
+// gemm.hip; 19 of them more, by over 2 %: most are a few rows past whole tiles there and 4 to 10 % slower, three of N = 5632 at 616 to 638
+// rows 30 %, since the 64-column tiles have become up to a fifth faster than the 1.4 ns counted for them.  Others: K x N 4096 x 6144
+// 700 rows 77 -> 61 us, 14336 x 4096 1500 rows 260 -> 202, 4096 x 28672 4096 rows 955 -> 859 (1.12 PFLOP/s; torch's product of two
+// 8192 x 8192 matrices reaches 1.19 on the same card).
 namespace {
 
 long long rounds(long long wgs) { return (wgs + 255) / 256; }
@@ -295,8 +296,10 @@ int gemm_wide_rows(int M, int N, int K, int cb)
         cost = span(M, N / 128, 256, [&](int x) { return (long long)t * (34 * 256 + 66 * x) / 25600; });
     }
     static const struct {
-        int rbw, cost, cost8;  // cost8: 128-column packings
-    } kTiles[4] = {{4, 4500, 4500}, {5, 5400, 6060}, {6, 6000, 6060}, {8, 7800, 7800}};
+        // cost8: 128-column packings.  While 128 rows of those counted 4500 too, launches took them that are faster in other heights or in
+        // gemm.hip: 3328 x 25088 1590 rows 316 us instead of 282, 13824 x 27904 1109 rows (now 160) 15 % more.
+        int rbw, cost, cost8;
+    } kTiles[4] = {{4, 4500, 4900}, {5, 5400, 6060}, {6, 6000, 6060}, {8, 7800, 7800}};
     int best = 0;
     long long best_cost = 100 * cost;
     for (const auto& t : kTiles) {

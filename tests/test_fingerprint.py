@@ -21,7 +21,7 @@ def geometry():
 
 def test_a_changed_geometry_has_a_new_revision():
     """Two builds that cut launches differently must not name themselves alike: with a new digest goes a new revision."""
-    assert (tag()[0], geometry()) == ("tiles-6", "445eac4993878d8c")
+    assert (tag()[0], geometry()) == ("tiles-7", "303d196ef16e01e3")
 
 
 def test_the_tag_states_the_rules():
