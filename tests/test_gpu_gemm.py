@@ -375,6 +375,15 @@ def test_fused_swiglu_epilogue_equals_unfused_bytes(d, orc, M, K, F):
     assert np.array_equal(down_bf16(fused), orc.swiglu(np.ascontiguousarray(guh[:, :F]), np.ascontiguousarray(guh[:, F:])))
 
 
+# 64-column tiles of more than 64 rows, which four waves compute, of 16- and 32-column packings: heights around whole numbers of blocks
+@pytest.mark.parametrize("M,K,N,rows", [(300, 512, 4096, 80), (520, 256, 4096, 136), (700, 256, 3072, 144), (1000, 256, 4096, 256),
+                                        (176, 256, 6144, 88), (300, 512, 6144, 152)])
+def test_epilogues_of_tiles_that_four_waves_compute(d, orc, M, K, N, rows):
+    assert d.det_gemm_tile(M, N, K) == (rows, 64)
+    test_fused_residual_epilogue_equals_unfused_bytes(d, orc, M, K, N)
+    test_fused_swiglu_epilogue_equals_unfused_bytes(d, orc, M, K, N // 2)
+
+
 @pytest.mark.parametrize("M,Hq,Hkv,K,Lmax,use_slots", [(1, 32, 8, 4096, 64, False), (7, 4, 2, 256, 40, True),
                                                        (33, 8, 2, 1024, 96, True), (300, 32, 8, 4096, 320, False),
                                                        (1300, 32, 8, 512, 700, True), (130, 2, 1, 512, 130, True)])

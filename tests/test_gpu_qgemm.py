@@ -283,3 +283,10 @@ def test_qgemm_rope_append_epilogue_equals_unfused_bytes(d, M, Hq, Hkv, K, Lmax,
     assert torch.equal(qbuf.view(torch.int16), qk_rot[:, :Hq, :].contiguous().view(torch.int16))
     assert torch.equal(kc.view(torch.int16), k_ref.view(torch.int16))
     assert torch.equal(vc.view(torch.int16), v_ref.view(torch.int16))
+
+
+# 64 x 128 tiles of 32- and 16-column packings
+@pytest.mark.parametrize("M,Hq,Hkv,K,Lmax,use_slots", [(600, 32, 8, 256, 320, True), (1030, 16, 4, 64, 530, True)])
+def test_rope_append_epilogue_of_tall_tiles(d, M, Hq, Hkv, K, Lmax, use_slots):
+    assert d.det_qgemm_tile(M, (Hq + 2 * Hkv) * 128, K) == (64, 128)
+    test_qgemm_rope_append_epilogue_equals_unfused_bytes(d, M, Hq, Hkv, K, Lmax, use_slots)

@@ -15,7 +15,7 @@ def d():
     return d
 
 
-def parts(M, n=100):
+def parts(M, n=48):
     return [slice(i, min(i + n, M)) for i in range(0, M, n)]
 
 
@@ -23,7 +23,15 @@ def parts(M, n=100):
 @pytest.mark.parametrize("M,K,N", [(385, 64, 2048), (450, 192, 2048), (449, 1088, 3072), (225, 64, 5120), (257, 320, 5248),
                                    (129, 192, 11008), (256, 128, 11264), (129, 64, 20480), (200, 704, 28672)])
 def test_rows_equal_small_calls(d, M, K, N):
-    rows_equal_small_calls(d, M, K, N, 100)
+    assert d.det_qgemm_tile(M, N, K) == ((64, 128) if N >= 20480 else (64, 64) if N >= 11008 else (32, 64))
+    rows_equal_small_calls(d, M, K, N)
+
+
+# 64 x 128 tiles of every packing: a tile of one row, nearly whole ones, odd and even numbers of blocks
+@pytest.mark.parametrize("M,K,N", [(1601, 64, 2048), (1540, 192, 2048), (1087, 128, 3072), (900, 320, 5120), (300, 192, 11264), (321, 64, 11264)])
+def test_rows_of_tall_tiles_equal_small_calls(d, M, K, N):
+    assert d.det_qgemm_tile(M, N, K) == (64, 128)
+    rows_equal_small_calls(d, M, K, N)
 
 
 # 32 x 64 tiles of packings of 16, 32 and 64 columns, the last row in a tile of its own, at its end and before it; 64 x 64 tiles, also of
@@ -31,10 +39,13 @@ def test_rows_equal_small_calls(d, M, K, N):
 @pytest.mark.parametrize("M,K,N", [(97, 64, 4096), (96, 192, 3072), (161, 320, 2048), (129, 128, 6144), (65, 64, 11264),
                                    (257, 192, 8192), (700, 64, 3072), (1000, 64, 4160), (96, 192, 20480)])
 def test_rows_of_small_tiles_equal_small_calls(d, M, K, N):
-    rows_equal_small_calls(d, M, K, N, 48)
+    rows_equal_small_calls(d, M, K, N)
 
 
-def rows_equal_small_calls(d, M, K, N, few):
+def rows_equal_small_calls(d, M, K, N):
+    for n in {48, M % 48 or 48}:  # the calls compared with take the kernel that is held to the oracle: columns and rows of no tile above
+        rows, columns = d.det_qgemm_tile(n, N, K)
+        assert columns == d.det_qgemm_tile(1, N, K)[1] and (columns != 64 or rows == 256)
     w = up_bf16(ds.normal_bf16(7000 + N, (K, N), 0.02))
     a = up_bf16(ds.normal_bf16(7100 + M, (M, K)))
     r = up_bf16(ds.normal_bf16(7200 + M, (M, N)))
@@ -48,7 +59,7 @@ def rows_equal_small_calls(d, M, K, N, few):
     d.det_qgemm_w4a8_residual(codes, scales, wp, r, res, N)
     d.det_qgemm_w4a8_swiglu(codes, scales, gu, swi, N // 2)
     torch.cuda.synchronize()
-    for p in parts(M, few):
+    for p in parts(M):
         c, s = d.quant_activations(a[p].contiguous())
         n = p.stop - p.start
         o1 = torch.empty((n, N), device=DEV)
@@ -91,7 +102,7 @@ def test_quantized_layer_rows_equal_small_calls(d, R, H, Hq, Hkv, F):
         return x.view(torch.int16), k.view(torch.int16), v.view(torch.int16)
 
     step(f"quantized layer R={R} H={H} heads {Hq}/{Hkv} F={F}")
-    for got, want in zip(run([slice(0, R)]), run(parts(R, 48))):
+    for got, want in zip(run([slice(0, R)]), run(parts(R))):
         assert torch.equal(got, want)
 
 
@@ -152,3 +163,9 @@ def test_strided_rows(d, M, K, N):
         cols = want.shape[1]
         assert torch.isnan(got[:, cols:]).all(), "written between the rows"
         assert torch.equal(got[:, :cols].contiguous().view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,K,N", [(1601, 64, 2048), (900, 64, 5120), (300, 192, 11264)])
+def test_strided_rows_of_tall_tiles(d, M, K, N):
+    assert d.det_qgemm_tile(M, N, K) == (64, 128)
+    test_strided_rows(d, M, K, N)
