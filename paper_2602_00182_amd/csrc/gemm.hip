@@ -212,6 +212,8 @@ static bool plan_fits_load_counter(const gemm_tile_plan& t, int cb)
     return t.nslots >= 2 && (t.nslots - 1) * per_chunk <= 62;
 }
 
+// ROWS_FIRST: a chunk's rows are loaded in front of its weights (gemm_rows_first).
+//
 // PCB: column blocks per slab of the packed weights.  PCB == CB: the workgroup's weights are one slab.
 // PCB < CB (tall launches of narrow matrices, see gemm_dispatch): the workgroup owns CB/PCB adjacent
 // slabs of a matrix packed for narrower tiles, and its rows are a tile of plan_full.mrem rows.
@@ -222,7 +224,7 @@ static bool plan_fits_load_counter(const gemm_tile_plan& t, int cb)
 // RMSNorm kernel has them) straight into LDS, where they stay for the whole K range in the first K/64
 // blocks, one 8-row half block a stage; the ring behind them carries weights only, loaded by the NL waves
 // that never compute, which start streaming before the rows are read.
-template <int CB, int RINGB, int EPI, int NW, int NL, int PCB, bool NORM>
+template <int CB, int RINGB, int EPI, int NW, int NL, int PCB, bool NORM, bool ROWS_FIRST>
 __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __restrict__ A, int lda,
                                                           const uint4* __restrict__ Bp, void* C, int ldc,
                                                           const uint16_t* R, int ldr, int K, int out_f32,
@@ -406,15 +408,6 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
         auto wave_loads = [&](int c) { return c < nchunks - 1 ? loads_full : (c == nchunks - 1 ? loads_last : 0); };
         const int nw_full = strided(SPC * 2 * CB, wrank);  // weight blocks of a chunk, this wave
         const int nw_last = strided(tp.last_cnt * 2 * CB, wrank);
-        // Whether a chunk's rows are loaded in front of its weights.  Issued behind them, without the twenty instructions a load that
-        // ragged rows once took, they made tiles of 48 to 112 columns 1 to 6 % slower than those had been.  Medians over random shapes,
-        // behind and in front against then: 48 columns, 3, 5 or 6 half blocks 1.01 and 0.99; 64 columns, 8 to 12 half blocks
-        // 1.00 and 0.985; 80 to 112 columns, 3 to 12 half blocks 1.01 and 0.99 (4096 x 15360 88 rows 32.5 us then, 34.4 behind, 32.5 in
-        // front; 9216 x 12800 80 rows 58.1, 60.5, 58.1).  Elsewhere in front is level or slower (four half blocks of 48 columns 1 %,
-        // 128 columns 1 to 2 %); 33 to 56 rows of 64 columns stay up to 4 % slower than then in either order, with K of 10000 and more.
-        constexpr bool kRowsFirst = CB >= 3 && CB < 8 && PCB == CB && RINGB == kRingBig && !NORM;
-        const bool rows_first = HB <= 12 && (CB >= 5 ? HB >= 3 : (CB == 4 ? HB >= 8 : HB == 3 || HB == 5 || HB == 6));
-
         auto load_chunk = [&](int c, int slot_idx) {
             const int s_cnt = chunk_stages(c);
             if (s_cnt == 0) return;
@@ -433,7 +426,7 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
                     }
                 }
             };
-            if (kRowsFirst && rows_first) load_rows();
+            if constexpr (ROWS_FIRST) load_rows();
             if constexpr (PCB == CB) {
                 dma_run(wbytes, w_lane_off + (uint32_t)(s0 * (2 * CB) + wrank) * 1024u, (uint32_t)nload * 1024u,
                         slot_addr + (uint32_t)wrank * 1024u, (uint32_t)nload * 1024u, s_cnt == SPC ? nw_full : nw_last);
@@ -446,7 +439,7 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
                             slot_addr + (uint32_t)u * 1024u, (uint32_t)(2 * CB) * 1024u, s_cnt);
                 }
             }
-            if (!NORM && !(kRowsFirst && rows_first)) load_rows();  // NORM: the activations are resident
+            if constexpr (!NORM && !ROWS_FIRST) load_rows();  // NORM: the activations are resident
         };
 
         if constexpr (NORM) asm volatile("s_barrier" ::: "memory");  // the rows' loads are issued (see normalize_rows)
@@ -749,7 +742,7 @@ __global__ __launch_bounds__(256) void gemm_pack_kernel(const uint16_t* __restri
 // while it is shorter than the wait for the first weights (measured on the layer: 4 us gained at one row, 3 at
 // two, 1 at four, 3 lost at eight).
 constexpr int kNormRows = 4;
-template <int CB, int RINGB, int EPI, int NW, int NL, int PCB = CB, bool NORM = false>
+template <int CB, int RINGB, int EPI, int NW, int NL, int PCB = CB, bool NORM = false, bool ROWS_FIRST = false>
 static bool launch_gemm(const void* A, int lda, const void* Bp, void* C, int ldc, const void* R, int ldr,
                         const gemm_rope_args& ra, int M, int N, int K, int out_f32, hipStream_t s,
                         int tile_rows = 256, float eps = 0.0f)
@@ -760,7 +753,7 @@ static bool launch_gemm(const void* A, int lda, const void* Bp, void* C, int ldc
     const gemm_tile_plan tail = make_tile_plan(M - tile_rows * ((M - 1) / tile_rows), CB, RINGB, NW, NL, K, NORM);
     const gemm_tile_plan full = NORM ? tail : make_tile_plan(tile_rows, CB, RINGB, NW, NL, K);  // NORM: the one tile is the tail
     if (!plan_fits_load_counter(full, CB) || !plan_fits_load_counter(tail, CB)) return false;
-    hipLaunchKernelGGL((gemm_kernel<CB, RINGB, EPI, NW, NL, PCB, NORM>), grid, dim3(64 * (NW + NL)), 0, s,
+    hipLaunchKernelGGL((gemm_kernel<CB, RINGB, EPI, NW, NL, PCB, NORM, ROWS_FIRST>), grid, dim3(64 * (NW + NL)), 0, s,
                        static_cast<const uint16_t*>(A), lda, static_cast<const uint4*>(Bp), C, ldc,
                        static_cast<const uint16_t*>(R), ldr, K, out_f32, full, tail, ra, eps);
     return true;
@@ -878,6 +871,19 @@ static gemm_tiling gemm_pick(int M, int N, int K, bool fixed)
     return {kGemmOwn, base_height};
 }
 
+// Whether a launch of M rows loads each chunk's rows in front of its weights (ROWS_FIRST).  Issued behind them, without the twenty
+// instructions a load that ragged rows once took, they made tiles of 48 to 112 columns 1 to 6 % slower than those had been.  Medians over
+// random shapes, behind and in front against then: 48 columns, 3, 5 or 6 half blocks 1.01 and 0.99; 64 columns, 8 to 12 half blocks
+// 1.00 and 0.985; 80 to 112 columns, 3 to 12 half blocks 1.01 and 0.99 (4096 x 15360 88 rows 32.5 us then, 34.4 behind, 32.5 in
+// front; 9216 x 12800 80 rows 58.1, 60.5, 58.1).  Elsewhere in front is level or slower (four half blocks of 48 columns 1 %,
+// 128 columns 1 to 2 %); 33 to 56 rows of 64 columns stay up to 5 % slower than then in either order, with K of 7000 and more.
+// A kernel of its own: with both orders in one, launches of other heights took 0.4 % longer.
+constexpr bool gemm_rows_first(int cb, int M)
+{
+    const int HB = (M + 7) / 8;
+    return cb < 8 && HB <= 12 && (cb >= 5 ? HB >= 3 : (cb == 4 ? HB >= 8 : cb == 3 && (HB == 3 || HB == 5 || HB == 6)));
+}
+
 // Picks the kernel configuration (packing from N, tiling from M, N and K) and launches it.
 template <int EPI>
 static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ldc, const void* R, int ldr, int M,
@@ -919,6 +925,12 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
         if constexpr (CBV <= 3) {                                                                           \
             if (small) {                                                                                    \
                 ok = launch_gemm<CBV, gemm_small_ring_blocks(CBV), EPI, gemm_waves(CBV), gemm_loader_waves(CBV, true)>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s); \
+                break;                                                                                      \
+            }                                                                                               \
+        }                                                                                                   \
+        if constexpr (CBV >= 3) {                                                                           \
+            if (!fixed_tile && gemm_rows_first(CBV, M)) {                                                   \
+                ok = launch_gemm<CBV, kRingBig, EPI, gemm_waves(CBV), gemm_loader_waves(CBV, false), CBV, false, true>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, tile.rows); \
                 break;                                                                                      \
             }                                                                                               \
         }                                                                                                   \
