@@ -34,6 +34,11 @@ __device__ __forceinline__ void wait_then_barrier()
 
 }  // namespace
 
+// Where the pieces of a K row lie (piece p at p ^ k_swizzle): row 4q + r of an operand block.  A read of sixteen bytes a lane is
+// served in quarters of lanes 0-3, 12-15 and, of the next sixteen, 4-11 (the other way round in the second), which ask for
+// pieces four apart: with the row's own number as the swizzle the two halves met in the same banks.
+__device__ __forceinline__ int k_swizzle(int q, int r) { return r | (((0x78 >> (2 * q)) & 3) << 2); }
+
 // One workgroup (256 threads) = 64 / G consecutive rows x the G query heads of one KV head; wave w owns the
 // pairs 16w .. 16w+15 from the scores to the output, so that nothing but K, V and the chunk maxima goes
 // through LDS.
@@ -67,11 +72,6 @@ __device__ __forceinline__ void wait_then_barrier()
 // The form does not pay for 17 to 32 pairs (five to eight rows of four heads), which walk and are the slowest here: 497 rows,
 // eight a slot, 32/8 heads, 200 tokens 25 -> 37 us, 1000 108 -> 117, 2048 198 -> 243; 994 rows 46 -> 47, 214 -> 154.
 // Deep rows are not touched here.
-// Where the pieces of a K row lie (piece p at p ^ k_swizzle): row 4q + r of an operand block.  A read of sixteen bytes a lane is
-// served in quarters of lanes 0-3, 12-15 and, of the next sixteen, 4-11 (the other way round in the second), which ask for
-// pieces four apart: with the row's own number as the swizzle the two halves met in the same banks.
-__device__ __forceinline__ int k_swizzle(int q, int r) { return r | (((0x78 >> (2 * q)) & 3) << 2); }
-
 template <int G, bool QUANT>
 __global__ __launch_bounds__(256, 2) void attn_walk_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kcache,
                                                           const uint16_t* __restrict__ vcache,

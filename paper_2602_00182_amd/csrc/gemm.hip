@@ -4,8 +4,8 @@
 // no atomics).
 //
 // Shape of the kernel
-//   * A workgroup owns BN = 16*CB output columns and up to 256 rows; grid.x = N/BN, grid.y =
-//     ceil(M/256).  It has NW (4 or 8) wavefronts that can compute plus NL (2 or 4) that only load.
+//   * A workgroup owns BN = 16*CB output columns and up to 256 rows; grid.x = N/BN, grid.y = M over the
+//     tile's rows.  It has NW (4 or 8) wavefronts that can compute plus NL (2, 4 or 8) that only load.
 //     The packing (CB), the matrix-core shape and the K order are functions of N alone.  The tile a
 //     launch cuts C into also looks at M (gemm_dispatch: narrow matrices cut their rows so that every
 //     compute unit gets a workgroup, tall launches of narrow packings take 64- or 128-column tiles

@@ -688,10 +688,10 @@ __global__ __launch_bounds__(64 * kTileWaves, 3) void qgemm_tile_kernel(
     const char* wbytes = reinterpret_cast<const char*>(wp) + (size_t)(n0 / 16) * nblk * qstage_w_bytes(1);
     const char* dbytes = reinterpret_cast<const char*>(da);
 
-    // This lane's sources.  Activations, unit u = 2*wave + i: row 8u + lane/8 (rows past M repeat the last), its 16-byte piece
-    // (lane%8) ^ (row/2)%8, which spreads the sixteen rows of an operand read over the banks.  Weights, unit u = wave,
-    // wave + 4 (and 8, half a unit, wave 0): piece 64u + lane of the chunk's 544, of slab piece / (68*CB).  Scales (wave 1):
-    // block lane/16, rows 4*(lane%16) .. +3.  `odd`: a last chunk of one block repeats that block's bytes.
+    // This lane's sources.  Activations, unit u = AU*wave + i: row 8u + lane/8 (rows past M repeat the last), its 16-byte piece
+    // (lane%8) ^ (row/2)%8, which spreads the sixteen rows of an operand read over the banks.  Weights, unit u = wave (and wave + 4
+    // in 128-column tiles), the last 16*JB pieces by wave 0: piece 64u + lane of the chunk's 272*JB, of slab piece / (68*CB).  Scales
+    // (wave 1): block lane / (TR/4), rows 4*(lane % (TR/4)) .. +3.  `odd`: a last chunk of one block repeats that block's bytes.
     uint32_t a_off[2][AU];
     const char* a_base[AU];
 #pragma unroll

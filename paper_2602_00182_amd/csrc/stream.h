@@ -60,7 +60,9 @@ __device__ __forceinline__ void dma_run_next(const void* base, uint32_t& lane_of
         : "s"(base), "s"(src_stride), "s"(lds_stride)
         : "memory", "scc");
 }
-// The next load of a run whose sources have no constant stride: a base and offset of its own.
+// The next load of a run whose sources have no constant stride: a base and offset of its own.  A write to M0 must be followed by
+// one other instruction before a load into LDS: here by the caller's branch between two loads (a s_nop in its place cost tall
+// tiles 1 to 2 %), so this is not for straight-line runs.
 __device__ __forceinline__ void dma_run_next(const void* base, uint32_t lane_off, uint32_t lds_stride)
 {
     asm volatile(
