@@ -74,6 +74,9 @@ __host__ __device__ constexpr int gemm_waves(int cb) { return cb >= 4 ? 8 : 4; }
 // Wavefronts that never compute and only issue loads (on top of those above): one per SIMD for wide tiles.
 __host__ __device__ constexpr int gemm_loader_waves(int cb, bool small_ring) { return small_ring ? 2 : 4; }
 
+// How a chunk's rows are loaded (gemm_order).
+enum { kRowsBehind, kRowsFirst, kRowsPaced };
+
 constexpr int kRingBig = 144;
 __host__ __device__ constexpr int gemm_small_ring_blocks(int cb) { return 4 * (cb + 16); }
 bool gemm_small_ring(int N)
@@ -212,7 +215,7 @@ static bool plan_fits_load_counter(const gemm_tile_plan& t, int cb)
     return t.nslots >= 2 && (t.nslots - 1) * per_chunk <= 62;
 }
 
-// ROWS_FIRST: a chunk's rows are loaded in front of its weights (gemm_rows_first).
+// ORDER: where and how a chunk's rows are loaded (gemm_order).
 //
 // PCB: column blocks per slab of the packed weights.  PCB == CB: the workgroup's weights are one slab.
 // PCB < CB (tall launches of narrow matrices, see gemm_dispatch): the workgroup owns CB/PCB adjacent
@@ -224,7 +227,7 @@ static bool plan_fits_load_counter(const gemm_tile_plan& t, int cb)
 // RMSNorm kernel has them) straight into LDS, where they stay for the whole K range in the first K/64
 // blocks, one 8-row half block a stage; the ring behind them carries weights only, loaded by the NL waves
 // that never compute, which start streaming before the rows are read.
-template <int CB, int RINGB, int EPI, int NW, int NL, int PCB, bool NORM, bool ROWS_FIRST>
+template <int CB, int RINGB, int EPI, int NW, int NL, int PCB, bool NORM, int ORDER>
 __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __restrict__ A, int lda,
                                                           const uint4* __restrict__ Bp, void* C, int ldc,
                                                           const uint16_t* R, int ldr, int K, int out_f32,
@@ -423,10 +426,11 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
                     for (int i = 0; i < kMaxHalf; ++i) {
                         if (i >= nh) break;
                         dma_run_next(asrc, a_off[i], (uint32_t)nload * 1024u);
+                        if constexpr (ORDER == kRowsPaced) asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15");
                     }
                 }
             };
-            if constexpr (ROWS_FIRST) load_rows();
+            if constexpr (ORDER == kRowsFirst) load_rows();
             if constexpr (PCB == CB) {
                 dma_run(wbytes, w_lane_off + (uint32_t)(s0 * (2 * CB) + wrank) * 1024u, (uint32_t)nload * 1024u,
                         slot_addr + (uint32_t)wrank * 1024u, (uint32_t)nload * 1024u, s_cnt == SPC ? nw_full : nw_last);
@@ -439,7 +443,7 @@ __global__ __launch_bounds__(64 * (NW + NL)) void gemm_kernel(const uint16_t* __
                             slot_addr + (uint32_t)u * 1024u, (uint32_t)(2 * CB) * 1024u, s_cnt);
                 }
             }
-            if constexpr (!NORM && !ROWS_FIRST) load_rows();  // NORM: the activations are resident
+            if constexpr (!NORM && ORDER != kRowsFirst) load_rows();  // NORM: the activations are resident
         };
 
         if constexpr (NORM) asm volatile("s_barrier" ::: "memory");  // the rows' loads are issued (see normalize_rows)
@@ -742,7 +746,7 @@ __global__ __launch_bounds__(256) void gemm_pack_kernel(const uint16_t* __restri
 // while it is shorter than the wait for the first weights (measured on the layer: 4 us gained at one row, 3 at
 // two, 1 at four, 3 lost at eight).
 constexpr int kNormRows = 4;
-template <int CB, int RINGB, int EPI, int NW, int NL, int PCB = CB, bool NORM = false, bool ROWS_FIRST = false>
+template <int CB, int RINGB, int EPI, int NW, int NL, int PCB = CB, bool NORM = false, int ORDER = kRowsBehind>
 static bool launch_gemm(const void* A, int lda, const void* Bp, void* C, int ldc, const void* R, int ldr,
                         const gemm_rope_args& ra, int M, int N, int K, int out_f32, hipStream_t s,
                         int tile_rows = 256, float eps = 0.0f)
@@ -753,7 +757,7 @@ static bool launch_gemm(const void* A, int lda, const void* Bp, void* C, int ldc
     const gemm_tile_plan tail = make_tile_plan(M - tile_rows * ((M - 1) / tile_rows), CB, RINGB, NW, NL, K, NORM);
     const gemm_tile_plan full = NORM ? tail : make_tile_plan(tile_rows, CB, RINGB, NW, NL, K);  // NORM: the one tile is the tail
     if (!plan_fits_load_counter(full, CB) || !plan_fits_load_counter(tail, CB)) return false;
-    hipLaunchKernelGGL((gemm_kernel<CB, RINGB, EPI, NW, NL, PCB, NORM, ROWS_FIRST>), grid, dim3(64 * (NW + NL)), 0, s,
+    hipLaunchKernelGGL((gemm_kernel<CB, RINGB, EPI, NW, NL, PCB, NORM, ORDER>), grid, dim3(64 * (NW + NL)), 0, s,
                        static_cast<const uint16_t*>(A), lda, static_cast<const uint4*>(Bp), C, ldc,
                        static_cast<const uint16_t*>(R), ldr, K, out_f32, full, tail, ra, eps);
     return true;
@@ -871,17 +875,24 @@ static gemm_tiling gemm_pick(int M, int N, int K, bool fixed)
     return {kGemmOwn, base_height};
 }
 
-// Whether a launch of M rows loads each chunk's rows in front of its weights (ROWS_FIRST).  Issued behind them, without the twenty
-// instructions a load that ragged rows once took, they made tiles of 48 to 112 columns 1 to 6 % slower than those had been.  Medians over
-// random shapes, behind and in front against then: 48 columns, 3, 5 or 6 half blocks 1.01 and 0.99; 64 columns, 8 to 12 half blocks
-// 1.00 and 0.985; 80 to 112 columns, 3 to 12 half blocks 1.01 and 0.99 (4096 x 15360 88 rows 32.5 us then, 34.4 behind, 32.5 in
-// front; 9216 x 12800 80 rows 58.1, 60.5, 58.1).  Elsewhere in front is level or slower (four half blocks of 48 columns 1 %,
-// 128 columns 1 to 2 %); 33 to 56 rows of 64 columns stay up to 5 % slower than then in either order, with K of 7000 and more.
-// A kernel of its own: with both orders in one, launches of other heights took 0.4 % longer.
-constexpr bool gemm_rows_first(int cb, int M)
+// How a launch of M rows loads each chunk's rows: behind its weights, in front of them, or behind them with 64 clocks between two loads.
+// Close behind one another and behind the weights, without the twenty instructions a load that ragged rows once took, they made
+// tiles of 48 to 112 columns 1 to 6 % slower than those had been (a compute unit takes a load in some 40 clocks, and the other
+// waves' weights queue with them).  Medians over random shapes, behind and in front against then: 48 columns, 3, 5 or 6 half blocks 1.01
+// and 0.99; 64 columns, 8 to 12 half blocks 1.00 and 0.985; 80 to 112 columns, 3 to 12 half blocks 1.01 and 0.99 (4096 x 15360 88
+// rows 32.5 us then, 34.4 behind, 32.5 in front; 9216 x 12800 80 rows 58.1, 60.5, 58.1).  64 columns, 5 to 7 half blocks, in either order
+// up to 5 % slower than then, spaced out level (13312 x 12288 48 rows 64.4, 67.6, 65.5; K of 8700 and more 1.03 and 1.015, 5 or 6 half
+// blocks, 1.02 and 0.99, 7; half the spacing mends half, twice as much costs 17 to 30 %).  Elsewhere behind is level or faster (in
+// front four half blocks of 48 columns 1 %, 128 columns 1 to 2 %; spaced out 5 or 6 half blocks of shorter K 1 %, more than 256
+// workgroups 3 to 7 %, 32 and 48 columns 5 to 15 %).
+// Kernels of their own: with both orders in one, launches of other heights took 0.4 % longer.
+constexpr int gemm_order(int cb, int M, int N, int K)
 {
     const int HB = (M + 7) / 8;
-    return cb < 8 && HB <= 12 && (cb >= 5 ? HB >= 3 : (cb == 4 ? HB >= 8 : cb == 3 && (HB == 3 || HB == 5 || HB == 6)));
+    if (cb < 3 || cb > 7 || HB > 12) return kRowsBehind;
+    if (cb == 3) return HB == 3 || HB == 5 || HB == 6 ? kRowsFirst : kRowsBehind;
+    if (cb == 4 && HB < 8) return N <= 64 * 256 && (HB == 7 || (HB >= 5 && K >= 5120)) ? kRowsPaced : kRowsBehind;
+    return cb == 4 || HB >= 3 ? kRowsFirst : kRowsBehind;
 }
 
 // Picks the kernel configuration (packing from N, tiling from M, N and K) and launches it.
@@ -929,8 +940,14 @@ static int gemm_dispatch(const void* A, int lda, const void* Bp, void* C, int ld
             }                                                                                               \
         }                                                                                                   \
         if constexpr (CBV >= 3) {                                                                           \
-            if (!fixed_tile && gemm_rows_first(CBV, M)) {                                                   \
-                ok = launch_gemm<CBV, kRingBig, EPI, gemm_waves(CBV), gemm_loader_waves(CBV, false), CBV, false, true>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, tile.rows); \
+            if (!fixed_tile && gemm_order(CBV, M, N, K) == kRowsFirst) {                                          \
+                ok = launch_gemm<CBV, kRingBig, EPI, gemm_waves(CBV), gemm_loader_waves(CBV, false), CBV, false, kRowsFirst>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, tile.rows); \
+                break;                                                                                      \
+            }                                                                                               \
+        }                                                                                                   \
+        if constexpr (CBV == 4) {                                                                           \
+            if (!fixed_tile && gemm_order(CBV, M, N, K) == kRowsPaced) {                                          \
+                ok = launch_gemm<CBV, kRingBig, EPI, gemm_waves(CBV), gemm_loader_waves(CBV, false), CBV, false, kRowsPaced>(A, lda, Bp, C, ldc, R, ldr, ra, M, N, K, f32, s, tile.rows); \
                 break;                                                                                      \
             }                                                                                               \
         }                                                                                                   \

@@ -95,8 +95,9 @@ def test_ragged_rows_whatever_the_split_of_the_loads(d, orc, M, N):
     assert np.array_equal(down_bf16(C), want)
 
 
-# Tiles of 48 to 112 columns whose rows are loaded in front of the weights, and the heights beside those
+# Tiles of 48 to 112 columns whose rows are loaded in front of the weights or spaced out, and the heights beside those
 @pytest.mark.parametrize("M,N", [(M, N) for N in (10752, 12800, 15360, 17920) for M in (16, 17, 56, 57, 64, 75, 96, 97)] +
+                         [(M, 10752) for M in (32, 33, 40, 47)] +
                          [(M, 9984) for M in (16, 23, 24, 25, 33, 48, 49)])
 def test_rows_loaded_in_front_of_the_weights(d, orc, M, N):
     test_ragged_rows_whatever_the_split_of_the_loads(d, orc, M, N)
