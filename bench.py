@@ -35,7 +35,7 @@ MS = [1, 2, 4, 8, 16, 32, 64, 128, 256]
 N_SETS = 3
 PEAK_MFMA_TFLOPS = 2500.0   # MI355X dense bf16
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
-DOMINANT = (4096, 28672)    # the launch that moves most of the step's bytes (gemm_kernel<8,144,0,8,4,8,false,false>)
+DOMINANT = (4096, 28672)    # the launch that moves most of the step's bytes (gemm_kernel<8,144,0,8,4,8,false,0>)
 LINE_BYTES = 4000
 LINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
              "dtype", "data", "config", "roofline", "fingerprint", "cpu_baseline", "bit_identical")
@@ -250,7 +250,7 @@ def main():
     dom_bytes = float(np.mean([gemm_bytes(M, DOMINANT[1], DOMINANT[0]) for M in MS]))
     dom_avg_ms = float(np.mean(dom_ms))
     achieved = dom_bytes / dom_avg_ms / 1e6
-    roofline = {"bound": "hbm", "kernel": "det::gemm_kernel<8,144,0,8,4,8,false,false> (K=4096, N=28672, M=1..256)",
+    roofline = {"bound": "hbm", "kernel": "det::gemm_kernel<8,144,0,8,4,8,false,0> (K=4096, N=28672, M=1..256)",
                 "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": round(achieved / PEAK_HBM_GBS, 4), "traffic": dominant_traffic_bytes(),
                 "avg_launch_us": round(dom_avg_ms * 1e3, 2), "bytes_per_launch": int(dom_bytes),

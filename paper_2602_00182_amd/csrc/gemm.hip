@@ -879,12 +879,13 @@ static gemm_tiling gemm_pick(int M, int N, int K, bool fixed)
 // Close behind one another and behind the weights, without the twenty instructions a load that ragged rows once took, they made
 // tiles of 48 to 112 columns 1 to 6 % slower than those had been (a compute unit takes a load in some 40 clocks, and the other
 // waves' weights queue with them).  Medians over random shapes, behind and in front against then: 48 columns, 3, 5 or 6 half blocks 1.01
-// and 0.99; 64 columns, 8 to 12 half blocks 1.00 and 0.985; 80 to 112 columns, 3 to 12 half blocks 1.01 and 0.99 (4096 x 15360 88
-// rows 32.5 us then, 34.4 behind, 32.5 in front; 9216 x 12800 80 rows 58.1, 60.5, 58.1).  64 columns, 5 to 7 half blocks, in either order
-// up to 5 % slower than then, spaced out level (13312 x 12288 48 rows 64.4, 67.6, 65.5; K of 8700 and more 1.03 and 1.015, 5 or 6 half
-// blocks, 1.02 and 0.99, 7; half the spacing mends half, twice as much costs 17 to 30 %).  Elsewhere behind is level or faster (in
-// front four half blocks of 48 columns 1 %, 128 columns 1 to 2 %; spaced out 5 or 6 half blocks of shorter K 1 %, more than 256
-// workgroups 3 to 7 %, 32 and 48 columns 5 to 15 %).
+// and 0.99; 64 columns, 8 half blocks 1.02 and 0.99; 80 to 112 columns, 3 to 12 half blocks 1.01 and 0.99 (4096 x 15360 88 rows 32.5 us
+// then, 34.4 behind, 32.5 in front; 9216 x 12800 80 rows 58.1, 60.5, 58.1).  64 columns, 9 to 12 half blocks: in front up to 2 % faster
+// for K up to 10880 (4352 x 12928 80 rows 29.7 -> 29.1), up to 4 % slower from 11904 on (12800 x 15808 95 rows 88.4 -> 91.6).
+// 64 columns, 5 to 7 half blocks, in either order up to 5 % slower than then, spaced out level (13312 x 12288 48 rows 64.4, 67.6, 65.5;
+// K of 8700 and more 1.03 and 1.015, 5 or 6 half blocks, 1.02 and 0.99, 7; half the spacing mends half, twice as much costs 17 to 30 %).
+// Elsewhere behind is level or faster (in front four half blocks of 48 columns 1 %, 128 columns 1 to 2 %; spaced out 5 or 6 half blocks
+// of shorter K 1 %, more than 256 workgroups 3 to 7 %, 32 and 48 columns 5 to 15 %).
 // Kernels of their own: with both orders in one, launches of other heights took 0.4 % longer.
 constexpr int gemm_order(int cb, int M, int N, int K)
 {
@@ -892,7 +893,8 @@ constexpr int gemm_order(int cb, int M, int N, int K)
     if (cb < 3 || cb > 7 || HB > 12) return kRowsBehind;
     if (cb == 3) return HB == 3 || HB == 5 || HB == 6 ? kRowsFirst : kRowsBehind;
     if (cb == 4 && HB < 8) return N <= 64 * 256 && (HB == 7 || (HB >= 5 && K >= 5120)) ? kRowsPaced : kRowsBehind;
-    return cb == 4 || HB >= 3 ? kRowsFirst : kRowsBehind;
+    if (cb == 4) return HB == 8 || K < 11520 ? kRowsFirst : kRowsBehind;
+    return HB >= 3 ? kRowsFirst : kRowsBehind;
 }
 
 // Picks the kernel configuration (packing from N, tiling from M, N and K) and launches it.

@@ -82,25 +82,29 @@ def test_ragged_rows_whatever_the_split_of_the_loads(d, orc, M, N):
     """Row counts around every split of a tile's half blocks over the loading waves, in the row-cut (N = 2048), two-workgroups-a-
     compute-unit (6224) and wide (11264) forms, and every pipeline of the 64-column tiles (4096 and 6144: tiles of 32 to 256
     rows), the rows behind the last one NaN: small integers, so exact."""
-    K = 64 * 11
+    check_small_integers(d, orc, M, N, 64 * 11)
+
+
+def check_small_integers(d, orc, M, N, K):
     A = ds.small_int_bf16(500 + M, (M, K))
     Bm = ds.small_int_bf16(600 + N, (K, N))
     want = orc.bf16_rne((ds.bf16_bits_to_f32(A) @ ds.bf16_bits_to_f32(Bm)).astype(np.float32))  # |sum| < 2^24: exact in fp32
     buf = torch.full((M + 16, K), float("nan"), dtype=torch.bfloat16, device=DEV)
     buf[:M] = up_bf16(A)
     C = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
-    step(f"gemm ragged M={M} N={N}")
+    step(f"gemm ragged M={M} N={N} K={K}")
     d.det_gemm_bf16(buf[:M], d.pack_weight(up_bf16(Bm)), C, N, K)
     torch.cuda.synchronize()
     assert np.array_equal(down_bf16(C), want)
 
 
-# Tiles of 48 to 112 columns whose rows are loaded in front of the weights or spaced out, and the heights beside those
-@pytest.mark.parametrize("M,N", [(M, N) for N in (10752, 12800, 15360, 17920) for M in (16, 17, 56, 57, 64, 75, 96, 97)] +
-                         [(M, 10752) for M in (32, 33, 40, 47)] +
-                         [(M, 9984) for M in (16, 23, 24, 25, 33, 48, 49)])
-def test_rows_loaded_in_front_of_the_weights(d, orc, M, N):
-    test_ragged_rows_whatever_the_split_of_the_loads(d, orc, M, N)
+# Tiles of 48 to 112 columns whose rows are loaded in front of the weights or spaced out, and the heights and depths beside those
+@pytest.mark.parametrize("M,N,K", [(M, N, 704) for N in (10752, 12800, 15360, 17920) for M in (16, 17, 56, 57, 64, 75, 96, 97)] +
+                         [(M, 9984, 704) for M in (16, 23, 24, 25, 33, 48, 49)] +
+                         [(M, 10752, K) for M in (32, 33, 40, 47, 49) for K in (5056, 5120)] + [(49, 16384, 704), (49, 16448, 704)] +
+                         [(M, 10752, 11520) for M in (64, 65)] + [(96, 10752, 11456)])
+def test_rows_loaded_in_front_of_the_weights(d, orc, M, N, K):
+    check_small_integers(d, orc, M, N, K)
 
 
 def test_rne_ties_and_identity(d, orc):
