@@ -41,7 +41,8 @@ __device__ __forceinline__ int wide_swizzle(int q) { return (0x78 >> (2 * q)) & 
 // step leaves a load one to two steps to land in instead of three to four, and where weights come from memory or a round is
 // not full that is too short.  129 launches that take them, K = 1024 to 14336, 1.3 % less time with half the barriers than with reads
 // and loads in a row, 29 of them more, up to 8 %; 2.9 % less with a barrier a step, none more (4096 x 28672 512 rows 122.3, 128.3, 118.7;
-// 4480 x 6400 2041 rows 113.4, 121.0, 110.5; full rounds lose 1 to 2 % of their gain, 4096 x 4096 4096 rows 119.9, 115.7, 117.6).
+// 4480 x 6400 2041 rows 113.4, 121.0, 110.5; rounds that are nearly full lose 1 to 4 % of their gain, 4096 x 4096 4096 rows 119.9, 115.7,
+// 117.6, 10752 x 8192 1656 rows 266, 252, 262).
 // Of 160-row tiles' 158 us the products alone take 115, and 133 with no
 // loads, 148 with no reads, 151 with no barriers, 155 with no wait for the loads: what is left is the fill, 26 KB a step at 43
 // bytes a ns, near what a compute unit gets of data that does not hit in L2 (50 to 55).
