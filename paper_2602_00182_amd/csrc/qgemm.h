@@ -1,0 +1,44 @@
+// Shared by the forms of the block-quantized GEMM (qgemm.hip, qgemm_few.hip).
+#pragma once
+
+#include "common.h"
+
+namespace det {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// The codes q of a column block's 64 k, stored as q + 8, two a byte, become 16*q as signed bytes (the nibble in the upper half
+// of a byte, its top bit flipped), and the matrix core sums 16*p*q from the bits of 786432, a float whose last place is worth
+// 1/16: read as a float the sum is 786432 + P, exactly (|P| <= 64 * 128 * 8), and one subtraction gives P.  Neither the +8 (which
+// took a matrix instruction more for every row block, or six vector instructions more a column block) nor the conversion to
+// floating point, which issues at half the rate of a subtraction, costs anything of its own.  us before and after: 1962 rows
+// 2048 x 11264 113 -> 102, 5632 x 2048 58 -> 52, 14336 x 4096 266 -> 245, 4096 x 28672 521 -> 465; 24 rows of 4096 x 28672
+// 22.7 -> 20.6, 128 rows of 14336 x 4096 77 -> 73, one row of 4096 x 28672 16.2 -> 15.2.
+constexpr v4i kProductStart = {0x49400000, 0x49400000, 0x49400000, 0x49400000};
+__device__ __forceinline__ float product(int sum) { return __int_as_float(sum) - 786432.0f; }
+__device__ __forceinline__ v4i code_bytes(const uint2& c)
+{
+    auto hi = [](uint32_t x) { return (int)((x & 0xF0F0F0F0u) ^ 0x80808080u); };
+    return v4i{hi(c.x << 4), hi(c.x), hi(c.y << 4), hi(c.y)};
+}
+
+// Bytes of a stage (64 k) of a packed slab of 16*cb columns: codes, then scales.
+__host__ __device__ constexpr int qstage_w_bytes(int cb) { return 544 * cb; }
+
+// Launches of a few rows (qgemm_few.hip).  x != nullptr: the rows are raw activations [M, K] (bf16), which the kernel normalizes
+// (RMSNorm with w_norm, eps) and quantizes itself; codes and scales are then not used.
+struct qgemm_few_args {
+    const void *codes, *scales, *wp;
+    void* C;
+    int ldc;
+    const void* R;
+    int ldr, M, N, K, out_f32;
+    gemm_rope_args ra;
+    const void *x, *w_norm;
+    float eps;
+};
+constexpr int kFewRows = 4;
+bool qgemm_few_fits(int M, int cb, int K, bool norm);
+void qgemm_few(int epi, int cb, const qgemm_few_args& a, hipStream_t s);
+
+}  // namespace det

@@ -18,31 +18,16 @@
 // w % CB, row blocks w / CB, w / CB + 8/CB, ...): at small M the work per stage is the unpacking of
 // the codes, which a single wave could not do at the rate the weights stream in.  Tiles of at most 8
 // rows and 2 column blocks go further and split the stages of a chunk over the waves (run_sp below):
-// only the accumulation chain has a defined order, and it keeps it.  Launches of more rows take tiles of 32
+// only the accumulation chain has a defined order, and it keeps it.  Launches of at most four rows have a kernel
+// of their own where their weights fit LDS (qgemm_few.hip).  Launches of more rows take tiles of 32
 // or 64 rows x 64 or 128 columns instead (qgemm_tile_kernel).
 #include <type_traits>
 
 #include "internal.h"
+#include "qgemm.h"
 #include "stream.h"
 
 namespace det {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-// The codes q of a column block's 64 k, stored as q + 8, two a byte, become 16*q as signed bytes (the nibble in the upper half
-// of a byte, its top bit flipped), and the matrix core sums 16*p*q from the bits of 786432, a float whose last place is worth
-// 1/16: read as a float the sum is 786432 + P, exactly (|P| <= 64 * 128 * 8), and one subtraction gives P.  Neither the +8 (which
-// took a matrix instruction more for every row block, or six vector instructions more a column block) nor the conversion to
-// floating point, which issues at half the rate of a subtraction, costs anything of its own.  us before and after: 1962 rows
-// 2048 x 11264 113 -> 102, 5632 x 2048 58 -> 52, 14336 x 4096 266 -> 245, 4096 x 28672 521 -> 465; 24 rows of 4096 x 28672
-// 22.7 -> 20.6, 128 rows of 14336 x 4096 77 -> 73, one row of 4096 x 28672 16.2 -> 15.2.
-constexpr v4i kProductStart = {0x49400000, 0x49400000, 0x49400000, 0x49400000};
-__device__ __forceinline__ float product(int sum) { return __int_as_float(sum) - 786432.0f; }
-__device__ __forceinline__ v4i code_bytes(const uint2& c)
-{
-    auto hi = [](uint32_t x) { return (int)((x & 0xF0F0F0F0u) ^ 0x80808080u); };
-    return v4i{hi(c.x << 4), hi(c.x), hi(c.y << 4), hi(c.y)};
-}
 
 constexpr int kQRing = 144;   // KB of LDS ring
 constexpr int kQWaves = 8;    // waves that can compute
@@ -57,8 +42,6 @@ int qgemm_cols_per_block(int N)
         if (nb % cb == 0 && nb / cb >= 160) return cb;
     return 1;
 }
-
-__host__ __device__ constexpr int qstage_w_bytes(int cb) { return 544 * cb; }
 
 // ------------------------------------------------------------------------------------------------
 // Weight quantizer + packer: one thread per (block b, column n).
@@ -934,6 +917,10 @@ static void launch_qgemm(const void* qa, const void* da, int ldd, const void* wp
                          int M, int N, int K, int out_f32, hipStream_t s, float* qscales_out = nullptr,
                          const gemm_rope_args& ra = gemm_rope_args{})
 {
+    if (EPI != kEpiSwigluQuant && qgemm_few_fits(M, CB, K, false)) {
+        qgemm_few(EPI, CB, qgemm_few_args{qa, da, wp, C, ldc, R, ldr, M, N, K, out_f32, ra, nullptr, nullptr, 0.0f}, s);
+        return;
+    }
     const qgemm_form form = qgemm_pick(M, N, CB);
     if (form == kQ64x128) {
         launch_qgemm_tile<CB, EPI, 4, 2>(qa, da, ldd, wp, C, ldc, R, ldr, M, N, K, out_f32, s, qscales_out, ra);
@@ -1143,10 +1130,10 @@ int det::qgemm_swiglu_quant(const void* codes, const void* scales, const void* p
     return check_launch();
 }
 
-extern "C" int det_qgemm_w4a8_qkv_rope_append(const void* codes, const void* scales, const void* packed_qkv, void* qbuf,
-                                              void* kcache, void* vcache, const int32_t* positions, const int32_t* slots,
-                                              const float* rope_cos, const float* rope_sin, int M, int Hq, int Hkv, int D,
-                                              int Lmax, int K, void* stream)
+// Arguments of the fused query/key/value projection; `codes` and `scales` only have to be aligned.
+static int qkv_args(const void* codes, const void* scales, const void* packed_qkv, void* qbuf, void* kcache, void* vcache,
+                    const int32_t* positions, const int32_t* slots, const float* rope_cos, const float* rope_sin, int M, int Hq,
+                    int Hkv, int D, int Lmax, int K, gemm_rope_args& ra)
 {
     if (Hq < 1 || Hkv < 1 || D != 128 || Lmax < 1) return DET_ESHAPE;
     const int N = (Hq + 2 * Hkv) * D;
@@ -1154,7 +1141,6 @@ extern "C" int det_qgemm_w4a8_qkv_rope_append(const void* codes, const void* sca
     if (rc != DET_OK) return rc;
     if (!kcache || !vcache || !positions || !rope_cos || !rope_sin) return DET_EINVAL;
     if (!aligned16(kcache) || !aligned16(vcache) || !aligned16(rope_cos) || !aligned16(rope_sin)) return DET_EALIGN;
-    gemm_rope_args ra;
     ra.pos = positions;
     ra.slots = slots;
     ra.cos_t = rope_cos;
@@ -1163,6 +1149,46 @@ extern "C" int det_qgemm_w4a8_qkv_rope_append(const void* codes, const void* sca
     ra.kcache = static_cast<uint16_t*>(kcache);
     ra.vcache = static_cast<uint16_t*>(vcache);
     ra.Hq = Hq, ra.Hkv = Hkv, ra.Lmax = Lmax;
-    return qgemm_dispatch<kEpiRopeAppend>(codes, scales, packed_qkv, qbuf, 4, nullptr, 0, M, N, K, 0,
+    return DET_OK;
+}
+
+extern "C" int det_qgemm_w4a8_qkv_rope_append(const void* codes, const void* scales, const void* packed_qkv, void* qbuf,
+                                              void* kcache, void* vcache, const int32_t* positions, const int32_t* slots,
+                                              const float* rope_cos, const float* rope_sin, int M, int Hq, int Hkv, int D,
+                                              int Lmax, int K, void* stream)
+{
+    gemm_rope_args ra;
+    const int rc = qkv_args(codes, scales, packed_qkv, qbuf, kcache, vcache, positions, slots, rope_cos, rope_sin, M, Hq, Hkv, D, Lmax, K, ra);
+    if (rc != DET_OK) return rc;
+    return qgemm_dispatch<kEpiRopeAppend>(codes, scales, packed_qkv, qbuf, 4, nullptr, 0, M, (Hq + 2 * Hkv) * D, K, 0,
                                           static_cast<hipStream_t>(stream), ra);
+}
+
+// The projections behind an RMSNorm on raw rows x [M, K], where one launch does it all (the decoder layer's own calls).
+bool det::qgemm_norm_fits(int M, int N, int K)
+{
+    return M > 0 && qgemm_shape_ok(N, K) && qgemm_few_fits(M, qgemm_cols_per_block(N), K, true);
+}
+int det::qgemm_norm_qkv_rope_append(const void* x, const void* w_norm, float eps, const void* packed_qkv, void* qbuf, void* kcache,
+                                    void* vcache, const int32_t* positions, const int32_t* slots, const float* rope_cos,
+                                    const float* rope_sin, int M, int Hq, int Hkv, int D, int Lmax, int K, void* stream)
+{
+    gemm_rope_args ra;
+    const int rc = qkv_args(x, w_norm, packed_qkv, qbuf, kcache, vcache, positions, slots, rope_cos, rope_sin, M, Hq, Hkv, D, Lmax, K, ra);
+    if (rc != DET_OK) return rc;
+    const int N = (Hq + 2 * Hkv) * D;
+    qgemm_few(kEpiRopeAppend, qgemm_cols_per_block(N),
+              qgemm_few_args{nullptr, nullptr, packed_qkv, qbuf, 4, nullptr, 0, M, N, K, 0, ra, x, w_norm, eps},
+              static_cast<hipStream_t>(stream));
+    return check_launch();
+}
+int det::qgemm_norm_swiglu(const void* x, const void* w_norm, float eps, const void* packed_gate_up, void* Y, int ldy, int M, int F,
+                           int K, void* stream)
+{
+    const int rc = qgemm_args_ok(x, w_norm, packed_gate_up, Y, ldy, M, 2 * F, F, K);
+    if (rc != DET_OK) return rc;
+    qgemm_few(kEpiSwiglu, qgemm_cols_per_block(2 * F),
+              qgemm_few_args{nullptr, nullptr, packed_gate_up, Y, ldy, nullptr, 0, M, 2 * F, K, 0, gemm_rope_args{}, x, w_norm, eps},
+              static_cast<hipStream_t>(stream));
+    return check_launch();
 }

@@ -46,33 +46,13 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint4* __restrict__ 
         const int v = threadIdx.x + i * 256;
         if (v < nvec) {
             const uint4 yv = rms_apply(xv[i], wv[i], r);
-            const uint32_t o[4] = {yv.x, yv.y, yv.z, yv.w};
             if constexpr (!QUANT) {
                 yr[v] = yv;
             } else {
-                float a[8];
-                float amax = 0.0f;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    a[2 * k] = bf16lo_to_f32(o[k]);
-                    a[2 * k + 1] = bf16hi_to_f32(o[k]);
-                    amax = fmaxf(amax, fmaxf(fabsf(a[2 * k]), fabsf(a[2 * k + 1])));
-                }
                 // H % 64 == 0: the eight threads of a block are all here or all absent
-                amax = fmaxf(amax, __shfl_xor(amax, 1, kWave));
-                amax = fmaxf(amax, __shfl_xor(amax, 2, kWave));
-                amax = fmaxf(amax, __shfl_xor(amax, 4, kWave));
-                const float df = amax / 127.0f;
-                uint32_t c[2] = {0u, 0u};
-                if (df != 0.0f) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const float q = rintf(a[k] / df);
-                        const int iv = q < -127.0f ? -127 : (q > 127.0f ? 127 : (int)q);
-                        c[k >> 2] |= (uint32_t)(iv & 0xFF) << (8 * (k & 3));
-                    }
-                }
-                *reinterpret_cast<uint2*>(codes + (size_t)blockIdx.x * H + 8 * (size_t)v) = make_uint2(c[0], c[1]);
+                float df;
+                const uint2 c = quant_vector_q8(yv, df);
+                *reinterpret_cast<uint2*>(codes + (size_t)blockIdx.x * H + 8 * (size_t)v) = c;
                 if ((threadIdx.x & 7) == 0) scales[(size_t)(v >> 3) * ldd + blockIdx.x] = df;
             }
         }

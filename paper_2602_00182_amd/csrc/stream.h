@@ -114,6 +114,27 @@ __device__ __forceinline__ void wait_loads_then_barrier(int n)
         :
         : "memory", "scc", "s98", "s99");
 }
+// The wait alone.
+__device__ __forceinline__ void wait_loads(int n)
+{
+    uint32_t off = (uint32_t)(n > 62 ? 0 : n) << 3;
+    asm volatile(
+        "s_getpc_b64 s[98:99]\n"
+        ".Ldet_wbase%=:\n\t"
+        "s_add_u32 %0, %0, .Ldet_wtab%=-.Ldet_wbase%=\n\t"
+        "s_add_u32 s98, s98, %0\n\t"
+        "s_addc_u32 s99, s99, 0\n\t"
+        "s_setpc_b64 s[98:99]\n"
+        ".Ldet_wtab%=:\n\t"
+        DET_W8(0, 1, 2, 3, 4, 5, 6, 7) DET_W8(8, 9, 10, 11, 12, 13, 14, 15)
+        DET_W8(16, 17, 18, 19, 20, 21, 22, 23) DET_W8(24, 25, 26, 27, 28, 29, 30, 31)
+        DET_W8(32, 33, 34, 35, 36, 37, 38, 39) DET_W8(40, 41, 42, 43, 44, 45, 46, 47)
+        DET_W8(48, 49, 50, 51, 52, 53, 54, 55) DET_W8(56, 57, 58, 59, 60, 61, 62, 63)
+        ".Ldet_wend%=:"
+        : "+s"(off)
+        :
+        : "memory", "scc", "s98", "s99");
+}
 #undef DET_W8
 #undef DET_W1
 
