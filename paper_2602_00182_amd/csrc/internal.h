@@ -31,6 +31,9 @@ bool qgemm_norm_fits(int M, int N, int K);
 int qgemm_norm_qkv_rope_append(const void* x, const void* w_norm, float eps, const void* packed_qkv, void* qbuf, void* kcache,
                                void* vcache, const int32_t* positions, const int32_t* slots, const float* rope_cos,
                                const float* rope_sin, int M, int Hq, int Hkv, int D, int Lmax, int K, void* stream);
+bool qgemm_norm_swiglu_quant_fits(int M, int F, int K);
+int qgemm_norm_swiglu_quant(const void* x, const void* w_norm, float eps, const void* packed_gate_up, void* codes_out,
+                            void* scales_out, int M, int F, int K, void* stream);
 int qgemm_norm_swiglu(const void* x, const void* w_norm, float eps, const void* packed_gate_up, void* Y, int ldy, int M, int F, int K,
                       void* stream);
 

@@ -165,18 +165,30 @@ extern "C" int det_qdecoder_layer(const det_layer_weights* w, const det_layer_cf
         rc = (call);                 \
         if (rc != DET_OK) return rc; \
     } while (0)
-    DET_TRY(det_rmsnorm_quant_q8(x_inout, w->w_norm1, codes, scales, R, c.H, c.eps, stream));
-    DET_TRY(det_qgemm_w4a8_qkv_rope_append(codes, scales, w->wqkv, qbuf, kcache, vcache, positions, slots, rope_cos,
-                                           rope_sin, R, c.Hq, c.Hkv, c.D, c.Lmax, c.H, stream));
+    if (qgemm_norm_fits(R, (c.Hq + 2 * c.Hkv) * c.D, c.H)) {
+        DET_TRY(qgemm_norm_qkv_rope_append(x_inout, w->w_norm1, c.eps, w->wqkv, qbuf, kcache, vcache, positions, slots,
+                                           rope_cos, rope_sin, R, c.Hq, c.Hkv, c.D, c.Lmax, c.H, stream));
+    } else {
+        DET_TRY(det_rmsnorm_quant_q8(x_inout, w->w_norm1, codes, scales, R, c.H, c.eps, stream));
+        DET_TRY(det_qgemm_w4a8_qkv_rope_append(codes, scales, w->wqkv, qbuf, kcache, vcache, positions, slots, rope_cos,
+                                               rope_sin, R, c.Hq, c.Hkv, c.D, c.Lmax, c.H, stream));
+    }
     DET_TRY(attn_decode_impl(qbuf, kcache, vcache, positions, slots, 1, codes, aws, l.attn_bytes, R, c.Hq, c.Hkv, c.D,
                              c.Lmax, c.scale, s, scales));
     DET_TRY(det_qgemm_w4a8_residual(codes, scales, w->wo, x_inout, c.H, x_inout, c.H, R, c.H, nq, stream));
-    DET_TRY(det_rmsnorm_quant_q8(x_inout, w->w_norm2, codes, scales, R, c.H, c.eps, stream));
-    if (qgemm_swiglu_quant_fits(R, c.F, c.H)) {
-        DET_TRY(qgemm_swiglu_quant(codes, scales, w->wgu, codes2, scales2, R, c.F, c.H, stream));
-    } else {
-        DET_TRY(det_qgemm_w4a8_swiglu(codes, scales, w->wgu, mm, c.F, R, c.F, c.H, stream));
+    if (qgemm_norm_swiglu_quant_fits(R, c.F, c.H)) {
+        DET_TRY(qgemm_norm_swiglu_quant(x_inout, w->w_norm2, c.eps, w->wgu, codes2, scales2, R, c.F, c.H, stream));
+    } else if (qgemm_norm_fits(R, 2 * c.F, c.H)) {
+        DET_TRY(qgemm_norm_swiglu(x_inout, w->w_norm2, c.eps, w->wgu, mm, c.F, R, c.F, c.H, stream));
         DET_TRY(det_quant_act_q8(mm, c.F, codes2, scales2, R, c.F, stream));
+    } else {
+        DET_TRY(det_rmsnorm_quant_q8(x_inout, w->w_norm2, codes, scales, R, c.H, c.eps, stream));
+        if (qgemm_swiglu_quant_fits(R, c.F, c.H)) {
+            DET_TRY(qgemm_swiglu_quant(codes, scales, w->wgu, codes2, scales2, R, c.F, c.H, stream));
+        } else {
+            DET_TRY(det_qgemm_w4a8_swiglu(codes, scales, w->wgu, mm, c.F, R, c.F, c.H, stream));
+            DET_TRY(det_quant_act_q8(mm, c.F, codes2, scales2, R, c.F, stream));
+        }
     }
     DET_TRY(det_qgemm_w4a8_residual(codes2, scales2, w->wdown, x_inout, c.H, x_inout, c.H, R, c.H, c.F, stream));
 #undef DET_TRY

@@ -22,11 +22,28 @@ __device__ __forceinline__ v4i code_bytes(const uint2& c)
     return v4i{hi(c.x << 4), hi(c.x), hi(c.y << 4), hi(c.y)};
 }
 
+// Counters in LDS by which the waves of a workgroup tell each other what is done.  LDS serves a wave's instructions in order.
+__device__ __forceinline__ void publish(int* counter, int value)
+{
+    if ((threadIdx.x & 63) == 0) *const_cast<volatile int*>(counter) = value;
+}
+// Waits until lane i < n finds counters[i] at its `need` or above.
+__device__ __forceinline__ void await(const int* counters, int n, int need)
+{
+    const int lane = threadIdx.x & 63;
+    for (;;) {
+        const int have = lane < n ? *const_cast<const volatile int*>(&counters[lane]) : 0x7FFFFFFF;
+        if (__ballot(have < need) == 0) break;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    asm volatile("" ::: "memory");
+}
+
 // Bytes of a stage (64 k) of a packed slab of 16*cb columns: codes, then scales.
 __host__ __device__ constexpr int qstage_w_bytes(int cb) { return 544 * cb; }
 
 // Launches of a few rows (qgemm_few.hip).  x != nullptr: the rows are raw activations [M, K] (bf16), which the kernel normalizes
-// (RMSNorm with w_norm, eps) and quantizes itself; codes and scales are then not used.
+// (RMSNorm with w_norm, eps) and quantizes itself (kEpiSwiglu and kEpiRopeAppend only); codes and scales are then not used.
 struct qgemm_few_args {
     const void *codes, *scales, *wp;
     void* C;

@@ -166,7 +166,8 @@ static int q_wrun_bytes(int s_cnt, int cb) { return (s_cnt * qstage_w_bytes(cb) 
 
 static int up1k(int n) { return (n + 1023) & ~1023; }
 
-static qgemm_plan make_qgemm_plan(int mrem, int cb, int K)
+// resident: LDS bytes at the end of the ring that hold all activations (the normalizing form); chunks are weights only then
+static qgemm_plan make_qgemm_plan(int mrem, int cb, int K, int resident = 0)
 {
     qgemm_plan t;
     t.mrem = mrem;
@@ -174,7 +175,10 @@ static qgemm_plan make_qgemm_plan(int mrem, int cb, int K)
     t.tile_bytes = t.RB == 1 ? (mrem <= 4 ? 256 : (mrem <= 8 ? 512 : 1024)) : 1024;
     t.inv_4rb = (1u << 20) / (uint32_t)(4 * t.RB) + 1u;
     // bytes of a chunk of spc stages: weight run, activation tiles, activation scales, each rounded up to 1 KB
-    auto chunk_bytes = [&](int spc) { return q_wrun_bytes(spc, cb) + up1k(spc * t.RB * t.tile_bytes) + up1k(spc * t.RB * 64); };
+    auto chunk_bytes = [&](int spc) {
+        return q_wrun_bytes(spc, cb) + (resident ? 0 : up1k(spc * t.RB * t.tile_bytes) + up1k(spc * t.RB * 64));
+    };
+    const int ring_bytes = kQRing * 1024 - resident;
     const int nstages = K >> 6;
     const int rg = 8 / cb;
     t.nrg = rg < t.RB ? rg : t.RB;
@@ -191,10 +195,10 @@ static qgemm_plan make_qgemm_plan(int mrem, int cb, int K)
         t.nslots = 4;
         t.res_off = 4 * t.slot_bytes;
     } else {
-        const int third = kQRing * 1024 / 3;  // the most stages whose chunk fits a third of the ring
+        const int third = ring_bytes / 3;  // the most stages whose chunk fits a third of the ring
         while (chunk_bytes(t.SPC + 1) <= third) ++t.SPC;
         t.slot_bytes = chunk_bytes(t.SPC);
-        t.nslots = kQRing * 1024 / t.slot_bytes < 4 ? kQRing * 1024 / t.slot_bytes : 4;
+        t.nslots = ring_bytes / t.slot_bytes < 4 ? ring_bytes / t.slot_bytes : 4;
     }
     t.nchunks = (nstages + t.SPC - 1) / t.SPC;
     t.last_cnt = nstages - (t.nchunks - 1) * t.SPC;
@@ -208,13 +212,19 @@ static qgemm_plan make_qgemm_plan(int mrem, int cb, int K)
 
 // EPI: the epilogues of the bf16 kernel (plain store, residual add, SwiGLU on gate/up-interleaved columns),
 // applied to the accumulator rounded to bf16, so each gives the bytes of the unfused sequence.
-template <int CB, int EPI>
+// NORM (one tile of at most kFewRows rows, 128-column packings): the rows are raw activations x, which the computing waves normalize
+// and quantize while the first weights are on their way (as in qgemm_few.hip, which such packings are too wide for); they stay in
+// LDS, [stage][row][64] and [stage][4], and the ring in front of them carries weights only.
+template <int CB, int EPI, bool NORM = false>
 __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
     const int8_t* __restrict__ qa, int K, const float* __restrict__ da, int ldd, const uint8_t* __restrict__ wp, void* C,
     int ldc, const uint16_t* R, int ldr, int out_f32, qgemm_plan plan_full, qgemm_plan plan_tail, float* qscales_out,
-    gemm_rope_args ra)
+    gemm_rope_args ra, const uint4* __restrict__ x, const uint4* __restrict__ w_norm, float eps)
 {
+    static_assert(!NORM || CB == 8, "every computing wave has the tile's row block");
     __shared__ uint4 ring[kQRing * 64];
+    __shared__ float norm_part[NORM ? 4 * kFewRows : 1];
+    __shared__ int normed;
     __shared__ float rowmax[EPI == kEpiSwigluQuant ? 8 * 256 : 1];  // row maxima of the eight waves, that epilogue only
     static_assert(EPI != kEpiSwigluQuant || CB == 8, "a 128-column tile holds one 64-output block per row");
     constexpr int RG = 8 / CB;        // row groups: wave w computes column block w % CB for row group w / CB
@@ -255,8 +265,8 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
         const uint32_t a_lane_off = (uint32_t)lrow * (uint32_t)K + 16u * (uint32_t)((lane & 3) ^ ((lane >> 4) & 3));
         auto strided = [&](int n) { return n > lrank ? (int)(((uint32_t)(n - lrank + nload - 1) * tp.inv_nload) >> 20) : 0; };
         auto loads_for = [&](int s_cnt) {
-            return strided((int)(wrun(s_cnt) >> 10)) + strided((int)(abytes_of(s_cnt) >> 10)) +
-                   strided((int)(sbytes_of(s_cnt) >> 10));
+            return strided((int)(wrun(s_cnt) >> 10)) +
+                   (NORM ? 0 : strided((int)(abytes_of(s_cnt) >> 10)) + strided((int)(sbytes_of(s_cnt) >> 10)));
         };
         // short tiles: a load covers 1024/TB stages; lane -> (stage lane/(TB/16), row (lane/4) % (TB/64), piece lane%4)
         const int srow = (lane >> 2) & ((TB >> 6) - 1);
@@ -284,6 +294,7 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
                 const uint32_t off = (uint32_t)nfull << 10;
                 if (off + lane16 < wlen) dma_block(wsrc + off, lane16, slot_addr + off);
             }
+            if constexpr (NORM) return;
             // activation tiles; rows past M load nothing
             const uint32_t tiles = slot_addr + wrun(s_cnt);
             if (TB == 1024) {  // unit (stage, row block)
@@ -323,6 +334,7 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
             }
         };
 
+        if constexpr (NORM) asm volatile("s_barrier" ::: "memory");  // the rows' loads are issued: the memory pipe returns loads in order
         for (int c = 0; c < P; ++c) load_chunk(c, c);
         const int younger_steady = (P - 1) * loads_full;
         int slot_c = 0, slot_new = P;
@@ -474,6 +486,58 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
         return;
     }
 
+    char* const xres = reinterpret_cast<char*>(ring) + kQRing * 1024 - nstages * (64 * mrem + 16);  // NORM: codes, then scales
+    char* const dres = xres + nstages * 64 * mrem;
+    const int lrow = min(lr, mrem - 1);
+    if constexpr (NORM) {
+        // A team of four waves is the 256 threads of rmsnorm_kernel, thread t with the vectors t and t + 256 of a row; team i
+        // takes the rows i, i + 2.
+        const int team = wave >> 2, vt = tid & 255, nvec = K >> 3;
+        uint4 wv[2], xv[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (vt + 256 * i < nvec) wv[i] = w_norm[vt + 256 * i];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (team + 2 * u < mrem && vt + 256 * i < nvec) xv[u][i] = x[(size_t)(team + 2 * u) * nvec + vt + 256 * i];
+        if (tid == 0) normed = 0;
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (team + 2 * u >= mrem) continue;
+            float ss = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (vt + 256 * i < nvec) ss = rms_fold(xv[u][i], ss);
+            ss = wave_tree_sum(ss);
+            if (lane == 0) norm_part[4 * (team + 2 * u) + (wave & 3)] = ss;
+        }
+        // the eight computing waves meet (the loading ones are not waited for)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (lane == 0) atomicAdd(&normed, 1);
+        await(&normed, 1, kQWaves);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int row = team + 2 * u;
+            if (row >= mrem) continue;
+            const float a = norm_part[4 * row] + norm_part[4 * row + 2], b = norm_part[4 * row + 1] + norm_part[4 * row + 3];
+            const float rs = rms_scale(a + b, K, eps);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int v = vt + 256 * i;
+                if (v < nvec) {
+                    float df;
+                    const uint2 c = quant_vector_q8(rms_apply(xv[u][i], wv[i], rs), df);
+                    *reinterpret_cast<uint2*>(xres + ((v >> 3) * mrem + row) * 64 + 8 * (v & 7)) = c;
+                    if ((lane & 7) == 0) *reinterpret_cast<float*>(dres + 16 * (v >> 3) + 4 * row) = df;
+                }
+            }
+        }
+        // (published by the barrier that opens the first chunk)
+    }
+
     auto run = [&](auto nr_tag) {
         constexpr int NR = decltype(nr_tag)::value;  // cnt rounded up to a power of two; the surplus
                                                      // repeats the last row block and is not stored
@@ -519,10 +583,15 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
                     for (int u = 0; u < UU; ++u)
 #pragma unroll
                         for (int r = 0; r < G; ++r) {
-                            const v4i xa = *reinterpret_cast<const v4i*>(tiles + (size_t)((sl + u) * RB + rbs[r0 + r]) * TB +
-                                                                         64 * lrc + 16 * (g ^ ((lrc >> 2) & 3)));
-                            dv[u][r] = *reinterpret_cast<const float*>(scales + (size_t)(sl + u) * RB * 64 +
-                                                                       (16 * rbs[r0 + r] + lr) * 4);
+                            const char* xp = tiles + (size_t)((sl + u) * RB + rbs[r0 + r]) * TB + 64 * lrc + 16 * (g ^ ((lrc >> 2) & 3));
+                            const char* dp = scales + (size_t)(sl + u) * RB * 64 + (16 * rbs[r0 + r] + lr) * 4;
+                            if constexpr (NORM) {
+                                const int st = c * SPC + sl + u;
+                                xp = xres + (st * mrem + lrow) * 64 + 16 * g;
+                                dp = dres + 16 * st + 4 * lrow;
+                            }
+                            const v4i xa = *reinterpret_cast<const v4i*>(xp);
+                            dv[u][r] = *reinterpret_cast<const float*>(dp);
                             pr[u][r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wq[u], xa, kProductStart, 0, 0, 0);
                         }
 #pragma unroll
@@ -602,8 +671,9 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
         }
     };
     // the weight codes of a stage are expanded once per wave whatever the number of row blocks
-    if (cnt == 1) {
+    if (NORM || cnt == 1) {
         run(std::integral_constant<int, 1>{});
+        if constexpr (NORM) return;
     } else if (cnt == 2) {
         run(std::integral_constant<int, 2>{});
     } else if (MAXR >= 4 && cnt <= 4) {
@@ -942,7 +1012,7 @@ static void launch_qgemm(const void* qa, const void* da, int ldd, const void* wp
     const qgemm_plan tail = make_qgemm_plan(M - tile_rows * ((M - 1) / tile_rows), CB, K);
     hipLaunchKernelGGL((qgemm_kernel<CB, EPI>), grid, dim3(64 * (kQWaves + kQLoaders)), 0, s,
                        static_cast<const int8_t*>(qa), K, static_cast<const float*>(da), ldd, static_cast<const uint8_t*>(wp),
-                       C, ldc, static_cast<const uint16_t*>(R), ldr, out_f32, full, tail, qscales_out, ra);
+                       C, ldc, static_cast<const uint16_t*>(R), ldr, out_f32, full, tail, qscales_out, ra, nullptr, nullptr, 0.0f);
 }
 
 // N: columns of the packed matrix (2F for the SwiGLU epilogue).
@@ -1180,6 +1250,24 @@ int det::qgemm_norm_qkv_rope_append(const void* x, const void* w_norm, float eps
     qgemm_few(kEpiRopeAppend, qgemm_cols_per_block(N),
               qgemm_few_args{nullptr, nullptr, packed_qkv, qbuf, 4, nullptr, 0, M, N, K, 0, ra, x, w_norm, eps},
               static_cast<hipStream_t>(stream));
+    return check_launch();
+}
+bool det::qgemm_norm_swiglu_quant_fits(int M, int F, int K)
+{
+    return M > 0 && M <= kFewRows && K <= 4096 && F % 64 == 0 && det_qgemm_w4a8_swiglu_quant_supported(F, K);
+}
+int det::qgemm_norm_swiglu_quant(const void* x, const void* w_norm, float eps, const void* packed_gate_up, void* codes_out,
+                                 void* scales_out, int M, int F, int K, void* stream)
+{
+    const int rc = qgemm_args_ok(x, w_norm, packed_gate_up, codes_out, F, M, 2 * F, F, K);
+    if (rc != DET_OK) return rc;
+    if (!scales_out) return DET_EINVAL;
+    if (!aligned16(scales_out)) return DET_EALIGN;
+    const qgemm_plan plan = make_qgemm_plan(M, 8, K, (K >> 6) * (64 * M + 16));
+    hipLaunchKernelGGL((qgemm_kernel<8, kEpiSwigluQuant, true>), dim3(2 * F / 128), dim3(64 * (kQWaves + kQLoaders)), 0,
+                       static_cast<hipStream_t>(stream), nullptr, K, nullptr, 0, static_cast<const uint8_t*>(packed_gate_up), codes_out,
+                       F, nullptr, q_ldd(M), 0, plan, plan, static_cast<float*>(scales_out), gemm_rope_args{},
+                       static_cast<const uint4*>(x), static_cast<const uint4*>(w_norm), eps);
     return check_launch();
 }
 int det::qgemm_norm_swiglu(const void* x, const void* w_norm, float eps, const void* packed_gate_up, void* Y, int ldy, int M, int F,

@@ -12,30 +12,17 @@ namespace {
 constexpr int kProducers = 8;
 constexpr int kBatch = 4;        // blocks of K a producer takes at a time: their activations are the sixteen columns of one operand
 constexpr int kFewLds = 158 * 1024, kFewLdsHalf = 79 * 1024;
-constexpr int kFewNormK = 4096;  // longest rows that are normalized here: two vectors of eight a thread
+// The rows that are normalized here: two vectors of eight a thread, and up to three of them.  Every workgroup does it again, which is
+// hidden by the wait for the first weights while it is short.  Quantized layer at a context of 512 with the norms' own launches, and
+// without, us: small model 40.4 and 37.4 at one row, 40.9 and 38.5 at two, 41.3 and 40.0 at three, 42.2 and 42.5 at four; hidden
+// 4096 (of its two norms one is in qgemm.hip's kernel, which gains at four too) 59.3 and 52.3, 58.3 and 52.7, 62.7 and 59.7, 63.5 and 63.3.
+constexpr int kFewNormK = 4096, kFewNormRows = 3;
 
 // LDS: the packed weights as they lie in memory, activation codes [block][row][64], scales [block][4] and, with the norm, the rows
 // as they come and the norm's weight.
 __host__ __device__ constexpr int few_lds_bytes(int M, int cb, int K, bool norm)
 {
     return (K >> 6) * (qstage_w_bytes(cb) + 16) + M * K + (norm ? (M + 1) * 2 * K : 0);
-}
-
-// Counters in LDS by which the waves of a workgroup tell each other what is done.  LDS serves a wave's instructions in order.
-__device__ __forceinline__ void publish(int* counter, int value)
-{
-    if ((threadIdx.x & 63) == 0) *const_cast<volatile int*>(counter) = value;
-}
-// Waits until lane i < n finds counters[i] at its `need` or above.
-__device__ __forceinline__ void await(const int* counters, int n, int need)
-{
-    const int lane = threadIdx.x & 63;
-    for (;;) {
-        const int have = lane < n ? *const_cast<const volatile int*>(&counters[lane]) : 0x7FFFFFFF;
-        if (__ballot(have < need) == 0) break;
-        __builtin_amdgcn_s_sleep(1);
-    }
-    asm volatile("" ::: "memory");
 }
 
 }  // namespace
@@ -280,7 +267,7 @@ void launch_epi(int epi, const qgemm_few_args& a, hipStream_t s)
 
 bool qgemm_few_fits(int M, int cb, int K, bool norm)
 {
-    return M <= kFewRows && cb <= 4 && K <= (norm ? kFewNormK : 32768) && few_lds_bytes(M, cb, K, norm) <= kFewLds;
+    return M <= (norm ? kFewNormRows : kFewRows) && cb <= 4 && K <= (norm ? kFewNormK : 32768) && few_lds_bytes(M, cb, K, norm) <= kFewLds;
 }
 
 void qgemm_few(int epi, int cb, const qgemm_few_args& a, hipStream_t s)

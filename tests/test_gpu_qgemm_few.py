@@ -70,3 +70,32 @@ def test_epilogues_equal_unfused_bytes(d, orc, M, K, N):
     torch.cuda.synchronize()
     assert np.array_equal(down_bf16(wide[:, :N].contiguous()), orc.residual(r, plain)) and torch.isnan(wide[:, N:]).all()
     assert np.array_equal(down_bf16(y), down_bf16(want))
+
+
+# hidden and inner sizes: rows of less than one and of two vectors a thread, and one too long to be normalized in the projection;
+# gate/up packings of 16, 64 and 128 columns (the last with its output quantized in the projection), down projections that fit or not
+@pytest.mark.parametrize("H,F,Hq,Hkv", [(192, 10240, 2, 1), (1984, 704, 4, 2), (2048, 5632, 16, 4), (4096, 14336, 32, 8), (4160, 1088, 8, 8)])
+def test_layer_of_few_rows_equals_the_larger_batch(d, H, F, Hq, Hkv):
+    """Up to four rows the layer normalizes and quantizes inside the projections; six rows take launches of their own for it."""
+    Lmax, D, s = 300, 128, ds.tensor_seed(6, 710) + H
+    n = lambda i, shape, std, mean=0.0: ds.normal_bf16_torch(s + i, shape, std, mean, DEV)
+    w = d.layer_weights(n(0, (H,), 0.1, 1.0), d.quant_pack_qkv(n(1, (H, (Hq + 2 * Hkv) * D), 0.02), Hq, Hkv, D), d.quant_pack_weight(n(2, (Hq * D, H), 0.02)),
+                        n(3, (H,), 0.1, 1.0), d.quant_pack_gate_up(n(4, (H, 2 * F), 0.02)), d.quant_pack_weight(n(5, (F, H), 0.02)))
+    cfg = d.layer_cfg(H, Hq, Hkv, D, F, Lmax, 1e-5, float(np.float32(D ** -0.5)))
+    cos, sin = (torch.from_numpy(t).to(DEV) for t in ds.rope_tables(Lmax, D))
+    pos = torch.tensor([299, 0, 130, 255, 256, 7], dtype=torch.int32, device=DEV)
+    x, k, v = n(6, (6, H), 1.0), n(7, (6, Hkv, Lmax, D), 1.0), n(8, (6, Hkv, Lmax, D), 1.0)
+    x[1] = 0  # scales that are zero
+
+    def run(R):
+        xr, kr, vr = x[:R].clone(), k[:R].clone(), v[:R].clone()
+        ws = torch.full((d.det_qdecoder_layer_workspace_bytes(cfg, R),), 0xFF, dtype=torch.uint8, device=DEV)
+        step(f"quantized layer H={H} F={F} rows={R}")
+        d.det_qdecoder_layer(w, cfg, xr, kr, vr, pos[:R].contiguous(), None, cos, sin, ws)
+        torch.cuda.synchronize()
+        return [down_bf16(t) for t in (xr, kr, vr)]
+
+    full = run(6)
+    for R in (1, 2, 3, 4):
+        for got, want in zip(run(R), full):
+            assert np.array_equal(got, want[:R]), R
