@@ -231,9 +231,8 @@ int det_attn_decode_static(const void *q, const void *kcache, const void *vcache
                            void *out, int B, int Hq, int Hkv, int D, int Lmax, float scale, void *stream);
 
 /* Test hook: the softmax statistics of det_attn_decode on caller-provided fp32 scores.  The per-chunk
- * statistics (m_c, e_j, l_c) come from the device routine that the attention of larger decode launches and of
- * eight rows a workgroup calls; small decode launches and calls of many rows compute them in the same order with code
- * of their own, which the tests hold to those bytes.  The combination over chunks is the same ascending fold, written
+ * statistics (m_c, e_j, l_c) come from the device routine that the attention of eight rows a workgroup calls;
+ * decode and calls of many rows compute them in the same order with code of their own, which the tests hold to those bytes.  The combination over chunks is the same ascending fold, written
  * for one row per workgroup.
  * s, p [R, Lmax] fp32; lens [R]; m_out, l_out [R] fp32.
  * p_j = (w_c * e_j) / L for j < lens[r]; entries at or past lens[r] are not written.

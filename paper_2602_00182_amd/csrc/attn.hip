@@ -31,7 +31,7 @@ constexpr int kHalfTok = 128;  // tokens of the half chunk whose V^T sits in LDS
 // m_c and l_c are returned in every lane.  No LDS, no barrier: the waves of a workgroup run it independently
 // on different rows.  attn_tile and det_softmax_f32 call it.  attn_chunk_kernel below and attn_walk_kernel (attn_rows.hip) compute
 // the same statistics, in the same order, from other lane layouts (add32, add16 and exp_nonpos of attn_lane.h); the tests hold
-// their bytes to attn_tile's (test_gpu_attn_chunk.py, test_gpu_attn_walk.py, test_gpu_attn_few.py).
+// their bytes to attn_tile's (test_gpu_attn_decode_forms.py, test_gpu_attn_walk.py, test_gpu_attn_few.py).
 __device__ __forceinline__ int chunk_token(int lane, int k) { return ((lane >> 4) << 6) + (k << 4) + (lane & 15); }
 __device__ __forceinline__ float lane_value(float v, int lane)
 {
@@ -76,10 +76,9 @@ __device__ __forceinline__ float combine_max(const float* mc, int nc)
 // ------------------------------------------------------------------ attention, pass 1
 
 // One workgroup: one 256-token chunk of one cache slot's K/V, for up to RT query rows (tokens) times G
-// query heads that share the KV head ("pairs").  Decode launches of more than 512 workgroups (and all with G = 1) take it with
-// RT = 1 (every row has a cache slot of its own); the rows form with RT = 8 lets the rows of one prompt share each chunk of K
-// and V (causal prefill: row i of a prompt has length p + i), in calls too small for attn_rows.hip and for the rows it leaves.
-// Grid (chunk, head group, row tile), one row a workgroup with the chunks permuted, see attn_chunk_of; 256 threads.
+// query heads that share the KV head ("pairs"): the rows of one prompt share each chunk of K and V (causal prefill: row i of a
+// prompt has length p + i), in calls too small for attn_rows.hip and for the rows it leaves.  (Rows that share nothing have
+// attn_chunk_kernel.)  Grid (chunk, head group, row tile); 256 threads.
 //
 // The arithmetic of one (row, head, chunk) is the same whatever else sits in the workgroup:
 //   scores: wave w takes tokens 64w..64w+63 of the chunk as four 16-token blocks; the K rows are the row
@@ -145,9 +144,8 @@ __device__ __forceinline__ void attn_tile(const uint16_t* __restrict__ q, const 
     for (int ri = 0; ri < RT; ++ri) any = any || len[ri] > t0;
     if (!any) return;  // uniform over the workgroup
 
-    // (a tile of one row, which has no groups to find, is 1 % slower with its length and slot in scalar registers)
-    auto row_len = [&](int ri) { return RT > 1 ? uni(len[ri]) : len[ri]; };
-    auto row_slot = [&](int ri) { return RT > 1 ? uni(slot[ri]) : slot[ri]; };
+    auto row_len = [&](int ri) { return uni(len[ri]); };
+    auto row_slot = [&](int ri) { return uni(slot[ri]); };
     uint32_t done = 0, alone = 0;  // rows computed, and rows that are groups of their own
     bool first_group = true;
 #pragma unroll 1
@@ -169,7 +167,7 @@ __device__ __forceinline__ void attn_tile(const uint16_t* __restrict__ q, const 
         if (!first_group) __syncthreads();  // the previous group's LDS contents are no longer read
         first_group = false;
         // tokens of this chunk at or past the shortest length and below the longest (uniform over the workgroup)
-        const bool window = RT > 1 && minlen < maxlen && minlen < t0 + kChunk;
+        const bool window = minlen < maxlen && minlen < t0 + kChunk;
         if (window && tid == 0) s_nan = 0;  // (set below, barriers later)
 
         const size_t kv_base = ((size_t)group_slot * Hkv + kvh) * (size_t)Lmax * kD;
@@ -391,26 +389,8 @@ __device__ __forceinline__ void attn_tile(const uint16_t* __restrict__ q, const 
     }
 }
 
-// The chunk of workgroup (x, stream) of attn_tile_kernel with one row a workgroup, a stream being one (row, KV head), counted in grid
-// order.  Workgroups go round-robin over the eight XCDs, and inside one over its compute units: where the number of chunks has
-// factors of two, chunk x of every stream would fall to the same places, and those that always get the first chunks, which more
-// rows reach, work while the others wait (16 chunks, 48 rows of 200 to 4096 tokens: the first XCD 1.37 times the mean).  So the
-// chunks of a group as long as that power of two change places from stream to stream, by the leading bits of the stream's
-// number times the golden ratio, whose values are even over any run of streams; a stream stays in eight-chunk order or nearly so.
-// us without, and with: 48 rows of 200 to 4096 tokens, 32/8 heads 110.8 -> 89.1 (the bytes at the rate of a copy 80), of 100 to 2000,
-// 16/16 heads 103 -> 84.5, 32 rows of 1001, 32/8 heads 43 -> 34.  Over 800 launches (2 to 32 chunks, 8 to 64 rows, 2 to 16 KV heads;
-// lengths equal, all half, of the upper half and of twenty to one) 4.5 % less time, equal lengths level, 15 launches slower by more
-// than 1.5 %, at most 4.  Heads in front of chunks in the grid, an earlier order for the same reason, took 3 % less, 86 launches
-// slower, up to 17 % (9 chunks, 16 rows of 1151 tokens, 16/4 heads 17.8 -> 20.5, now 17.4).  An odd number of chunks spreads by
-// itself.  Above 32 the chunks stay where they are: as even already (level over 60 launches).
-__device__ __forceinline__ int attn_chunk_of(int x, int stream, int ncmax)
-{
-    const int group = ncmax <= 32 ? ncmax & -ncmax : 1;
-    return x ^ (int)__umulhi((uint32_t)stream * 0x9E3779B9u, (uint32_t)group);
-}
-
 template <int G, int RT, bool DIRECT>
-__global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const uint16_t* __restrict__ q,
+__global__ __launch_bounds__(256, 2) void attn_tile_kernel(const uint16_t* __restrict__ q,
                                                         const uint16_t* __restrict__ kcache,
                                                         const uint16_t* __restrict__ vcache,
                                                         const int32_t* __restrict__ seqlens,
@@ -421,7 +401,7 @@ __global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const u
                                                         int len_offset)
 {
     const int hgrp = blockIdx.y, tile = blockIdx.z, tid = threadIdx.x;
-    const int c = RT == 1 ? attn_chunk_of(blockIdx.x, hgrp + Hkv * tile, ncmax) : (int)blockIdx.x;
+    const int c = blockIdx.x;
     // the tile's rows: length (0: no such row) and slot
     __shared__ int len[RT], slot[RT];
     if (tid < RT) {
@@ -450,12 +430,40 @@ __global__ __launch_bounds__(256, RT == 1 ? 4 : 2) void attn_tile_kernel(const u
     attn_tile<G, RT, DIRECT>(q, kcache, vcache, ws_m, ws_l, ws_o, out, Hq, Hkv, Lmax, ncmax, scale, c, hgrp, tile, len, slot);
 }
 
+// The chunk of workgroup (x, stream) of attn_chunk_kernel, a stream being one (row, KV head), counted in grid
+// order.  Workgroups go round-robin over the eight XCDs, and inside one over its compute units: where the number of chunks has
+// factors of two, chunk x of every stream would fall to the same places, and those that always get the first chunks, which more
+// rows reach, work while the others wait (16 chunks, 48 rows of 200 to 4096 tokens: the first XCD 1.37 times the mean).  So the
+// chunks of a group as long as that power of two change places from stream to stream, by the leading bits of the stream's
+// number times the golden ratio, whose values are even over any run of streams; a stream stays in eight-chunk order or nearly so.
+// us without, and with (in attn_tile_kernel with one row a workgroup, which had these launches before): 48 rows of 200 to 4096
+// tokens, 32/8 heads 110.8 -> 89.1 (the bytes at the rate of a copy 80), of 100 to 2000,
+// 16/16 heads 103 -> 84.5, 32 rows of 1001, 32/8 heads 43 -> 34.  Over 800 launches (2 to 32 chunks, 8 to 64 rows, 2 to 16 KV heads;
+// lengths equal, all half, of the upper half and of twenty to one) 4.5 % less time, equal lengths level, 15 launches slower by more
+// than 1.5 %, at most 4.  Heads in front of chunks in the grid, an earlier order for the same reason, took 3 % less, 86 launches
+// slower, up to 17 % (9 chunks, 16 rows of 1151 tokens, 16/4 heads 17.8 -> 20.5, now 17.4).  An odd number of chunks spreads by
+// itself.  Above 32 the chunks stay where they are: as even already (level over 60 launches).
+__device__ __forceinline__ int attn_chunk_of(int x, int stream, int ncmax)
+{
+    const int group = ncmax <= 32 ? ncmax & -ncmax : 1;
+    return x ^ (int)__umulhi((uint32_t)stream * 0x9E3779B9u, (uint32_t)group);
+}
+
 // Pass 1 for rows that share nothing (one row a workgroup: decode), one chunk for the G heads of a KV head.  The order of
-// every operation is attn_tile's; what differs is where things are: V is loaded with the keys in one go and lies in LDS as
-// it does in memory, transposed by the LDS read, so that the whole chunk's weighted sums follow one another, and a lane gets
-// the scores of eight tokens of each 32-token step of its pair in registers (the tokens are dealt to the operand's rows that
-// way), so that maximum, exp and tree need no pass over LDS.  Two barriers: the waves' maxima, then e and V.
-// What bounds the launches that take it is this chain of one memory round trip and two barriers.
+// every operation is attn_tile's; what differs is where things are.  A wave's share of the chunk is 64 tokens up to the weights, then
+// 32 dimensions.  K comes as whole rows by LDS-DMA and V in whole rows through registers, all in one round trip; a wave reads
+// its K operands from its own part of the buffer and leaves its V there (transposed by the LDS read), so that two workgroups fit
+// a compute unit.  Loaded as the operand lies in registers, sixteen rows an instruction, K took the memory pipe twice as long (one
+// workgroup of a launch of 4096 tokens, 32/8 heads: 3.4 of 7.5 us until everything had landed).
+// A wave has at most eight pairs where the operand has sixteen columns, and alone on its SIMD it issues a vector instruction
+// every 5.6 clocks: so the scores are dealt out over all lanes before the exponentials (2600 clocks before, 800 now), and the
+// three pieces of e are cut once, not by each wave for its dimensions (second product 4300 -> 1300).
+// Two barriers: the waves' maxima, then e and V.  What bounds the small launches is this chain of one memory round trip and
+// two barriers, the large ones memory: 64 rows of 4096 tokens, 32/8 heads 5.4 TB/s.
+// Against the form before (both passes, us): one sequence of 4096 tokens, 32/8 heads 12.0 -> 9.9, of 512, 16/4 heads 10.5 -> 8.2; 24 of
+// 30 to 536, 16/4 14.6 -> 11.6; 64 of 300, 16/4 8.6 -> 6.7; against attn_tile_kernel with one row a workgroup, which took launches of
+// more than 512 workgroups: 48 of 200 to 4096, 32/8 93.2 -> 89.1; 32 of 1024 to 2048 45.5 -> 41.2; 64 of 100 to 4096 114.5 -> 107.4;
+// 128 of 300 to 2048 122.9 -> 113.7; 64 of 4096 203 -> 198; 48 of 200 to 4096, 16/16 163 -> 155; none of 50 launches slower.
 template <int G, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void attn_chunk_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kcache,
                                                            const uint16_t* __restrict__ vcache,
@@ -465,15 +473,27 @@ __global__ __launch_bounds__(256, 2) void attn_chunk_kernel(const uint16_t* __re
                                                            uint16_t* __restrict__ out, int Hq, int Hkv, int Lmax, int ncmax,
                                                            float scale, int len_offset)
 {
-    __shared__ uint4 vbuf[kChunk * 16];             // V of the chunk, [token][piece], swizzled as in attn_rows.hip
-    __shared__ __align__(16) float es[G * kChunk];  // e, [pair][token], sc_index
+    constexpr int GP = G < 4 ? 4 : G;     // pairs a row of sixteen lanes is dealt out for
+    constexpr int NX = GP;                // scores a lane goes on with (of sixteen it gets from the products)
+    constexpr int kPieceRow = 2 * kChunk + 64;  // bytes of a pair's pieces, so that the pairs' rows lie in different banks
+    __shared__ uint4 vbuf[kChunk * 16];  // K of the chunk, then V, [token][piece], swizzled as in attn_rows.hip
+    __shared__ uint4 pieces[3][GP][kPieceRow / 16];  // e's three bf16 pieces, [piece][pair][token]
     __shared__ float wave_m[4][16], wave_l[4][16];
-    const int c = blockIdx.x, hgrp = blockIdx.y, r = blockIdx.z;
+    const int hgrp = blockIdx.y, r = blockIdx.z;
+    const int c = attn_chunk_of(blockIdx.x, hgrp + (int)gridDim.y * r, ncmax);
     const int kvh = (hgrp * G) / (Hq / Hkv);
     const int t0 = c * kChunk;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, lr = lane & 15;
+    uint4 qf[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) qf[i] = make_uint4(0, 0, 0, 0);
+    if (lr < G) {
+        const uint4* qp = reinterpret_cast<const uint4*>(q + ((size_t)r * Hq + (size_t)hgrp * G + lr) * kD + 32 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qf[i] = qp[i];
+    }
     const int len = __builtin_amdgcn_readfirstlane(attn_row_len(seqlens, r, len_offset, Lmax));
     uint16_t* orow = DIRECT ? out + ((size_t)r * Hq + (size_t)hgrp * G) * kD : nullptr;
     if (DIRECT && c == 0 && len <= 0) {  // a row without any token: zeros (there is no second pass to write them)
@@ -483,92 +503,128 @@ __global__ __launch_bounds__(256, 2) void attn_chunk_kernel(const uint16_t* __re
     const int slot = slots ? __builtin_amdgcn_readfirstlane(slots[r]) : r;
     const int held = min(kChunk, len - t0);  // tokens of the chunk
     const size_t kv_base = (((size_t)slot * Hkv + kvh) * (size_t)Lmax + t0) * kD;
-    const uint4* kp = reinterpret_cast<const uint4*>(kcache + kv_base);
-    const uint4* vp = reinterpret_cast<const uint4*>(vcache + kv_base);
 
-    // ---- loads: this lane's query piece, its keys (token 64w + 32st + 8(lr/4) + 4b + lr%4 is row lr of operand block (st, b)),
-    // and its share of V; tokens past the length are zeros and never read
-    uint4 qf[4], kf[2][2][4], vr[16];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) qf[i] = make_uint4(0, 0, 0, 0);
-    if (lr < G) {
-        const uint4* qp = reinterpret_cast<const uint4*>(q + ((size_t)r * Hq + (size_t)hgrp * G + lr) * kD + 32 * g);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) qf[i] = qp[i];
-    }
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int tok = 64 * wave + 32 * st + 8 * (lr >> 2) + 4 * b + (lr & 3);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) kf[st][b][i] = make_uint4(0, 0, 0, 0);
-            if (tok < held) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) kf[st][b][i] = kp[tok * 16 + 4 * g + i];
-            }
-        }
-#pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        const int tok = 64 * wave + 4 * b + g;
-        vr[b] = make_uint4(0, 0, 0, 0);
-        if (tok < held) vr[b] = vp[tok * 16 + lr];
-    }
-
-    // ---- scores and the chunk's maximum
-    float s[2][8];
-    float m_c = -INFINITY;
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[st][b][i]),
-                                                              __builtin_bit_cast(bf16x8, qf[i]), acc, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int tok = 64 * wave + 32 * st + 8 * g + 4 * b + v;
-                s[st][4 * b + v] = tok < held ? acc[v] * scale : -INFINITY;
-                m_c = fmaxf(m_c, s[st][4 * b + v]);
-            }
-        }
-    m_c = max_rows(m_c);
-    if (g == 0) wave_m[wave][lr] = m_c;
-    __syncthreads();
-    m_c = fmaxf(fmaxf(wave_m[0][lr], wave_m[1][lr]), fmaxf(wave_m[2][lr], wave_m[3][lr]));
-
-    // ---- e and this wave's 64 leaves of the tree: stride 32 pairs the steps, 16 and 8 lanes, 4 registers, 2 and 1 lanes
+    uint4 vr[16];
     {
-        float a[8];
+        typedef __attribute__((address_space(3))) uint32_t lds_u32;
+        typedef __attribute__((address_space(1))) const uint32_t glob_u32;
+        const char* kp = reinterpret_cast<const char*>(kcache + kv_base);
+        const uint4* vp = reinterpret_cast<const uint4*>(vcache + kv_base);
+#pragma unroll
+        for (int b = 0; b < 16; ++b) {
+            const uint32_t off = (uint32_t)min(64 * wave + 4 * b + g, held - 1) * 256u + 16u * (uint32_t)(lr ^ k_swizzle((b >> 1) & 3, g));
+            __builtin_amdgcn_global_load_lds((glob_u32*)(kp + off), (lds_u32*)(vbuf + wave * 1024 + b * 64), 16, 0, 0);
+        }
+#pragma unroll
+        for (int b = 0; b < 16; ++b) {
+            vr[b] = vp[min(64 * wave + 4 * b + g, held - 1) * 16 + lr];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x4F70);  // vmcnt(16): all but V
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    uint4 kf[2][2][4];  // row lr of operand block (st, b): token 32st + 8(lr/4) + 4b + lr%4 of the wave's
+    {
+        const char* base = reinterpret_cast<const char*>(vbuf) + wave * 16384 + (8 * (lr >> 2) + (lr & 3)) * 256;
+        const int kz = k_swizzle(lr >> 2, lr & 3);
 #pragma unroll
         for (int st = 0; st < 2; ++st)
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                s[st][k] = exp_nonpos(s[st][k] - m_c);
-                a[k] = st == 0 ? s[st][k] : a[k] + s[st][k];
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    kf[st][b][i] = *reinterpret_cast<const uint4*>(base + st * 8192 + b * 1024 + (((4 * g + i) ^ kz) << 4));
+    }
+
+    // ---- scores.  The products leave the sixteen tokens 32 st + 8 g + k (st = 0, 1, k = 0 .. 7) of pair lr in lane (g, lr), lr < G,
+    // and nothing of use in the other lanes, so they are dealt out: lane (g, lr) goes on with the NX scores x = NX*(lr / GP) ..
+    // of pair lr % GP, x = 8 st + k, in the order of the tokens.
+    float s[NX];
+    {
+        float all[16];
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[st][b][i]),
+                                                                  __builtin_bit_cast(bf16x8, qf[i]), acc, 0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) all[8 * st + 4 * b + v] = acc[v];
             }
-        const float r0 = add32(a[0], a[1]), r1 = add32(a[2], a[3]), r2 = add32(a[4], a[5]), r3 = add32(a[6], a[7]);
-        const float t4 = add16(r0, r1) + add16(r2, r3);
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+            s[x] = all[x];
+            if constexpr (GP == 4) {
+                s[x] = lanes_from<4>(s[x], all[4 + x]);
+                s[x] = lanes_from<8>(s[x], all[8 + x]);
+                s[x] = lanes_from<12>(s[x], all[12 + x]);
+            } else {
+                s[x] = lanes_from<8>(s[x], all[8 + x]);
+            }
+        }
+    }
+    const int share = lr / GP;                                                               // which of a pair's scores
+    const int first = GP == 4 ? 32 * (share >> 1) + 8 * g + 4 * (share & 1) : 32 * share + 8 * g;  // their first token of the wave's 64
+    float m_c = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+        s[x] = 64 * wave + first + x < held ? s[x] * scale : -INFINITY;
+        m_c = fmaxf(m_c, s[x]);
+    }
+    if constexpr (GP == 4) m_c = fmaxf(m_c, row_ror<4>(m_c));
+    m_c = fmaxf(m_c, row_ror<8>(m_c));
+    m_c = max_rows(m_c);
+    if (g == 0) wave_m[wave][lr] = m_c;
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    m_c = fmaxf(fmaxf(wave_m[0][lr], wave_m[1][lr]), fmaxf(wave_m[2][lr], wave_m[3][lr]));
+
+    // ---- e and this wave's 64 leaves of the tree, leaf 32 st + 8 g + k: stride 32 pairs the halves of the row of lanes, 16 and 8 the rows
+    {
+#pragma unroll
+        for (int x = 0; x < NX; ++x) s[x] = exp_nonpos(s[x] - m_c);
+        float a[NX];
+#pragma unroll
+        for (int x = 0; x < NX; ++x) a[x] = s[x] + row_ror<8>(s[x]);
+        const float r0 = add32(a[0], a[1]), r1 = add32(a[2], a[3]);
+        float t4 = add16(r0, r1);  // rows hold k = 0 2 1 3, and below 4 6 5 7
+        if constexpr (GP == 4)
+            t4 = t4 + row_ror<4>(t4);  // stride 4: the neighbouring quarters of the row of lanes
+        else
+            t4 = t4 + add16(add32(a[NX - 4], a[NX - 3]), add32(a[NX - 2], a[NX - 1]));
         const float t2 = add16(t4, t4);
         const float t1 = add32(t2, t2);
         if (g == 0) wave_l[wave][lr] = t1;
-        if (lr < G) {
+        // the three pieces (split_pieces: truncation, exact), once for all waves
+        uint32_t w[3][NX];
 #pragma unroll
-            for (int st = 0; st < 2; ++st)
+        for (int x = 0; x < NX; ++x) {
+            w[0][x] = fbits(s[x]) & 0xFFFF0000u;
+            const float rest = s[x] - bitsf(w[0][x]);
+            w[1][x] = fbits(rest) & 0xFFFF0000u;
+            w[2][x] = fbits(rest - bitsf(w[1][x]));
+        }
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    *reinterpret_cast<float4*>(&es[sc_index(lr, 64 * wave + 32 * st + 8 * g + 4 * h)]) =
-                        make_float4(s[st][4 * h], s[st][4 * h + 1], s[st][4 * h + 2], s[st][4 * h + 3]);
+        for (int y = 0; y < 3; ++y) {
+            uint32_t* to = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(pieces[y][lr % GP]) + 2 * (64 * wave + first));
+            const uint2 lo = make_uint2(__builtin_amdgcn_perm(w[y][1], w[y][0], 0x07060302u), __builtin_amdgcn_perm(w[y][3], w[y][2], 0x07060302u));
+            if constexpr (NX == 4) {
+                *reinterpret_cast<uint2*>(to) = lo;
+            } else {
+                *reinterpret_cast<uint4*>(to) = make_uint4(lo.x, lo.y, __builtin_amdgcn_perm(w[y][NX - 3], w[y][NX - 4], 0x07060302u),
+                                                           __builtin_amdgcn_perm(w[y][NX - 1], w[y][NX - 2], 0x07060302u));
+            }
         }
     }
 #pragma unroll
     for (int b = 0; b < 16; ++b) {
         const int tok = 64 * wave + 4 * b + g;  // token % 4 = g, token / 8 % 2 = b / 2 % 2
+        if (tok >= held) vr[b] = make_uint4(0, 0, 0, 0);
         vbuf[tok * 16 + ((((lr >> 1) ^ (g | (((b >> 1) & 1) << 2))) << 1) | (lr & 1))] = vr[b];
     }
-    __syncthreads();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const float l_c = (wave_l[0][lr] + wave_l[2][lr]) + (wave_l[1][lr] + wave_l[3][lr]);
 
     // ---- weighted sums: wave w owns d = 32w .. 32w+31, all tokens in ascending steps (steps past the length would add zeros)
@@ -577,17 +633,9 @@ __global__ __launch_bounds__(256, 2) void attn_chunk_kernel(const uint16_t* __re
     const uint32_t vbase = (uint32_t)(uintptr_t)(lds_char_t*)vbuf + (uint32_t)(8 * g + (lr >> 2)) * 256u + 8u * (uint32_t)(lr & 3);
     const uint32_t f = (uint32_t)((lr >> 2) | ((g & 1) << 2));
     auto pv_step = [&](int st) {
-        float e[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) e[k] = 0.0f;
-        if (lr < G) {
-            const float4 a = *reinterpret_cast<const float4*>(&es[sc_index(lr, 32 * st + 8 * g)]);
-            const float4 b = *reinterpret_cast<const float4*>(&es[sc_index(lr, 32 * st + 8 * g + 4)]);
-            e[0] = a.x, e[1] = a.y, e[2] = a.z, e[3] = a.w;
-            e[4] = b.x, e[5] = b.y, e[6] = b.z, e[7] = b.w;
-        }
         bf16x8 piece[3];
-        split_pieces(e, piece);
+#pragma unroll
+        for (int y = 0; y < 3; ++y) piece[y] = __builtin_bit_cast(bf16x8, pieces[y][lr % GP][4 * st + g]);  // (columns from G on are not used)
         bf16x8 vf[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -1028,11 +1076,7 @@ int det::attn_decode_impl(const void* q, const void* kcache, const void* vcache,
     //   * rows that name their slots (prefill: consecutive rows of a prompt share a slot) walk their chunks in
     //     one workgroup where there are enough of them (kWalkWorkgroups); fewer, but sixteen or more, go eight to
     //     a workgroup per chunk, so that they share each chunk of K and V;
-    //   * other rows: launches that are one round of two workgroups a compute unit are all latency and take
-    //     attn_chunk_kernel (one sequence of 4096 tokens, 32/8 heads 15.7 -> 12.6 us, where a workgroup for every query
-    //     head, each reading the chunk again, was the best of the other; 64 of 100 tokens 10.0 -> 8.1); larger ones
-    //     want the four workgroups a compute unit that attn_tile_kernel has room for (64 ragged sequences of up to 1024
-    //     tokens 37.1 against 39.2, 32 of 600 21.8 against 24.7), and so do heads with K and V of their own (G = 1).
+    //   * other rows take attn_chunk_kernel.
     const bool tiled = slots != nullptr && B >= 16;
     if (tiled && attn_walk_workgroups(B, G, Hkv) >= kWalkWorkgroups) {
         if (qscales && !aligned16(qscales)) return DET_EALIGN;
@@ -1043,7 +1087,6 @@ int det::attn_decode_impl(const void* q, const void* kcache, const void* vcache,
                          Hq, Hkv, Lmax, ncmax, scale, s);
     }
     const int RT = tiled ? 8 : 1;
-    const bool by_chunk = !tiled && G > 1 && (size_t)ncmax * Hkv * B <= 512;
     const dim3 grid(ncmax, Hkv, (B + RT - 1) / RT);
     const uint16_t* qq = static_cast<const uint16_t*>(q);
     const uint16_t* kk = static_cast<const uint16_t*>(kcache);
@@ -1057,20 +1100,16 @@ int det::attn_decode_impl(const void* q, const void* kcache, const void* vcache,
 #define DET_LAUNCH_CHUNK(GG, DIR)                                                                                       \
     hipLaunchKernelGGL((attn_chunk_kernel<GG, DIR>), grid, dim3(256), 0, s, qq, kk, vv, seqlens, slots, ws_m, ws_l, ws_o, \
                        out16, Hq, Hkv, Lmax, ncmax, scale, len_offset)
-#define DET_LAUNCH_ATTN(GG)                                \
-    do {                                                   \
-        if (tiled && direct)                               \
-            DET_LAUNCH_TILE(GG, 8, true);                  \
-        else if (tiled)                                    \
-            DET_LAUNCH_TILE(GG, 8, false);                 \
-        else if (GG > 1 && by_chunk && direct)             \
-            DET_LAUNCH_CHUNK((GG > 1 ? GG : 2), true);     \
-        else if (GG > 1 && by_chunk)                       \
-            DET_LAUNCH_CHUNK((GG > 1 ? GG : 2), false);    \
-        else if (direct)                                   \
-            DET_LAUNCH_TILE(GG, 1, true);                  \
-        else                                               \
-            DET_LAUNCH_TILE(GG, 1, false);                 \
+#define DET_LAUNCH_ATTN(GG)                   \
+    do {                                      \
+        if (tiled && direct)                  \
+            DET_LAUNCH_TILE(GG, 8, true);     \
+        else if (tiled)                       \
+            DET_LAUNCH_TILE(GG, 8, false);    \
+        else if (direct)                      \
+            DET_LAUNCH_CHUNK(GG, true);       \
+        else                                  \
+            DET_LAUNCH_CHUNK(GG, false);      \
     } while (0)
     switch (G) {
         case 1: DET_LAUNCH_ATTN(1); break;

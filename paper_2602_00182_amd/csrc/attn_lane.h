@@ -27,6 +27,18 @@ __device__ __forceinline__ float add16(float a, float b)
     const uint2v r = __builtin_amdgcn_permlane16_swap(fbits(a), fbits(b), false, false);
     return bitsf(r[0]) + bitsf(r[1]);
 }
+// Within the rows of sixteen lanes: the value of lane (l + N) % 16; and `mine` in the lanes below N and from N + 4 (N + 8 for
+// <8> of eight lanes) on, the value lane l - N has of `from` in lanes N ..
+template <int N>
+__device__ __forceinline__ float row_ror(float v)
+{
+    return bitsf((uint32_t)__builtin_amdgcn_update_dpp(0, (int)fbits(v), 0x120 + N, 0xF, 0xF, true));
+}
+template <int N>
+__device__ __forceinline__ float lanes_from(float mine, float from)
+{
+    return bitsf((uint32_t)__builtin_amdgcn_update_dpp((int)fbits(mine), (int)fbits(from), 0x110 + N, 0xF, 0xF & ~((1 << (N / 4)) - 1), false));
+}
 // maximum over the four lanes that hold one pair (lr, lr+16, lr+32, lr+48), in all four
 __device__ __forceinline__ float max_rows(float v)
 {
@@ -35,6 +47,11 @@ __device__ __forceinline__ float max_rows(float v)
     r = __builtin_amdgcn_permlane16_swap(fbits(v), fbits(v), false, false);
     return fmaxf(bitsf(r[0]), bitsf(r[1]));
 }
+
+// Where the pieces of a K row lie (piece p at p ^ k_swizzle): row 4q + r of an operand block.  A read of sixteen bytes a lane is
+// served in quarters of lanes 0-3, 12-15 and, of the next sixteen, 4-11 (the other way round in the second), which ask for
+// pieces four apart: with the row's own number as the swizzle the two halves met in the same banks.
+__device__ __forceinline__ int k_swizzle(int q, int r) { return r | (((0x78 >> (2 * q)) & 3) << 2); }
 
 // det_expf for arguments that are never positive (a score minus the maximum of its chunk): the same operations
 // without the overflow test.  NaN stays NaN (the integer conversion of NaN is 0 in hardware; written as the

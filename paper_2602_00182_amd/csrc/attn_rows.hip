@@ -34,11 +34,6 @@ __device__ __forceinline__ void wait_then_barrier()
 
 }  // namespace
 
-// Where the pieces of a K row lie (piece p at p ^ k_swizzle): row 4q + r of an operand block.  A read of sixteen bytes a lane is
-// served in quarters of lanes 0-3, 12-15 and, of the next sixteen, 4-11 (the other way round in the second), which ask for
-// pieces four apart: with the row's own number as the swizzle the two halves met in the same banks.
-__device__ __forceinline__ int k_swizzle(int q, int r) { return r | (((0x78 >> (2 * q)) & 3) << 2); }
-
 // One workgroup (256 threads) = 64 / G consecutive rows x the G query heads of one KV head; wave w owns the
 // pairs 16w .. 16w+15 from the scores to the output, so that nothing but K, V and the chunk maxima goes
 // through LDS.
