@@ -33,12 +33,16 @@ __device__ __forceinline__ float order_key_inv(uint32_t k)
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
 
+// order_key with NaN = -inf and -0 = +0: the same candidate value has the same key.
+__device__ __forceinline__ uint32_t value_key(float z)
+{
+    if (z != z) z = -INFINITY;
+    if (z == 0.0f) z = 0.0f;
+    return order_key(z);
+}
 __device__ __forceinline__ uint64_t candidate_key(float logit, float temperature, int j)
 {
-    float z = logit / temperature;
-    if (z != z) z = -INFINITY;
-    if (z == 0.0f) z = 0.0f;  // -0 and +0 are the same candidate value
-    return ((uint64_t)order_key(z) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)j);
+    return ((uint64_t)value_key(logit / temperature) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)j);
 }
 
 __device__ __forceinline__ uint64_t splitmix64_mix(uint64_t z)
@@ -153,19 +157,31 @@ __global__ __launch_bounds__(256) void sample_kernel(const float* __restrict__ l
 }
 
 // The same selection for rows of at most 1024*KPT logits, with the row read once: 1024 threads, each
-// keeps the z keys of its KPT candidates (j = tid + 1024 i) in registers, so the radix passes, the
-// gather and the division by the temperature touch no memory but the LDS histogram.  The sort and the
-// exponentials use all threads; the prefix sums stay one thread's sequential adds in rank order (their
-// order is part of the definition), the two searches over them are minimum reductions (the first
-// index that satisfies a condition does not depend on how it is found).
+// keeps the keys of its KPT candidates in registers, so that what follows touches no memory but LDS.  VEC: rows of 16-byte
+// pieces, which are loaded as such.  The prefix sums are sequential adds in rank order (their order is part of the definition); the
+// two searches over them take the first index that satisfies a condition, which does not depend on how it is found.
+//
+// Up to top-k 256 the candidates come from group maxima: at least k of G groups of threads hold a logit that is at least the k-th
+// largest of the groups' largest logits, so that value bounds the k-th largest logit of the row from below, and with G of
+// two to four times k few more than k logits reach it (of 32000 normal ones some 65 for k = 50).  Dividing by the temperature keeps
+// the order up to ties, so only the logits that may reach the bound's quotient are divided.
+// What bounds it is one chain in one workgroup a row: the row's 128 KB (9 us of 16 with loads of four bytes and a division for
+// each logit), then steps that wait for LDS.  64 rows of 32000, us before (the k-th largest of the threads' maxima by two
+// histograms, every logit divided, sums and searches through LDS with a barrier each) and now: top-k 1 17.9 -> 9.4, 50 20.7 -> 11.7,
+// 64 21.4 -> 12.1, 100 to 128 25 -> 20, 256 34 -> 28, 1000 51 -> 50; of 8000 at 40 12.4 -> 6.3, of 50000 at 50 36 -> 27.
+// A row where more than kMaxRanked keys reach the bound (ties) has paid for the bound in vain and is selected by radix.
 constexpr int kSampleThreads = 1024;
-// Up to this top-k the candidates come from the threads' maxima: of 32000 normal logits about 1.1 k reach the bound.
-// 64 rows of 32000: top-k 1 18.7 -> 13.3 us, 50 24.2 -> 16.4, 200 31.5 -> 23.7, 256 32.2 -> 29.7; of 50000 with ties
-// (bf16 values) top-k 50 75.9 -> 29.6.  A row where more than kMaxRanked keys reach the bound has paid for it in vain: 4.5 us
-// where all logits are equal (V = 1000 16.4 -> 20.9, 32000 153 -> 157), up to 15 where they take a dozen values (V = 50000,
-// top-k 256: 87 -> 102).  Above 32768 logits the keys do not all fit the registers (104 spilled).
-constexpr int kBoundTopK = 256, kMaxRanked = 512;
-template <int KPT>
+constexpr int kBoundTopK = 256, kGroupTopK = 128, kMaxRanked = 512;
+
+// The value of the lane N away inside a group of 2, 4, 8 or 16 lanes whose halves each agree on their value (xor 1, xor 2, and mirror
+// images of the group of 8 and of 16).
+template <int N>
+__device__ __forceinline__ int other_half(int v)
+{
+    constexpr int ctrl = N == 1 ? 0xB1 : (N == 2 ? 0x4E : (N == 4 ? 0x141 : 0x140));
+    return __builtin_amdgcn_update_dpp(0, v, ctrl, 0xF, 0xF, true);
+}
+template <int KPT, bool VEC>
 __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float* __restrict__ logits, int V,
                                                                     float temperature, int top_k, float top_p,
                                                                     uint64_t seed, const int32_t* __restrict__ seq_ids,
@@ -175,7 +191,9 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
     constexpr int T = kSampleThreads;
     __shared__ uint32_t hist2[2][2 * kSampleThreads];  // the histogram of pass p is hist2[p & 1]; the other one is cleared meanwhile
     __shared__ uint64_t sel[kMaxTopK], cand[kMaxRanked];
-    __shared__ float ebuf[kMaxTopK];
+    __shared__ uint4 maxima[kSampleThreads / 4 / 4];
+    __shared__ uint32_t s_bound;
+    __shared__ __align__(16) float ebuf[kMaxTopK];
     __shared__ int s_digit, s_need, s_bin, s_count, s_n, s_pick;
     __shared__ float s_cut, s_target;
     __shared__ uint32_t wave_tot[kSampleThreads / kWave];
@@ -184,13 +202,46 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
     const float* row = logits + (size_t)blockIdx.x * V;
     const int k = top_k < V ? top_k : V;
 
-    uint32_t zk[KPT];  // high half of candidate_key; the low half is 0xFFFFFFFF - j
+    const uint64_t ctr = ((uint64_t)(uint32_t)seq_ids[blockIdx.x] << 32) | (uint64_t)(uint32_t)steps[blockIdx.x];
+
+    auto index_of = [&](int i) { return VEC ? 4 * (tid + T * (i >> 2)) + (i & 3) : tid + T * i; };
+    // Keys of the logits as long as `divided` is false, then those of their quotients (the high half of candidate_key; the low half is
+    // 0xFFFFFFFF - index).  An absent one is 0, below every real one.
+    uint32_t zk[KPT];
+    constexpr bool kLate = KPT <= 32;  // (of 64 a thread they are divided first: keys and divisions do not fit the registers)
+    bool divided = !kLate || k > kBoundTopK;
+    {
+        float x[KPT];
+        if constexpr (VEC) {
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-        const int j = tid + T * i;
-        zk[i] = j < V ? (uint32_t)(candidate_key(row[j], temperature, j) >> 32) : 0u;
+            for (int i = 0; i < KPT; i += 4) {
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (index_of(i) < V) v = reinterpret_cast<const float4*>(row)[tid + T * (i >> 2)];
+                x[i] = v.x, x[i + 1] = v.y, x[i + 2] = v.z, x[i + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < KPT; ++i) x[i] = index_of(i) < V ? row[index_of(i)] : 0.0f;
+        }
+        if (divided) {
+#pragma unroll
+            for (int i = 0; i < KPT; ++i) {
+                x[i] = x[i] / temperature;
+                if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) zk[i] = index_of(i) < V ? value_key(x[i]) : 0u;
     }
-    auto key_of = [&](int i) { return ((uint64_t)zk[i] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)(tid + T * i)); };
+    auto divide = [&]() {
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) {
+            zk[i] = zk[i] != 0 ? value_key(order_key_inv(zk[i]) / temperature) : 0u;
+            if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // (all divisions side by side do not fit the registers)
+        }
+        divided = true;
+    };
+    auto key_of = [&](int i) { return ((uint64_t)zk[i] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)index_of(i)); };
 
     // The digit of the rank-`need` key of a 2048-bin histogram (thread t owns bins 2t and 2t+1): above(b) = keys with a
     // larger digit than b, from the suffix sums of the threads' pair sums inside each wave and the totals of the higher waves.
@@ -222,49 +273,90 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
         __syncthreads();
     };
 
-    // ---- candidates from the threads' maxima.  At least k threads hold a key that is at least the k-th largest of the
-    // threads' largest keys, so that value bounds the k-th largest key of the row from below, and for small k few
-    // more than k keys reach it: two histograms of one increment a thread (11 bits of the key, then 11 more) instead of
-    // one of an increment a key, and no pass over the rest.  Of n such keys each counts the larger ones among them, which
-    // is its rank.  More than kMaxRanked (ties) go to the radix select below.
+    // ---- candidates from the groups' maxima
     bool done = false;
     if (k <= kBoundTopK) {
-        uint32_t top = 0;
+        const int l = tid & (kWave - 1);
+        uint32_t top = 0, bound_key;
 #pragma unroll
-        for (int i = 0; i < KPT; ++i) top = zk[i] > top ? zk[i] : top;  // an absent key is 0, below every real one
-        uint32_t prefix = 0;
-        int need = k;
-        hist2[0][2 * tid] = 0;
-        hist2[0][2 * tid + 1] = 0;
-        hist2[1][2 * tid] = 0;
-        hist2[1][2 * tid + 1] = 0;
-        if (tid == 0) s_count = 0;
-        __syncthreads();
-        for (int pass = 0; pass < 2; ++pass) {
-            if (top != 0 && (pass == 0 || (top >> 21) == prefix)) atomicAdd(&hist2[pass][(pass == 0 ? top >> 21 : top >> 10) & 2047u], 1u);
+        for (int i = 0; i < KPT; ++i) top = zk[i] > top ? zk[i] : top;
+        if (tid == 0) s_count = 0, s_bound = 0xFFFFFFFFu;
+        if (k <= kGroupTopK) {  // the smallest maximum that fewer than k others exceed
+            const int per = k <= 64 ? 8 : 4;  // threads of a group, which look at a share of the other groups' maxima each
+            top = max(top, (uint32_t)other_half<1>((int)top));
+            top = max(top, (uint32_t)other_half<2>((int)top));
+            if (per >= 8) top = max(top, (uint32_t)other_half<4>((int)top));
+            if (tid % per == 0) reinterpret_cast<uint32_t*>(maxima)[tid / per] = top;
             __syncthreads();
-            find_digit(hist2[pass], need, [] {});
-            prefix = (prefix << 11) | (uint32_t)s_digit;
-            need = s_need;
+            const int share = T / per / 4 / per;  // of uint4
+            const uint4* from = maxima + (tid % per) * share;
+            int above = 0;
+#pragma unroll 4
+            for (int c = 0; c < share; ++c) {
+                const uint4 w = from[c];
+                above += (w.x > top ? 1 : 0) + (w.y > top ? 1 : 0) + (w.z > top ? 1 : 0) + (w.w > top ? 1 : 0);
+            }
+            above += other_half<1>(above);
+            above += other_half<2>(above);
+            if (per >= 8) above += other_half<4>(above);
+            uint32_t least = above < k ? top : 0xFFFFFFFFu;
+            least = min(least, (uint32_t)other_half<4>((int)least));
+            least = min(least, (uint32_t)other_half<8>((int)least));
+            if ((l & 15) == 0 && least != 0xFFFFFFFFu) atomicMin(&s_bound, least);
+            __syncthreads();
+            bound_key = s_bound;
+        } else {  // of the threads' maxima, by two histograms of one increment a thread: 11 bits of the key, then 11 more
+            uint32_t prefix = 0;
+            int need = k;
+            hist2[0][2 * tid] = 0;
+            hist2[0][2 * tid + 1] = 0;
+            hist2[1][2 * tid] = 0;
+            hist2[1][2 * tid + 1] = 0;
+            __syncthreads();
+            for (int pass = 0; pass < 2; ++pass) {
+                if (top != 0 && (pass == 0 || (top >> 21) == prefix)) atomicAdd(&hist2[pass][(pass == 0 ? top >> 21 : top >> 10) & 2047u], 1u);
+                __syncthreads();
+                find_digit(hist2[pass], need, [] {});
+                prefix = (prefix << 11) | (uint32_t)s_digit;
+                need = s_need;
+            }
+            bound_key = prefix << 10;
         }
-        const uint32_t bound = prefix << 10;
-        const bool few = k - need + s_bin <= kMaxRanked;  // of the maxima alone
+        // `low`: every logit whose quotient reaches the bound's has this key or a larger one
+        const float bound = order_key_inv(max(bound_key, 1u)), quotient = bound / temperature;
+        uint32_t low;
+        if (!kLate) {
+            low = max(bound_key, 1u);
+        } else if (fabsf(bound) >= 0x1p-100f && fabsf(quotient) >= 0x1p-100f && fabsf(bound) <= 0x1p120f && fabsf(quotient) <= 0x1p120f) {
+            low = order_key(bound - fabsf(bound) * 0x1p-20f);  // 2^-20 below it is more than a rounding away
+        } else {  // zeros, infinities, quotients that round coarsely: by the quotients themselves
+            divide();
+            low = bound == bound ? value_key(quotient) : 1u;  // (no number: fewer than k groups have a logit, all are candidates)
+        }
+        int count = 0;
 #pragma unroll
-        for (int i = 0; i < KPT; ++i) {
-            if (!few) break;
-            const bool in = zk[i] >= bound && tid + T * i < V;
-            const uint64_t m = __ballot(in);
-            if (m != 0) {  // one add a wave; the order of the list does not matter
-                const int l = tid & (kWave - 1), lead = __builtin_ctzll(m);
-                int at = 0;
-                if (l == lead) at = atomicAdd(&s_count, __builtin_popcountll(m));
-                at = __shfl(at, lead, kWave) + __builtin_popcountll(m & ((1ull << l) - 1ull));
-                if (in && at < kMaxRanked) cand[at] = key_of(i);
+        for (int i = 0; i < KPT; ++i) count += __builtin_popcountll(__ballot(zk[i] >= low));
+        if (count != 0) {  // one add a wave; the order of the list does not matter
+            int at = 0;
+            if (l == 0) at = atomicAdd(&s_count, count);
+            at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+            for (int i = 0; i < KPT; ++i) {
+                const bool in = zk[i] >= low;
+                const uint64_t m = __ballot(in);
+                if (m == 0 || at >= kMaxRanked) continue;
+                const int to = at + __builtin_popcountll(m & ((1ull << l) - 1ull));
+                if (in && to < kMaxRanked) cand[to] = key_of(i);
+                at += __builtin_popcountll(m);
             }
         }
         __syncthreads();
-        const int n = few ? s_count : kMaxRanked + 1;
-        if (n <= kMaxRanked) {
+        const int n = s_count;
+        if (kLate && n <= kMaxRanked && !divided) {
+            if (tid < n) cand[tid] = candidate_key(order_key_inv((uint32_t)(cand[tid] >> 32)), temperature, (int)(0xFFFFFFFFu - (uint32_t)cand[tid]));
+            __syncthreads();
+        }
+        if (n <= kMaxRanked) {  // each candidate counts the larger ones, which is its rank
             int np = 16;  // candidates rounded up to a power of two; T / np neighbouring threads share one
             while (np < n) np <<= 1;
             const int parts = T / np;
@@ -272,9 +364,15 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
             const uint64_t mine = i < n ? cand[i] : 0;
             int above = 0;
             for (int j = tid % parts; j < n; j += parts) above += cand[j] > mine ? 1 : 0;
-            for (int off = 1; off < parts; off <<= 1) above += __shfl_xor(above, off, kWave);
+            if (parts > 1) above += other_half<1>(above);
+            if (parts > 2) above += other_half<2>(above);
+            if (parts > 4) above += other_half<4>(above);
+            if (parts > 8) above += other_half<8>(above);
+            for (int off = 16; off < parts; off <<= 1) above += __shfl_xor(above, off, kWave);
             if (i < n && tid % parts == 0 && above < k) sel[above] = mine;
             done = true;
+        } else if (kLate && !divided) {
+            divide();
         }
         __syncthreads();
     }
@@ -298,7 +396,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
             uint32_t* hist = hist2[pass & 1];
 #pragma unroll
             for (int i = 0; i < KPT; ++i) {
-                const bool in = tid + T * i < V;
+                const bool in = zk[i] != 0;
                 const uint64_t key = key_of(i);
                 if (in && (pass == 0 || (key >> (shift + width)) == prefix)) atomicAdd(&hist[(uint32_t)(key >> shift) & dmask], 1u);
             }
@@ -321,7 +419,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < KPT; ++i) {
-            if (tid + T * i < V) {
+            if (zk[i] != 0) {
                 const uint64_t key = key_of(i);
                 if (key >= threshold) sel[atomicAdd(&s_count, 1)] = key;
             }
@@ -346,6 +444,34 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
                 __syncthreads();
             }
         }
+    }
+
+    if (k <= kWave) {  // all of them in the lanes of one wave: no barriers
+        if (tid >= kWave) return;
+        const uint64_t mine = tid < k ? sel[tid] : 0;
+        const float z = order_key_inv((uint32_t)(mine >> 32));
+        auto lane_of = [](float v, int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l)); };
+        ebuf[tid] = det_expf(z - lane_of(z, 0));
+        float c = 0.0f;  // lane i adds the first i + 1 of them, in order (what lanes from k on add is not used)
+        for (int i = 0; i < k; i += 8) {
+            const float4 a = *reinterpret_cast<const float4*>(&ebuf[i]), b = *reinterpret_cast<const float4*>(&ebuf[i + 4]);
+            const float e[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float with = c + e[u];
+                c = tid >= i + u ? with : c;
+            }
+        }
+        const float cut = top_p * lane_of(c, k - 1);
+        const uint64_t reach = __ballot(tid < k && c >= cut);
+        const int n = reach != 0 ? __builtin_ctzll(reach) + 1 : k;
+        const uint64_t r = splitmix64_mix(seed + (ctr + 1) * 0x9E3779B97F4A7C15ull);
+        const float u = (float)(uint32_t)(r >> 40) * 0x1p-24f;
+        const float target = u * lane_of(c, n - 1);
+        const uint64_t over = __ballot(tid < n && c > target);
+        const int pick = over != 0 ? __builtin_ctzll(over) : n - 1;
+        if (tid == pick) tokens[blockIdx.x] = (int32_t)(0xFFFFFFFFu - (uint32_t)mine);
+        return;
     }
 
     // ---- probabilities in rank order
@@ -388,7 +514,6 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
     __syncthreads();
     const int n = s_n;
     if (tid == 0) {
-        const uint64_t ctr = ((uint64_t)(uint32_t)seq_ids[blockIdx.x] << 32) | (uint64_t)(uint32_t)steps[blockIdx.x];
         const uint64_t r = splitmix64_mix(seed + (ctr + 1) * 0x9E3779B97F4A7C15ull);
         const float u = (float)(uint32_t)(r >> 40) * 0x1p-24f;
         s_target = u * ebuf[n - 1];
@@ -419,13 +544,24 @@ extern "C" int det_sample(const float* logits, int B, int V, float temperature, 
     if (!(temperature > 0.0f) || !(top_p > 0.0f) || !(top_p <= 1.0f)) return DET_EINVAL;
     if (top_k < 1 || top_k > kMaxTopK) return DET_ESHAPE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (V <= kSampleThreads * 32)
-        hipLaunchKernelGGL(sample_kernel_reg<32>, dim3(B), dim3(kSampleThreads), 0, s, logits, V, temperature, top_k, top_p,
-                           seed, seq_ids, steps, tokens);
-    else if (V <= kSampleThreads * 64)
-        hipLaunchKernelGGL(sample_kernel_reg<64>, dim3(B), dim3(kSampleThreads), 0, s, logits, V, temperature, top_k, top_p,
-                           seed, seq_ids, steps, tokens);
-    else
+    // 16-byte pieces where every row is made of such and every thread gets one.  Of more than 32768 logits only where the
+    // candidates come from few groups: the radix select spills more registers with them (V = 50000, top-k 1000 94 us with and 75 without).
+    const bool vec = aligned16(logits) && V % 4 == 0 && V >= 4 * kSampleThreads && (V <= 32 * kSampleThreads || top_k <= kGroupTopK);
+#define DET_SAMPLE(KPT)                                                                                                      \
+    if (vec)                                                                                                                 \
+        hipLaunchKernelGGL((sample_kernel_reg<KPT, true>), dim3(B), dim3(kSampleThreads), 0, s, logits, V, temperature,     \
+                           top_k, top_p, seed, seq_ids, steps, tokens);                                                      \
+    else                                                                                                                     \
+        hipLaunchKernelGGL((sample_kernel_reg<KPT, false>), dim3(B), dim3(kSampleThreads), 0, s, logits, V, temperature,    \
+                           top_k, top_p, seed, seq_ids, steps, tokens)
+    if (V <= kSampleThreads * 8) {
+        DET_SAMPLE(8);
+    } else if (V <= kSampleThreads * 32) {
+        DET_SAMPLE(32);
+    } else if (V <= kSampleThreads * 64) {
+        DET_SAMPLE(64);
+    } else
+#undef DET_SAMPLE
         hipLaunchKernelGGL(sample_kernel, dim3(B), dim3(256), 0, s, logits, V, temperature, top_k, top_p, seed, seq_ids,
                            steps, tokens);
     return check_launch();
