@@ -19,7 +19,7 @@ extern "C" const char* det_fingerprint(void)
         // (attention) select.  They move no output byte, but a receipt pins them all the same, so a change of
         // what det_gemm_tile() or det_qgemm_tile() answers for any launch, or of the forms and grids attention takes, is a new revision.
         " tiles-7(gemm:n256@rounds,n128@256wg,rowcut8,n64@m65|m64r64|m161,reads@m96|m192,norm-in-kernel@4rows;"
-        "qgemm:few@4rows,norm@3rows,norm128@4rows,sp@8rows,32x64+64x64@768wg,64x128;"
+        "qgemm:few@4rows,norm@3rows,norm128@4rows,mid@48rows,32x64+64x64@768wg,64x128;"
         "attn:chunk,rows8@16rows,walk@256wg,few@16pairs,turn@32chunks)";
 }
 

@@ -23,20 +23,28 @@ __device__ __forceinline__ v4i code_bytes(const uint2& c)
 }
 
 // Counters in LDS by which the waves of a workgroup tell each other what is done.  LDS serves a wave's instructions in order.
+// Written as instructions: a volatile access of the C language goes by way of flat addresses, whose wait takes in every load under
+// way (14336 x 4096 with it and without, us: qgemm_mid.hip, 8 rows, 22.4 and 14.1; qgemm_few.hip, one row, 11.2 and 10.9).
+__device__ __forceinline__ uint32_t lds_address(const int* p) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) int*)p; }
 __device__ __forceinline__ void publish(int* counter, int value)
 {
-    if ((threadIdx.x & 63) == 0) *const_cast<volatile int*>(counter) = value;
+    if ((threadIdx.x & 63) == 0) asm volatile("ds_write_b32 %0, %1" ::"v"(lds_address(counter)), "v"(value) : "memory");
+}
+__device__ __forceinline__ int lds_look(const int* counter)
+{
+    int v;
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_address(counter)) : "memory");
+    return v;
 }
 // Waits until lane i < n finds counters[i] at its `need` or above.
 __device__ __forceinline__ void await(const int* counters, int n, int need)
 {
     const int lane = threadIdx.x & 63;
     for (;;) {
-        const int have = lane < n ? *const_cast<const volatile int*>(&counters[lane]) : 0x7FFFFFFF;
-        if (__ballot(have < need) == 0) break;
+        const int have = lds_look(&counters[lane < n ? lane : 0]);
+        if (__ballot(lane < n && have < need) == 0) break;
         __builtin_amdgcn_s_sleep(1);
     }
-    asm volatile("" ::: "memory");
 }
 
 // Bytes of a stage (64 k) of a packed slab of 16*cb columns: codes, then scales.
@@ -57,5 +65,8 @@ struct qgemm_few_args {
 constexpr int kFewRows = 4;
 bool qgemm_few_fits(int M, int cb, int K, bool norm);
 void qgemm_few(int epi, int cb, const qgemm_few_args& a, hipStream_t s);
+// Launches of more, in tiles of at most 48 rows (qgemm_mid.hip); x is not taken.
+bool qgemm_mid_fits(int M, int cb, int rows);
+void qgemm_mid(int epi, int cb, const qgemm_few_args& a, int rows, hipStream_t s);
 
 }  // namespace det

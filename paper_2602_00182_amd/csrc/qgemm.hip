@@ -16,11 +16,10 @@
 // matrix-core operand order, then 16 scales), so a chunk's weights are one contiguous run copied as
 // it lies.  And the eight computing waves split the tile by column block first (wave w: column block
 // w % CB, row blocks w / CB, w / CB + 8/CB, ...): at small M the work per stage is the unpacking of
-// the codes, which a single wave could not do at the rate the weights stream in.  Tiles of at most 8
-// rows and 2 column blocks go further and split the stages of a chunk over the waves (run_sp below):
-// only the accumulation chain has a defined order, and it keeps it.  Launches of at most four rows have a kernel
-// of their own where their weights fit LDS (qgemm_few.hip).  Launches of more rows take tiles of 32
-// or 64 rows x 64 or 128 columns instead (qgemm_tile_kernel).
+// the codes, which a single wave could not do at the rate the weights stream in.  Where few rows and narrow
+// packings leave a workgroup one or two column blocks and at most three of rows, the stages are dealt out as well, in a kernel of its
+// own (qgemm_mid.hip); launches of at most four rows have another where their weights fit LDS (qgemm_few.hip).  Launches of more rows
+// take tiles of 32 or 64 rows x 64 or 128 columns instead (qgemm_tile_kernel).
 #include <type_traits>
 
 #include "internal.h"
@@ -155,9 +154,7 @@ struct qgemm_plan {
     int tile_bytes;  // bytes of an activation tile: 1024 (16 rows), or 512 / 256 for a single row block of <= 8 / <= 4 rows
     uint32_t inv_4rb;  // floor(2^20/(4*RB))+1
     int nrg;         // row groups in use: min(8/CB, RB)
-    int SG;          // stage groups: 8 / (CB * nrg) waves share a (column block, row group) pair, see run_sp
-    int res_off;     // SG > 1: byte offset in the ring of the two result buffers
-    int ncomp;       // waves that do not load
+    int ncomp;       // waves that do not load: one per (column block, row group)
     int nload;
     uint32_t inv_nload;  // floor(2^20/nload)+1
 };
@@ -182,29 +179,14 @@ static qgemm_plan make_qgemm_plan(int mrem, int cb, int K, int resident = 0)
     const int nstages = K >> 6;
     const int rg = 8 / cb;
     t.nrg = rg < t.RB ? rg : t.RB;
-    // stage-parallel form (see run_sp) where the results stay small enough for chunks of twenty stages and
-    // more: at most two column blocks of at most 8 rows
-    t.SG = cb <= 2 && t.tile_bytes < 1024 ? 8 / cb : 1;
-    t.res_off = 0;
+    const int third = ring_bytes / 3;  // the most stages whose chunk fits a third of the ring
     t.SPC = 1;
-    if (t.SG > 1) {
-        // four slots and two result buffers of 128 bytes per (stage, column block, row group, row kept)
-        const int res_stage = 2 * t.tile_bytes * cb * t.nrg;
-        while (4 * chunk_bytes(t.SPC + 1) + 2 * (t.SPC + 1) * res_stage <= kQRing * 1024 && t.SPC < 64) ++t.SPC;
-        t.slot_bytes = chunk_bytes(t.SPC);
-        t.nslots = 4;
-        t.res_off = 4 * t.slot_bytes;
-    } else {
-        const int third = ring_bytes / 3;  // the most stages whose chunk fits a third of the ring
-        while (chunk_bytes(t.SPC + 1) <= third) ++t.SPC;
-        t.slot_bytes = chunk_bytes(t.SPC);
-        t.nslots = ring_bytes / t.slot_bytes < 4 ? ring_bytes / t.slot_bytes : 4;
-    }
+    while (chunk_bytes(t.SPC + 1) <= third) ++t.SPC;
+    t.slot_bytes = chunk_bytes(t.SPC);
+    t.nslots = ring_bytes / t.slot_bytes < 4 ? ring_bytes / t.slot_bytes : 4;
     t.nchunks = (nstages + t.SPC - 1) / t.SPC;
     t.last_cnt = nstages - (t.nchunks - 1) * t.SPC;
-    // waves that do not load: one per (column block, row group, stage group), plus in the stage-parallel
-    // form one wave per pair that only runs the ordered chain
-    t.ncomp = cb * t.nrg * t.SG + (t.SG > 1 ? cb * t.nrg : 0);
+    t.ncomp = cb * t.nrg;
     t.nload = kQWaves + kQLoaders - t.ncomp;
     t.inv_nload = (1u << 20) / (uint32_t)t.nload + 1u;
     return t;
@@ -349,142 +331,13 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
             slot_new = slot_c;
             slot_c = slot_c + 1 == nslots ? 0 : slot_c + 1;
         }
-        if (tp.SG > 1) __builtin_amdgcn_s_barrier();  // the barrier after which the last chunk's results are read
         if constexpr (EPI == kEpiSwigluQuant) __builtin_amdgcn_s_barrier();  // the epilogue's exchange of row maxima
         return;
     }
 
     // -------------------------------------------------------------------- computing wave
-    const int nstagew = CB * tp.nrg * tp.SG;  // waves that work on stages; any further non-loading wave runs a chain
-    const int pw = wave < nstagew ? wave : wave - nstagew;
-    const int j = pw % CB, rg = (pw / CB) % tp.nrg;  // column block and row group of the wave
-    const int cnt = (RB - rg + RG - 1) / RG;         // its row blocks: rg, rg + RG, ... (cnt >= 1 here)
-
-    // Stage-parallel form for tiles with fewer row blocks than row groups (M <= 16*(8/CB - 1)): one wave
-    // per (column block, row group) would leave most of the compute unit's vector units idle while it
-    // works through every stage by itself.  The SG waves of a pair split the stages of a chunk
-    // (stage sl -> wave sl % SG); for its stages a wave computes t = d*s and the block's integer
-    // product as fp32 (exact) and leaves both in LDS.  After the next barrier the pair's chain wave
-    // (a wave with no other work, so that the chain of chunk c runs beside the stage work of chunk
-    // c+1) runs acc = fma(t, P, acc) over the chunk's stages in ascending order: the chain, the only
-    // part whose order is defined, is the same sequence of operations as in the serial form.
-    auto run_sp = [&]() {
-        const int SG = tp.SG, npair = CB * tp.nrg;
-        const bool chain_wave = wave >= nstagew;
-        const int sg = wave / npair, pair = j + CB * rg;
-        // results of a stage: for each pair RT = TB/64 rows x 16 columns of t, then of P; lane (g, lr) holds the
-        // four columns 4g .. 4g+3 of row lr and takes part if its row is kept
-        const int RT = TB >> 6;
-        const int res_pair = RT * 128, res_stage = npair * res_pair;
-        const bool row_kept = lr < RT;
-        char* const resbase = reinterpret_cast<char*>(ring) + tp.res_off;
-        const int res_chunk = SPC * res_stage;
-        const int res_lane = pair * res_pair + (g * RT + lr) * 16;
-        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        auto chain = [&](int c) {
-            const int s_cnt = chunk_stages(c);
-            if (!row_kept) return;
-            const char* rr = resbase + (c & 1) * res_chunk + res_lane;
-            const int stride = res_stage, pf_off = RT * 64;
-            // eight stages' operands are read before their (ordered) chain runs, so that one LDS latency is
-            // paid per eight stages
-            constexpr int W = 8;
-            int sl = 0;
-            for (; sl + W <= s_cnt; sl += W) {
-                float4 t[W], pf[W];
-#pragma unroll
-                for (int u = 0; u < W; ++u) {
-                    t[u] = *reinterpret_cast<const float4*>(rr + u * stride);
-                    pf[u] = *reinterpret_cast<const float4*>(rr + u * stride + pf_off);
-                }
-#pragma unroll
-                for (int u = 0; u < W; ++u) {
-                    acc[0] = __builtin_fmaf(t[u].x, pf[u].x, acc[0]);
-                    acc[1] = __builtin_fmaf(t[u].y, pf[u].y, acc[1]);
-                    acc[2] = __builtin_fmaf(t[u].z, pf[u].z, acc[2]);
-                    acc[3] = __builtin_fmaf(t[u].w, pf[u].w, acc[3]);
-                }
-                rr += W * stride;
-            }
-            for (; sl < s_cnt; ++sl) {
-                const float4 t = *reinterpret_cast<const float4*>(rr);
-                const float4 pf = *reinterpret_cast<const float4*>(rr + pf_off);
-                acc[0] = __builtin_fmaf(t.x, pf.x, acc[0]);
-                acc[1] = __builtin_fmaf(t.y, pf.y, acc[1]);
-                acc[2] = __builtin_fmaf(t.z, pf.z, acc[2]);
-                acc[3] = __builtin_fmaf(t.w, pf.w, acc[3]);
-                rr += stride;
-            }
-        };
-        int slot_c = 0;
-        for (int c = 0; c < nchunks; ++c) {
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if (chain_wave) {
-                if (c > 0) chain(c - 1);
-                continue;
-            }
-            const int s_cnt = chunk_stages(c);
-            const char* slot = reinterpret_cast<const char*>(ring) + (size_t)slot_c * tp.slot_bytes;
-            const char* tiles = slot + wrun(s_cnt);
-            const char* scales = tiles + abytes_of(s_cnt);
-            char* rw = resbase + (c & 1) * res_chunk + res_lane;
-            // UU of the wave's stages at a time: all reads and matrix-core instructions first
-            auto stages = [&](int sl, auto uu_tag) {
-                constexpr int UU = decltype(uu_tag)::value;
-                v4i wu[UU], xa[UU];
-                uint2 sraw[UU];
-                float dv[UU];
-#pragma unroll
-                for (int u = 0; u < UU; ++u) {
-                    const int s = sl + u * SG;
-                    const char* wst = slot + s * WST;
-                    const uint2 codes = *reinterpret_cast<const uint2*>(wst + j * 512 + lane * 8);
-                    sraw[u] = *reinterpret_cast<const uint2*>(wst + 512 * CB + j * 32 + g * 8);
-                    xa[u] = *reinterpret_cast<const v4i*>(tiles + (size_t)(s * RB + rg) * TB + 64 * lrc +
-                                                          16 * (g ^ ((lrc >> 2) & 3)));
-                    dv[u] = *reinterpret_cast<const float*>(scales + (size_t)s * RB * 64 + (16 * rg + lr) * 4);
-                    wu[u] = code_bytes(codes);
-                }
-                v4i pr[UU];
-#pragma unroll
-                for (int u = 0; u < UU; ++u) pr[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[u], xa[u], kProductStart, 0, 0, 0);
-#pragma unroll
-                for (int u = 0; u < UU; ++u) {
-                    const int s = sl + u * SG;
-                    const float4 t = make_float4(dv[u] * bf16lo_to_f32(sraw[u].x), dv[u] * bf16hi_to_f32(sraw[u].x),
-                                                 dv[u] * bf16lo_to_f32(sraw[u].y), dv[u] * bf16hi_to_f32(sraw[u].y));
-                    const float4 pf = make_float4(product(pr[u][0]), product(pr[u][1]), product(pr[u][2]), product(pr[u][3]));
-                    if (row_kept) {
-                        *reinterpret_cast<float4*>(rw + (size_t)s * res_stage) = t;
-                        *reinterpret_cast<float4*>(rw + (size_t)s * res_stage + RT * 64) = pf;
-                    }
-                }
-            };
-            int sl = sg;
-            for (; sl + SG < s_cnt; sl += 2 * SG) stages(sl, std::integral_constant<int, 2>{});
-            for (; sl < s_cnt; sl += SG) stages(sl, std::integral_constant<int, 1>{});
-            slot_c = slot_c + 1 == nslots ? 0 : slot_c + 1;
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (!chain_wave) return;
-        chain(nchunks - 1);
-        const int n = blockIdx.x * (16 * CB) + 16 * j + 4 * g;
-        const int rowl = 16 * rg + lr;
-        if (rowl < mrem) {
-            const size_t row = (size_t)(m0 + rowl);
-            if constexpr (EPI == kEpiRopeAppend) {
-                int p = ra.pos[row];
-                p = p < 0 ? 0 : (p >= ra.Lmax ? ra.Lmax - 1 : p);
-                gemm_epilogue_rope_append(acc, ra, row, p, ra.slots ? ra.slots[row] : (int)row, n);
-            } else {
-                gemm_epilogue_store<EPI>(acc, C, ldc, R, ldr, row, n, out_f32);
-            }
-        }
-    };
-    if (tp.SG > 1) {
-        run_sp();
-        return;
-    }
+    const int j = wave % CB, rg = wave / CB;  // column block and row group of the wave
+    const int cnt = (RB - rg + RG - 1) / RG;  // its row blocks: rg, rg + RG, ... (cnt >= 1 here)
 
     char* const xres = reinterpret_cast<char*>(ring) + kQRing * 1024 - nstages * (64 * mrem + 16);  // NORM: codes, then scales
     char* const dres = xres + nstages * 64 * mrem;
@@ -1007,6 +860,10 @@ static void launch_qgemm(const void* qa, const void* da, int ldd, const void* wp
         }
     }
     const int tile_rows = qgemm_tile_rows(M, N, CB);
+    if (qgemm_mid_fits(M, CB, tile_rows)) {
+        qgemm_mid(EPI, CB, qgemm_few_args{qa, da, wp, C, ldc, R, ldr, M, N, K, out_f32, ra, nullptr, nullptr, 0.0f}, tile_rows, s);
+        return;
+    }
     dim3 grid(N / (16 * CB), (M + tile_rows - 1) / tile_rows);
     const qgemm_plan full = make_qgemm_plan(tile_rows, CB, K);
     const qgemm_plan tail = make_qgemm_plan(M - tile_rows * ((M - 1) / tile_rows), CB, K);
