@@ -543,23 +543,29 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
 // side by side of 16*RB rows x 16*JB columns each.  64 x 128 (RB 4, JB 2) where there are enough of them, 64 x 64 and 32 x 64
 // below (qgemm_pick).
 //
-// What bounds the first is the scaling arithmetic, three vector instructions per output and block (d*s, the subtraction that makes
-// the product a float, the fma), a wave having eight 16 x 16 outputs of it a block against eight matrix instructions, and a SIMD's
+// What bounds the first is the scaling arithmetic: the subtraction that makes the product a float and the fma, a vector instruction
+// each for every output and block, a wave having eight 16 x 16 outputs of it a block against eight matrix instructions, and a SIMD's
 // vector and matrix instructions add up: 16 clocks each of these, at best 2.3 each of those whatever the waves (measured
-// in a loop of nothing else), 410 clocks a wave and block, of which a launch reaches 75 %.  So a wave owns a tile that is
-// tall: it unpacks the codes of two column blocks for four row blocks.  The operands of two blocks of K (a chunk) travel
-// together through a ring of LDS slots, each wave loading its share; activation rows come as whole 128-byte lines.  Three slots
-// and three workgroups a compute unit (four slots and two workgroups measured 5 to 15 % slower).  The outer products d*s on the
-// matrix cores (four 16 x 16 x 1 of fp32 an instruction) were no faster: while they run a SIMD issues no vector
-// instruction.  Against the kernel above, us: 1962 rows K x N 2048 x 2048 92 -> 23, 5632 x 2048 227 -> 52, 14336 x 4096
-// 1084 -> 245, 2048 x 11264 160 -> 102, 4096 x 28672 593 -> 465 (0.99 POP/s).
+// in a loop of nothing else).  The products d*s come from the matrix cores, four tiles' outer products (16 x 16 x 1 of fp32) an
+// instruction of 32 clocks, where multiplies would take 42 and eight conversions of scales more; the bits are those of a multiply,
+// also where they are subnormal, infinite or NaN.  So a wave and block are some 400 clocks, of which a launch reaches two thirds.  A
+// wave owns a tile that is tall: it unpacks the codes of two column blocks for four row blocks.  The operands of two blocks of K (a
+// chunk) travel together through a ring of LDS slots, each wave loading its share; activation rows come as whole 128-byte lines.
+// Three slots and three workgroups a compute unit (four slots and two workgroups measured 5 to 15 % slower).  Outer products against
+// multiplies, us: 1962 rows K x N 2048 x 11264 102.4 -> 99.4, 2048 x 3072 34.1 -> 33.5, 2048 x 2048 and 5632 x 2048 level, 1000 rows of
+// 4096 x 6144 60.0 -> 56.9, 256 rows of 4096 x 28672 76.3 -> 73.2.  Against the kernel above: 1962 rows 2048 x 2048 92 -> 23, 5632 x 2048 227
+// -> 52, 14336 x 4096 1084 -> 245, 2048 x 11264 160 -> 99, 4096 x 28672 593 -> 465 (0.99 POP/s).
 //
 // A launch of fewer workgroups than the chip holds takes the time of one walk over K, a chain of 0.2 (32 x 64) to 0.45 us
 // (64 x 128) a block: loads' latency where the ring is short (32 x 64 tiles 0.25 us with three slots), one wave's instructions
 // otherwise (reading a chunk's operands while the chunk before it is computed gained nothing).  So the smaller the launch, the
-// smaller its tile: 4096 x 4096 33.5 -> 19 us at 192 rows, 14336 x 4096 106 -> 57, 5632 x 2048 at 500 rows 43 -> 26.
+// smaller its tile: 4096 x 4096 33.5 -> 19 us at 192 rows, 14336 x 4096 106 -> 57, 5632 x 2048 at 500 rows 43 -> 26.  The 64-column tiles
+// read a chunk's operands at once, in front of its arithmetic (with the outer products 100 rows of 4096 x 4096 17.2 -> 15.7 us, of
+// 2112 x 4096 10.3 -> 9.6, 300 of 14336 x 4096 71.1 -> 67.4); in 64 x 128 tiles, whose waves are enough to hide the reads, that was up to
+// 8 % slower.
 // Six and four slots, so that three workgroups of every size fit a compute unit.
 constexpr int kTileWaves = 4;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 __host__ __device__ constexpr int qtile_slots(int rb, int jb) { return rb * jb == 8 ? 3 : (rb * jb == 4 ? 4 : 6); }
 
 template <int N>
@@ -662,39 +668,46 @@ __global__ __launch_bounds__(64 * kTileWaves, 3) void qgemm_tile_kernel(
         if (c + NS - 1 < nchunks) issue(c + NS - 1);
         return reinterpret_cast<const char*>(ring) + (c % NS) * SLOT;
     };
-    auto block = [&](const char* slot, int s) __attribute__((always_inline)) {
-        const char* wslot = slot + ABYTES;
-        const char* dslot = wslot + WBYTES;
-        v4i xa[RB];
-        float dv[RB];
-        uint2 codes[JB], sraw[JB];
+    // t = d*s of four 16 x 16 tiles by one outer product: of the row blocks of a block of K, or of the two of both blocks of a chunk.
+    // Lane (b, i): column i's weight scale and row i's activation scale of tile b; register 4b + v: as register v of tile b's product.
+    struct Block {
+        uint2 codes[JB];
+        float s[JB], d;
+        v4i x[RB];
+    };
+    auto read_scales = [&](const char* slot, int s, Block& b) __attribute__((always_inline)) {
+        b.d = *reinterpret_cast<const float*>(slot + ABYTES + WBYTES + s * (TR * 4) + lane * 4);
 #pragma unroll
         for (int j = 0; j < JB; ++j) {
-            const int cbk = JB * wave + j;  // column block of the tile
-            const char* wst = wslot + (cbk / CB) * (2 * WST) + s * WST;
-            codes[j] = *reinterpret_cast<const uint2*>(wst + (cbk % CB) * 512 + lane * 8);
-            sraw[j] = *reinterpret_cast<const uint2*>(wst + 512 * CB + (cbk % CB) * 32 + g * 8);
+            const int cbk = JB * wave + j, st = RB == 4 ? s : lane >> 5;  // cbk: column block of the tile
+            const char* wst = slot + ABYTES + (cbk / CB) * (2 * WST) + st * WST;
+            b.s[j] = bf16_to_f32(*reinterpret_cast<const uint16_t*>(wst + 512 * CB + (cbk % CB) * 32 + lr * 2));
         }
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            xa[r] = *reinterpret_cast<const v4i*>(slot + (16 * r + lr) * 128 + (((4 * s + g) ^ zr) << 4));
-            dv[r] = *reinterpret_cast<const float*>(dslot + s * (TR * 4) + (16 * r + lr) * 4);
-        }
-        v4i wu[JB];
-        float sc[JB][4];
+    };
+    auto read_codes = [&](const char* slot, int s, Block& b) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < JB; ++j) {
-            wu[j] = code_bytes(codes[j]);
-            sc[j][0] = bf16lo_to_f32(sraw[j].x);
-            sc[j][1] = bf16hi_to_f32(sraw[j].x);
-            sc[j][2] = bf16lo_to_f32(sraw[j].y);
-            sc[j][3] = bf16hi_to_f32(sraw[j].y);
+            const int cbk = JB * wave + j;
+            const char* wst = slot + ABYTES + (cbk / CB) * (2 * WST) + s * WST;
+            b.codes[j] = *reinterpret_cast<const uint2*>(wst + (cbk % CB) * 512 + lane * 8);
         }
-        v4i pr[RB][JB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) b.x[r] = *reinterpret_cast<const v4i*>(slot + (16 * r + lr) * 128 + (((4 * s + g) ^ zr) << 4));
+    };
+    f32x16 t[JB];
+    auto scales = [&](const Block& b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < JB; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x1f32(b.s[j], b.d, f32x16{}, 0, 0, 0);
+    };
+    auto products = [&](const Block& b, auto first) __attribute__((always_inline)) {
+        constexpr int T0 = 4 * decltype(first)::value;
+        v4i wu[JB], pr[RB][JB];
+#pragma unroll
+        for (int j = 0; j < JB; ++j) wu[j] = code_bytes(b.codes[j]);
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
 #pragma unroll
-            for (int j = 0; j < JB; ++j) pr[r][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[j], xa[r], kProductStart, 0, 0, 0);
+            for (int j = 0; j < JB; ++j) pr[r][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wu[j], b.x[r], kProductStart, 0, 0, 0);
         }
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -702,14 +715,43 @@ __global__ __launch_bounds__(64 * kTileWaves, 3) void qgemm_tile_kernel(
             for (int j = 0; j < JB; ++j)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    acc[r][j][v] = __builtin_fmaf(dv[r] * sc[j][v], product(pr[r][j][v]), acc[r][j][v]);
+                    acc[r][j][v] = __builtin_fmaf(t[j][T0 + 4 * r + v], product(pr[r][j][v]), acc[r][j][v]);
     };
+    static_assert(RB == 4 || RB == 2, "four tiles an outer product");
+    using zeroth = std::integral_constant<int, 0>;
+    using second = std::integral_constant<int, RB == 4 ? 0 : 2>;
     for (int c = 0; c < (nblk >> 1); ++c) {
         const char* slot = open(c);
-        block(slot, 0);
-        block(slot, 1);
+        Block b0, b1;
+        if constexpr (JB == 1) {
+            read_scales(slot, 0, b0);
+            read_codes(slot, 0, b0);
+            if constexpr (RB == 4) read_scales(slot, 1, b1);
+            read_codes(slot, 1, b1);
+            __builtin_amdgcn_sched_barrier(0);
+            scales(b0);
+            products(b0, zeroth{});
+            if constexpr (RB == 4) scales(b1);
+            products(b1, second{});
+        } else {
+            read_scales(slot, 0, b0);
+            scales(b0);
+            read_codes(slot, 0, b0);
+            products(b0, zeroth{});
+            read_scales(slot, 1, b1);
+            scales(b1);
+            read_codes(slot, 1, b1);
+            products(b1, zeroth{});
+        }
     }
-    if (nblk & 1) block(open(nchunks - 1), 0);
+    if (nblk & 1) {
+        const char* slot = open(nchunks - 1);
+        Block b0;
+        read_scales(slot, 0, b0);
+        read_codes(slot, 0, b0);
+        scales(b0);
+        products(b0, zeroth{});
+    }
 
     // Lane holds C[row = m0 + 16r + lr][n0 + 16*JB*wave + 16j + 4g + v].
     const int n = n0 + 16 * JB * wave + 4 * g;
@@ -794,8 +836,9 @@ static int qgemm_tile_rows(int M, int N, int cb)
 // The kernel and tile of a launch, a function of M, N and the packing (which is one of N).
 //   * `rows`, the height of the tiles the kernel above would cut the launch into, decides whether it does: a stage
 //     of it takes about 0.0025 us a row from 64 rows on, and a chain of 32 x 64 tiles 0.2 us a block, less against wider
-//     packings.  They meet at about 90, 80 and 60 rows (us there and here: N = 4096, K = 4096 80 rows 15.7 and 17.0, 96 rows
-//     18.5 and 17.1; N = 6144 64 rows 15.6 and 18.4, 80 rows 18.9 and 18.6; 2048 x 11264 48 rows 10.4 and 10.8, 64 rows 11.9 and 11.0).
+//     packings.  They meet at about 90, 65 and 49 rows of 16-, 32- and 64-column packings (us there and here: K x N 4096 x 4096 80 rows
+//     15.5 and 15.7, 96 rows 18.5 and 15.6, 14336 x 4096 80 rows 41.6 and 47.6; 4096 x 6144 64 rows 15.3 and 15.6, 72 rows 18.7 and 17.7;
+//     2048 x 11264 48 rows level, 49 rows 12.0 and 10.8).
 //     128-column packings have no tile of 64 columns; they meet 64 x 128 tiles between 64 and 96 rows (28672: 31.6 and
 //     35.6, 44.8 and 38.5).
 //   * The smallest tile of which the chip holds all (768): 2048 x 11264 128 rows, 704 of 32 x 64: 13.2 us against 14.7 in 64 x 64 and
@@ -809,7 +852,7 @@ static qgemm_form qgemm_pick(int M, int N, int cb)
     const int tile_rows = qgemm_tile_rows(M, N, cb), rows = tile_rows < M ? tile_rows : M;
     if (M > 65535 * 64 || N % 64 != 0) return kQBase;
     if (cb == 8) return rows > 80 && qtiles(M, N, 64, 128) >= 256 ? kQ64x128 : kQBase;
-    if (rows + 10 * cb < 100) return kQBase;
+    if (rows < (cb == 1 ? 90 : (cb == 2 ? 65 : 49))) return kQBase;
     if (qtiles(M, N, 32, 64) <= kHeld) return kQ32x64;
     return qtiles(M, N, 64, 64) <= kHeld || N % 128 != 0 ? kQ64x64 : kQ64x128;
 }
