@@ -761,10 +761,13 @@ __global__ __launch_bounds__(256, 2) void attn_left_kernel(const uint16_t* __res
 // ------------------------------------------------------------------ attention, pass 2
 
 // Grid (query head, sequence); 128 threads, thread = d.  The arithmetic is the ascending-chunk fold
-// of the canonical order; only the data movement is parallel: the chunk maxima are reduced across
-// the threads (max is exact, so order free), the weights w_c = det_expf(m_c - m) are computed one
-// chunk per thread into LDS, and each thread then folds L and its own O[d] over the chunks in
-// ascending order with the loads of 8 chunks in flight at a time.
+// of the canonical order; only the data movement is parallel.  What bounds it is its chain of memory round trips: the
+// length, beside it the statistics, then the first eight chunks' sums, asked for in front of everything that needs the
+// statistics; the next eight while these are folded.  Each of the two waves has the statistics of 64 chunks in its lanes (the
+// maximum is exact, so order free; the weights w_c = det_expf(m_c - m) one chunk a lane) and hands them out as scalars, without LDS
+// and barriers.  Both passes, us, with the statistics through LDS, twice from memory, in front of the sums, and now: one
+// sequence of 512 tokens, 16/4 heads 7.9 -> 7.0, of 4096, 32/8 9.8 -> 9.3; 24 of 30 to 536, 16/4 11.5 -> 10.6, of 100 to 1024 14.5 -> 13.0;
+// 32 of 1024 to 2048, 32/8 42.9 -> 40.6; 48 of 200 to 4096 87.3 -> 84.9; two of 32768 level.
 // QUANT: instead of the bf16 output row the kernel writes its 8-bit block quantization (the bytes
 // det_quant_act_q8 makes of it): a wave's 64 values are one block, so the block maximum is a wave
 // reduction; `out` is then the int8 code array [B, Hq*128] and `scales` the block-major scale array
@@ -775,9 +778,6 @@ __device__ __forceinline__ void attn_combine(int h, int b, int len, const float*
                                              void* __restrict__ out, int Hq, int ncmax, float* __restrict__ scales, int ldd,
                                              int first_pass_wrote_short_rows)
 {
-    __shared__ float s_w[128];
-    __shared__ float s_l[128];
-    __shared__ float s_red[2];
     const int d = threadIdx.x;
     const size_t o_idx = ((size_t)b * Hq + h) * kD + d;
     auto store = [&](uint16_t y) {
@@ -785,9 +785,7 @@ __device__ __forceinline__ void attn_combine(int h, int b, int len, const float*
             static_cast<uint16_t*>(out)[o_idx] = y;
         } else {
             const float a = bf16_to_f32(y);
-            float amax = fabsf(a);
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, kWave));
+            const float amax = max_lanes(fabsf(a));
             const float df = amax / 127.0f;
             int v = 0;
             if (df != 0.0f) {
@@ -798,51 +796,57 @@ __device__ __forceinline__ void attn_combine(int h, int b, int len, const float*
             if ((d & 63) == 0) scales[(size_t)(2 * h + (d >> 6)) * ldd + b] = df;
         }
     };
+    const int lane = d & 63;
+    const size_t part = ((size_t)b * Hq + h) * ncmax;
+    float mc = lane < ncmax ? ws_m[part + lane] : 0.0f, lc = lane < ncmax ? ws_l[part + lane] : 0.0f;  // (what is past the length is not used)
     if (first_pass_wrote_short_rows && len <= kChunk) return;  // rows of at most one chunk are complete (uniform)
     if (len <= 0) {  // uniform over the workgroup
         store(0);
         return;
     }
     const int nc = (len + kChunk - 1) / kChunk;
-    const size_t part = ((size_t)b * Hq + h) * ncmax;
-    float m = -INFINITY;
-    for (int c = d; c < nc; c += 128) m = fmaxf(m, ws_m[part + c]);
+    const float* op = ws_o + part * kD + d;
+    constexpr int W = 8;
+    float o[W];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
-    if ((d & 63) == 0) s_red[d >> 6] = m;
-    __syncthreads();
-    m = fmaxf(s_red[0], s_red[1]);
+    for (int u = 0; u < W; ++u) o[u] = op[(size_t)min(u, nc - 1) * kD];
+    float m = lane < nc ? mc : -INFINITY;
+    for (int c = lane + kWave; c < nc; c += kWave) m = fmaxf(m, ws_m[part + c]);
+    m = max_lanes(m);
 
     float L = 0.0f, O = 0.0f;
-    for (int c0 = 0; c0 < nc; c0 += 128) {
-        const int n = min(128, nc - c0);
-        __syncthreads();  // the previous tile's s_w / s_l are no longer read
-        if (d < n) {
-            s_w[d] = det_expf(ws_m[part + c0 + d] - m);
-            s_l[d] = ws_l[part + c0 + d];
+    for (int c0 = 0; c0 < nc; c0 += kWave) {
+        const int n = min(kWave, nc - c0);
+        if (c0 > 0) {
+            mc = lane < n ? ws_m[part + c0 + lane] : 0.0f;
+            lc = lane < n ? ws_l[part + c0 + lane] : 0.0f;
         }
-        __syncthreads();
-        const float* op = ws_o + (part + c0) * kD + d;
-        int c = 0;
-        for (; c + 8 <= n; c += 8) {
-            float o[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) o[u] = op[(size_t)(c + u) * kD];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float w = s_w[c + u];
-                const float wl = w * s_l[c + u];
-                L = L + wl;
-                const float wo = w * o[u];
-                O = O + wo;
-            }
-        }
-        for (; c < n; ++c) {
-            const float w = s_w[c];
-            const float wl = w * s_l[c];
-            L = L + wl;
-            const float wo = w * op[(size_t)c * kD];
+        const float w = det_expf(mc - m);
+        const float wl = w * lc;
+        auto fold = [&](int c, float oc) __attribute__((always_inline)) {
+            L = L + bitsf((uint32_t)__builtin_amdgcn_readlane((int)fbits(wl), c));
+            const float wo = bitsf((uint32_t)__builtin_amdgcn_readlane((int)fbits(w), c)) * oc;
             O = O + wo;
+        };
+        for (int c = 0; c < n; c += W) {
+            float next[W];
+            const bool more = c0 + c + W < nc;
+            if (more) {
+#pragma unroll
+                for (int u = 0; u < W; ++u) next[u] = op[(size_t)min(c0 + c + W + u, nc - 1) * kD];
+            }
+            if (c + W <= n) {
+#pragma unroll
+                for (int u = 0; u < W; ++u) fold(c + u, o[u]);
+            } else {
+#pragma unroll
+                for (int u = 0; u < W - 1; ++u)
+                    if (c + u < n) fold(c + u, o[u]);
+            }
+            if (more) {
+#pragma unroll
+                for (int u = 0; u < W; ++u) o[u] = next[u];
+            }
         }
     }
     store(f32_to_bf16_rne(O / L));

@@ -48,6 +48,16 @@ __device__ __forceinline__ float max_rows(float v)
     return fmaxf(bitsf(r[0]), bitsf(r[1]));
 }
 
+// maximum over the wave, in every lane
+__device__ __forceinline__ float max_lanes(float v)
+{
+    v = fmaxf(v, row_ror<8>(v));
+    v = fmaxf(v, row_ror<4>(v));
+    v = fmaxf(v, row_ror<2>(v));
+    v = fmaxf(v, row_ror<1>(v));
+    return max_rows(v);
+}
+
 // Where the pieces of a K row lie (piece p at p ^ k_swizzle): row 4q + r of an operand block.  A read of sixteen bytes a lane is
 // served in quarters of lanes 0-3, 12-15 and, of the next sixteen, 4-11 (the other way round in the second), which ask for
 // pieces four apart: with the row's own number as the swizzle the two halves met in the same banks.

@@ -35,7 +35,7 @@ __host__ __device__ constexpr int few_lds_bytes(int M, int cb, int K, bool norm)
 // acc = fma(t, P, acc) over all blocks in ascending order, which is all that has an order, eight batches (one of each producer)
 // at a time.  Only those waves wait for others, so every wait ends.
 // Against the general kernel, one row, us: K x N 2048 x 2048 5.8 -> 3.5, 4096 x 4096 7.7 -> 5.0, 4096 x 6144 9.9 -> 6.2, 2048 x 11264
-// 8.4 -> 6.3, 5632 x 2048 9.1 -> 5.4, 14336 x 4096 15.5 -> 11.2; 40 random launches of one to four rows 1.4 to 2.5 times as fast, the
+// 8.4 -> 6.3, 5632 x 2048 9.1 -> 5.3, 14336 x 4096 15.5 -> 10.9; 40 random launches of one to four rows 1.4 to 2.5 times as fast, the
 // same bytes.  (A launch of nothing takes 1.85, the loads alone of 14336 x 4096 9.4.)  What bounded earlier forms was the number
 // of LDS instructions: an operand, scales and results for every single block of one to four rows instead of for four blocks took 13.7.
 // 128-column packings stay with the general kernel: 2048 x 32000 11.2 there and 12.7 here.
