@@ -28,6 +28,8 @@
 
 namespace det {
 
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
 constexpr int kQRing = 144;   // KB of LDS ring
 constexpr int kQWaves = 8;    // waves that can compute
 constexpr int kQLoaders = 4;  // waves that only load
@@ -416,35 +418,28 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
                 constexpr int UU = decltype(uu_tag)::value;
                 constexpr int G = NR < 4 ? NR : 4;  // row blocks at a time
                 v4i wq[UU];
-                float sc[UU][4];
 #pragma unroll
-                for (int u = 0; u < UU; ++u) {
-                    const char* wst = slot + (sl + u) * WST;
-                    const uint2 codes = *reinterpret_cast<const uint2*>(wst + j * 512 + lane * 8);
-                    const uint2 sraw = *reinterpret_cast<const uint2*>(wst + 512 * CB + j * 32 + g * 8);
-                    wq[u] = code_bytes(codes);
-                    sc[u][0] = bf16lo_to_f32(sraw.x);
-                    sc[u][1] = bf16hi_to_f32(sraw.x);
-                    sc[u][2] = bf16lo_to_f32(sraw.y);
-                    sc[u][3] = bf16hi_to_f32(sraw.y);
-                }
+                for (int u = 0; u < UU; ++u)
+                    wq[u] = code_bytes(*reinterpret_cast<const uint2*>(slot + (sl + u) * WST + j * 512 + lane * 8));
+                // The products d*s of the UU * G tiles, tile u*G + r, as one outer product (as in qgemm_tile_kernel below): this lane's
+                // scales are those of tile g.  us against four conversions a stage, a multiply for each output and a load of scales for each
+                // tile: 4096 x 28672 16 rows 15.3 -> 14.7, 24 rows 20.2 -> 18.9, 48 rows 29.5 -> 25.8, 64 rows 31.1 -> 27.2; 2048 x 11264
+                // 8 rows 7.9 -> 7.4, 48 rows 11.1 -> 10.8; 4096 x 6144 64 rows 16.0 -> 15.4.
+                const int ub = sl + min(g / G, UU - 1), rb = g % G;
+                const float sa = bf16_to_f32(*reinterpret_cast<const uint16_t*>(slot + ub * WST + 512 * CB + j * 32 + lr * 2));
 #pragma unroll
                 for (int r0 = 0; r0 < NR; r0 += G) {
                     v4i pr[UU][G];
-                    float dv[UU][G];
+                    const char* dp = scales + (size_t)ub * RB * 64 + (16 * (rg + RG * min(r0 + rb, cnt - 1)) + lr) * 4;
+                    if constexpr (NORM) dp = dres + 16 * (c * SPC + ub) + 4 * lrow;
+                    const f32x16 t = __builtin_amdgcn_mfma_f32_16x16x1f32(sa, *reinterpret_cast<const float*>(dp), f32x16{}, 0, 0, 0);
 #pragma unroll
                     for (int u = 0; u < UU; ++u)
 #pragma unroll
                         for (int r = 0; r < G; ++r) {
                             const char* xp = tiles + (size_t)((sl + u) * RB + rbs[r0 + r]) * TB + 64 * lrc + 16 * (g ^ ((lrc >> 2) & 3));
-                            const char* dp = scales + (size_t)(sl + u) * RB * 64 + (16 * rbs[r0 + r] + lr) * 4;
-                            if constexpr (NORM) {
-                                const int st = c * SPC + sl + u;
-                                xp = xres + (st * mrem + lrow) * 64 + 16 * g;
-                                dp = dres + 16 * st + 4 * lrow;
-                            }
+                            if constexpr (NORM) xp = xres + ((c * SPC + sl + u) * mrem + lrow) * 64 + 16 * g;
                             const v4i xa = *reinterpret_cast<const v4i*>(xp);
-                            dv[u][r] = *reinterpret_cast<const float*>(dp);
                             pr[u][r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wq[u], xa, kProductStart, 0, 0, 0);
                         }
 #pragma unroll
@@ -453,7 +448,7 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
                         for (int r = 0; r < G; ++r)
 #pragma unroll
                             for (int v = 0; v < 4; ++v)
-                                acc[r0 + r][v] = __builtin_fmaf(dv[u][r] * sc[u][v], product(pr[u][r][v]), acc[r0 + r][v]);
+                                acc[r0 + r][v] = __builtin_fmaf(t[4 * (u * G + r) + v], product(pr[u][r][v]), acc[r0 + r][v]);
                 }
             };
             constexpr int U = NR == 1 ? 4 : (NR == 2 ? 2 : 1);
@@ -565,7 +560,6 @@ __global__ __launch_bounds__(64 * (kQWaves + kQLoaders)) void qgemm_kernel(
 // 8 % slower.
 // Six and four slots, so that three workgroups of every size fit a compute unit.
 constexpr int kTileWaves = 4;
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 __host__ __device__ constexpr int qtile_slots(int rb, int jb) { return rb * jb == 8 ? 3 : (rb * jb == 4 ? 4 : 6); }
 
 template <int N>
@@ -837,7 +831,7 @@ static int qgemm_tile_rows(int M, int N, int cb)
 //   * `rows`, the height of the tiles the kernel above would cut the launch into, decides whether it does: a stage
 //     of it takes about 0.0025 us a row from 64 rows on, and a chain of 32 x 64 tiles 0.2 us a block, less against wider
 //     packings.  They meet at about 90, 80 and 60 rows of 16-, 32- and 64-column packings (us there and here: K x N 4096 x 4096 80 rows
-//     15.5 and 15.7, 96 rows 18.5 and 15.6, 14336 x 4096 80 rows 41.6 and 47.6; 4096 x 6144 64 rows 15.3 and 15.6, 80 rows 18.9 and 17.7;
+//     15.1 and 15.7, 96 rows 18.5 and 15.6, 14336 x 4096 80 rows 41.6 and 47.6; 4096 x 6144 64 rows 15.3 and 15.6, 80 rows 18.9 and 17.7;
 //     2048 x 11264 48 rows level, 64 rows 11.9 and 11.0; since the scale products are outer products the latter two meet at 65 and 49
 //     rows, 4096 x 6144 72 rows 18.7 and 17.7, 2048 x 11264 49 rows 12.0 and 10.8: the lines stay with the revision tiles-7).
 //     128-column packings have no tile of 64 columns; they meet 64 x 128 tiles between 64 and 96 rows (28672: 31.6 and

@@ -1,4 +1,4 @@
-"""Scale products of the quantized GEMM's tiles: subnormal, zero, infinite and NaN scales, odd and even counts of blocks.  A row's bits
+"""Scale products of the quantized GEMM's tiles and of its kernel of fewer rows: subnormal, zero, infinite and NaN scales, odd and even counts of blocks.  A row's bits
 are those of the row by itself, whose products are taken by vector multiplies."""
 import numpy as np
 import pytest
@@ -17,7 +17,10 @@ def d():
 
 
 # tiles of 32 x 64, 64 x 64 and 64 x 128; packings of 16, 32, 64 and 128 columns
-@pytest.mark.parametrize("M,K,N", [(97, 64 * 9, 4096), (250, 64, 11264), (191, 64 * 8, 11264), (300, 64 * 3, 4096), (1000, 64 * 5, 6144), (131, 64 * 2, 28672)])
+@pytest.mark.parametrize("M,K,N", [(97, 64 * 9, 4096), (250, 64, 11264), (191, 64 * 8, 11264), (300, 64 * 3, 4096), (1000, 64 * 5, 6144), (131, 64 * 2, 28672),
+                                   # fewer rows: one, two, three to four, eight and more row blocks of a wave, stages that do not come out even
+                                   (13, 64 * 7, 28672), (30, 64 * 5, 28672), (61, 64 * 3, 28672), (80, 64 * 2, 28672), (14, 64 * 5, 11264), (41, 64 * 3, 11264),
+                                   (70, 64 * 3, 4096), (300, 64 * 3, 5072)])
 def test_rows_equal_single_rows(d, M, K, N):
     a = ds.normal_bf16_torch(ds.tensor_seed(6, 820) + K + N, (M, K), 1.0, 0.0, DEV)
     for i, factor in enumerate((2.0 ** -100, 2.0 ** -120, 0.0, float("inf"), float("nan"))):
@@ -35,7 +38,7 @@ def test_rows_equal_single_rows(d, M, K, N):
     d.det_qgemm_w4a8(codes, scales, packed, c, N)
     torch.cuda.synchronize()
     assert torch.isnan(c[3]).any() and (c[2, :].abs().sum() if K == 64 else torch.zeros(())) == 0
-    for i in (*range(8), 31, 32, 63, 64, M - 1):
+    for i in (*range(8), *(i for i in (15, 16, 31, 32, 63, 64) if i < M), M - 1):
         codes1, scales1 = d.quant_activations(a[i:i + 1].contiguous())
         one = torch.full((1, N), 7.0, dtype=torch.float32, device=DEV)
         d.det_qgemm_w4a8(codes1, scales1, packed, one, N)
