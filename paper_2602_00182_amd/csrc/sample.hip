@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256) void sample_kernel(const float* __restrict__ l
 //
 // Up to top-k 256 the candidates come from group maxima: at least k of G groups of threads hold a logit that is at least the k-th
 // largest of the groups' largest logits, so that value bounds the k-th largest logit of the row from below, and with G of
-// two to four times k few more than k logits reach it (of 32000 normal ones some 65 for k = 50).  Dividing by the temperature keeps
+// two to four times k few more than k logits reach it (of 32000 normal ones some 65 for k = 50).  Dividing by a finite temperature keeps
 // the order up to ties, so only the logits that may reach the bound's quotient are divided.
 // What bounds it is one chain in one workgroup a row: the row's 128 KB (9 us of 16 with loads of four bytes and a division for
 // each logit), then steps that wait for LDS.  64 rows of 32000, us before (the k-th largest of the threads' maxima by two
@@ -209,7 +209,8 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
     // 0xFFFFFFFF - index).  An absent one is 0, below every real one.
     uint32_t zk[KPT];
     constexpr bool kLate = KPT <= 32;  // (of 64 a thread they are divided first: keys and divisions do not fit the registers)
-    bool divided = !kLate || k > kBoundTopK;
+    // (an infinite temperature changes the order: +inf / T is NaN, behind the zeros that finite logits become)
+    bool divided = !kLate || k > kBoundTopK || !(temperature < INFINITY);
     {
         float x[KPT];
         if constexpr (VEC) {
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel_reg(const float*
         // `low`: every logit whose quotient reaches the bound's has this key or a larger one
         const float bound = order_key_inv(max(bound_key, 1u)), quotient = bound / temperature;
         uint32_t low;
-        if (!kLate) {
+        if (divided) {
             low = max(bound_key, 1u);
         } else if (fabsf(bound) >= 0x1p-100f && fabsf(quotient) >= 0x1p-100f && fabsf(bound) <= 0x1p120f && fabsf(quotient) <= 0x1p120f) {
             low = order_key(bound - fabsf(bound) * 0x1p-20f);  // 2^-20 below it is more than a rounding away

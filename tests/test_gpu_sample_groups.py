@@ -47,3 +47,21 @@ def test_sizes(d, orc, V, k):
 @pytest.mark.parametrize("k", [50, 100])
 def test_temperatures(d, orc, T, k):
     check(d, orc, rows(5000, k), k, T)
+
+
+# Divided by an infinite temperature, +inf is no number and comes behind the finite logits, which are all zeros.  Rows where groups of
+# either kind are fewer than k, both together more.  A call before it leaves sorted lists of its own in every compute unit's LDS.
+@pytest.mark.parametrize("V", [513, 5000, 8201, 40000])
+@pytest.mark.parametrize("k", [2, 50, 100, 200, 300])
+def test_infinite_temperature(d, orc, V, k):
+    x = np.full((8, V), -np.inf, np.float32)
+    x[0, 0], x[0, 8 * (V // 16)] = np.inf, 5.0
+    for row, apart in zip(x[1:4], (4, 16, 64)):
+        row[::apart], row[apart // 2::apart] = np.inf, 5.0
+    x[4:6] = rows(V, V + k)[[0, 5]]
+    x[5, ::7] = np.inf
+    x[6] = np.inf
+    before = np.random.default_rng(V).standard_normal((1024, V)).astype(np.float32) + 60
+    n = torch.zeros(1024, dtype=torch.int32, device=DEV)
+    d.det_sample(torch.from_numpy(before).to(DEV), 1.0, 1000, 0.95, 99, n, n, torch.empty_like(n))
+    check(d, orc, x, k, float("inf"))
