@@ -228,21 +228,8 @@ __device__ __forceinline__ void rope_pair(uint16_t xlo, uint16_t xhi, float c, f
 
 // kEpiRopeAppend for one lane: packed columns n..n+3 of head n / 128 are the pairs i0 = (n % 128) / 2
 // and i0 + 1; p and slot are the row's (clamped) position and cache slot.
-struct rope_factors {
-    float2 c, s;
-};
-__device__ __forceinline__ rope_factors gemm_rope_factors(const gemm_rope_args& ra, int p, int n)
-{
-    rope_factors f{make_float2(0.f, 0.f), make_float2(0.f, 0.f)};
-    if ((n >> 7) < ra.Hq + ra.Hkv) {  // value heads are copied
-        const size_t at = (size_t)p * 64 + ((n & 127) >> 1);
-        f.c = *reinterpret_cast<const float2*>(ra.cos_t + at);
-        f.s = *reinterpret_cast<const float2*>(ra.sin_t + at);
-    }
-    return f;
-}
 __device__ __forceinline__ void gemm_epilogue_rope_append(const float (&v)[4], const gemm_rope_args& ra, size_t row,
-                                                          int p, int slot, int n, const rope_factors& f)
+                                                          int p, int slot, int n)
 {
     constexpr int D = 128, half = 64;
     const int head = n >> 7, i0 = (n & (D - 1)) >> 1;
@@ -251,8 +238,10 @@ __device__ __forceinline__ void gemm_epilogue_rope_append(const float (&v)[4], c
     for (int e = 0; e < 4; ++e) x[e] = f32_to_bf16_rne(v[e]);
     uint16_t* dst;
     if (head < ra.Hq + ra.Hkv) {
-        rope_pair(x[0], x[1], f.c.x, f.s.x, lo0, hi0);
-        rope_pair(x[2], x[3], f.c.y, f.s.y, lo1, hi1);
+        const float2 c = *reinterpret_cast<const float2*>(ra.cos_t + (size_t)p * half + i0);
+        const float2 s = *reinterpret_cast<const float2*>(ra.sin_t + (size_t)p * half + i0);
+        rope_pair(x[0], x[1], c.x, s.x, lo0, hi0);
+        rope_pair(x[2], x[3], c.y, s.y, lo1, hi1);
         dst = head < ra.Hq ? ra.qbuf + (row * ra.Hq + head) * D
                            : ra.kcache + (((size_t)slot * ra.Hkv + (head - ra.Hq)) * ra.Lmax + p) * D;
     } else {
@@ -262,30 +251,12 @@ __device__ __forceinline__ void gemm_epilogue_rope_append(const float (&v)[4], c
     *reinterpret_cast<uint32_t*>(dst + i0) = lo0 | ((uint32_t)lo1 << 16);
     *reinterpret_cast<uint32_t*>(dst + half + i0) = hi0 | ((uint32_t)hi1 << 16);
 }
-__device__ __forceinline__ void gemm_epilogue_rope_append(const float (&v)[4], const gemm_rope_args& ra, size_t row,
-                                                          int p, int slot, int n)
-{
-    gemm_epilogue_rope_append(v, ra, row, p, slot, n, gemm_rope_factors(ra, p, n));
-}
 
 __device__ __forceinline__ float silu_mul(float gate, float up)
 {
     const float den = 1.0f + det_expf(-gate);
     const float sg = gate / den;
     return sg * up;
-}
-
-// kEpiResidual for one lane: rv holds the residual's four values.
-__device__ __forceinline__ uint2 gemm_residual(const float (&v)[4], const uint2& rv)
-{
-    float y[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] = bf16_to_f32(f32_to_bf16_rne(v[e]));
-    y[0] = y[0] + bf16lo_to_f32(rv.x);
-    y[1] = y[1] + bf16hi_to_f32(rv.x);
-    y[2] = y[2] + bf16lo_to_f32(rv.y);
-    y[3] = y[3] + bf16hi_to_f32(rv.y);
-    return make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
 }
 
 // The epilogue of one lane's four consecutive output columns v[0..3] of row `row`, first column n
@@ -301,7 +272,15 @@ __device__ __forceinline__ void gemm_epilogue_store(const float (&v)[4], void* C
         *dst = pack_bf16x2(silu_mul(g0, u0), silu_mul(g1, u1));
     } else if constexpr (EPI == kEpiResidual) {
         const uint2 rv = *reinterpret_cast<const uint2*>(R + row * ldr + n);
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(C) + row * ldc + n) = gemm_residual(v, rv);
+        float y[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = bf16_to_f32(f32_to_bf16_rne(v[e]));
+        y[0] = y[0] + bf16lo_to_f32(rv.x);
+        y[1] = y[1] + bf16hi_to_f32(rv.x);
+        y[2] = y[2] + bf16lo_to_f32(rv.y);
+        y[3] = y[3] + bf16hi_to_f32(rv.y);
+        uint2* dst = reinterpret_cast<uint2*>(static_cast<uint16_t*>(C) + row * ldc + n);
+        *dst = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
     } else if (out_f32) {
         float4* dst = reinterpret_cast<float4*>(static_cast<float*>(C) + row * ldc + n);
         *dst = make_float4(v[0], v[1], v[2], v[3]);

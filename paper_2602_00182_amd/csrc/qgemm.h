@@ -47,6 +47,58 @@ __device__ __forceinline__ void await(const int* counters, int n, int need)
     }
 }
 
+// Epilogues for waves that read what they need besides the sums before these are there: kEpiResidual from the residual's four
+// values, kEpiRopeAppend from the pairs' cosines and sines.  The same operations as gemm_epilogue_store and
+// gemm_epilogue_rope_append, which stay in one piece: made of these parts they compile to other code for the kernels that read at
+// the end (the wide bf16 tiles 7 % more instructions; one row of 4096 x 4096 with the residual 8.01 us instead of 7.89 on one
+// card, level on two others).
+__device__ __forceinline__ uint2 gemm_residual(const float (&v)[4], const uint2& rv)
+{
+    float y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = bf16_to_f32(f32_to_bf16_rne(v[e]));
+    y[0] = y[0] + bf16lo_to_f32(rv.x);
+    y[1] = y[1] + bf16hi_to_f32(rv.x);
+    y[2] = y[2] + bf16lo_to_f32(rv.y);
+    y[3] = y[3] + bf16hi_to_f32(rv.y);
+    return make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+}
+
+struct rope_factors {
+    float2 c, s;
+};
+__device__ __forceinline__ rope_factors gemm_rope_factors(const gemm_rope_args& ra, int p, int n)
+{
+    rope_factors f{make_float2(0.f, 0.f), make_float2(0.f, 0.f)};
+    if ((n >> 7) < ra.Hq + ra.Hkv) {  // value heads are copied
+        const size_t at = (size_t)p * 64 + ((n & 127) >> 1);
+        f.c = *reinterpret_cast<const float2*>(ra.cos_t + at);
+        f.s = *reinterpret_cast<const float2*>(ra.sin_t + at);
+    }
+    return f;
+}
+__device__ __forceinline__ void gemm_rope_append(const float (&v)[4], const gemm_rope_args& ra, size_t row, int p, int slot, int n,
+                                                 const rope_factors& f)
+{
+    constexpr int D = 128, half = 64;
+    const int head = n >> 7, i0 = (n & (D - 1)) >> 1;
+    uint16_t x[4], lo0, hi0, lo1, hi1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = f32_to_bf16_rne(v[e]);
+    uint16_t* dst;
+    if (head < ra.Hq + ra.Hkv) {
+        rope_pair(x[0], x[1], f.c.x, f.s.x, lo0, hi0);
+        rope_pair(x[2], x[3], f.c.y, f.s.y, lo1, hi1);
+        dst = head < ra.Hq ? ra.qbuf + (row * ra.Hq + head) * D
+                           : ra.kcache + (((size_t)slot * ra.Hkv + (head - ra.Hq)) * ra.Lmax + p) * D;
+    } else {
+        lo0 = x[0], hi0 = x[1], lo1 = x[2], hi1 = x[3];
+        dst = ra.vcache + (((size_t)slot * ra.Hkv + (head - ra.Hq - ra.Hkv)) * ra.Lmax + p) * D;
+    }
+    *reinterpret_cast<uint32_t*>(dst + i0) = lo0 | ((uint32_t)lo1 << 16);
+    *reinterpret_cast<uint32_t*>(dst + half + i0) = hi0 | ((uint32_t)hi1 << 16);
+}
+
 // Bytes of a stage (64 k) of a packed slab of 16*cb columns: codes, then scales.
 __host__ __device__ constexpr int qstage_w_bytes(int cb) { return 544 * cb; }
 

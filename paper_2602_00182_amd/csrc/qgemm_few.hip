@@ -105,7 +105,7 @@ __global__ __launch_bounds__(64 * 16) void qgemm_few_kernel(const int8_t* __rest
         if constexpr (EPI == kEpiResidual)
             *reinterpret_cast<uint2*>(static_cast<uint16_t*>(C) + (size_t)row * ldc + n) = gemm_residual(v, rv);
         else if constexpr (EPI == kEpiRopeAppend)
-            gemm_epilogue_rope_append(v, ra, row, p, slot, n, rf);
+            gemm_rope_append(v, ra, row, p, slot, n, rf);
         else
             gemm_epilogue_store<EPI>(v, C, ldc, R, ldr, row, n, out_f32);
         return;
