@@ -10,6 +10,7 @@
 
 #include "attn_lane.h"
 #include "attn_rows.h"
+#include "geometry.h"
 #include "internal.h"
 #include "stream.h"
 
@@ -445,7 +446,7 @@ __global__ __launch_bounds__(256, 2) void attn_tile_kernel(const uint16_t* __res
 // itself.  Above 32 the chunks stay where they are: as even already (level over 60 launches).
 __device__ __forceinline__ int attn_chunk_of(int x, int stream, int ncmax)
 {
-    const int group = ncmax <= 32 ? ncmax & -ncmax : 1;
+    const int group = ncmax <= DET_ATTN_TURN_CHUNKS ? ncmax & -ncmax : 1;
     return x ^ (int)__umulhi((uint32_t)stream * 0x9E3779B9u, (uint32_t)group);
 }
 
@@ -1010,7 +1011,7 @@ static int attn_left(const void* q, const void* kcache, const void* vcache, cons
 // unit one.  Below, the chunks of a row in workgroups of their own are the better split: sixteen rows at the end
 // of 4000 tokens take 23 us that way and 176 walking, 256 such rows (128 workgroups) 165 and 180, 512 rows (256
 // workgroups) 309 and 178; 1000 rows of one prompt (504) 170 and 60.
-constexpr long long kWalkWorkgroups = 256;
+constexpr long long kWalkWorkgroups = DET_ATTN_WALK_WGS;
 
 static size_t attn_ws_floats(int B, int Hq, int Lmax)
 {
@@ -1082,7 +1083,7 @@ int det::attn_decode_impl(const void* q, const void* kcache, const void* vcache,
     //     one workgroup where there are enough of them (kWalkWorkgroups); fewer, but sixteen or more, go eight to
     //     a workgroup per chunk, so that they share each chunk of K and V;
     //   * other rows take attn_chunk_kernel.
-    const bool tiled = slots != nullptr && B >= 16;
+    const bool tiled = slots != nullptr && B >= DET_ATTN_NAMED_ROWS;
     if (tiled && attn_walk_workgroups(B, G, Hkv) >= kWalkWorkgroups) {
         if (qscales && !aligned16(qscales)) return DET_EALIGN;
         const int rc = attn_walk(q, kcache, vcache, seqlens, slots, len_offset, out, static_cast<float*>(qscales), ws_o, B, Hq,

@@ -6,6 +6,7 @@
 
 #include "attn_lane.h"
 #include "attn_rows.h"
+#include "geometry.h"
 #include "internal.h"
 #include "stream.h"
 
@@ -19,7 +20,7 @@ constexpr int kD = 128;
 constexpr int kSlots = 4;     // ring of staged subtiles
 constexpr int kTableChunks = 44;  // chunks whose maxima are kept in LDS between the sweeps
 // Groups of rows that are not walked (see `few`): pairs, chunks whose sums wait in registers, and chunks in all.
-constexpr int kFewPairs = 16, kFewChunks = 8, kFewMax = 80;
+constexpr int kFewPairs = DET_ATTN_FEW_PAIRS, kFewChunks = 8, kFewMax = 80;
 
 // index (in floats) of token tok in pair p's row of e: the row's 16-byte pieces are rotated by p, to spread over the banks
 __device__ __forceinline__ int e_index(int p, int tok) { return p * kChunk + ((((tok >> 2) + p) & 63) << 2) + (tok & 3); }

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.h"
+#include "geometry.h"
 
 namespace det {
 
@@ -114,7 +115,7 @@ struct qgemm_few_args {
     const void *x, *w_norm;
     float eps;
 };
-constexpr int kFewRows = 4;
+constexpr int kFewRows = DET_QGEMM_FEW_ROWS;
 bool qgemm_few_fits(int M, int cb, int K, bool norm);
 void qgemm_few(int epi, int cb, const qgemm_few_args& a, hipStream_t s);
 // Launches of more, in tiles of at most 48 rows (qgemm_mid.hip); x is not taken.

@@ -16,7 +16,7 @@ constexpr int kFewLds = 158 * 1024, kFewLdsHalf = 79 * 1024;
 // hidden by the wait for the first weights while it is short.  Quantized layer at a context of 512 with the norms' own launches, and
 // without, us: small model 40.4 and 37.4 at one row, 40.9 and 38.5 at two, 41.3 and 40.0 at three, 42.2 and 42.5 at four; hidden
 // 4096 (of its two norms one is in qgemm.hip's kernel, which gains at four too) 59.3 and 52.3, 58.3 and 52.7, 62.7 and 59.7, 63.5 and 63.3.
-constexpr int kFewNormK = 4096, kFewNormRows = 3;
+constexpr int kFewNormK = 4096, kFewNormRows = DET_QGEMM_NORM_ROWS;
 
 // LDS: the packed weights as they lie in memory, activation codes [block][row][64], scales [block][4] and, with the norm, the rows
 // as they come and the norm's weight.
@@ -49,6 +49,7 @@ __global__ __launch_bounds__(64 * 16) void qgemm_few_kernel(const int8_t* __rest
 {
     constexpr int WST = qstage_w_bytes(CB), TC = 16 * CB;
     constexpr int U = kBatch;
+    static_assert(U * kFewRows == 16, "a batch's rows are the columns of one operand");
     __shared__ uint4 lds[LDSB / 16];
     __shared__ float part[NORM ? 4 * kFewRows : 1];
     __shared__ int produced[kProducers], normed[2];  // what is done: batches of each producer, the two steps of the norm

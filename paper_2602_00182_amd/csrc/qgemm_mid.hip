@@ -198,7 +198,8 @@ void launch(int epi, const qgemm_few_args& a, int rows, hipStream_t s)
 // packings, 64 rows in one tile, us in the general kernel and here: 4096 x 4096 13.6 and 14.5, 14336 x 4096 35.6 and 37.6 (and 39.5 as two
 // tiles of 32), 2048 x 3072 9.1 and 10.5; 64-column packings have four chains for a producer's every block: 2048 x 11264, 8 rows, 8.2
 // and 8.6.
-bool qgemm_mid_fits(int M, int cb, int rows) { return (M <= rows ? M : rows) <= (cb == 1 ? 48 : (cb == 2 ? 32 : 0)); }
+static_assert(DET_QGEMM_MID16_ROWS <= 48 && DET_QGEMM_MID32_ROWS <= 32, "the row blocks that qgemm_mid has kernels for");
+bool qgemm_mid_fits(int M, int cb, int rows) { return (M <= rows ? M : rows) <= (cb == 1 ? DET_QGEMM_MID16_ROWS : (cb == 2 ? DET_QGEMM_MID32_ROWS : 0)); }
 
 void qgemm_mid(int epi, int cb, const qgemm_few_args& a, int rows, hipStream_t s)
 {
