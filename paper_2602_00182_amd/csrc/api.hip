@@ -20,7 +20,7 @@ extern "C" const char* det_fingerprint(void)
         // (attention) select.  They move no output byte, but a receipt pins them all the same, so a change of
         // what det_gemm_tile() or det_qgemm_tile() answers for any launch, or of the forms and grids the quantized GEMM and attention
         // take, is a new revision.
-        " tiles-8(gemm:n256@rounds,n128@256wg,rowcut8,n64@m65|m64r64|m161,reads@m96|m192,norm-in-kernel@4rows;"
+        " tiles-9(gemm:n256@rounds,n128@256wg,rowcut8,n64@m65|m64r64|m161,reads@m96|m192,norm-in-kernel@4rows;"
         "qgemm:few@" DET_STR(DET_QGEMM_FEW_ROWS) "rows,norm@" DET_STR(DET_QGEMM_NORM_ROWS) "rows,norm128@" DET_STR(
             DET_QGEMM_FEW_ROWS) "rows,mid@" DET_STR(DET_QGEMM_MID16_ROWS) "rows|" DET_STR(DET_QGEMM_MID32_ROWS) "rows,"
         "32x64+64x64@768wg,64x128;"

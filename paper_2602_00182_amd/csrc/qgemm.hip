@@ -830,10 +830,11 @@ static int qgemm_tile_rows(int M, int N, int cb)
 // The kernel and tile of a launch, a function of M, N and the packing (which is one of N).
 //   * `rows`, the height of the tiles the kernel above would cut the launch into, decides whether it does: a stage
 //     of it takes about 0.0025 us a row from 64 rows on, and a chain of 32 x 64 tiles 0.2 us a block, less against wider
-//     packings.  They meet at about 90, 80 and 60 rows of 16-, 32- and 64-column packings (us there and here: K x N 4096 x 4096 80 rows
-//     15.1 and 15.7, 96 rows 18.5 and 15.6, 14336 x 4096 80 rows 41.6 and 47.6; 4096 x 6144 64 rows 15.3 and 15.6, 80 rows 18.9 and 17.7;
-//     2048 x 11264 48 rows level, 64 rows 11.9 and 11.0; since the scale products are outer products the latter two meet at 65 and 49
-//     rows, 4096 x 6144 72 rows 18.7 and 17.7, 2048 x 11264 49 rows 12.0 and 10.8: the lines stay with the revision tiles-7).
+//     packings.  They meet at 90, 65 and 49 rows of 16-, 32- and 64-column packings, with the row block that the kernel above begins
+//     there (us there and here): K x N 4096 x 4096 80 rows 15.1 and 15.7, 96 rows 18.5 and 15.6, 14336 x 4096 80 rows 41.6 and 47.6; 4096 x 6144
+//     64 rows 14.8 (here 17.4), 65 to 79 rows 19.2 and 17.4, 2048 x 10112 17.8, then 21.9 and 11.7, 14336 x 6144 41.1, then 55.4 and 53.1;
+//     2048 x 11264 48 rows 10.0, 49 to 59 rows 11.6 and 10.3, 4096 x 11264 18.6 and 17.4, 2048 x 19968 21.7 and 12.7, 5632 x 12800 24.2 and
+//     23.6; the longest K, 14336 x 11264, 52.7 and 53.0.
 //     128-column packings have no tile of 64 columns; they meet 64 x 128 tiles between 64 and 96 rows (28672: 31.6 and
 //     35.6, 44.8 and 38.5).
 //   * The smallest tile of which the chip holds all (768): 2048 x 11264 128 rows, 704 of 32 x 64: 13.2 us against 14.7 in 64 x 64 and
@@ -847,7 +848,7 @@ static qgemm_form qgemm_pick(int M, int N, int cb)
     const int tile_rows = qgemm_tile_rows(M, N, cb), rows = tile_rows < M ? tile_rows : M;
     if (M > 65535 * 64 || N % 64 != 0) return kQBase;
     if (cb == 8) return rows > 80 && qtiles(M, N, 64, 128) >= 256 ? kQ64x128 : kQBase;
-    if (rows + 10 * cb < 100) return kQBase;
+    if (rows < (cb == 1 ? 90 : (cb == 2 ? 65 : 49))) return kQBase;
     if (qtiles(M, N, 32, 64) <= kHeld) return kQ32x64;
     return qtiles(M, N, 64, 64) <= kHeld || N % 128 != 0 ? kQ64x64 : kQ64x128;
 }

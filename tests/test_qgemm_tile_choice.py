@@ -13,6 +13,13 @@ def test_choice(M, K, N, tile):
     assert d.det_qgemm_tile(M, N, K) == tile
 
 
+# From one row more than the whole row blocks at which the tiles of 64 columns and the packing's own meet
+@pytest.mark.parametrize("last,K,N,columns", [(89, 4096, 4096, 16), (64, 4096, 6144, 32), (64, 14336, 5120, 32), (64, 2048, 8192, 32), (48, 2048, 11264, 64),
+                                              (48, 5632, 12800, 64)])
+def test_lines_of_the_small_tiles(last, K, N, columns):
+    assert d.det_qgemm_tile(last, N, K) == (256, columns) and d.det_qgemm_tile(last + 1, N, K) == (32, 64)
+
+
 def test_every_launch_has_a_tile_of_whole_slabs():
     for N in list(range(16, 2049, 16)) + [3072, 4160, 4608, 5632, 6144, 8192, 11008, 11264, 20480, 22528, 28672, 32000]:
         for M in list(range(1, 300)) + [385, 500, 768, 1000, 1962, 3302, 4096, 70000, 65535 * 64 + 1]:
