@@ -1,6 +1,6 @@
-"""Decode attention in the form small launches take (at most 512 workgroups, one for a chunk and KV head): the bytes of the
-same sequences in a larger batch, which takes the other form, at lengths around the steps, subtiles and chunks, with cache
-tails that are not finite, and with the output quantized."""
+"""Decode attention (a workgroup for one row's chunk and KV head), alone, in a small and in a large batch: the bytes of the same sequences
+in the form that takes eight rows a workgroup, at lengths around the steps, subtiles and chunks, with cache tails that are not
+finite, and with the output quantized; and every chunk wherever the grid has it."""
 import math
 
 import numpy as np
@@ -26,7 +26,7 @@ def d():
 @pytest.mark.parametrize("quant", [False, True])
 def test_small_launch_equals_large_launch(d, Hq, Hkv, quant):
     Lmax = 700
-    B = 3 * 512 // (3 * Hkv) + len(LENS)          # more than 512 workgroups of three chunks
+    B = 3 * 512 // (3 * Hkv) + len(LENS)          # several rounds of workgroups
     lens = LENS + [1] * (B - len(LENS))
     q = up_bf16(ds.normal_bf16(9500 + Hq, (B, Hq, 128)))
     k = up_bf16(ds.normal_bf16(9501 + Hq, (B, Hkv, Lmax, 128)))
@@ -36,24 +36,31 @@ def test_small_launch_equals_large_launch(d, Hq, Hkv, quant):
         v[b, :, max(n, 0):] = float("nan")
     lens_t = up(np.asarray(lens, dtype=np.int32))
 
-    def run(p):
+    def run(p, slots=None):
         n = p.stop - p.start
         ws = torch.full((d.det_attn_decode_workspace_bytes(n, Hq, 128, Lmax),), 0xFF, dtype=torch.uint8, device=DEV)
         if not quant:
             out = torch.full((n, Hq, 128), 7.0, dtype=torch.bfloat16, device=DEV)
-            d.det_attn_decode(q[p], k[p], v[p], lens_t[p], out, ws, SCALE)
+            if slots is None:
+                d.det_attn_decode(q[p], k[p], v[p], lens_t[p], out, ws, SCALE)
+            else:
+                d.det_attn_decode_rows(q[p], k[p], v[p], lens_t[p], slots, out, ws, SCALE)
             return out.view(torch.int16)
         codes = torch.full((n, Hq * 128), 99, dtype=torch.int8, device=DEV)
         scales = torch.full((Hq * 2, (n + 3) & ~3), 7.0, dtype=torch.float32, device=DEV)
-        d.det_attn_decode_quant_q8(q[p], k[p], v[p], lens_t[p], None, codes, scales.view(-1), ws, SCALE)
+        d.det_attn_decode_quant_q8(q[p], k[p], v[p], lens_t[p], slots, codes, scales.view(-1), ws, SCALE)
         return torch.cat([codes.view(torch.int32), scales[:, :n].t().contiguous().view(torch.int32)], 1)
 
+    # rows that name their slots, too few to walk their chunks: eight a workgroup
+    n = len(LENS)
+    assert n >= 16 and -(-n // (64 // (Hq // Hkv))) * Hkv < 256
     step(f"attention by chunk, heads {Hq}/{Hkv} quant={quant}")
-    want = run(slice(0, B))
+    want = run(slice(0, n), torch.arange(n, dtype=torch.int32, device=DEV))
+    large = run(slice(0, B))
     torch.cuda.synchronize()
-    for i in range(0, len(LENS), 5):
-        p = slice(i, min(i + 5, len(LENS)))
-        assert 3 * Hkv * (p.stop - p.start) <= 512 < 3 * Hkv * B
+    assert torch.equal(large[:n], want)
+    for i in range(0, n, 5):
+        p = slice(i, min(i + 5, n))
         assert torch.equal(run(p), want[p]), LENS[p]
 
 

@@ -10,7 +10,7 @@ from gpu_util import DEV, step, up, up_bf16
 
 pytestmark = pytest.mark.gpu
 
-LENS = [600, 1, 15, 16, 31, 32, 33, 63, 64, 65, 0, 127, 129, 191, 193, 223, 224, 225, 255, 256, 257, 287, 289, 511, 512, 513, 599]
+LENS = [600, -3, 1, 15, 16, 31, 32, 33, 63, 64, 65, 0, 127, 129, 191, 193, 223, 224, 225, 255, 256, 257, 287, 289, 511, 512, 513, 599]
 
 
 @pytest.fixture(scope="module")
@@ -19,19 +19,22 @@ def d():
     return d
 
 
+# three chunks, and four and eight, whose places in the grid change from stream to stream
+@pytest.mark.parametrize("Lmax,longest", [(600, []), (1024, [1024, 767, 768, 769, 1023]), (2048, [2048, 1025, 1791, 1793])])
 @pytest.mark.parametrize("Hq,Hkv", [(4, 4), (8, 4), (16, 4), (16, 2)])
 @pytest.mark.parametrize("quant", [False, True])
 @pytest.mark.parametrize("scale", [0.088, -0.3])
-def test_one_row_a_workgroup_equals_eight(d, Hq, Hkv, quant, scale):
-    Lmax, B = 600, len(LENS)
+def test_one_row_a_workgroup_equals_eight(d, Lmax, longest, Hq, Hkv, quant, scale):
+    lengths = LENS + longest
+    B = len(lengths)
     assert B >= 16 and -(-B // (64 // (Hq // Hkv))) * Hkv < 256   # rows that name their slots: eight a workgroup, not the walk
     q = up_bf16(ds.normal_bf16(9700 + Hq, (B, Hq, 128)))
     k = up_bf16(ds.normal_bf16(9701 + Hq, (B, Hkv, Lmax, 128)))
     v = up_bf16(ds.normal_bf16(9702 + Hq, (B, Hkv, Lmax, 128)))
-    for b, n in enumerate(LENS):
-        k[b, :, n:] = float("nan")
-        v[b, :, n:] = float("inf")
-    lens = up(np.asarray(LENS, dtype=np.int32))
+    for b, n in enumerate(lengths):
+        k[b, :, max(n, 0):] = float("nan")
+        v[b, :, max(n, 0):] = float("inf")
+    lens = up(np.asarray(lengths, dtype=np.int32))
     slots = torch.arange(B, dtype=torch.int32, device=DEV)
 
     def run(named):
@@ -48,7 +51,7 @@ def test_one_row_a_workgroup_equals_eight(d, Hq, Hkv, quant, scale):
             d.det_attn_decode(q, k, v, lens, out, ws, scale)
         return (out.view(torch.int16),)
 
-    step(f"decode attention against eight rows a workgroup, heads {Hq}/{Hkv} quant={quant} scale={scale}")
+    step(f"decode attention against eight rows a workgroup, cache of {Lmax}, heads {Hq}/{Hkv} quant={quant} scale={scale}")
     got, want = run(False), run(True)
     torch.cuda.synchronize()
     for a, b in zip(got, want):
