@@ -1,5 +1,6 @@
 """Scale products of the quantized GEMM's tiles and of its kernel of fewer rows: subnormal, zero, infinite and NaN scales, odd and even counts of blocks.  A row's bits
-are those of the row by itself, whose products are taken by vector multiplies."""
+are those of the row by itself, whose products are taken by vector multiplies: in the kernel of few rows, which packings of 128 columns
+are too wide for, so that of those the single row's matrix is cut into narrower ones."""
 import numpy as np
 import pytest
 import torch
@@ -38,8 +39,13 @@ def test_rows_equal_single_rows(d, M, K, N):
     d.det_qgemm_w4a8(codes, scales, packed, c, N)
     torch.cuda.synchronize()
     assert torch.isnan(c[3]).any() and (c[2, :].abs().sum() if K == 64 else torch.zeros(())) == 0
+    parts = [(0, N)] if d.det_qgemm_tile(1, N, K)[1] < 128 else [(n, n + 4096) for n in range(0, N, 4096)]
+    assert parts[-1][1] == N
+    narrow = [(n0, n1, d.quant_pack_weight(w[:, n0:n1].contiguous())) for n0, n1 in parts]
     for i in (*range(8), *(i for i in (15, 16, 31, 32, 63, 64) if i < M), M - 1):
         codes1, scales1 = d.quant_activations(a[i:i + 1].contiguous())
         one = torch.full((1, N), 7.0, dtype=torch.float32, device=DEV)
-        d.det_qgemm_w4a8(codes1, scales1, packed, one, N)
+        for n0, n1, part in narrow:
+            assert d.det_qgemm_tile(1, n1 - n0, K)[1] <= 64
+            d.det_qgemm_w4a8(codes1, scales1, part, one[:, n0:n1], n1 - n0)
         assert np.array_equal(one.cpu().numpy().view(np.uint32)[0], c[i].cpu().numpy().view(np.uint32)), i
