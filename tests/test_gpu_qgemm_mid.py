@@ -1,5 +1,5 @@
 """The quantized GEMM of up to 48 rows on packings of 16 and 32 columns on the GPU: row counts around the tiles' edges, blocks of K that
-do not come out even over the producing waves and the groups of results, every epilogue; bytes against the oracle or the unfused steps."""
+do not come out even over the producing waves and the groups of results, every epilogue; and the short last tiles of higher ones; bytes against the oracle or the unfused steps."""
 import numpy as np
 import pytest
 import torch
@@ -39,6 +39,16 @@ def test_bytes_match_oracle(d, orc, M, K, N):
     torch.cuda.synchronize()
     assert np.array_equal(cf.cpu().numpy().view(np.uint32), acc.view(np.uint32))
     assert np.array_equal(down_bf16(c), out)
+
+
+# Higher tiles, which the general kernel has: a last one of one to eight rows, whose one or two computing waves are fed by ten or eleven
+# in long chunks; tiles of 64 rows (1024 and 512 columns) and of 256 (widths that no 64-column tile fits), the last chunk a part of one
+@pytest.mark.parametrize("M,K,N", [(196, 64 * 130, 1024), (193, 64 * 3, 1024), (200, 64 * 130, 1024), (387, 320, 512), (257, 64 * 70, 5072), (261, 64 * 30, 5152),
+                                   (264, 64 * 77, 5152)])
+def test_short_last_tiles(d, orc, M, K, N):
+    rows, columns = d.det_qgemm_tile(M, N, K)
+    assert columns < 64 and rows > 48 and 0 < M % rows <= 8
+    test_bytes_match_oracle(d, orc, M, K, N)
 
 
 @pytest.mark.parametrize("M,K,N", [(7, 576, 2048), (45, 320, 3072), (19, 2112, 6144)])
