@@ -516,7 +516,7 @@ __global__ __launch_bounds__(256, 2) void attn_chunk_kernel(const uint16_t* __re
             const uint32_t off = (uint32_t)min(64 * wave + 4 * b + g, held - 1) * 256u + 16u * (uint32_t)(lr ^ k_swizzle((b >> 1) & 3, g));
             __builtin_amdgcn_global_load_lds((glob_u32*)(kp + off), (lds_u32*)(vbuf + wave * 1024 + b * 64), 16, 0, 0);
         }
-        __builtin_amdgcn_sched_barrier(0);  // the wait below counts on this order: loads return in order
+        asm volatile("" ::: "memory");  // the wait below counts on this order: loads return in order
 #pragma unroll
         for (int b = 0; b < 16; ++b) {
             vr[b] = vp[min(64 * wave + 4 * b + g, held - 1) * 16 + lr];
