@@ -1,4 +1,4 @@
-// Shared by the forms of the block-quantized GEMM (qgemm.hip, qgemm_few.hip).
+// Shared by the forms of the block-quantized GEMM (qgemm.hip, qgemm_few.hip, qgemm_mid.hip).
 #pragma once
 
 #include "common.h"
@@ -51,8 +51,9 @@ __device__ __forceinline__ void await(const int* counters, int n, int need)
 // Epilogues for waves that read what they need besides the sums before these are there: kEpiResidual from the residual's four
 // values, kEpiRopeAppend from the pairs' cosines and sines.  The same operations as gemm_epilogue_store and
 // gemm_epilogue_rope_append, which stay in one piece: made of these parts they compile to other code for the kernels that read at
-// the end (the wide bf16 tiles 7 % more instructions; one row of 4096 x 4096 with the residual 8.01 us instead of 7.89 on one
-// card, level on two others).
+// the end (the wide bf16 tiles 7 % more instructions).  us whole and cut up: one row of 4096 x 4096 with the residual 7.89 and 8.01 on one card, level
+// on others, 55 rows of 5632 x 2048 10.16 and 9.97; with the rotation 55 rows of hidden 4096 14.6 and 14.8, 128 rows 19.8 and 19.4, of hidden 2048 9.33
+// and 9.56; else level.
 __device__ __forceinline__ uint2 gemm_residual(const float (&v)[4], const uint2& rv)
 {
     float y[4];
