@@ -67,10 +67,11 @@ def test_epilogues_equal_unfused_bytes(d, orc, M, K, N):
     assert np.array_equal(down_bf16(y[:M].contiguous()), orc.swiglu(plain[:, :N // 2], plain[:, N // 2:]))
 
 
-@pytest.mark.parametrize("H,F,Hq,Hkv", [(2048, 5632, 16, 4), (4096, 1408, 32, 8)])
-def test_layer_rows_equal_single_rows(d, H, F, Hq, Hkv):
+# 50 and 66 rows: the gate/up and the fused projection in the smallest tiles of 64 columns
+@pytest.mark.parametrize("H,F,Hq,Hkv,R", [(2048, 5632, 16, 4, 43), (4096, 1408, 32, 8, 43), (2048, 5632, 16, 4, 50), (4096, 1408, 32, 8, 66)])
+def test_layer_rows_equal_single_rows(d, H, F, Hq, Hkv, R):
     """The rotation and cache append among the epilogues: each row's bytes are those of the row by itself."""
-    Lmax, D, R, s = 300, 128, 43, ds.tensor_seed(6, 810) + H
+    Lmax, D, s = 300, 128, ds.tensor_seed(6, 810) + H
     n = lambda i, shape, std, mean=0.0: ds.normal_bf16_torch(s + i, shape, std, mean, DEV)
     w = d.layer_weights(n(0, (H,), 0.1, 1.0), d.quant_pack_qkv(n(1, (H, (Hq + 2 * Hkv) * D), 0.02), Hq, Hkv, D), d.quant_pack_weight(n(2, (Hq * D, H), 0.02)),
                         n(3, (H,), 0.1, 1.0), d.quant_pack_gate_up(n(4, (H, 2 * F), 0.02)), d.quant_pack_weight(n(5, (F, H), 0.02)))

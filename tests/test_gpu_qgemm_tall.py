@@ -37,7 +37,9 @@ def test_rows_of_tall_tiles_equal_small_calls(d, M, K, N):
 # 32 x 64 tiles of packings of 16, 32 and 64 columns, the last row in a tile of its own, at its end and before it; 64 x 64 tiles, also of
 # a width that is no multiple of 128; 64 x 128 of the first row count that takes them with 128-column packings
 @pytest.mark.parametrize("M,K,N", [(97, 64, 4096), (96, 192, 3072), (161, 320, 2048), (129, 128, 6144), (65, 64, 11264),
-                                   (257, 192, 8192), (700, 64, 3072), (1000, 64, 4160), (96, 192, 20480)])
+                                   (257, 192, 8192), (700, 64, 3072), (1000, 64, 4160), (96, 192, 20480),
+                                   # where the tiles of 32- and 64-column packings begin
+                                   (65, 64 * 7, 6144), (79, 64 * 20, 5120), (66, 64, 10112), (49, 64 * 7, 11264), (59, 64 * 20, 12800), (50, 128, 19968)])
 def test_rows_of_small_tiles_equal_small_calls(d, M, K, N):
     rows_equal_small_calls(d, M, K, N)
 
